@@ -221,12 +221,19 @@ int kvcomm_align_kv_batch(const kvcomm_model *model, int32_t gran, kvcomm_tensor
  *                   positions n_ctx .. n_ctx+tq-1.
  *   softmax_scale   <= 0 selects 1/sqrt(D).
  *   lse_out         DEVICE [L, Hq, tq] fp32 natural-log-sum-exp of the scaled scores, or NULL.
- *   workspace       kvcomm_suffix_attn_workspace() bytes (may be 0, then NULL is accepted).
+ *   workspace       DEVICE scratch of kvcomm_suffix_attn_workspace() bytes, 16-byte aligned, or NULL.  It is for
+ *                   launches that are too small to fill the GPU (a layer at a time, a few decoded tokens): with
+ *                   it the keys of a row tile are shared out over several thread blocks and a second small kernel joins
+ *                   their partial results.  Without it (NULL, too small or misaligned) each row tile is one block's
+ *                   work: the same result up to rounding, only slower.  The query returns 0 when no scratch is
+ *                   used: f32, caches of fewer than KVCOMM_ATTN_MIN_SPLIT_KEYS tokens, launches that fill the GPU.
  * bf16 tensors use bf16 MFMA with fp32 accumulation and an fp32 online softmax; f32 tensors
  * use fp32 arithmetic throughout.
  * Errors: KVCOMM_EINVAL for null/misaligned pointers, tq <= 0, n_ctx < 0;
  * KVCOMM_EUNSUPPORTED for bf16 caches whose token stride is D * 2^21 elements or more
  * (the kernel addresses a group of 512 / D rows with a 32-bit byte offset).                 */
+#define KVCOMM_ATTN_MIN_SPLIT_KEYS 512
+
 size_t kvcomm_suffix_attn_workspace(const kvcomm_model *model, int32_t n_ctx, int32_t tq);
 
 int kvcomm_suffix_attn(const kvcomm_model *model, kvcomm_tensor q,
@@ -235,21 +242,27 @@ int kvcomm_suffix_attn(const kvcomm_model *model, kvcomm_tensor q,
                        kvcomm_tensor out, float *lse_out,
                        void *workspace, size_t workspace_bytes, void *stream);
 
-/* The same attention (workflow step 4), same arguments, results bit-identical to kvcomm_suffix_attn, launched
- * as at most `max_blocks` thread blocks that each walk a fixed share of the (layer, kv head, query tile) work
+/* The same attention (workflow step 4), same arguments, results bit-identical to kvcomm_suffix_attn without a
+ * workspace (the _ws form: with the same workspace), launched as at most `max_blocks` thread blocks that each walk a fixed share of the (layer, kv head, query tile) work
  * items.  A block of the bf16 kernel fills a compute unit, so the launch occupies max_blocks of the GPU's 256
  * compute units and leaves the others to kernels that run beside it on another stream: the memory-bound
  * alignment of the next agent next to the matrix-core-bound attention of the current one.  (Under the chip's
  * power limit the attention loses less than its share of compute units: measured 0.82 ms on 160 of 256 against
  * 0.66 ms on all of them.)  max_blocks is spread over the 8 XCDs in launch order; values of at least the number
  * of work items give the plain launch.  f32 tensors ignore max_blocks (their kernel is small-block and never fills
- * the chip's registers).
+ * the chip's registers).  The kernel that joins the partial results of a split launch is small-block too.
  * Errors: as kvcomm_suffix_attn; KVCOMM_EINVAL for max_blocks < 8 (one block per XCD is the minimum).          */
 int kvcomm_suffix_attn_confined(const kvcomm_model *model, kvcomm_tensor q,
                                 kvcomm_tensor cache_k, kvcomm_tensor cache_v,
                                 int32_t n_ctx, int32_t tq, float softmax_scale,
                                 kvcomm_tensor out, float *lse_out,
                                 int32_t max_blocks, void *stream);
+
+int kvcomm_suffix_attn_confined_ws(const kvcomm_model *model, kvcomm_tensor q,
+                                   kvcomm_tensor cache_k, kvcomm_tensor cache_v,
+                                   int32_t n_ctx, int32_t tq, float softmax_scale,
+                                   kvcomm_tensor out, float *lse_out,
+                                   int32_t max_blocks, void *workspace, size_t workspace_bytes, void *stream);
 
 /* --------------------------------------------------------------------------------------
  * Weighting variants of the appendix on the approximation method: the default rule

@@ -20,6 +20,7 @@ W_LAYER_HEAD_TOKEN = 1
 W_SEGMENT = 2
 MAX_ANCHORS = 64
 MAX_BATCH = 8
+ATTN_MIN_SPLIT_KEYS = 512   # shorter caches never use the attention's scratch
 RULE_L2_SOFTMAX = 0
 RULE_NEAREST = 1
 RULE_COSINE_SOFTMAX = 2
@@ -124,6 +125,9 @@ def load_library():
     lib.kvcomm_suffix_attn.restype = ctypes.c_int
     lib.kvcomm_suffix_attn_confined.argtypes = [mp, _CTensor, _CTensor, _CTensor, i32, i32, f32, _CTensor, vp, i32, vp]
     lib.kvcomm_suffix_attn_confined.restype = ctypes.c_int
+    lib.kvcomm_suffix_attn_confined_ws.argtypes = [mp, _CTensor, _CTensor, _CTensor, i32, i32, f32, _CTensor, vp, i32,
+                                                   vp, sz, vp]
+    lib.kvcomm_suffix_attn_confined_ws.restype = ctypes.c_int
     lib.kvcomm_anchor_weights_rule_workspace.argtypes = [mp, i32, i32, i32, i32]
     lib.kvcomm_anchor_weights_rule_workspace.restype = sz
     lib.kvcomm_anchor_weights_rule.argtypes = [mp, i32, i32, f32, _CTensor, i32, ctypes.POINTER(vp), _CTensor,
@@ -282,9 +286,28 @@ def kvcomm_suffix_attn_workspace(model, n_ctx, tq):
     return int(load_library().kvcomm_suffix_attn_workspace(ctypes.byref(model.c()), int(n_ctx), int(tq)))
 
 
+def _attn_workspace(cmodel, n_ctx, tq, workspace, device, stream):
+    """(pointer, bytes, tensor to keep until the call has returned) of the attention's scratch.  A workspace that is
+    made here belongs to the stream the kernels run on, so the allocator does not hand it out under them."""
+    if workspace is None:
+        if n_ctx + tq < ATTN_MIN_SPLIT_KEYS:
+            return None, 0, None
+        need = load_library().kvcomm_suffix_attn_workspace(ctypes.byref(cmodel), n_ctx, tq)
+        if not need:
+            return None, 0, None
+        if stream is None:
+            workspace = torch.empty((need,), dtype=torch.uint8, device=device)
+        else:
+            with torch.cuda.stream(stream):
+                workspace = torch.empty((need,), dtype=torch.uint8, device=device)
+    return workspace.data_ptr(), workspace.numel() * workspace.element_size(), workspace
+
+
 def kvcomm_suffix_attn(model, q, cache_k, cache_v, n_ctx, softmax_scale=0.0, out=None, lse_out=None,
-                       want_lse=False, stream=None):
-    """Causal attention of the suffix queries q [L,Hq,Tq,D] over cache_k/v [L,Hkv,n_ctx+Tq,D]."""
+                       want_lse=False, stream=None, workspace=None):
+    """Causal attention of the suffix queries q [L,Hq,Tq,D] over cache_k/v [L,Hkv,n_ctx+Tq,D].
+
+    workspace: kvcomm_suffix_attn_workspace() bytes on the device (made here if not given)."""
     lib = load_library()
     tq = q.shape[2]
     if cache_k.shape[2] != n_ctx + tq or cache_v.shape[2] != n_ctx + tq:
@@ -293,16 +316,26 @@ def kvcomm_suffix_attn(model, q, cache_k, cache_v, n_ctx, softmax_scale=0.0, out
         out = torch.empty_like(q)
     if want_lse and lse_out is None:
         lse_out = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device)
-    _check(lib.kvcomm_suffix_attn(ctypes.byref(model.c()), _desc(q, model.dtype, "q"),
+    cmodel = model.c()
+    ws, ws_bytes, _keep = _attn_workspace(cmodel, int(n_ctx), tq, workspace, q.device, stream)
+    _check(lib.kvcomm_suffix_attn(ctypes.byref(cmodel), _desc(q, model.dtype, "q"),
                                   _desc(cache_k, model.dtype, "cache_k"), _desc(cache_v, model.dtype, "cache_v"),
                                   int(n_ctx), tq, float(softmax_scale), _desc(out, model.dtype, "out"),
-                                  None if lse_out is None else lse_out.data_ptr(), None, 0, _stream_ptr(stream)))
+                                  None if lse_out is None else lse_out.data_ptr(), ws, ws_bytes, _stream_ptr(stream)))
     return (out, lse_out) if want_lse else out
 
 
 def kvcomm_suffix_attn_confined(model, q, cache_k, cache_v, n_ctx, max_blocks, softmax_scale=0.0, out=None,
                                 lse_out=None, want_lse=False, stream=None):
     """kvcomm_suffix_attn as at most max_blocks persistent thread blocks (one per compute unit)."""
+    return kvcomm_suffix_attn_confined_ws(model, q, cache_k, cache_v, n_ctx, max_blocks, softmax_scale, out, lse_out,
+                                          want_lse, stream)
+
+
+def kvcomm_suffix_attn_confined_ws(model, q, cache_k, cache_v, n_ctx, max_blocks, softmax_scale=0.0, out=None,
+                                   lse_out=None, want_lse=False, stream=None, workspace=None):
+    """kvcomm_suffix_attn_confined with the scratch of kvcomm_suffix_attn (made here if not given): the same bits as
+    kvcomm_suffix_attn with a workspace."""
     lib = load_library()
     tq = q.shape[2]
     if cache_k.shape[2] != n_ctx + tq or cache_v.shape[2] != n_ctx + tq:
@@ -311,12 +344,14 @@ def kvcomm_suffix_attn_confined(model, q, cache_k, cache_v, n_ctx, max_blocks, s
         out = torch.empty_like(q)
     if want_lse and lse_out is None:
         lse_out = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device)
-    _check(lib.kvcomm_suffix_attn_confined(ctypes.byref(model.c()), _desc(q, model.dtype, "q"),
-                                           _desc(cache_k, model.dtype, "cache_k"),
-                                           _desc(cache_v, model.dtype, "cache_v"), int(n_ctx), tq,
-                                           float(softmax_scale), _desc(out, model.dtype, "out"),
-                                           None if lse_out is None else lse_out.data_ptr(), int(max_blocks),
-                                           _stream_ptr(stream)))
+    cmodel = model.c()
+    ws, ws_bytes, _keep = _attn_workspace(cmodel, int(n_ctx), tq, workspace, q.device, stream)
+    _check(lib.kvcomm_suffix_attn_confined_ws(ctypes.byref(cmodel), _desc(q, model.dtype, "q"),
+                                              _desc(cache_k, model.dtype, "cache_k"),
+                                              _desc(cache_v, model.dtype, "cache_v"), int(n_ctx), tq,
+                                              float(softmax_scale), _desc(out, model.dtype, "out"),
+                                              None if lse_out is None else lse_out.data_ptr(), int(max_blocks), ws,
+                                              ws_bytes, _stream_ptr(stream)))
     return (out, lse_out) if want_lse else out
 
 

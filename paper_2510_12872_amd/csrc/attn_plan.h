@@ -1,0 +1,105 @@
+// Host-side choice of the bf16 attention kernel and of the cut of the key axis, and the launches that
+// suffix_attn.hip takes from attn_rows.hip.
+#pragma once
+
+#include "attn_common.h"
+
+namespace kvc {
+
+constexpr int kAttnWaves = 8;   // wavefronts of a 256-row block; measured: 2 % faster than two blocks of 4 per CU (every K/V tile enters LDS once per CU)
+constexpr int rows_waves(int D) { return D == 256 ? 4 : 8; }   // wavefronts of a rows-kernel block: what LDS holds
+constexpr int kChipCUs = 256;
+constexpr int kRowsMaxSplits = 16;  // attn_combine_kernel takes 4 us up to here, 6 us at 25, 11 us at 64
+constexpr int kTileMaxSplits = 8;
+constexpr int kMinSplitKeys = KVCOMM_ATTN_MIN_SPLIT_KEYS;
+constexpr int64_t kLastLevelCache = (int64_t)256 << 20;
+
+struct AttnPlan {
+    bool rows_kernel;
+    int tile_rows;      // packed (query, head) rows of a row tile
+    int n_row_tiles;
+    int n_splits;
+};
+
+// Rounds that `x` chips full of blocks take (a last round that is not full costs less than a whole one).
+static inline double attn_rounds(double x) { return x <= 1.0 ? 1.0 : x + 0.3 * (ceil(x) - x); }
+
+// Microseconds of a launch of the rows kernel (32 rows per block, the keys shared out over its wavefronts) with `items`
+// (row tile, layer, kv head) triples: 6 us plus 1.1 us per iteration (32 keys of every wavefront) when few CUs are
+// busy, 1.5 us when all are.  8 kv heads, G = 4, D = 128, 3100 keys (13 iterations): 22 / 24 / 26 / 50 us in 64 / 128 /
+// 256 / 512 blocks.
+static inline double attn_rows_us(const kvcomm_model &m, int64_t items, int64_t its)
+{
+    const double x = (double)items / kChipCUs, scale = m.head_dim == 64 ? 0.65 : m.head_dim == 128 ? 1.0 : 2.0;
+    return attn_rounds(x) * (6.0 + scale * (1.1 + 0.4 * std::min(1.0, x)) * (double)its);
+}
+
+// Microseconds of a launch of the 256-row kernel (a block fills a CU) with the keys cut into `ns` runs: a block is 9 us
+// of set-up and epilogue plus 1.15 us per 64-key tile when few CUs are busy and 1.7 us when all are; the partial
+// results are written and read at about 8 TB/s, plus 3.5 us for the combine launch.  One layer, Tq 512, 3072 keys, 64
+// row tiles: 66 us unsplit, 50 / 42 / 42 / 49 us in 2 / 3 / 4 / 5 runs; 320 row tiles: 141 us unsplit, 139 us in two runs.
+static inline double attn_tiles_us(const kvcomm_model &m, int64_t items, int tile_rows, int64_t tiles, int ns)
+{
+    const double x = (double)items * ns / kChipCUs, scale = m.head_dim == 64 ? 0.65 : m.head_dim == 128 ? 1.0 : 1.45;
+    const double part_bytes = (double)items * tile_rows * m.head_dim * 8;
+    return attn_rounds(x) * (9.0 + scale * (1.15 + 0.55 * std::min(1.0, x)) * (double)((tiles + ns - 1) / ns)) +
+           (ns > 1 ? 3.5 + part_bytes * ns / 8e6 : 0.0);
+}
+
+// Which kernel, and into how many runs the keys of a row tile are cut (one if the caller has no workspace).
+// The rows kernel takes a launch whose blocks all fit the chip at once, and a larger one where it is clearly
+// faster (few rows, so that most of a 256-row tile would be empty).  rows kernel / 256-row kernel unsplit / with its
+// best split and combine launch, 8 kv heads, 3100 keys: 64 blocks 22 / 63 / 23 us, 256 blocks 26 / 65 / 30 us, 512 blocks
+// 50 / 67 / 40 us.  Above two rounds of rows-kernel blocks the 256-row kernel wins whenever rows fill its tiles.
+// Splits of the rows kernel pay when they take off more than the combine launch (4 us, its gap and its launch on the
+// host), and only up to one round of blocks.  One decoded token, 3100 keys, 8 kv heads: 20 us in 8 blocks, 8.7 + 4.1 us in 104.
+static inline AttnPlan attn_plan(const kvcomm_model &m, int n_ctx, int tq, bool may_split)
+{
+    const int G = m.n_q_heads / m.n_kv_heads, D = m.head_dim;
+    const int64_t rows = (int64_t)G * tq, LH = (int64_t)m.n_layers * m.n_kv_heads, N = (int64_t)n_ctx + tq;
+
+    const int tile_rows = D == 256 ? 128 : 32 * kAttnWaves;
+    const int64_t tile_items = LH * ((rows + tile_rows - 1) / tile_rows), tiles = (N + 63) / 64;
+    may_split = may_split && N >= kMinSplitKeys;
+    int tile_ns = 1;
+    double tile_us = attn_tiles_us(m, tile_items, tile_rows, tiles, 1);
+    for (int ns = 2; may_split && tile_items <= 2 * kChipCUs && ns <= kTileMaxSplits && ns * 4 <= tiles; ++ns) {
+        const double t = attn_tiles_us(m, tile_items, tile_rows, tiles, ns);
+        if (t < 0.95 * tile_us) {
+            tile_us = t;
+            tile_ns = ns;
+        }
+    }
+
+    const int64_t rows_items = LH * ((rows + 31) / 32);
+    const int64_t its = (N + 32 * rows_waves(D) - 1) / (32 * rows_waves(D));
+    AttnPlan pl{};
+    pl.rows_kernel = rows_items <= kChipCUs || attn_rows_us(m, rows_items, its) < 0.7 * tile_us;
+    pl.tile_rows = pl.rows_kernel ? 32 : tile_rows;
+    pl.n_row_tiles = (int)((rows + pl.tile_rows - 1) / pl.tile_rows);
+    pl.n_splits = pl.rows_kernel ? 1 : tile_ns;
+    if (pl.rows_kernel && may_split && rows_items <= kChipCUs / 2) {
+        int64_t ns = std::min<int64_t>(std::min<int64_t>(kRowsMaxSplits, kChipCUs / rows_items), its);
+        const int64_t split_its = (its + ns - 1) / ns;
+        ns = (its + split_its - 1) / split_its;   // the fewest runs of that many iterations
+        const double gain = attn_rows_us(m, rows_items, its) - attn_rows_us(m, rows_items * ns, split_its);
+        if (ns > 1 && gain > 8.0) pl.n_splits = (int)ns;
+    }
+    return pl;
+}
+
+// (32-row group, split) pairs of a launch.
+static inline size_t attn_parts(const kvcomm_model &m, const AttnPlan &pl)
+{
+    return (size_t)m.n_layers * m.n_kv_heads * pl.n_row_tiles * (pl.tile_rows / 32) * pl.n_splits;
+}
+
+static inline size_t attn_workspace(const kvcomm_model &m, const AttnPlan &pl)
+{
+    return pl.n_splits > 1 ? attn_parts(m, pl) * sizeof(float) * (32 * (size_t)m.head_dim + 64) : 0;
+}
+
+int launch_attn_rows(const AttnParams &p, int D, unsigned n_blocks, hipStream_t stream);
+int launch_attn_combine(const AttnParams &p, int D, hipStream_t stream);
+
+}  // namespace kvc

@@ -1,0 +1,370 @@
+// bf16 suffix attention for few query rows (decoded tokens, very short suffixes), and the kernel that joins the
+// partial results of a launch that splits the key axis.
+#include "attn_plan.h"
+
+namespace {
+
+using namespace kvc;
+
+template <int N>
+__device__ __forceinline__ void wait_loads()   // at most N of this wavefront's vector-memory operations stay outstanding
+{
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
+
+// attn_rows_kernel: 32 packed (query, head) rows per block (GQA packing and transposed products as in
+// attn_mfma_kernel), which the wavefronts SHARE: each takes every NW-th 32-key sub-step of the block's key
+// run with its own softmax state, and the states are joined through LDS at the end.  The 256-row kernel would leave
+// seven of eight wavefronts without rows and walk the keys one 64-key tile after the other (one layer, one token,
+// 3100 keys: 62 us; here 20 us in one block per kv head, 9 + 4 us with the keys cut into runs).
+// What bounds it is the latency of the K / V stream, and HBM where every layer is in one launch (32 layers: 64 us =
+// 6.4 TB/s): K and V of a sub-step go global -> LDS into the wavefront's own buffers (no block barrier in the loop),
+// K of the next sub-step is requested as soon as its operands are in registers and V likewise, so a wavefront
+// always has 8 ... 16 KB in flight (D = 128).  Eight wavefronts measured 10 % better than two blocks of four.
+template <int D, bool NT>
+__global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_rows_kernel(const AttnParams p)
+{
+    constexpr int NW = rows_waves(D);
+    constexpr int NKS = D / 16, NDB = D / 32, KCH = D / 8, ROWB = D * 2, HALFB = 32 * ROWB;
+    constexpr int RPL = 64 / KCH;    // key rows filled by one wavefront-wide direct load
+    constexpr int LPT = 32 / RPL;    // direct loads of a 32-key half
+    constexpr int KSWZ = (KCH < 16 ? KCH : 16) - 1;  // chunk swizzles as in attn_mfma_kernel
+    constexpr int VSWZ = KCH - 1;
+    constexpr int KD = (KSWZ + 1) / RPL > 1 ? (KSWZ + 1) / RPL : 1;  // loads after which the swizzle pattern of the rows repeats
+    constexpr int VD = 4 / RPL > 1 ? 4 / RPL : 1;
+    constexpr int CDB = NDB < 4 ? NDB : 4;           // 32-channel blocks joined per round
+    constexpr int BUFB = NW * 2 * HALFB, JOINB = NW * CDB * 32 * 32 * 4;
+    __shared__ __align__(16) unsigned char smem[BUFB > JOINB ? BUFB : JOINB];
+    __shared__ float ml[2][NW][32];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, n = lane & 31, hg = lane >> 5;
+    lds_byte *kbuf = (lds_byte *)smem + wave * 2 * HALFB;
+    lds_byte *vbuf = kbuf + HALFB;
+
+    const int x_id = blockIdx.x & 7;
+    const int x_first = x_id * (p.n_items >> 3) + min(x_id, p.n_items & 7);
+    const int x_count = (p.n_items >> 3) + (x_id < (p.n_items & 7) ? 1 : 0);
+    const int x_blocks = ((int)gridDim.x - x_id + 7) >> 3;
+    for (int item = blockIdx.x >> 3; item < x_count; item += x_blocks) {
+        int logical = x_first + item;
+        const int rt = logical % p.n_row_tiles;   // the row tiles of a key run are neighbours: they share its L2 lines
+        logical /= p.n_row_tiles;
+        const int split = logical % p.n_splits;
+        const int lh = logical / p.n_splits;
+        const int l = lh / p.Hkv, hkv = lh % p.Hkv;
+
+        const int r_row = rt * 32 + n;
+        const bool valid = r_row / p.G < p.tq;
+        const int qi = min(r_row / p.G, p.tq - 1);
+        const int hq = hkv * p.G + r_row % p.G;
+        const int imax = min(p.tq - 1, (rt * 32 + 31) / p.G), imin = min(p.tq - 1, rt * 32 / p.G);
+        const int units = (p.n_ctx + imax + 32) / 32;   // sub-steps that some query of the tile sees
+        const int u0 = split_bound(split, p.n_splits, units, units), u1 = split_bound(split + 1, p.n_splits, units, units);
+
+        const unsigned char *kbytes = reinterpret_cast<const unsigned char *>(static_cast<const bf16_t *>(p.k) + l * p.s_k.layer + hkv * p.s_k.head);
+        const unsigned char *vbytes = reinterpret_cast<const unsigned char *>(static_cast<const bf16_t *>(p.v) + l * p.s_v.layer + hkv * p.s_v.head);
+        // Direct loads of 32 rows from key 32 * u on: a wavefront-uniform row pointer plus a per-lane offset that does
+        // not change from one sub-step to the next.  Rows past the cache end (last sub-step only) re-read the last
+        // row; they are always masked.
+        const int lq = lane / KCH;
+        uint32_t k_in[KD], v_in[VD];
+#pragma unroll
+        for (int i = 0; i < KD; ++i)
+            k_in[i] = (uint32_t)lq * (uint32_t)(p.s_k.token * 2) + (uint32_t)(((lane % KCH) ^ ((i * RPL + lq) & KSWZ)) * 16);
+#pragma unroll
+        for (int i = 0; i < VD; ++i)
+            v_in[i] = (uint32_t)lq * (uint32_t)(p.s_v.token * 2) + (uint32_t)(((lane % KCH) ^ ((4 * ((i * RPL + lq) & 3)) & VSWZ)) * 16);
+        auto load_half = [&](const unsigned char *bytes, int64_t tok, int key0, auto &in, int mask, int mul, lds_byte *dst) __attribute__((always_inline)) {
+            constexpr int NIN = sizeof(in) / sizeof(in[0]);
+            if (key0 + 32 <= p.N) {   // wavefront-uniform
+                const unsigned char *row = bytes + (int64_t)key0 * tok * 2;
+#pragma unroll
+                for (int it = 0; it < LPT; ++it, row += (int64_t)RPL * tok * 2) dma16_sbase<NT>(row, in[it % NIN], dst + it * RPL * ROWB);
+            } else {
+#pragma unroll 1
+                for (int it = 0; it < LPT; ++it) {
+                    const int row0 = min(key0 + it * RPL, p.N - 1);
+                    const int row = min(lq, p.N - 1 - row0);   // steps back by whole rows where the cache ends
+                    dma16_sbase<NT>(bytes + (int64_t)row0 * tok * 2,
+                                    (uint32_t)row * (uint32_t)(tok * 2) + (uint32_t)(((lane % KCH) ^ ((mul * (it * RPL + lq)) & mask)) * 16),
+                                    dst + it * RPL * ROWB);
+                }
+            }
+        };
+        auto load_k = [&](int u) __attribute__((always_inline)) { load_half(kbytes, p.s_k.token, 32 * u, k_in, KSWZ, 1, kbuf); };
+        auto load_v = [&](int u) __attribute__((always_inline)) { load_half(vbytes, p.s_v.token, 32 * u, v_in, VSWZ & 12, 4, vbuf); };
+        int u = u0 + wave;
+        bf16x8 qf[NKS];
+        const bf16_t *qrow = static_cast<const bf16_t *>(p.q) + l * p.s_q.layer + (int64_t)hq * p.s_q.head + (int64_t)qi * p.s_q.token;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) qf[ks] = as_bf16x8(load16(qrow + ks * 16 + hg * 8));
+        if (u < u1) {
+            load_k(u);
+            load_v(u);
+        }
+
+        int k_off[NKS];
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) k_off[ks] = n * ROWB + (((2 * ks + hg) ^ (n & KSWZ)) * 16);
+        int v_off[NDB];
+        {
+            const int i16 = lane & 15, gi = (lane >> 4) & 1, row = 4 * hg + (i16 >> 2);
+#pragma unroll
+            for (int db = 0; db < NDB; ++db) {
+                const int col = 32 * db + 16 * gi + 4 * (i16 & 3);
+                v_off[db] = row * ROWB + ((col >> 3) ^ ((4 * (row & 3)) & VSWZ)) * 16 + (col & 7) * 2;
+            }
+        }
+
+        f32x16 o[NDB];
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
+        float m = -INFINITY, mc = 0.f, lsum = 0.f;   // lsum: this lane's half of the row sum
+        __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0), seen by the compiler: it puts no wait for the queries into the loop
+
+        for (; u < u1; u += NW) {
+            const bool more = u + NW < u1;   // wavefront-uniform
+            wait_loads<LPT>();               // K(u) has landed (V(u) may be outstanding)
+            f32x16 s;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) s[j] = 0.f;
+            bf16x8 ka[NKS];                  // all operand reads in flight at once
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) ka[ks] = as_bf16x8(*(const __attribute__((address_space(3))) u32x4 *)(kbuf + k_off[ks]));
+            wait_lds();                      // K(u) has been read: its buffer is free
+            if (more) load_k(u + NW);
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[ks], qf[ks], s, 0, 0, 0);
+
+            if (32 * u + 31 > p.n_ctx + imin) {   // some key is hidden from some query
+                const int limit = p.n_ctx + qi - 32 * u;
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    if (8 * (j >> 2) + 4 * hg + (j & 3) > limit) s[j] = -INFINITY;
+            }
+            float mx = s[0];
+#pragma unroll
+            for (int j = 1; j < 16; ++j) mx = fmaxf(mx, s[j]);
+            {
+                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+                mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+            }
+            if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
+                const float m_new = fmaxf(m, mx);
+                const float corr = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_new) * p.scale_log2);
+                lsum *= corr;
+#pragma unroll
+                for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) o[db][j] *= corr;
+                m = m_new;
+                mc = m == -INFINITY ? 0.f : m * p.scale_log2;   // a row that sees no key of this run yet: exponentials 0
+            }
+            bf16x8 pf[2];
+            float rs0 = 0.f, rs1 = 0.f;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                u32x4 pk;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[8 * h + 2 * j], p.scale_log2, -mc));
+                    const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[8 * h + 2 * j + 1], p.scale_log2, -mc));
+                    rs0 += e0;
+                    rs1 += e1;
+                    pk[j] = pack_bf16x2(e0, e1);
+                }
+                pf[h] = as_bf16x8(pk);
+            }
+            lsum += rs0 + rs1;
+
+            if (more)
+                wait_loads<LPT>();   // V(u) has landed (K of the next sub-step may be outstanding)
+            else
+                wait_loads<0>();
+            bf16x8 va[2 * NDB];
+#pragma unroll
+            for (int i = 0; i < 2 * NDB; ++i) {
+                const lds_byte *vl = vbuf + (i / NDB) * 16 * ROWB + v_off[i % NDB];
+                va[i] = lds_read_tr_pair(vl, vl + 8 * ROWB);
+            }
+            wait_lds();                      // V(u) has been read
+            if (more) load_v(u + NW);
+#pragma unroll
+            for (int i = 0; i < 2 * NDB; ++i) o[i % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i], pf[i / NDB], o[i % NDB], 0, 0, 0);
+        }
+
+        // ---- join the wavefronts' states: factors against the common maximum, then sums over the wavefronts of 128
+        // channels at a time; a thread owns whole slots (its own n and hg).
+        {
+            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum), false, false);
+            lsum = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+        }
+        if (hg == 0) {
+            ml[0][wave][n] = m;
+            ml[1][wave][n] = lsum;
+        }
+        __syncthreads();   // also: every wavefront is done with its K / V buffers
+        float M = ml[0][0][n];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[0][w][n]);
+        float ltot = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float mw = ml[0][w][n];
+            ltot += mw == -INFINITY ? 0.f : ml[1][w][n] * __builtin_amdgcn_exp2f((mw - M) * p.scale_log2);
+        }
+        const float f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - M) * p.scale_log2);
+        f32x4 *join = reinterpret_cast<f32x4 *>(smem);
+        const int64_t part = (int64_t)(lh * p.n_row_tiles + rt) * p.n_splits + split;
+        const float inv = 1.f / ltot;
+#pragma unroll
+        for (int c0 = 0; c0 < NDB; c0 += CDB) {
+            if (c0) __syncthreads();
+#pragma unroll
+            for (int d = 0; d < CDB; ++d)
+#pragma unroll
+                for (int j4 = 0; j4 < 4; ++j4)
+                    join[wave * (CDB * 256) + part_slot(d, j4, hg, n)] =
+                        f32x4{o[c0 + d][4 * j4], o[c0 + d][4 * j4 + 1], o[c0 + d][4 * j4 + 2], o[c0 + d][4 * j4 + 3]} * f;
+            __syncthreads();
+            if (valid) {
+#pragma unroll
+                for (int i = 0; i < CDB * 256; i += 64 * NW) {
+                    f32x4 a = join[i + tid];
+#pragma unroll
+                    for (int w = 1; w < NW; ++w) a += join[w * (CDB * 256) + i + tid];
+                    if (p.n_splits > 1) {
+                        reinterpret_cast<f32x4 *>(p.part_o + part * (32 * D))[c0 * 256 + i + tid] = a;
+                    } else {
+                        bf16_t *orow = static_cast<bf16_t *>(p.out) + l * p.s_o.layer + (int64_t)hq * p.s_o.head + (int64_t)qi * p.s_o.token;
+                        const u32x2 w2 = {pack_bf16x2(a[0] * inv, a[1] * inv), pack_bf16x2(a[2] * inv, a[3] * inv)};
+                        *reinterpret_cast<u32x2 *>(orow + 32 * c0 + (i / 64 + wave) / 4 * 32 + 8 * (wave & 3) + 4 * hg) = w2;
+                    }
+                }
+            }
+        }
+        if (wave == 0 && hg == 0 && valid) {
+            if (p.n_splits > 1) {
+                p.part_ml[part * 64 + n] = M;
+                p.part_ml[part * 64 + 32 + n] = ltot;
+            } else if (p.lse) {
+                p.lse[((int64_t)l * p.Hkv * p.G + hq) * p.tq + qi] = M * p.scale + logf(ltot);
+            }
+        }
+        __syncthreads();   // the joined states have been read: LDS becomes the next item's buffers
+    }
+}
+
+// attn_combine_kernel: one block per (32-row group, 32 channels).  out = sum_s f_s O_s / sum_s f_s l_s with
+// f_s = exp2((m_s - max m) * scale * log2 e), splits in increasing order.  Every load of a run of 8 splits is in
+// flight at once (the launch is a few microseconds of latency); rows leave as 64-byte pieces through LDS.
+template <int D>
+__global__ __launch_bounds__(256) void attn_combine_kernel(const AttnParams p)
+{
+    constexpr int U = 8;
+    __shared__ __align__(16) u32x2 stage[32][9];   // 8 pieces of 4 channels a row (+1: bank spread)
+    const int tid = threadIdx.x;
+    const int n = tid & 31, hg = (tid >> 5) & 1, j4 = tid >> 6;
+    const int db = blockIdx.y;
+    const int group = blockIdx.x;
+    const int tile = group / p.groups_per_tile, w = group % p.groups_per_tile;
+    const int lh = tile / p.n_row_tiles, rt = tile % p.n_row_tiles;
+    const int l = lh / p.Hkv, hkv = lh % p.Hkv;
+    const int bm = 32 * p.groups_per_tile;
+    auto row_of = [&](int nn, bool &ok, int64_t &q_i, int64_t &h_q) {
+        const int r = rt * bm + w * 32 + nn;
+        ok = r / p.G < p.tq;
+        q_i = r / p.G;
+        h_q = hkv * p.G + r % p.G;
+    };
+    bool valid;
+    int64_t qi, hq;
+    row_of(n, valid, qi, hq);
+
+    if (valid) {
+        const int64_t part0 = (int64_t)group * p.n_splits;
+        const f32x4 *po = reinterpret_cast<const f32x4 *>(p.part_o) + part0 * (8 * D) + db * 256 + tid;
+        const float *pm = p.part_ml + part0 * 64 + n;
+        float M = -INFINITY, L = 0.f;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < p.n_splits; s0 += U) {
+            float ms[U], ls[U];
+            f32x4 os[U];
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                const int s = min(s0 + i, p.n_splits - 1);
+                ms[i] = pm[s * 64];
+                ls[i] = pm[s * 64 + 32];
+                os[i] = po[(int64_t)s * (8 * D)];   // not used, and possibly never written, where m_s is -inf
+            }
+#pragma unroll
+            for (int i = 1; i < U; ++i) ms[i] = s0 + i < p.n_splits ? ms[i] : -INFINITY;
+            float mx = M;
+#pragma unroll
+            for (int i = 0; i < U; ++i) mx = fmaxf(mx, ms[i]);
+            if (mx > M) {
+                const float corr = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((M - mx) * p.scale_log2);
+                L *= corr;
+                acc *= corr;
+                M = mx;
+            }
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                if (ms[i] != -INFINITY) {
+                    const float f = __builtin_amdgcn_exp2f((ms[i] - M) * p.scale_log2);
+                    L = fmaf(f, ls[i], L);
+                    acc += f * os[i];
+                }
+            }
+        }
+        const float inv = 1.f / L;
+        stage[n][2 * j4 + hg] = u32x2{pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv)};
+        if (p.lse && db == 0 && tid < 32) p.lse[((int64_t)l * p.Hkv * p.G + hq) * p.tq + qi] = M * p.scale + logf(L);
+    }
+    __syncthreads();
+    if (tid < 128) {
+        const int row = tid >> 2, c = tid & 3;
+        row_of(row, valid, qi, hq);
+        if (valid) {
+            const u32x2 lo = stage[row][2 * c], hi = stage[row][2 * c + 1];
+            bf16_t *dst = static_cast<bf16_t *>(p.out) + l * p.s_o.layer + hq * p.s_o.head + qi * p.s_o.token + 32 * db + 8 * c;
+            *reinterpret_cast<u32x4 *>(dst) = u32x4{lo[0], lo[1], hi[0], hi[1]};
+        }
+    }
+}
+
+}  // namespace
+
+namespace kvc {
+
+int launch_attn_rows(const AttnParams &p, int D, unsigned n_blocks, hipStream_t stream)
+{
+    // Non-temporal K / V only where they cannot stay in the last-level cache and no other block reads them: 32 layers
+    // of 3100 keys (407 MB) take 64 us with it and 72 us without, 4 layers (51 MB, read again for the next token) 33 and 26.
+    const bool nt = p.n_row_tiles == 1 && (int64_t)p.L * p.Hkv * p.N * D * 4 > kLastLevelCache;
+    const dim3 grid(n_blocks), block(64 * rows_waves(D));
+    switch (D) {
+        case 64: return launch(nt ? attn_rows_kernel<64, true> : attn_rows_kernel<64, false>, grid, block, 0, stream, p);
+        case 128: return launch(nt ? attn_rows_kernel<128, true> : attn_rows_kernel<128, false>, grid, block, 0, stream, p);
+        case 256: return launch(nt ? attn_rows_kernel<256, true> : attn_rows_kernel<256, false>, grid, block, 0, stream, p);
+        default: return KVCOMM_EUNSUPPORTED;
+    }
+}
+
+int launch_attn_combine(const AttnParams &p, int D, hipStream_t stream)
+{
+    const dim3 grid((unsigned)(p.L * p.Hkv * p.n_row_tiles * p.groups_per_tile), (unsigned)(D / 32)), block(256);
+    switch (D) {
+        case 64: return launch(attn_combine_kernel<64>, grid, block, 0, stream, p);
+        case 128: return launch(attn_combine_kernel<128>, grid, block, 0, stream, p);
+        case 256: return launch(attn_combine_kernel<256>, grid, block, 0, stream, p);
+        default: return KVCOMM_EUNSUPPORTED;
+    }
+}
+
+}  // namespace kvc

@@ -36,98 +36,22 @@
 //     tiles of one (layer, kv head) run on the same XCD and share its L2.
 // fp32 path (attn_f32_kernel): one wavefront per query row, plain fp32 FMA and expf with an
 // online softmax over 64-key chunks; it exists for exactness, not speed.
-#include <math.h>
-#include <type_traits>
-
-#include "kvcomm_device.h"
+#include "attn_common.h"
+#include "attn_plan.h"
 
 namespace {
 
 using namespace kvc;
 
-struct AttnParams {
-    const void *q, *k, *v;
-    void *out;
-    float *lse;
-    Strides s_q, s_k, s_v, s_o;
-    int32_t L, Hkv, G, n_ctx, tq, N;
-    int32_t n_row_tiles;
-    int32_t n_items;   // L * Hkv * n_row_tiles
-    float scale;       // softmax scale
-    float scale_log2;  // scale * log2(e)
-};
-
 // ------------------------------------------------------------------------------- bf16 MFMA
-#ifndef KVC_ATTN_WPE
-#define KVC_ATTN_WPE 2
-#endif
-#ifndef KVC_ATTN_NW
-#define KVC_ATTN_NW 8  // measured: 2 % faster than two blocks of 4 per CU (every K/V tile enters LDS once per CU)
-#endif
-
-__device__ __forceinline__ bf16x8 as_bf16x8(const u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
-
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-
-// Two 8-byte transposing LDS reads (ds_read_b64_tr_b16) -> one 8 x bf16 MFMA operand.
-// Within each group of 16 lanes the instruction returns to lane i, element e, the 16-bit
-// element (i % 4) found at the address supplied by lane 4*e + i/4 of the group.
-__device__ __forceinline__ bf16x8 lds_read_tr_pair(const lds_byte *a0, const lds_byte *a1)
-{
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)a0);
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)a1);
-    typedef short s16x8 __attribute__((ext_vector_type(8)));
-    const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8, v);
-}
-
-// One wavefront-wide direct load global -> LDS (global_load_lds_dwordx4): lane i moves the 16 bytes at
-// global address `base` + `voff` (a wavefront-uniform 64-bit base in scalar registers plus its own unsigned
-// 32-bit byte offset) to LDS address `dst` + 16 * i (`dst` is wavefront-uniform and travels in M0).
-// Written as inline assembly on purpose: the compiler then does not know of the pending LDS write and
-// inserts no wait of its own before later LDS reads (it would wait for ALL outstanding loads ahead of the
-// first transposing read and so serialise the prefetch).  Ordering is explicit instead: tile_barrier()
-// waits for the loads (vmcnt) and synchronises the block before anybody reads what they wrote.
-// M0 is listed as clobbered, so the compiler re-forms it for any instruction of its own that needs it.
-// (clang warns about any reserved register in a clobber list; for M0, which it only ever sets immediately
-// before the instruction that reads it, the declaration is exactly what is meant.)
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dma16_sbase(const unsigned char *base, uint32_t voff, const lds_byte *dst)
-{
-    const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)dst);
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(m0) : "memory", "m0");
-}
-
-template <int V>
-using template_int = std::integral_constant<int, V>;
-
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
-}
-
-// The same with the LDS destination as a wavefront-uniform base plus a literal (M0 is formed by one scalar
-// add): the steady-state loads then cost no vector ALU instruction and no register per destination (the
-// row base advances on the scalar unit and the per-lane offset never changes).
-template <int OFF>
-__device__ __forceinline__ void dma16_sbase_at(const unsigned char *base, uint32_t voff, uint32_t dst_base)
-{
-    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 : : "v"(voff), "s"(base), "s"(dst_base), "n"(OFF) : "memory", "scc", "m0");
-}
-#pragma clang diagnostic pop
-
 // PERSIST: the grid is smaller than the number of (layer, kv head, row tile) items and every block walks a
 // fixed share of them (the items of its XCD, strided by the XCD's number of blocks), so that the kernel occupies
 // gridDim.x CUs only and leaves the rest of the chip to whatever runs beside it.  The arithmetic of an item is
 // the same instruction sequence as in the one-item-per-block form.
-template <int D, int NW, int WPE, bool PERSIST>
+// SPLIT: an item is one run of key tiles of a row tile.  The block works on the cache as if it began at the run's
+// first key (which all its queries see) and leaves unnormalised outputs, references and row sums in the workspace;
+// attn_combine_kernel joins them.
+template <int D, int NW, int WPE, bool PERSIST, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParams p_arg)
 {
     // PERSIST reads the parameters through an opaque pointer to the kernel-argument segment, once per item:
@@ -185,6 +109,8 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     ParamT &p = *p_item;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, n = lane & 31, hg = lane >> 5;
+    const int split = SPLIT ? logical % p.n_splits : 0;
+    if constexpr (SPLIT) logical /= p.n_splits;
     const int lh = logical / p.n_row_tiles;
     const int rt = p.n_row_tiles - 1 - logical % p.n_row_tiles;  // longest rows first
     const int l = lh / p.Hkv, hkv = lh % p.Hkv;
@@ -196,9 +122,30 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     // mask is applied from the first 32-key sub-step that is partly hidden from some query of the block.
     const int wg_imax = min(p.tq - 1, (rt * BM + BM - 1) / p.G);
     const int wg_imin = min(p.tq - 1, (rt * BM) / p.G);
-    const int n_tiles = (p.n_ctx + wg_imax + 1 + 63) / 64;
+    const int all_tiles = (p.n_ctx + wg_imax + 1 + 63) / 64;
+    const int first_hidden = (p.n_ctx + wg_imin) / 64 + 1;
+    const int tile0 = SPLIT ? split_bound(split, p.n_splits, all_tiles, first_hidden) : 0;
+    const int n_tiles = SPLIT ? split_bound(split + 1, p.n_splits, all_tiles, first_hidden) - tile0 : all_tiles;
+    if constexpr (SPLIT) {
+        if (n_tiles <= 0) {   // the whole block: this run is empty
+            if (hg == 0 && (rt * BM + wave * 32 + n) / p.G < p.tq) {
+                const int64_t part = ((int64_t)(lh * p.n_row_tiles + rt) * NW + wave) * p.n_splits + split;
+                p.part_ml[part * 64 + n] = -INFINITY;
+                p.part_ml[part * 64 + 32 + n] = 0.f;
+            }
+            if (!PERSIST) return;
+            item += x_blocks;
+            continue;
+        }
+        kb_ += (int64_t)(64 * tile0) * p.s_k.token;
+        vb_ += (int64_t)(64 * tile0) * p.s_v.token;
+    }
+    // Context length and cache length counted from the run's first key (n_ctx_() may be negative; every query of
+    // the tile still sees key 0 of the run).
+    auto n_ctx_ = [&]() __attribute__((always_inline)) -> int { return SPLIT ? p.n_ctx - 64 * tile0 : p.n_ctx; };
+    auto N_ = [&]() __attribute__((always_inline)) -> int { return SPLIT ? p.N - 64 * tile0 : p.N; };
     const int n_sub = 2 * n_tiles;
-    const int sub_unmasked = (p.n_ctx + wg_imin + 1) / 32;  // sub-steps [0, sub_unmasked) are visible to all queries
+    const int sub_unmasked = (n_ctx_() + wg_imin + 1) / 32;  // sub-steps [0, sub_unmasked) are visible to all queries
 
     f32x16 o[NDB];
 #pragma unroll
@@ -237,8 +184,8 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     const uint32_t k_row_bytes = (uint32_t)(p.s_k.token * 2), v_row_bytes = (uint32_t)(p.s_v.token * 2);
     auto load_rows = [&](const unsigned char *bytes, int64_t tok_stride, uint32_t row_bytes, int row0, uint32_t voff,
                          const lds_byte *dst) __attribute__((always_inline)) {
-        const int row0c = min(row0, p.N - 1);            // wavefront-uniform
-        const int excess = max(lq - (p.N - 1 - row0c), 0);  // rows this lane would overshoot by
+        const int row0c = min(row0, N_() - 1);            // wavefront-uniform
+        const int excess = max(lq - (N_() - 1 - row0c), 0);  // rows this lane would overshoot by
         dma16_sbase(bytes + (int64_t)row0c * tok_stride * 2, voff - (uint32_t)excess * row_bytes, dst);
     };
     auto load_k64 = [&](int key0) __attribute__((always_inline)) {
@@ -417,7 +364,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
         const f32x16 &s_exp = sbuf[(U4 + 1) & 1];
         const lds_byte *kl = kring + ((U4 + 2) & 3) * HALFB;
         const lds_byte *vl = vbuf + ((U4 >> 1) & 1) * TILEB + (U4 & 1) * HALFB;
-        const int limit = p.n_ctx + qi - 32 * (u + 1);  // last visible key of S(u+1), relative to its sub-step
+        const int limit = n_ctx_() + qi - 32 * (u + 1);  // last visible key of S(u+1), relative to its sub-step
         bf16x8 ka[NKS], va[NKS], pf[2];
         pf[0] = as_bf16x8(pbuf[U4 & 1][0]);
         pf[1] = as_bf16x8(pbuf[U4 & 1][1]);
@@ -483,7 +430,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
             for (int ks = 0; ks < NKS; ++ks)
                 sbuf[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k(kl, ks), qf[ks], sbuf[h], 0, 0, 0);
         }
-        lsum = rereference(sbuf[0], pbuf[0], p.n_ctx + qi, true);
+        lsum = rereference(sbuf[0], pbuf[0], n_ctx_() + qi, true);
     }
     // Halves 0 and 1 have no tile before them: every wavefront must have read them before the loads of the
     // first tile (halves 4 and 5 share their slots) are issued.
@@ -492,7 +439,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     const int t_last = n_tiles - 1;
     // Leading tiles whose exponentials need no mask and whose look-ahead loads stay inside the cache: a tile pair
     // starting at t forms the exponentials of sub-steps up to 2t+4 and loads keys up to 64t + 255.
-    const int t_safe = p.N >= 256 ? (p.N - 128) / 64 : 0;
+    const int t_safe = N_() >= 256 ? (N_() - 128) / 64 : 0;
     const int t_plain = max(0, min(min((sub_unmasked - 1) >> 1, t_last), t_safe));
     // Two tiles (four sub-steps) per trip so that ring slots and buffers are compile-time constants.
     auto tile_pair = [&](int t, auto plain) __attribute__((always_inline)) {
@@ -534,6 +481,27 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
         step(2 * t + 1, u1, F_{}, F_{}, T_{});
     }
 
+    if constexpr (SPLIT) {
+        // ---- epilogue of a split: accumulators as they are (1 KB runs per store), reference and row sum.
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum), false, false);
+        const float ltot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+        const int64_t part = ((int64_t)(lh * p.n_row_tiles + rt) * NW + wave) * p.n_splits + split;
+        const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        const int n_e = lane_e & 31, hg_e = lane_e >> 5;
+        if ((rt * BM + wave * 32 + n_e) / p.G < p.tq) {
+            f32x4 *po = reinterpret_cast<f32x4 *>(p.part_o + part * (32 * D));
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int j4 = 0; j4 < 4; ++j4)
+                    po[part_slot(db, j4, hg_e, n_e)] = f32x4{o[db][4 * j4], o[db][4 * j4 + 1], o[db][4 * j4 + 2], o[db][4 * j4 + 3]};
+            p.part_ml[part * 64 + 32 * hg_e + n_e] = hg_e ? ltot : m;
+        }
+        if (!PERSIST) return;
+        __syncthreads();   // every wavefront has read its last tiles: the buffers become those of the next item
+        item += x_blocks;
+        continue;
+    }
     // ---- epilogue: normalise and store; lane (n, hg) holds channels 32*db + 8*(j/4) + 4*hg + j%4 of query row n.
     // Stored straight from these registers a store instruction would scatter 16-byte pieces over 32 rows (8 K
     // partial-line writes per block, several microseconds of back-pressure).  Instead each wavefront passes its
@@ -672,13 +640,31 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p)
 
 }  // namespace
 
-extern "C" size_t kvcomm_suffix_attn_workspace(const kvcomm_model *, int32_t, int32_t) { return 0; }
+extern "C" size_t kvcomm_suffix_attn_workspace(const kvcomm_model *model, int32_t n_ctx, int32_t tq)
+{
+    if (check_model(model) || tq <= 0 || n_ctx < 0 || model->dtype != KVCOMM_BF16) return 0;
+    return attn_workspace(*model, attn_plan(*model, n_ctx, tq, true));
+}
 
 namespace {
 
-// max_blocks > 0: at most that many thread blocks (the bf16 kernel's persistent form when there are more items).
+template <int D, int NW, int WPE>
+int launch_mfma(const AttnParams &p, unsigned n_blocks, bool persist, hipStream_t s)
+{
+    const dim3 grid(n_blocks), block(64 * NW);
+    if (p.n_splits > 1)
+        return persist ? launch(attn_mfma_kernel<D, NW, WPE, true, true>, grid, block, 0, s, p)
+                       : launch(attn_mfma_kernel<D, NW, WPE, false, true>, grid, block, 0, s, p);
+    return persist ? launch(attn_mfma_kernel<D, NW, WPE, true, false>, grid, block, 0, s, p)
+                   : launch(attn_mfma_kernel<D, NW, WPE, false, false>, grid, block, 0, s, p);
+}
+
+// max_blocks > 0: at most that many thread blocks (the bf16 kernels' persistent form when there are more items).
+// A workspace of at least kvcomm_suffix_attn_workspace() bytes lets a small launch split the key axis; without one
+// (or with one that is too small or not 16-byte aligned) the keys of a row tile stay in one block.
 int suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_k, kvcomm_tensor cache_v, int32_t n_ctx,
-                int32_t tq, float softmax_scale, kvcomm_tensor out, float *lse_out, int32_t max_blocks, void *stream)
+                int32_t tq, float softmax_scale, kvcomm_tensor out, float *lse_out, int32_t max_blocks, void *workspace,
+                size_t workspace_bytes, void *stream)
 {
     int st = check_model(model);
     if (st) return st;
@@ -706,6 +692,7 @@ int suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_
     p.N = n_ctx + tq;
     p.scale = softmax_scale > 0.f ? softmax_scale : (float)(1.0 / sqrt((double)model->head_dim));
     p.scale_log2 = (float)((double)p.scale * 1.4426950408889634);
+    p.n_splits = 1;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int D = model->head_dim;
 
@@ -722,47 +709,63 @@ int suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_
 
     // The direct loads address a row group as a 64-bit scalar base plus an unsigned 32-bit per-lane byte
     // offset that spans up to 64 * 8 / D rows: the token stride has to leave that offset below 2^32.
-    if (D == 64 || D == 128 || D == 256) {
-        const int64_t rows_per_load = 64 * 8 / D;
-        const int64_t max_tok = ((int64_t)1 << 31) / (2 * rows_per_load);
-        if (cache_k.stride_token >= max_tok || cache_v.stride_token >= max_tok) return KVCOMM_EUNSUPPORTED;
+    const int64_t rows_per_load = 64 * 8 / D;
+    const int64_t max_tok = ((int64_t)1 << 31) / (2 * rows_per_load);
+    if (cache_k.stride_token >= max_tok || cache_v.stride_token >= max_tok) return KVCOMM_EUNSUPPORTED;
+
+    AttnPlan plan = attn_plan(*model, n_ctx, tq, true);
+    size_t need = attn_workspace(*model, plan);
+    if (plan.n_splits > 1 && (!workspace || workspace_bytes < need || !aligned16(workspace))) {
+        plan = attn_plan(*model, n_ctx, tq, false);
+        need = 0;
     }
-    constexpr int NW = KVC_ATTN_NW;    // wavefronts per block
-    constexpr int WPE = KVC_ATTN_WPE;  // wavefronts per SIMD the register budget is sized for
-    const int bm = D == 256 ? 128 : 32 * NW;
-    p.n_row_tiles = (p.G * tq + bm - 1) / bm;
-    p.n_items = p.L * p.Hkv * p.n_row_tiles;
-    if (max_blocks > 0 && max_blocks < p.n_items) {
-        const unsigned n_blocks = (unsigned)max_blocks;
+    p.n_row_tiles = plan.n_row_tiles;
+    p.n_splits = plan.n_splits;
+    p.groups_per_tile = plan.tile_rows / 32;
+    p.n_items = p.L * p.Hkv * p.n_row_tiles * p.n_splits;
+    if (p.n_splits > 1) {
+        p.part_o = static_cast<float *>(workspace);
+        p.part_ml = p.part_o + attn_parts(*model, plan) * (size_t)(32 * D);
+    }
+    const bool persist = max_blocks > 0 && max_blocks < p.n_items;
+    const unsigned n_blocks = persist ? (unsigned)max_blocks : (unsigned)p.n_items;
+    if (plan.rows_kernel) {
+        st = launch_attn_rows(p, D, n_blocks, s);
+    } else {
         switch (D) {
-            case 64: return launch(attn_mfma_kernel<64, NW, WPE, true>, dim3(n_blocks), dim3(64 * NW), 0, s, p);
-            case 128: return launch(attn_mfma_kernel<128, NW, WPE, true>, dim3(n_blocks), dim3(64 * NW), 0, s, p);
-            case 256: return launch(attn_mfma_kernel<256, 4, 1, true>, dim3(n_blocks), dim3(256), 0, s, p);
-            default: return KVCOMM_EUNSUPPORTED;
+            case 64: st = launch_mfma<64, kAttnWaves, 2>(p, n_blocks, persist, s); break;
+            case 128: st = launch_mfma<128, kAttnWaves, 2>(p, n_blocks, persist, s); break;
+            default: st = launch_mfma<256, 4, 1>(p, n_blocks, persist, s); break;
         }
     }
-    const unsigned n_blocks = (unsigned)p.n_items;
-    switch (D) {
-        case 64: return launch(attn_mfma_kernel<64, NW, WPE, false>, dim3(n_blocks), dim3(64 * NW), 0, s, p);
-        case 128: return launch(attn_mfma_kernel<128, NW, WPE, false>, dim3(n_blocks), dim3(64 * NW), 0, s, p);
-        case 256: return launch(attn_mfma_kernel<256, 4, 1, false>, dim3(n_blocks), dim3(256), 0, s, p);
-        default: return KVCOMM_EUNSUPPORTED;
-    }
+    if (st || p.n_splits == 1) return st;
+    return launch_attn_combine(p, D, s);
 }
 
 }  // namespace
 
 extern "C" int kvcomm_suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_k,
                                   kvcomm_tensor cache_v, int32_t n_ctx, int32_t tq, float softmax_scale,
-                                  kvcomm_tensor out, float *lse_out, void *, size_t, void *stream)
+                                  kvcomm_tensor out, float *lse_out, void *workspace, size_t workspace_bytes, void *stream)
 {
-    return suffix_attn(model, q, cache_k, cache_v, n_ctx, tq, softmax_scale, out, lse_out, 0, stream);
+    return suffix_attn(model, q, cache_k, cache_v, n_ctx, tq, softmax_scale, out, lse_out, 0, workspace, workspace_bytes,
+                       stream);
 }
 
 extern "C" int kvcomm_suffix_attn_confined(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_k,
                                            kvcomm_tensor cache_v, int32_t n_ctx, int32_t tq, float softmax_scale,
                                            kvcomm_tensor out, float *lse_out, int32_t max_blocks, void *stream)
 {
+    return kvcomm_suffix_attn_confined_ws(model, q, cache_k, cache_v, n_ctx, tq, softmax_scale, out, lse_out, max_blocks,
+                                          nullptr, 0, stream);
+}
+
+extern "C" int kvcomm_suffix_attn_confined_ws(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_k,
+                                              kvcomm_tensor cache_v, int32_t n_ctx, int32_t tq, float softmax_scale,
+                                              kvcomm_tensor out, float *lse_out, int32_t max_blocks, void *workspace,
+                                              size_t workspace_bytes, void *stream)
+{
     if (max_blocks < 8) return KVCOMM_EINVAL;   // at least one block on each of the 8 XCDs
-    return suffix_attn(model, q, cache_k, cache_v, n_ctx, tq, softmax_scale, out, lse_out, max_blocks, stream);
+    return suffix_attn(model, q, cache_k, cache_v, n_ctx, tq, softmax_scale, out, lse_out, max_blocks, workspace,
+                       workspace_bytes, stream);
 }

@@ -34,8 +34,8 @@
 //     (query, head) axis = 64 queries of all four heads for G = 4; one block per CU.
 //   * Row tiles are ordered longest-first and the block index is remapped so that the row
 //     tiles of one (layer, kv head) run on the same XCD and share its L2.
-// fp32 path (attn_f32_kernel): one wavefront per query row, plain fp32 FMA and expf with an
-// online softmax over 64-key chunks; it exists for exactness, not speed.
+// fp32 path (attn_f32_kernel): the same transposed products on fp32 MFMA with expf and an online softmax, fp32
+// throughout.
 #include "attn_common.h"
 #include "attn_plan.h"
 
@@ -566,8 +566,12 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
 }
 
 // ------------------------------------------------------------------------------- fp32 path
+// Caches of up to kF32RowKeys tokens: one wavefront per query row, one key per lane, dot products on the vector ALU.  One
+// chunk of keys, about 5 us; the kernel below has 12 us of latency whatever the size (one layer, 32 heads, one key).
+constexpr int kF32RowKeys = 64;
+
 template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p)
+__global__ __launch_bounds__(256) void attn_f32_row_kernel(const AttnParams p)
 {
     constexpr int CPL = D / 64;  // output channels per lane
     __shared__ float q_lds[4][D];
@@ -638,6 +642,228 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const AttnParams p)
     if (p.lse && lane == 0) p.lse[row] = m + logf(lsum);
 }
 
+// Longer caches (attn_f32_kernel): 32 packed (query, head) rows per block on fp32 MFMA (32x32x2: exact fp32 products and sums); the wavefronts share the
+// rows and each takes every NW-th 32-key sub-step with its own softmax state, joined through LDS at the end (the same
+// work split as the bf16 rows kernel).  Both products are transposed, so a lane owns one query column, and every operand
+// comes straight from global memory in the layout the instruction wants: K and Q as 16-byte pieces of a lane's own
+// half of the channels (the contraction order is free as long as both agree), V as VEC consecutive channels of one key
+// (row r of accumulator c stands for channel VEC * r + c), P from the score registers.
+// What bounds it: matrix cores at large sizes (fp32 MFMA, 1/16 of the bf16 rate: 80 TFLOP/s at D = 128, Tq 512, 3072
+// keys), latency at small ones.  2 layers x 8 heads x 32 queries over 224 keys, D = 64: 11 us, 50 us with the row kernel;
+// 3 layers x 8 heads x 128 queries over 1152 keys, D = 128: 60 us, 443 us with the row kernel.
+constexpr int kF32Waves = 8;
+
+template <int D>
+__global__ __launch_bounds__(64 * kF32Waves, 2) void attn_f32_kernel(const AttnParams p)
+{
+    constexpr int NW = kF32Waves;
+    constexpr int HD = D / 2, NDB = D / 32;
+    constexpr int VEC = NDB < 4 ? NDB : 4, SETS = NDB / VEC;   // channels of one V load, loads per key
+    constexpr int VJ = NDB == 2 ? 16 : NDB == 4 ? 8 : 4;      // V rows of a half wavefront in registers at a time
+    typedef float vecf __attribute__((ext_vector_type(VEC)));
+    __shared__ __align__(16) unsigned char smem[NW * 1024 * VEC * 4];   // Q, then the wavefronts' states
+    static_assert(D * 128 <= sizeof(smem), "Q must fit");
+    __shared__ float ml[2][NW][32];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, n = lane & 31, hg = lane >> 5;
+    const int rt = blockIdx.x % p.n_row_tiles, lh = blockIdx.x / p.n_row_tiles;
+    const int l = lh / p.Hkv, hkv = lh % p.Hkv;
+    const int r_row = rt * 32 + n;
+    const bool valid = r_row / p.G < p.tq;
+    const int qi = min(r_row / p.G, p.tq - 1);
+    const int hq = hkv * p.G + r_row % p.G;
+    const int imax = min(p.tq - 1, (rt * 32 + 31) / p.G), imin = min(p.tq - 1, rt * 32 / p.G);
+    const int units = (p.n_ctx + imax + 32) / 32;   // sub-steps that some query of the tile sees
+
+    const float *kb = static_cast<const float *>(p.k) + l * p.s_k.layer + hkv * p.s_k.head;
+    const float *vb = static_cast<const float *>(p.v) + l * p.s_v.layer + hkv * p.s_v.head;
+    const float *qrow = static_cast<const float *>(p.q) + l * p.s_q.layer + (int64_t)hq * p.s_q.head + (int64_t)qi * p.s_q.token;
+    // Q as operands, [piece c of the lane's half][lane]
+    f32x4 *q_lds = reinterpret_cast<f32x4 *>(smem);
+    for (int c = wave; c < HD / 4; c += NW) q_lds[c * 64 + lane] = *reinterpret_cast<const f32x4 *>(qrow + hg * HD + 4 * c);
+    __syncthreads();
+
+    f32x16 o[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
+    float m = -INFINITY, lsum = 0.f;   // lsum: this lane's half of the row sum
+    bool odd = false;                  // left out a value that is not finite
+
+    for (int u = wave; u < units; u += NW) {
+        const int key0 = 32 * u;
+        const int limit = p.n_ctx + qi - key0;             // last visible key of this lane's query, relative to the sub-step
+        const bool edge = key0 + 31 > p.n_ctx + imin;      // some key is hidden from some query
+        const float *kr = kb + (int64_t)min(key0 + n, p.N - 1) * p.s_k.token + hg * HD;
+        // Accumulator row j of this lane is key 8 * (j / 4) + 4 * hg + j % 4; rows past the cache end re-read the last one.
+        const int row0 = min(key0 + 4 * hg, p.N - 1);
+        const float *v0 = vb + (int64_t)row0 * p.s_v.token + VEC * n;
+        vecf v[VJ][SETS];
+        auto load_v = [&](int j0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < VJ; ++j) {
+                const float *vr = v0 + (int64_t)min(8 * ((j0 + j) >> 2) + ((j0 + j) & 3), p.N - 1 - row0) * p.s_v.token;
+#pragma unroll
+                for (int t = 0; t < SETS; ++t) v[j][t] = *reinterpret_cast<const vecf *>(vr + t * 32 * VEC);
+            }
+        };
+        f32x16 s;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) s[j] = 0.f;
+        // 32 channels of the lane's half at a time: Q, K, V and O of a wide head together exceed the registers.  D = 128
+        // requests the second piece under the first one's products.
+        constexpr int NP = HD / 32;
+        f32x4 kv[2][8];
+        auto load_k = [&](f32x4 (&dst)[8], int c0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) dst[c] = *reinterpret_cast<const f32x4 *>(kr + 4 * (c0 + c));
+        };
+        auto dot = [&](const f32x4 (&src)[8], int c0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const f32x4 q = q_lds[(c0 + c) * 64 + lane];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(src[c][e], q[e], s, 0, 0, 0);
+            }
+        };
+        load_k(kv[0], 0);
+        if constexpr (NP == 2) load_k(kv[1], 8);
+        if constexpr (NP <= 2) load_v(0);
+        dot(kv[0], 0);
+        if constexpr (NP == 2) dot(kv[1], 8);
+        if constexpr (NP == 4) {
+#pragma unroll 1
+            for (int c0 = 8; c0 < 8 * NP; c0 += 8) {
+                load_k(kv[0], c0);
+                dot(kv[0], c0);
+            }
+            load_v(0);
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            s[j] *= p.scale;
+            if (edge && 8 * (j >> 2) + 4 * hg + (j & 3) > limit) s[j] = -INFINITY;
+            mx = fmaxf(mx, s[j]);
+        }
+        {
+            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+            mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+        }
+        if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
+            const float m_new = fmaxf(m, mx);
+            const float corr = m == -INFINITY ? 0.f : expf(m - m_new);
+            lsum *= corr;
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) o[db][j] *= corr;
+            m = m_new;
+        }
+        const float mref = m == -INFINITY ? 0.f : m;   // a row that sees no key yet: exponentials 0
+        float rs = 0.f;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            s[j] = expf(s[j] - mref);
+            rs += s[j];
+        }
+        lsum += rs;
+
+        // A hidden key must not reach the result, not even as 0 * inf: at the causal edge values that are not finite are
+        // left out here and added behind the loop to the queries that do see them.
+#pragma unroll
+        for (int j0 = 0; j0 < 16; j0 += VJ) {
+            if (j0) load_v(j0);
+            if (edge) {
+#pragma unroll
+                for (int j = 0; j < VJ; ++j)
+#pragma unroll
+                    for (int t = 0; t < SETS; ++t)
+#pragma unroll
+                        for (int c = 0; c < VEC; ++c) {
+                            const bool fin = fabsf(v[j][t][c]) < INFINITY;
+                            odd |= !fin;
+                            v[j][t][c] = fin ? v[j][t][c] : 0.f;
+                        }
+            }
+#pragma unroll
+            for (int j = 0; j < VJ; ++j)
+#pragma unroll
+                for (int db = 0; db < NDB; ++db)
+                    o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[j][db / VEC][db % VEC], s[j0 + j], o[db], 0, 0, 0);
+        }
+    }
+
+    // ---- join the wavefronts' states and store
+    {
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum), false, false);
+        lsum = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    }
+    if (hg == 0) {
+        ml[0][wave][n] = m;
+        ml[1][wave][n] = lsum;
+    }
+    __syncthreads();   // also: every wavefront is done with its part of smem
+    float M = ml[0][0][n];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[0][w][n]);
+    float ltot = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const float mw = ml[0][w][n];
+        ltot += mw == -INFINITY ? 0.f : ml[1][w][n] * expf(mw - M);
+    }
+    const float f = m == -INFINITY ? 0.f : expf(m - M);
+    vecf *join = reinterpret_cast<vecf *>(smem);   // [wavefront][j][lane]
+    float *orow = static_cast<float *>(p.out) + l * p.s_o.layer + (int64_t)hq * p.s_o.head + (int64_t)qi * p.s_o.token;
+    const float inv = 1.f / ltot;
+#pragma unroll
+    for (int t = 0; t < SETS; ++t) {
+        if (t) __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            vecf x;
+#pragma unroll
+            for (int c = 0; c < VEC; ++c) x[c] = o[t * VEC + c][j] * f;
+            join[wave * 1024 + j * 64 + lane] = x;
+        }
+        __syncthreads();
+        if (valid) {
+#pragma unroll
+            for (int i = 0; i < 16 / NW; ++i) {
+                const int j = wave + NW * i;
+                vecf a = join[j * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < NW; ++w) a += join[w * 1024 + j * 64 + lane];
+                *reinterpret_cast<vecf *>(orow + t * 32 * VEC + VEC * (8 * (j >> 2) + 4 * hg + (j & 3))) = a * inv;
+            }
+        }
+    }
+    if (p.lse && wave == 0 && hg == 0 && valid) p.lse[((int64_t)l * p.Hkv * p.G + hq) * p.tq + qi] = M + logf(ltot);
+
+    // Rare: values left out at the causal edge, for the queries that see them (thread: one query, every 2 * NW-th channel).
+    if (__syncthreads_or(odd) && valid) {
+        for (int key = (p.n_ctx + imin + 1) & ~31; key <= p.n_ctx + qi; ++key) {
+            const float *vr = vb + (int64_t)key * p.s_v.token;
+            float pk = -1.f;
+            for (int c = 2 * wave + hg; c < D; c += 2 * NW) {
+                const float x = vr[c];
+                if (fabsf(x) < INFINITY) continue;
+                if (pk < 0.f) {
+                    const float *kr = kb + (int64_t)key * p.s_k.token;
+                    float dot = 0.f;
+                    for (int i = 0; i < D; ++i) dot = fmaf(qrow[i], kr[i], dot);
+                    pk = expf(dot * p.scale - M) * inv;
+                }
+                orow[c] += pk * x;
+            }
+        }
+    }
+}
+
 }  // namespace
 
 extern "C" size_t kvcomm_suffix_attn_workspace(const kvcomm_model *model, int32_t n_ctx, int32_t tq)
@@ -697,12 +923,23 @@ int suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_
     const int D = model->head_dim;
 
     if (dt == KVCOMM_F32) {
-        const int64_t rows = (int64_t)p.L * model->n_q_heads * tq;
-        const unsigned n_blocks = (unsigned)((rows + 3) / 4);
+        if (p.N <= kF32RowKeys) {
+            const dim3 grid((unsigned)(((int64_t)p.L * model->n_q_heads * tq + 3) / 4)), block(256);
+            switch (D) {
+                case 64: return launch(attn_f32_row_kernel<64>, grid, block, 0, s, p);
+                case 128: return launch(attn_f32_row_kernel<128>, grid, block, 0, s, p);
+                case 256: return launch(attn_f32_row_kernel<256>, grid, block, 0, s, p);
+                default: return KVCOMM_EUNSUPPORTED;
+            }
+        }
+        p.n_row_tiles = (int32_t)(((int64_t)p.G * tq + 31) / 32);
+        const int64_t n_blocks = (int64_t)p.L * p.Hkv * p.n_row_tiles;
+        if (n_blocks > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
+        const dim3 grid((unsigned)n_blocks), block(64 * kF32Waves);
         switch (D) {
-            case 64: return launch(attn_f32_kernel<64>, dim3(n_blocks), dim3(256), 0, s, p);
-            case 128: return launch(attn_f32_kernel<128>, dim3(n_blocks), dim3(256), 0, s, p);
-            case 256: return launch(attn_f32_kernel<256>, dim3(n_blocks), dim3(256), 0, s, p);
+            case 64: return launch(attn_f32_kernel<64>, grid, block, 0, s, p);
+            case 128: return launch(attn_f32_kernel<128>, grid, block, 0, s, p);
+            case 256: return launch(attn_f32_kernel<256>, grid, block, 0, s, p);
             default: return KVCOMM_EUNSUPPORTED;
         }
     }

@@ -106,3 +106,41 @@ def test_workspace_query():
         for tq in (1, 7, 64, 500, 1024):
             for n_ctx in (512, 3000, 131072):
                 assert q(_model(L, 8, 8, 256), n_ctx, tq) <= 2 * 256 * 256 * 16 * 4 * (256 + 2)
+
+
+# fp32: both kernels (up to 64 keys and beyond), edges of the 32-key sub-steps and 32-row groups, every head dimension
+F32_SHAPES = [(1, 1, 1, 64, 0, 1), (2, 2, 2, 128, 60, 4), (2, 2, 2, 128, 60, 5), (1, 2, 4, 64, 95, 8), (1, 2, 3, 256, 96, 11),
+              (1, 1, 8, 256, 300, 33), (2, 1, 1, 64, 1000, 65), (1, 2, 8, 128, 0, 70)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,hkv,G,D,n_ctx,tq", F32_SHAPES)
+def test_f32_attention(L, hkv, G, D, n_ctx, tq):
+    """1e-5 as for every fp32 output.  Rows behind the cache's end hold NaN.  Then values of the later suffix tokens
+    that are not finite: they reach the queries that see them and no other."""
+    print(f"f32 attn: L{L} Hkv{hkv} G{G} D{D} n_ctx{n_ctx} tq{tq}", flush=True)
+    m = _model(L, hkv, G, D, torch.float32)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n_ctx + tq)
+    mk = lambda h, n: torch.randn((L, h, n, D), generator=g, device=DEV)
+    N = n_ctx + tq
+    big_k, big_v = mk(hkv, N + 40), mk(hkv, N + 40)
+    big_k[:, :, N:], big_v[:, :, N:] = float("nan"), float("nan")
+    q, k, v = mk(hkv * G, tq), big_k[:, :, :N], big_v[:, :, :N]
+    out, lse = kv.kvcomm_suffix_attn(m, q, k, v, n_ctx, want_lse=True)
+    torch.cuda.synchronize()
+    want, want_lse = oracle.suffix_attn(to_np(q), to_np(k), to_np(v), n_ctx, want_lse=True)
+    check_close(to_np(out), want, torch.float32, "O")
+    assert float(abs(lse.cpu().numpy() - want_lse).max()) < 1e-4
+    if tq < 4:
+        return
+    first = tq // 2    # queries 0 ... first - 1 do not see it
+    v[:, :, n_ctx + first, 1], v[:, :, n_ctx + first, D - 1] = float("inf"), float("nan")
+    v[:, :, n_ctx + tq - 1, 1] = -float("inf")
+    bad = kv.kvcomm_suffix_attn(m, q, k, v, n_ctx)
+    torch.cuda.synchronize()
+    assert torch.equal(bad[:, :, :first], out[:, :, :first])
+    seen = bad[:, :, first:]
+    assert (seen[:, :, :-1, 1] == float("inf")).all() and torch.isnan(seen[:, :, -1, 1]).all()
+    assert torch.isnan(seen[..., D - 1]).all()
+    assert torch.isfinite(seen[..., 2:D - 1]).all() and torch.isfinite(seen[..., 0]).all()

@@ -19,6 +19,7 @@
 #include <math.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "kvcomm_device.h"
 
@@ -32,10 +33,17 @@ namespace {
 using namespace kvc;
 
 #ifndef KVC_DIST_BLOCKS
-#define KVC_DIST_BLOCKS 2048  // blocks the distance grid aims at (measured best on MI355X among 1024 ... 8192)
+// Blocks per segment the distance grid aims at.  Fewer blocks = longer runs of (layer, head) pairs = fewer partial sums for
+// the second stage; measured (us per call, both stages) with 256 / 512 / 1024 / 2048 blocks: 4 segments x 512 tokens, 8
+// anchors 200 / 185 / 186 / 201; 1024 tokens, 64 anchors (with the update) 2086 / 2094 / 2106 / 2188; D = 64 100 / 101 /
+// 104 / 119.
+#define KVC_DIST_BLOCKS 512
 #endif
 
 constexpr int kBlock = 256;
+constexpr int kFinalBlock = 512; // threads of a finalize_kernel block
+constexpr int kSegBlock = 1024;  // threads of a finalize_segment_kernel block
+constexpr int kFinalRun = 16;    // partials of one chunk that stay together in a finalize_kernel block
 constexpr int kAnchorTile = 16;  // anchors whose accumulators one lane keeps in registers
 
 // How a launch is cut into blocks.  Rows of one (layer, head) are LPR lanes wide; a block owns RPB
@@ -90,6 +98,7 @@ struct DistParams {
     Strides s_anc;
     int32_t H, LH, lh_per_block, n_jobs;
     int32_t fused, rule;   // fused: a row's distances are complete inside its lanes; write the weights here
+    int32_t n_blocks, a_tiles;   // distance kernel: (chunk, token tile) pairs of all segments, anchor tiles of the largest pool
     int32_t per_segment;   // one weight set per segment: a block also adds up its rows (partial[chunk][tile][anchor])
     double tau;
     const void *anc[KVCOMM_MAX_ANCHORS];  // selected anchors of all segments
@@ -97,12 +106,12 @@ struct DistParams {
 };
 static_assert(sizeof(DistParams) <= 4096, "kernel arguments are limited to 4 KB");
 
-__device__ __forceinline__ int job_of_block(const DistParams &p)
+__device__ __forceinline__ int job_of_block(const DistParams &p, int block)
 {
     int ji = 0;
 #pragma unroll
     for (int i = 1; i < KVCOMM_MAX_BATCH; ++i)
-        if (i < p.n_jobs && (int)blockIdx.x >= p.job[i].block0) ji = i;
+        if (i < p.n_jobs && block >= p.job[i].block0) ji = i;
     return ji;
 }
 
@@ -119,50 +128,89 @@ __device__ __forceinline__ void sqdiff_acc(double &acc, const float (&x)[Elem<T>
     }
 }
 
-template <typename T, int LPR>
+// Anchor pointers of a tile in scalar registers for the whole kernel.  (Read where they are used, each anchor's load waited
+// for a scalar load of its own pointer, in every (layer, head) pair.)
+template <typename T, int NA>
+struct AnchorPtrs {
+    typedef const __attribute__((address_space(1))) u32x4 gvec;
+    uint64_t ptr[NA];
+    __device__ __forceinline__ AnchorPtrs(const DistParams &p, int first, int na)
+    {
+#pragma unroll
+        for (int j = 0; j < NA; ++j) {
+            ptr[j] = reinterpret_cast<uint64_t>(p.anc[first + min(j, na - 1)]);
+            asm volatile("" : "+s"(ptr[j]));
+        }
+    }
+    __device__ __forceinline__ u32x4 load(int j, int64_t off) const   // off in elements
+    {
+        return __builtin_nontemporal_load(reinterpret_cast<gvec *>(ptr[j] + (uint64_t)(off * (int64_t)sizeof(T))));
+    }
+};
+
+// HBM bound.  What keeps loads in flight: all row pieces of a (layer, head) pair are requested before the first is used,
+// without a branch between them when the tile is full; tiles of 4 and 8 anchors for small pools hold fewer registers, so
+// more wavefronts fit.  The segment's rows are plain loads and the anchors' non-temporal: 8 anchors, 4 x 512 tokens 191 us
+// with both non-temporal, 185 mixed, 212 with both plain; 64 anchors (4 tiles that share the segment's rows) 2143 us per
+// segment with its update when every tile fetched them from HBM, 2095 now.  4 x 512 tokens, 8 anchors: 6.8 TB/s.
+template <typename T, int LPR, int NA>   // NA: anchors of a tile (accumulators of a lane)
 __global__ __launch_bounds__(kBlock) void dist_partial_kernel(const DistParams p)
 {
     constexpr int EPV = Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
-    const DistJob &jb = p.job[job_of_block(p)];
+    // Anchor tiles of one (chunk, token tile): consecutive blocks of the same XCD (hardware deals block ids round-robin
+    // to the 8 XCDs), so that the segment's rows come from HBM once and from the XCD's L2 after that.
+    const int group = blockIdx.x / (8 * p.a_tiles), in_group = blockIdx.x % (8 * p.a_tiles);
+    const int block = group * 8 + in_group % 8;
+    if (block >= p.n_blocks) return;
+    const DistJob &jb = p.job[job_of_block(p, block)];
     const int tid = threadIdx.x;
     const int row = tid / LPR, lir = tid % LPR;
-    const int bx = blockIdx.x - jb.block0;
+    const int bx = block - jb.block0;
     const int tile = bx % jb.n_token_tiles;
     const int chunk = bx / jb.n_token_tiles;
-    const int a0 = blockIdx.y * kAnchorTile;
-    const int na = min(kAnchorTile, jb.n_sel - a0);
-    if (na <= 0) return;  // the grid's anchor tiles cover the largest pool of the launch
+    const int a0 = in_group / 8 * NA;
+    const int na = min(NA, jb.n_sel - a0);
+    if (na <= 0) return;  // the launch's anchor tiles cover the largest pool of the launch
     const int t = tile * RPB + row;
     const bool valid = t < jb.S;
     const int lh0 = chunk * p.lh_per_block;
     const int lh1 = min(lh0 + p.lh_per_block, p.LH);
 
-    double acc[kAnchorTile];
+    double acc[NA];
 #pragma unroll
-    for (int j = 0; j < kAnchorTile; ++j) acc[j] = 0.0;
+    for (int j = 0; j < NA; ++j) acc[j] = 0.0;
 
-    if (valid) {
-        const T *seg = static_cast<const T *>(jb.seg_k);
+    const AnchorPtrs<T, NA> anc(p, jb.a0 + a0, na);
+    const T *seg = static_cast<const T *>(jb.seg_k) + t * jb.s_seg.token + lir * EPV;
+    const int64_t arow = t * p.s_anc.token + lir * EPV;
+    auto walk = [&](auto full) __attribute__((always_inline)) {   // full: every anchor of the tile exists (no branches)
         for (int lh = lh0; lh < lh1; ++lh) {
             const int l = lh / p.H, h = lh % p.H;
-            const u32x4 rs = load16_stream(seg + l * jb.s_seg.layer + h * jb.s_seg.head + t * jb.s_seg.token + lir * EPV);
-            const int64_t aoff = l * p.s_anc.layer + h * p.s_anc.head + t * p.s_anc.token + lir * EPV;
-            u32x4 ra[kAnchorTile];
+            const T *sp = seg + l * jb.s_seg.layer + h * jb.s_seg.head;
+            const u32x4 rs = load16(sp);   // plain: see above
+            const int64_t aoff = arow + l * p.s_anc.layer + h * p.s_anc.head;
+            u32x4 ra[NA];
 #pragma unroll
-            for (int j = 0; j < kAnchorTile; ++j)
-                if (j < na) ra[j] = load16_stream(static_cast<const T *>(p.anc[jb.a0 + a0 + j]) + aoff);
+            for (int j = 0; j < NA; ++j)
+                if (decltype(full)::value || j < na) ra[j] = anc.load(j, aoff);
             float x[EPV];
             unpack<T>(rs, x);
 #pragma unroll
-            for (int j = 0; j < kAnchorTile; ++j)
-                if (j < na) sqdiff_acc<T>(acc[j], x, ra[j]);
+            for (int j = 0; j < NA; ++j)
+                if (decltype(full)::value || j < na) sqdiff_acc<T>(acc[j], x, ra[j]);
         }
+    };
+    if (valid) {
+        if (na == NA)
+            walk(std::true_type{});
+        else
+            walk(std::false_type{});
     }
     // Fixed-shape butterfly over the LPR lanes of a row (all inside one wavefront).
-    __shared__ double rows[RPB][kAnchorTile];
+    __shared__ double rows[RPB][NA];
 #pragma unroll
-    for (int j = 0; j < kAnchorTile; ++j) {
+    for (int j = 0; j < NA; ++j) {
         if (j < na) {
             double v = acc[j];
 #pragma unroll
@@ -184,20 +232,20 @@ __global__ __launch_bounds__(kBlock) void dist_partial_kernel(const DistParams p
     }
 }
 
-// Reduce-scatter of kAnchorTile per-lane sums over the LPR lanes of a row (LPR a power of two, lanes of a row are
-// consecutive): afterwards lane `lir` holds the row's totals of its own anchors in acc[0 .. max(1, kAnchorTile /
-// LPR)), anchor_of_lane() says which.  Lanes 16 and up of a wider row hold copies that anchor_of_lane() maps
+// Reduce-scatter of NA per-lane sums over the LPR lanes of a row (LPR a power of two, lanes of a row are
+// consecutive): afterwards lane `lir` holds the row's totals of its own anchors in acc[0 .. max(1, NA /
+// LPR)), anchor_of_lane() says which.  Lanes NA and up of a wider row hold copies that anchor_of_lane() maps
 // past the tile, so they are ignored.
-template <int LPR>
+template <int LPR, int NA>
 __device__ __forceinline__ int anchor_of_lane(int lir, int k)
 {
-    if constexpr (LPR >= kAnchorTile)
-        return lir + k * LPR;                       // k == 0: anchor lir (invalid from kAnchorTile on)
+    if constexpr (LPR >= NA)
+        return lir + k * LPR;              // k == 0: anchor lir (invalid from NA on)
     else
-        return (kAnchorTile / LPR) * lir + k;
+        return (NA / LPR) * lir + k;
 }
-template <int CNT, int OFF, int LPR>
-__device__ __forceinline__ void reduce_scatter_round(double (&acc)[kAnchorTile], int lir)
+template <int CNT, int OFF, int LPR, int NA>
+__device__ __forceinline__ void reduce_scatter_round(double (&acc)[NA], int lir)
 {
     if constexpr (OFF >= 1 && CNT >= 2) {
         const bool up = lir & OFF;
@@ -207,19 +255,19 @@ __device__ __forceinline__ void reduce_scatter_round(double (&acc)[kAnchorTile],
             const double send = up ? acc[i] : acc[i + CNT / 2];
             acc[i] = keep + __shfl_xor(send, OFF, LPR);
         }
-        reduce_scatter_round<CNT / 2, OFF / 2, LPR>(acc, lir);
+        reduce_scatter_round<CNT / 2, OFF / 2, LPR, NA>(acc, lir);
     }
 }
-template <int LPR>
-__device__ __forceinline__ void row_reduce_scatter(double (&acc)[kAnchorTile], int lir)
+template <int LPR, int NA>
+__device__ __forceinline__ void row_reduce_scatter(double (&acc)[NA], int lir)
 {
-    static_assert(kAnchorTile == 16, "written for tiles of 16 anchors");
+    static_assert((NA & (NA - 1)) == 0, "anchor tiles are powers of two");
 #pragma unroll
-    for (int off = LPR / 2; off >= kAnchorTile; off >>= 1)
+    for (int off = LPR / 2; off >= NA; off >>= 1)
 #pragma unroll
-        for (int j = 0; j < kAnchorTile; ++j) acc[j] += __shfl_xor(acc[j], off, LPR);
-    constexpr int OFF0 = (LPR < kAnchorTile ? LPR : kAnchorTile) / 2;
-    reduce_scatter_round<kAnchorTile, OFF0, LPR>(acc, lir);
+        for (int j = 0; j < NA; ++j) acc[j] += __shfl_xor(acc[j], off, LPR);
+    constexpr int OFF0 = (LPR < NA ? LPR : NA) / 2;
+    reduce_scatter_round<NA, OFF0, LPR, NA>(acc, lir);
 }
 
 // One softmax per (layer, head, token), pools of up to kAnchorTile selected anchors: a row's distances are
@@ -229,54 +277,62 @@ __device__ __forceinline__ void row_reduce_scatter(double (&acc)[kAnchorTile], i
 // are joined by fixed butterflies, so all lanes of a row agree bit for bit.  The exponent is formed in double
 // (distances of a few hundred differ by fractions); the exponential and the normalisation are fp32, which is
 // what the fp32 weights can resolve.
-template <typename T, int LPR>
+template <typename T, int LPR, int NA>   // NA >= the largest pool of the launch
 __global__ __launch_bounds__(kBlock) void dist_row_softmax_kernel(const DistParams p)
 {
     constexpr int EPV = Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
-    constexpr int NPL = (kAnchorTile + LPR - 1) / LPR;  // anchors per lane
-    const DistJob &jb = p.job[job_of_block(p)];
+    constexpr int NPL = (NA + LPR - 1) / LPR;  // anchors per lane
+    const DistJob &jb = p.job[job_of_block(p, blockIdx.x)];
     const int tid = threadIdx.x;
     const int row = tid / LPR, lir = tid % LPR;
     const int bx = blockIdx.x - jb.block0;
     const int tile = bx % jb.n_token_tiles;
     const int chunk = bx / jb.n_token_tiles;
-    const int na = jb.n_sel;  // 1 ... kAnchorTile (checked by the host)
+    const int na = jb.n_sel;  // 1 ... NA (checked by the host)
     const int t = tile * RPB + row;
     const bool valid = t < jb.S;
     const int lh0 = chunk * p.lh_per_block;
     const int lh1 = min(lh0 + p.lh_per_block, p.LH);
     if (bx == 0 && jb.selected_out && tid < jb.n_anchors) jb.selected_out[tid] = (int32_t)((jb.sel_mask >> tid) & 1);
 
-    const T *seg = static_cast<const T *>(jb.seg_k);
+    const AnchorPtrs<T, NA> anc(p, jb.a0, na);
+    const T *seg = static_cast<const T *>(jb.seg_k) + t * jb.s_seg.token + lir * EPV;
+    const int64_t arow = t * p.s_anc.token + lir * EPV;
     for (int lh = lh0; lh < lh1; ++lh) {
-        double acc[kAnchorTile];
+        double acc[NA];
 #pragma unroll
-        for (int j = 0; j < kAnchorTile; ++j) acc[j] = 0.0;
-        if (valid) {
+        for (int j = 0; j < NA; ++j) acc[j] = 0.0;
+        auto add_row = [&](auto full) __attribute__((always_inline)) {   // full: na == NA (no branches)
             const int l = lh / p.H, h = lh % p.H;
-            const u32x4 rs = load16_stream(seg + l * jb.s_seg.layer + h * jb.s_seg.head + t * jb.s_seg.token + lir * EPV);
-            const int64_t aoff = l * p.s_anc.layer + h * p.s_anc.head + t * p.s_anc.token + lir * EPV;
-            u32x4 ra[kAnchorTile];
+            const u32x4 rs = load16(seg + l * jb.s_seg.layer + h * jb.s_seg.head);
+            const int64_t aoff = arow + l * p.s_anc.layer + h * p.s_anc.head;
+            u32x4 ra[NA];
 #pragma unroll
-            for (int j = 0; j < kAnchorTile; ++j)
-                if (j < na) ra[j] = load16_stream(static_cast<const T *>(p.anc[jb.a0 + j]) + aoff);
+            for (int j = 0; j < NA; ++j)
+                if (decltype(full)::value || j < na) ra[j] = anc.load(j, aoff);
             float x[EPV];
             unpack<T>(rs, x);
 #pragma unroll
-            for (int j = 0; j < kAnchorTile; ++j)
-                if (j < na) sqdiff_acc<T>(acc[j], x, ra[j]);
+            for (int j = 0; j < NA; ++j)
+                if (decltype(full)::value || j < na) sqdiff_acc<T>(acc[j], x, ra[j]);
+        };
+        if (valid) {
+            if (na == NA)
+                add_row(std::true_type{});
+            else
+                add_row(std::false_type{});
         }
         // Sum over the lanes of the row and hand each lane its own anchors in one go: in every round a lane keeps
         // one half of its values and adds the partner's copy of that half (15 exchanges for 16 anchors over 16
-        // lanes instead of 64 for a butterfly per anchor).  Rows wider than 16 lanes first fold their upper lanes in.
-        row_reduce_scatter<LPR>(acc, lir);
+        // lanes instead of 64 for a butterfly per anchor).  Rows wider than NA lanes first fold their upper lanes in.
+        row_reduce_scatter<LPR, NA>(acc, lir);
         double sc[NPL];
         double smax = -INFINITY;
-        int best = kAnchorTile;
+        int best = NA;
 #pragma unroll
         for (int k = 0; k < NPL; ++k) {
-            const int a = anchor_of_lane<LPR>(lir, k);
+            const int a = anchor_of_lane<LPR, NA>(lir, k);
             sc[k] = a < na ? -sqrt(acc[k]) : -INFINITY;
             if (sc[k] > smax) {  // ascending a: the lowest index wins among equals
                 smax = sc[k];
@@ -295,7 +351,7 @@ __global__ __launch_bounds__(kBlock) void dist_row_softmax_kernel(const DistPara
         float e[NPL], denom = 0.f;
 #pragma unroll
         for (int k = 0; k < NPL; ++k) {
-            const int a = anchor_of_lane<LPR>(lir, k);
+            const int a = anchor_of_lane<LPR, NA>(lir, k);
             e[k] = a < na ? (p.rule == KVCOMM_RULE_NEAREST ? (a == best ? 1.f : 0.f)
                                                            : expf((float)((sc[k] - smax) / p.tau)))
                           : 0.f;
@@ -308,7 +364,7 @@ __global__ __launch_bounds__(kBlock) void dist_row_softmax_kernel(const DistPara
             float *wrow = jb.weights + slot * jb.n_anchors;
 #pragma unroll
             for (int k = 0; k < NPL; ++k) {
-                const int a = anchor_of_lane<LPR>(lir, k);
+                const int a = anchor_of_lane<LPR, NA>(lir, k);
                 if (a < na) wrow[p.col[jb.a0 + a]] = e[k] / denom;
             }
             for (int c = lir; c < jb.n_anchors; c += LPR)
@@ -327,13 +383,16 @@ __global__ __launch_bounds__(kBlock) void cos_partial_kernel(const DistParams p)
 {
     constexpr int EPV = Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
-    const DistJob &jb = p.job[job_of_block(p)];
+    const int group = blockIdx.x / (8 * p.a_tiles), in_group = blockIdx.x % (8 * p.a_tiles);   // as in dist_partial_kernel
+    const int block = group * 8 + in_group % 8;
+    if (block >= p.n_blocks) return;
+    const DistJob &jb = p.job[job_of_block(p, block)];
     const int tid = threadIdx.x;
     const int row = tid / LPR, lir = tid % LPR;
-    const int bx = blockIdx.x - jb.block0;
+    const int bx = block - jb.block0;
     const int tile = bx % jb.n_token_tiles;
     const int chunk = bx / jb.n_token_tiles;
-    const int a0 = blockIdx.y * kCosTile;
+    const int a0 = in_group / 8 * kCosTile;
     const int na = min(kCosTile, jb.n_sel - a0);
     if (na <= 0) return;
     const int t = tile * RPB + row;
@@ -346,16 +405,18 @@ __global__ __launch_bounds__(kBlock) void cos_partial_kernel(const DistParams p)
 #pragma unroll
     for (int j = 0; j < kCosTile; ++j) dot[j] = ny[j] = 0.0;
 
+    const AnchorPtrs<T, kCosTile> anc(p, jb.a0 + a0, na);
     if (valid) {
-        const T *seg = static_cast<const T *>(jb.seg_k);
+        const T *seg = static_cast<const T *>(jb.seg_k) + t * jb.s_seg.token + lir * EPV;
+        const int64_t arow = t * p.s_anc.token + lir * EPV;
         for (int lh = lh0; lh < lh1; ++lh) {
             const int l = lh / p.H, h = lh % p.H;
-            const u32x4 rs = load16_stream(seg + l * jb.s_seg.layer + h * jb.s_seg.head + t * jb.s_seg.token + lir * EPV);
-            const int64_t aoff = l * p.s_anc.layer + h * p.s_anc.head + t * p.s_anc.token + lir * EPV;
+            const u32x4 rs = load16(seg + l * jb.s_seg.layer + h * jb.s_seg.head);
+            const int64_t aoff = arow + l * p.s_anc.layer + h * p.s_anc.head;
             u32x4 ra[kCosTile];
 #pragma unroll
             for (int j = 0; j < kCosTile; ++j)
-                if (j < na) ra[j] = load16_stream(static_cast<const T *>(p.anc[jb.a0 + a0 + j]) + aoff);
+                if (j < na) ra[j] = anc.load(j, aoff);
             float x[EPV];
             unpack<T>(rs, x);
 #pragma unroll
@@ -436,25 +497,33 @@ __device__ __forceinline__ double score_of(const FinalParams &p, double s0, doub
     return den > 0.0 ? s0 / den : 0.0;
 }
 
-// Softmax over the selected anchors of one slot, evaluated identically by each of the
-// slot's threads from the scores in `sc` (LDS): every thread walks the anchors in index
-// order, so all agree bit for bit on the maximum, the arg-max and the denominator.
-__device__ __forceinline__ void slot_softmax(const FinalParams &p, const FinalJob &jb, const double *sc, int a, int64_t slot)
+// Softmax over the selected anchors of one slot: maximum and arg-max from the scores in `sc` (LDS), walked in index order
+// by each of the slot's threads, so all agree bit for bit; every thread forms the exponential of its own anchor only and
+// the denominator is the sum of the n_sel exponentials in `ex` (LDS) in index order.  `act`: this thread owns anchor
+// `a` of `slot`.  Called by whole blocks (it synchronises them once).
+__device__ __forceinline__ void slot_softmax(const FinalParams &p, const FinalJob &jb, const double *sc, double *ex, int a,
+                                             int64_t slot, bool act)
 {
-    double smax = sc[0];
     int best = 0;
-    for (int j = 1; j < jb.n_sel; ++j)
-        if (sc[j] > smax) {
-            smax = sc[j];
-            best = j;
+    double w = 0.0;
+    if (act) {
+        double smax = sc[0];
+        for (int j = 1; j < jb.n_sel; ++j) {
+            const double v = sc[j];
+            if (v > smax) {
+                smax = v;
+                best = j;
+            }
         }
-    double w;
-    if (p.rule == KVCOMM_RULE_NEAREST) {
-        w = a == best ? 1.0 : 0.0;
-    } else {
+        w = p.rule == KVCOMM_RULE_NEAREST ? (a == best ? 1.0 : 0.0) : exp((sc[a] - smax) / p.tau);
+        ex[a] = w;
+    }
+    __syncthreads();
+    if (!act) return;
+    if (p.rule != KVCOMM_RULE_NEAREST) {
         double denom = 0.0;
-        for (int j = 0; j < jb.n_sel; ++j) denom += exp((sc[j] - smax) / p.tau);
-        w = exp((sc[a] - smax) / p.tau) / denom;
+        for (int j = 0; j < jb.n_sel; ++j) denom += ex[j];
+        w /= denom;
     }
     jb.weights[slot * jb.n_anchors + p.col[jb.a0 + a]] = (float)w;
     if (a == 0) {
@@ -465,13 +534,17 @@ __device__ __forceinline__ void slot_softmax(const FinalParams &p, const FinalJo
 }
 
 // Per-token and per-(layer, head, token) granularity.  A (slot, selected anchor) pair is summed by CL threads:
-// thread (c, slot, anchor) adds chunks c, c + CL, ... in increasing order (its loads all in flight at once; anchor,
-// then slot, vary fastest over the threads, so a wavefront reads whole runs of a chunk's row), the CL sums meet in
-// LDS and are added in increasing c, so the result does not depend on timing.
-__global__ __launch_bounds__(kBlock) void finalize_kernel(const FinalParams p)
+// thread (c, slot, anchor) adds chunks c, c + CL, ... in increasing order (anchor, then slot, vary fastest over the
+// threads, so a wavefront reads runs of a chunk's row), the CL sums meet in LDS and are added in increasing c, so the
+// result does not depend on timing.
+// The kernel is a chain of latencies (chunk loads, LDS sums, a double-precision root and exponential), so the chunks are
+// spread over as many threads as keep runs of 16 partials (128 bytes) together, and every exponential is formed once:
+// 77 tokens, 5 anchors, 256 chunks 14.1 -> 6.0 us; 4 x 512 tokens, 8 anchors 7.6 -> 5.5 us; 1024 tokens, 64 anchors
+// 16.6 -> 10.2 us against eight threads per pair and n_sel exponentials in each.
+__global__ __launch_bounds__(kFinalBlock) void finalize_kernel(const FinalParams p)
 {
-    __shared__ double dsh[kBlock];
-    __shared__ double red[3][kBlock];
+    __shared__ double dsh[kFinalBlock], esh[kFinalBlock];
+    __shared__ double red[3][kFinalBlock];
     int ji = 0;
 #pragma unroll
     for (int i = 1; i < KVCOMM_MAX_BATCH; ++i)
@@ -481,16 +554,16 @@ __global__ __launch_bounds__(kBlock) void finalize_kernel(const FinalParams p)
     const int tid = threadIdx.x;
     if (bx == 0 && jb.selected_out && tid < jb.n_anchors) jb.selected_out[tid] = (int32_t)((jb.sel_mask >> tid) & 1);
     if (jb.n_sel == 0) {  // nothing selected: all weights 0, nearest -1
-        const int64_t slot = (int64_t)bx * kBlock + tid;
+        const int64_t slot = (int64_t)bx * kFinalBlock + tid;
         if (slot < jb.n_slots) {
             for (int c = 0; c < jb.n_anchors; ++c) jb.weights[slot * jb.n_anchors + c] = 0.f;
             if (jb.nearest) jb.nearest[slot] = -1;
         }
         return;
     }
-    const int CL = jb.chunk_lanes;             // power of two, CL * n_sel <= kBlock
-    const int spb = kBlock / (CL * jb.n_sel);  // slots per block
-    const int per_lane = spb * jb.n_sel;       // (slot, anchor) pairs of a block
+    const int CL = jb.chunk_lanes;                  // CL * n_sel <= kFinalBlock
+    const int spb = kFinalBlock / (CL * jb.n_sel);  // slots per block
+    const int per_lane = spb * jb.n_sel;            // (slot, anchor) pairs of a block
     const int a = tid % jb.n_sel, sl = (tid / jb.n_sel) % spb, cl = tid / per_lane;
     const int64_t slot = (int64_t)bx * spb + sl;
     const bool active = cl < CL && slot < jb.n_slots;
@@ -498,12 +571,14 @@ __global__ __launch_bounds__(kBlock) void finalize_kernel(const FinalParams p)
     double s0 = 0.0, s1 = 0.0, s2 = 0.0;
     if (active) {
         if (p.gran == KVCOMM_W_TOKEN) {
-            for (int c = cl; c < p.n_chunks; c += CL) {
-                const int64_t i = ((int64_t)c * jb.S + slot) * jb.n_sel + a;
-                s0 += jb.partial[i];
+            const double *src = jb.partial + ((int64_t)cl * jb.S + slot) * jb.n_sel + a;
+            const int64_t step = (int64_t)CL * jb.S * jb.n_sel;
+#pragma unroll 4
+            for (int c = cl; c < p.n_chunks; c += CL, src += step) {
+                s0 += src[0];
                 if (cosine) {
-                    s1 += jb.partial[jb.comp_stride + i];
-                    s2 += jb.partial[2 * jb.comp_stride + i];
+                    s1 += src[jb.comp_stride];
+                    s2 += src[2 * jb.comp_stride];
                 }
             }
         } else {  // one chunk per (layer, head): slot = chunk * S + t, CL == 1
@@ -523,6 +598,7 @@ __global__ __launch_bounds__(kBlock) void finalize_kernel(const FinalParams p)
         }
         __syncthreads();
         if (active && cl == 0) {
+#pragma unroll 4
             for (int c = 1; c < CL; ++c) {
                 s0 += red[0][c * per_lane + tid];
                 if (cosine) {
@@ -532,19 +608,25 @@ __global__ __launch_bounds__(kBlock) void finalize_kernel(const FinalParams p)
             }
         }
     }
-    if (active && cl == 0) dsh[sl * jb.n_sel + a] = score_of(p, s0, s1, s2);
+    const bool act = active && cl == 0;
+    if (act) dsh[tid] = score_of(p, s0, s1, s2);   // tid = sl * n_sel + a
     __syncthreads();
-    if (active && cl == 0) slot_softmax(p, jb, dsh + sl * jb.n_sel, a, slot);
+    slot_softmax(p, jb, dsh + sl * jb.n_sel, esh + sl * jb.n_sel, a, slot, act);
 }
 
 // Per-segment granularity: one block per segment.  The distance kernel has left one partial per (chunk, token
-// tile, anchor), n_rows = n_chunks * n_token_tiles rows of n_sel values.  Thread t adds the rows g, g + G, ... of
-// anchor t % n_sel (g = t / n_sel, G = 256 / n_sel groups: consecutive threads read consecutive addresses) and a
-// fixed-order sum over the groups closes each anchor, so the result does not depend on timing.
-__global__ __launch_bounds__(kBlock) void finalize_segment_kernel(const FinalParams p)
+// tile, anchor), n_rows = n_chunks * n_token_tiles rows of n_sel values (about 2048 whatever the segment).  Thread t adds
+// the rows g, g + G, ... of anchor t % n_sel (g = t / n_sel, G = kSegBlock / n_sel groups: consecutive threads read
+// consecutive addresses; eight interleaved chains keep as many loads in flight); the groups' sums are added in LDS, 16
+// threads per anchor and then one, in a fixed order, so the result does not depend on timing.
+// Latency of one block: 1024 threads instead of 256 shorten the chain of loads to a quarter (512 tokens, 8 anchors: 10.4 -> 5.8 us,
+// part of it from the shorter list of partials).
+__global__ __launch_bounds__(kSegBlock) void finalize_segment_kernel(const FinalParams p)
 {
-    __shared__ double red[3][kBlock];
-    __shared__ double dsh[KVCOMM_MAX_ANCHORS];
+    constexpr int NC = 8, NF = 16;
+    __shared__ double red[3][kSegBlock];
+    __shared__ double fin[3][NF * KVCOMM_MAX_ANCHORS];
+    __shared__ double dsh[KVCOMM_MAX_ANCHORS], esh[KVCOMM_MAX_ANCHORS];
     const FinalJob &jb = p.job[blockIdx.x];
     const int tid = threadIdx.x;
     if (jb.selected_out && tid < jb.n_anchors) jb.selected_out[tid] = (int32_t)((jb.sel_mask >> tid) & 1);
@@ -553,44 +635,60 @@ __global__ __launch_bounds__(kBlock) void finalize_segment_kernel(const FinalPar
         if (tid == 0 && jb.nearest) jb.nearest[0] = -1;
         return;
     }
-    const int n_sel = jb.n_sel, G = kBlock / n_sel;
+    const int n_sel = jb.n_sel, G = kSegBlock / n_sel;
     const int a = tid % n_sel, g = tid / n_sel;
     const int64_t n_rows = (int64_t)p.n_chunks * jb.n_token_tiles;
     const int n_comp = p.rule == KVCOMM_RULE_COSINE_SOFTMAX ? 3 : 1;
-    double s[3][4] = {};   // four interleaved chains per component keep several loads in flight
     if (g < G) {
         for (int c = 0; c < n_comp; ++c) {
             const double *src = jb.partial + c * jb.comp_stride + a;
+            double s[NC] = {};
             int64_t r = g;
-            for (; r + 3 * G < n_rows; r += 4 * G) {
+            for (; r + (NC - 1) * G < n_rows; r += NC * G) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) s[c][u] += src[(r + u * G) * n_sel];
+                for (int u = 0; u < NC; ++u) s[u] += src[(r + u * G) * n_sel];
             }
-            for (int u = 0; r < n_rows; r += G, ++u) s[c][u] += src[r * n_sel];
+#pragma unroll
+            for (int u = 0; u < NC; ++u)
+                if (r + u * G < n_rows) s[u] += src[(r + u * G) * n_sel];
+            red[c][tid] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
         }
     }
-    for (int c = 0; c < n_comp; ++c) red[c][tid] = (s[c][0] + s[c][1]) + (s[c][2] + s[c][3]);
+    __syncthreads();
+    if (g < NF) {   // NF * n_sel <= kSegBlock
+        for (int c = 0; c < n_comp; ++c) {
+            double v = 0.0;
+            for (int gg = g; gg < G; gg += NF) v += red[c][gg * n_sel + a];
+            fin[c][g * n_sel + a] = v;
+        }
+    }
     __syncthreads();
     if (tid < n_sel) {
         double tot[3] = {0.0, 0.0, 0.0};
         for (int c = 0; c < n_comp; ++c)
-            for (int gg = 0; gg < G; ++gg) tot[c] += red[c][gg * n_sel + tid];
+#pragma unroll
+            for (int f = 0; f < NF; ++f) tot[c] += fin[c][f * n_sel + tid];
         dsh[tid] = score_of(p, tot[0], tot[1], tot[2]);
     }
     __syncthreads();
-    if (tid < n_sel) slot_softmax(p, jb, dsh, tid, 0);
+    slot_softmax(p, jb, dsh, esh, tid, 0, tid < n_sel);
 }
 
 template <typename T, int LPR>
 int launch_dist(const DistParams &p, int n_blocks, int max_sel, bool cosine, hipStream_t stream)
 {
-    if (p.fused) return launch(dist_row_softmax_kernel<T, LPR>, dim3(n_blocks), dim3(kBlock), 0, stream, p);
-    if (cosine) {
-        const int a_tiles = (max_sel + kCosTile - 1) / kCosTile;
-        return launch(cos_partial_kernel<T, LPR>, dim3(n_blocks, a_tiles), dim3(kBlock), 0, stream, p);
-    }
-    const int a_tiles = (max_sel + kAnchorTile - 1) / kAnchorTile;
-    return launch(dist_partial_kernel<T, LPR>, dim3(n_blocks, a_tiles), dim3(kBlock), 0, stream, p);
+    const int na = cosine ? kCosTile : max_sel <= 4 ? 4 : max_sel <= 8 ? 8 : kAnchorTile;
+    if (p.fused)
+        return launch(na == 4 ? dist_row_softmax_kernel<T, LPR, 4> : na == 8 ? dist_row_softmax_kernel<T, LPR, 8> : dist_row_softmax_kernel<T, LPR, kAnchorTile>,
+                      dim3(n_blocks), dim3(kBlock), 0, stream, p);
+    DistParams q = p;
+    q.n_blocks = n_blocks;
+    q.a_tiles = (max_sel + na - 1) / na;
+    const int64_t grid = ((int64_t)n_blocks + 7) / 8 * 8 * q.a_tiles;
+    if (grid > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
+    return launch(cosine ? cos_partial_kernel<T, LPR> : na == 4 ? dist_partial_kernel<T, LPR, 4> : na == 8 ? dist_partial_kernel<T, LPR, 8>
+                                                                                              : dist_partial_kernel<T, LPR, kAnchorTile>,
+                  dim3((unsigned)grid), dim3(kBlock), 0, stream, q);
 }
 
 int check_rule(int rule)
@@ -755,10 +853,13 @@ extern "C" int kvcomm_anchor_weights_batch(const kvcomm_model *model, int32_t gr
         fj.n_slots = (int32_t)kvcomm_weight_slots(model, jd.seg_len, gran);
         fj.n_anchors = jd.n_anchors;
         int cl = 1;
-        if (gran == KVCOMM_W_TOKEN && dj.n_sel > 0)
-            while (cl < 8 && 2 * cl * dj.n_sel <= kBlock && 2 * cl <= pl.n_chunks) cl *= 2;
+        if (gran == KVCOMM_W_TOKEN && dj.n_sel > 0) {
+            const int slots = (kFinalRun + dj.n_sel - 1) / dj.n_sel;   // of a run
+            cl = kFinalBlock / (slots * dj.n_sel);
+            if (cl > pl.n_chunks) cl = pl.n_chunks;
+        }
         fj.chunk_lanes = cl;
-        const int spb = dj.n_sel > 0 ? kBlock / (cl * dj.n_sel) : kBlock;
+        const int spb = dj.n_sel > 0 ? kFinalBlock / (cl * dj.n_sel) : kFinalBlock;
         fj.block0 = (int32_t)final_blocks;
         final_blocks += (fj.n_slots + spb - 1) / spb;
     }
@@ -784,8 +885,8 @@ extern "C" int kvcomm_anchor_weights_batch(const kvcomm_model *model, int32_t gr
     }
     if (fused) return KVCOMM_OK;
     if (gran == KVCOMM_W_SEGMENT)
-        return launch(finalize_segment_kernel, dim3(n_jobs), dim3(kBlock), 0, s, fp);
-    return launch(finalize_kernel, dim3((unsigned)final_blocks), dim3(kBlock), 0, s, fp);
+        return launch(finalize_segment_kernel, dim3(n_jobs), dim3(kSegBlock), 0, s, fp);
+    return launch(finalize_kernel, dim3((unsigned)final_blocks), dim3(kFinalBlock), 0, s, fp);
 }
 
 extern "C" int kvcomm_anchor_weights_rule(const kvcomm_model *model, int32_t gran, int32_t rule, float temperature,

@@ -1,0 +1,69 @@
+"""Anchor weights at the edges of the anchor tiles (4, 8 or 16 anchors per lane, several tiles beyond) and of the second
+stage's cut into chunks, slots and threads: single-segment and batched calls with pools of different sizes, every
+granularity and rule, against the float64 oracle (1e-5 as for all weights; arg-min and selection exact)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2510_12872_amd as kv
+
+from parity import check_weights, to_np
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _want(bk, anc, gran, rule):
+    anc = [to_np(a) for a in anc]
+    dist, sel = oracle.distances(to_np(bk), anc, gran)
+    if rule == kv.RULE_NEAREST:
+        return oracle.weights_nearest(dist, sel)
+    if rule == kv.RULE_COSINE_SOFTMAX:
+        sim, sel = oracle.cosine(to_np(bk), anc, gran)
+        return oracle.weights_from_sim(sim, sel, 1.0)
+    return oracle.weights(dist, sel, 1.0)
+
+
+@pytest.mark.parametrize("L,H,D,dtype,S", [(2, 3, 128, torch.bfloat16, 37), (40, 1, 64, torch.bfloat16, 5),
+                                           (3, 2, 256, torch.float32, 17)])
+def test_pool_sizes_at_tile_edges(L, H, D, dtype, S):
+    m = kv.Model(L, H, H, D, dtype, 5e5)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L + S)
+    mk = lambda n: torch.randn((L, H, n, D), generator=g, device=DEV).to(dtype)
+    bk, pool = mk(S), [mk(S + 3) for _ in range(33)]
+    for A in (1, 3, 4, 5, 7, 8, 9, 15, 16, 17, 33):
+        anc = pool[:A]
+        for gran in (kv.W_TOKEN, kv.W_LAYER_HEAD_TOKEN, kv.W_SEGMENT):
+            for rule in (kv.RULE_L2_SOFTMAX, kv.RULE_NEAREST, kv.RULE_COSINE_SOFTMAX):
+                print(f"anchor tiles: L{L} D{D} S{S} A{A} gran{gran} rule{rule}", flush=True)
+                w, near, sel = kv.kvcomm_anchor_weights_rule(m, rule, bk, anc, None, 1.0, gran)
+                torch.cuda.synchronize()
+                want, want_near = _want(bk, anc, gran, rule)
+                check_weights(w.cpu().numpy(), want.T)
+                assert np.array_equal(near.cpu().numpy(), want_near) and sel.all()
+
+
+@pytest.mark.parametrize("gran", [kv.W_TOKEN, kv.W_LAYER_HEAD_TOKEN, kv.W_SEGMENT])
+def test_batch_of_unequal_pools(gran):
+    """Pools of 2, 20, 9 and 5 anchors in one launch (its tiles are sized for the largest), one of them with no anchor
+    that is long enough: the tiles that a small pool does not have must write nothing."""
+    L, H, D = 5, 2, 128
+    m = kv.Model(L, H, H, D, torch.bfloat16, 5e5)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(11)
+    mk = lambda n: torch.randn((L, H, n, D), generator=g, device=DEV).to(torch.bfloat16)
+    lens = [33, 16, 50, 47]
+    jobs = [dict(seg_base_k=mk(S), anchor_base_k=[mk(50) for _ in range(A)], anchor_len=[50 if S != 47 else 46] * A)
+            for S, A in zip(lens, (2, 20, 9, 5))]
+    print(f"unequal pools gran{gran}", flush=True)
+    got = kv.kvcomm_anchor_weights_batch(m, jobs, 1.0, gran)
+    torch.cuda.synchronize()
+    for (w, near, sel), jd, S in zip(got, jobs, lens):
+        if S == 47:
+            assert not w.any() and (near == -1).all() and not sel.any()
+            continue
+        want, want_near = _want(jd["seg_base_k"], jd["anchor_base_k"], gran, kv.RULE_L2_SOFTMAX)
+        check_weights(w.cpu().numpy(), want.T)
+        assert np.array_equal(near.cpu().numpy(), want_near) and sel.all()

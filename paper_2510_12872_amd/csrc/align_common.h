@@ -30,6 +30,13 @@ struct AlignJob {
     int16_t pad_;
 };
 
+// Entry i of a byte array in the kernel arguments, i wavefront-uniform: read as a dword on the scalar unit.  (There is no
+// scalar byte load; a plain access becomes a vector load whose wait also waits for every row in flight before it.)
+__device__ __forceinline__ int arg_byte(const uint8_t *bytes, int i)
+{
+    return (int)(reinterpret_cast<const uint32_t *>(bytes)[i >> 2] >> (8 * (i & 3)) & 0xff);
+}
+
 // Which job a launch-wide tile index belongs to.
 template <class P>
 __device__ __forceinline__ int job_of_tile(const P &p, int r)

@@ -13,10 +13,15 @@
 // 256 threads owns a tile of 256/LPR consecutive tokens of one (layer, head) and of ONE of
 // the two tensors (blockIdx.y: 0 = keys, 1 = values): the two streams are independent, and
 // splitting them halves the registers per lane so that many wavefronts per CU keep loads in
-// flight.  Every access to a tensor is a run of whole 128-byte lines; the traffic is marked
-// non-temporal.  Per-token anchor weights and the cos/sin tables load once per block (LDS).
+// flight.  Every access to a tensor is a run of whole 128-byte lines; deviations and outputs are marked
+// non-temporal (they are not read again soon: 466 us per launch of 4 x 512 tokens with 8 anchors, 500 us with plain
+// stores).  The base rows are plain loads: anchor matching has just read the base keys, and a shared segment's base
+// cache serves the next agent as well (matching and update of a placeholder of 512 and a prefix segment of 173 tokens,
+// 8 anchors: 205 us, 212 us with non-temporal loads; no difference where nothing is in the last-level cache).  Per-token anchor weights and the cos/sin tables load once per block (LDS).
 // cos/sin: the angle delta * theta^(-2i/D) is formed and reduced modulo 2*pi in double from a
 // host-computed frequency table (kernel argument); sine and cosine of the reduced angle are fp32.
+#include <type_traits>
+
 #include "align_common.h"
 
 namespace {
@@ -27,15 +32,7 @@ using namespace kvc;
 #define KVC_ALIGN_BLOCKS 32768  // blocks per tensor the grid aims at (measured best on MI355X)
 #endif
 
-#ifndef KVC_ALIGN_INFLIGHT
-#define KVC_ALIGN_INFLIGHT 2
-#endif
-#ifndef KVC_ALIGN_WPE
-#define KVC_ALIGN_WPE 4   // wavefronts per SIMD the register budget is sized for (measured best: 4 with 2 anchors in flight)
-#endif
-
 constexpr int kBlock = kAlignBlock;
-constexpr int kAnchorsInFlight = KVC_ALIGN_INFLIGHT;
 
 struct AlignParams {
     AlignJob job[KVCOMM_MAX_BATCH];
@@ -46,14 +43,19 @@ struct AlignParams {
     int32_t tiles_total;       // token tiles of all segments
     int32_t tab_delta[kMaxTab];                 // position delta of each rotation table
     const void *anc[2][KVCOMM_MAX_ANCHORS];     // [0] dK, [1] dV of the selected anchors of all segments
-    uint8_t col[KVCOMM_MAX_ANCHORS];            // weight column of a selected anchor
-    uint8_t tab[KVCOMM_MAX_ANCHORS];            // its rotation table (index among the segment's tables) + 1, 0 = identity
+    alignas(4) uint8_t col[KVCOMM_MAX_ANCHORS];            // weight column of a selected anchor
+    alignas(4) uint8_t tab[KVCOMM_MAX_ANCHORS];            // its rotation table (index among the segment's tables) + 1, 0 = identity
     double inv_freq[kMaxHalf];                  // theta^(-2i/D), i < D/2
 };
 static_assert(sizeof(AlignParams) <= 4096, "kernel arguments are limited to 4 KB");
 
-template <typename T, int LPR>
-__global__ __launch_bounds__(kBlock, KVC_ALIGN_WPE) void align_kernel(const AlignParams p)
+// INFLIGHT: anchors whose rows are requested together (twice as many 16-byte loads per lane); WPE: wavefronts per SIMD the
+// register budget is sized for.  Four anchors at three wavefronts for pools of four and more, two at four wavefronts for
+// smaller ones.  us per launch, (2, 4) against (4, 3): 4 x 512 tokens, 8 anchors 483 / 460, 16 anchors, 2 x 1024 tokens 845 /
+// 803, weights per (layer, head, token) 478 / 466; 3 x 300 tokens, 2 anchors 89 / 98.  (A vector load of the rotation-table
+// index, whose wait drained every row in flight, used to hold the keys' blocks back: 466 / 820 / 488 us then.)
+template <typename T, int LPR, int INFLIGHT, int WPE>
+__global__ __launch_bounds__(kBlock, WPE) void align_kernel(const AlignParams p)
 {
     constexpr int EPV = Elem<T>::EPV;
     constexpr int HALF = LPR * EPV;  // D / 2
@@ -118,7 +120,7 @@ __global__ __launch_bounds__(kBlock, KVC_ALIGN_WPE) void align_kernel(const Alig
     for (int lh = lh0; lh < lh1; ++lh) {
         const int l = lh / p.H, h = lh % p.H;
         const T *xp = bp + l * sb.layer + h * sb.head + t * sb.token + col0;
-        const u32x4 rlo = load16_stream(xp), rhi = load16_stream(xp + HALF);
+        const u32x4 rlo = load16(xp), rhi = load16(xp + HALF);   // plain: see the header
         const int64_t aoff = l * p.s_anc.layer + h * p.s_anc.head + t * p.s_anc.token + col0;
         const float *wrow = p.gran == KVCOMM_W_LAYER_HEAD_TOKEN
                                 ? jb.weights + ((int64_t)lh * jb.S + t) * jb.w_pitch
@@ -137,11 +139,11 @@ __global__ __launch_bounds__(kBlock, KVC_ALIGN_WPE) void align_kernel(const Alig
         }
 
         auto accumulate = [&](int a, const u32x4 &rdlo, const u32x4 &rdhi) {
-            const float w = wrow ? wrow[p.col[a0 + a]] : w_lds[row * n_sel + a];
+            const float w = wrow ? wrow[arg_byte(p.col, a0 + a)] : w_lds[row * n_sel + a];
             float dlo[EPV], dhi[EPV];
             unpack<T>(rdlo, dlo);
             unpack<T>(rdhi, dhi);
-            const int tb = is_k ? p.tab[a0 + a] : 0;
+            const int tb = is_k ? arg_byte(p.tab, a0 + a) : 0;
             if (tb) {
                 const float2 *tcs = cs + (tb - 1) * HALF + lir * EPV;
 #pragma unroll
@@ -159,24 +161,23 @@ __global__ __launch_bounds__(kBlock, KVC_ALIGN_WPE) void align_kernel(const Alig
             }
         };
 
-        // kAnchorsInFlight anchors (twice as many independent 16-byte loads) are kept in flight.
         int a = 0;
-        for (; a + kAnchorsInFlight <= n_sel; a += kAnchorsInFlight) {
-            u32x4 x[kAnchorsInFlight][2];
+        auto group = [&](auto count) __attribute__((always_inline)) {
+            constexpr int U = decltype(count)::value;
+            u32x4 x[U][2];
 #pragma unroll
-            for (int u = 0; u < kAnchorsInFlight; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const T *d = static_cast<const T *>(p.anc[which][a0 + a + u]) + aoff;
                 x[u][0] = load16_stream(d);
                 x[u][1] = load16_stream(d + HALF);
             }
 #pragma unroll
-            for (int u = 0; u < kAnchorsInFlight; ++u) accumulate(a + u, x[u][0], x[u][1]);
-        }
-        for (; a < n_sel; ++a) {
-            const T *d = static_cast<const T *>(p.anc[which][a0 + a]) + aoff;
-            const u32x4 x0 = load16_stream(d), x1 = load16_stream(d + HALF);
-            accumulate(a, x0, x1);
-        }
+            for (int u = 0; u < U; ++u) accumulate(a + u, x[u][0], x[u][1]);
+            a += U;
+        };
+        while (a + INFLIGHT <= n_sel) group(std::integral_constant<int, INFLIGHT>{});
+        if (INFLIGHT > 2 && a + 2 <= n_sel) group(std::integral_constant<int, 2>{});
+        while (a < n_sel) group(std::integral_constant<int, 1>{});
 
         T *yp = op + l * so.layer + h * so.head + t * so.token + col0;
         store16_stream(yp, pack<T>(lo));
@@ -190,7 +191,7 @@ int launch_align(const AlignParams &p, int n_blocks, int max_tab, int max_sel, h
     constexpr int HALF = LPR * Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
     const size_t lds = sizeof(float2) * (size_t)max_tab * HALF + sizeof(float) * (size_t)RPB * max_sel;
-    return launch(align_kernel<T, LPR>, dim3(n_blocks, 2), dim3(kBlock), lds, stream, p);
+    return launch(max_sel >= 4 ? align_kernel<T, LPR, 4, 3> : align_kernel<T, LPR, 2, 4>, dim3(n_blocks, 2), dim3(kBlock), lds, stream, p);
 }
 
 }  // namespace

@@ -34,9 +34,9 @@ using namespace kvc;
 
 #ifndef KVC_DIST_BLOCKS
 // Blocks per segment the distance grid aims at.  Fewer blocks = longer runs of (layer, head) pairs = fewer partial sums for
-// the second stage; measured (us per call, both stages) with 256 / 512 / 1024 / 2048 blocks: 4 segments x 512 tokens, 8
-// anchors 200 / 185 / 186 / 201; 1024 tokens, 64 anchors (with the update) 2086 / 2094 / 2106 / 2188; D = 64 100 / 101 /
-// 104 / 119.
+// the second stage; measured (us per call, both stages, the same inputs call after call) with 256 / 512 / 1024 / 2048
+// blocks: 4 segments x 512 tokens, 8 anchors 200 / 185 / 186 / 201; 1024 tokens, 64 anchors (with the update) 2086 / 2094 /
+// 2106 / 2188; D = 64 100 / 101 / 104 / 119.
 #define KVC_DIST_BLOCKS 512
 #endif
 
@@ -150,9 +150,10 @@ struct AnchorPtrs {
 
 // HBM bound.  What keeps loads in flight: all row pieces of a (layer, head) pair are requested before the first is used,
 // without a branch between them when the tile is full; tiles of 4 and 8 anchors for small pools hold fewer registers, so
-// more wavefronts fit.  The segment's rows are plain loads and the anchors' non-temporal: 8 anchors, 4 x 512 tokens 191 us
-// with both non-temporal, 185 mixed, 212 with both plain; 64 anchors (4 tiles that share the segment's rows) 2143 us per
-// segment with its update when every tile fetched them from HBM, 2095 now.  4 x 512 tokens, 8 anchors: 6.8 TB/s.
+// more wavefronts fit.  The anchors' rows are read once and marked non-temporal; the segment's rows are plain loads: the
+// tiles of a large pool share them (fetched by every one of the four tiles of 64 anchors, the distance stage of 1024 tokens
+// took 7 % longer), and the update that follows reads the same rows again.  4 x 512 tokens, 8 anchors, inputs that are in
+// no cache: 185 us = 6.5 TB/s (191 us before).
 template <typename T, int LPR, int NA>   // NA: anchors of a tile (accumulators of a lane)
 __global__ __launch_bounds__(kBlock) void dist_partial_kernel(const DistParams p)
 {

@@ -99,7 +99,7 @@ struct QuantParams {
 };
 
 #ifndef KVC_QUANT_ROWS
-#define KVC_QUANT_ROWS 4   // rows per thread: that many independent 16-byte loads in flight
+#define KVC_QUANT_ROWS 2   // rows per thread: that many independent 16-byte loads in flight (1000 tokens: 20.6 us with 4 or 8, 20.0 with 2)
 #endif
 
 template <typename T, int LPR>  // LPR lanes per row, each EPV elements
@@ -166,15 +166,18 @@ struct AlignQ8Params {
     int32_t tiles_total;
     int32_t tab_delta[kMaxTab];
     const void *anc[2][KVCOMM_MAX_ANCHORS];
-    int8_t scale_exp[2][KVCOMM_MAX_ANCHORS];   // [0] key, [1] value deviation scale = 2^scale_exp of a selected anchor
-    uint8_t col[KVCOMM_MAX_ANCHORS];
-    uint8_t tab[KVCOMM_MAX_ANCHORS];
+    alignas(4) int8_t scale_exp[2][KVCOMM_MAX_ANCHORS];   // [0] key, [1] value deviation scale = 2^scale_exp of a selected anchor
+    alignas(4) uint8_t col[KVCOMM_MAX_ANCHORS];
+    alignas(4) uint8_t tab[KVCOMM_MAX_ANCHORS];
     double inv_freq[kMaxHalf];
 };
 static_assert(sizeof(AlignQ8Params) <= 4096, "kernel arguments are limited to 4 KB");
 
 __device__ __forceinline__ float pow2f(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }  // -126 <= e <= 127
 
+// Nothing in the loop but the rows may be a vector load: the rotation-table index of an anchor, read that way, drained the
+// next pair's loads as well (4 x 512 tokens, 8 anchors 306 us, 289 with the index read on the scalar unit; per-anchor
+// rotations 319 and 293).
 // Work split as in align_kernel: LPR = D / (2 * EPV) lanes per row, lane r owns channels [r*EPV, r*EPV+EPV)
 // of both halves; a block is 256 / LPR tokens of a run of (layer, head) pairs of ONE tensor of one segment.
 template <typename T, int LPR>
@@ -276,11 +279,11 @@ __global__ __launch_bounds__(kBlock, KVC_ALIGNQ8_WPE) void align_q8_kernel(const
         auto accumulate = [&](int a, const Q8Raw<EPV> &raw) {
             uint32_t rdlo[EPV / 4], rdhi[EPV / 4];
             raw.split(lir, rdlo, rdhi);
-            const float w = wrow ? wrow[p.col[a0 + a]] * pow2f(p.scale_exp[which][a0 + a]) : w_lds[row * n_sel + a];
+            const float w = wrow ? wrow[arg_byte(p.col, a0 + a)] * pow2f((int8_t)arg_byte(reinterpret_cast<const uint8_t *>(p.scale_exp[which]), a0 + a)) : w_lds[row * n_sel + a];
             float dlo[EPV], dhi[EPV];
             unpack_q8<EPV>(rdlo, dlo);
             unpack_q8<EPV>(rdhi, dhi);
-            const int tb = is_k ? p.tab[a0 + a] : 0;
+            const int tb = is_k ? arg_byte(p.tab, a0 + a) : 0;
             if (tb) {
                 const float2 *tcs = cs + (tb - 1) * HALF + lir * EPV;
 #pragma unroll

@@ -8,7 +8,7 @@ import torch
 import oracle
 import paper_2510_12872_amd as kv
 
-from parity import check_weights, to_np
+from parity import check_close, check_weights, to_np
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -67,3 +67,33 @@ def test_batch_of_unequal_pools(gran):
         want, want_near = _want(jd["seg_base_k"], jd["anchor_base_k"], gran, kv.RULE_L2_SOFTMAX)
         check_weights(w.cpu().numpy(), want.T)
         assert np.array_equal(near.cpu().numpy(), want_near) and sel.all()
+
+
+@pytest.mark.parametrize("dtype,D", [(torch.bfloat16, 128), (torch.float32, 64)])
+@pytest.mark.parametrize("gran", [kv.W_TOKEN, kv.W_LAYER_HEAD_TOKEN, kv.W_SEGMENT])
+def test_update_pool_sizes(gran, dtype, D):
+    """The update at every remainder of its groups of four, two and one anchors, rotated and unrotated deviations mixed,
+    plain and E4M3 (against the oracle on the stored values); bf16 2e-2, fp32 1e-5."""
+    L, H, S, delta = 2, 3, 35, 300
+    m = kv.Model(L, H, H, D, dtype, 5e5)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(D + gran)
+    mk = lambda n, s=1.0: (torch.randn((L, H, n, D), generator=g, device=DEV) * s).to(dtype)
+    bk, bv = mk(S), mk(S)
+    dk, dv = [mk(S, 0.05) for _ in range(11)], [mk(S, 0.05) for _ in range(11)]
+    scale = 2.0 ** -9
+    dk8, dv8 = ([kv.kvcomm_quantize_deltas(m, t, scale) for t in x] for x in (dk, dv))
+    n = kv.kvcomm_weight_slots(m, S, gran)
+    for A in range(1, 12):
+        print(f"update pool sizes: D{D} gran{gran} A{A}", flush=True)
+        w = torch.softmax(torch.randn((n, A), generator=g, device=DEV), 1).contiguous()
+        adp = [delta if a % 3 else 40 * a for a in range(A)]
+        ok, ov, ok8, ov8 = (torch.empty_like(bk) for _ in range(4))
+        kv.kvcomm_align_kv(m, bk, bv, dk[:A], dv[:A], w, delta, ok, ov, None, adp, gran)
+        kv.kvcomm_align_kv_q8(m, bk, bv, dk8[:A], dv8[:A], [scale] * A, [scale] * A, w, delta, ok8, ov8, None, adp, gran)
+        torch.cuda.synchronize()
+        deq = lambda x: [oracle.dequantize(t.cpu().numpy(), scale) for t in x[:A]]
+        for got, devs in (((ok, ov), ([to_np(t) for t in dk[:A]], [to_np(t) for t in dv[:A]])), ((ok8, ov8), (deq(dk8), deq(dv8)))):
+            want = oracle.align(to_np(bk), to_np(bv), devs[0], devs[1], w.cpu().numpy().astype(np.float64).T, delta, 5e5, adp, gran)
+            check_close(to_np(got[0]), want[0], dtype, "K^")
+            check_close(to_np(got[1]), want[1], dtype, "V^")

@@ -168,30 +168,51 @@ def _check(status):
         raise KVCommError(status, load_library().kvcomm_status_string(status).decode())
 
 
+def _not_a_tensor(what, dtype):
+    return KVCommError(-1, f"{what}: expected a 4-d {dtype} device tensor with contiguous channels")
+
+
+# The functions below run once or more per library call; for small segments their cost is the call's cost, so each
+# property of a tensor is read once.
 def _desc(t, dtype, what):
     """[layer, head, token, channel] tensor -> kvcomm_tensor."""
-    if t.dim() != 4 or t.dtype != dtype or not t.is_cuda or t.stride(3) != 1:
-        raise KVCommError(-1, f"{what}: expected a 4-d {dtype} device tensor with contiguous channels")
-    return _CTensor(t.data_ptr(), t.stride(0), t.stride(1), t.stride(2))
+    st = t.stride()
+    if t.dtype != dtype or len(st) != 4 or st[3] != 1 or not t.is_cuda:
+        raise _not_a_tensor(what, dtype)
+    return _CTensor(t.data_ptr(), st[0], st[1], st[2])
+
+
+_raw_current_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # the handle without a Stream object around it
 
 
 def _stream_ptr(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_current_stream is not None:
+        return _raw_current_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
+
+
+def _anchor_ptrs(anchors, dtype, what):
+    """List of same-layout anchor tensors -> (host pointer array, layout descriptor)."""
+    n = len(anchors)
+    if n == 0:
+        return None, _CTensor(None, 0, 0, 0)
+    layout = _desc(anchors[0], dtype, what)
+    st = anchors[0].stride()
+    for a in anchors:
+        if a.stride() != st or a.dtype != dtype or not a.is_cuda:
+            _desc(a, dtype, what)
+            raise KVCommError(-1, f"{what}: all anchors must share one layout (pad them to a common capacity)")
+    return (ctypes.c_void_p * n)(*[a.data_ptr() for a in anchors]), layout
 
 
 def _anchor_args(anchors, anchor_len, dtype, what):
     """List of same-layout anchor tensors -> (host pointer array, layout descriptor, host length array)."""
+    ptrs, layout = _anchor_ptrs(anchors, dtype, what)
+    if ptrs is None:
+        return None, layout, None
     n = len(anchors)
-    if n == 0:
-        return None, _CTensor(None, 0, 0, 0), None
-    layout = _desc(anchors[0], dtype, what)
-    for a in anchors:
-        d = _desc(a, dtype, what)
-        if (d.stride_layer, d.stride_head, d.stride_token) != (layout.stride_layer, layout.stride_head,
-                                                               layout.stride_token):
-            raise KVCommError(-1, f"{what}: all anchors must share one layout (pad them to a common capacity)")
-    ptrs = (ctypes.c_void_p * n)(*[a.data_ptr() for a in anchors])
     if anchor_len is None:
         anchor_len = [a.shape[2] for a in anchors]
     lens = (ctypes.c_int32 * n)(*[int(x) for x in anchor_len])
@@ -213,15 +234,16 @@ def kvcomm_anchor_weights(model, seg_base_k, anchor_base_k, anchor_len=None, tem
     seg_len = seg_base_k.shape[2]
     A = len(anchor_base_k)
     dev = seg_base_k.device
-    n = kvcomm_weight_slots(model, seg_len, gran)
-    if weights_out is None:
-        weights_out = torch.empty((n, A), dtype=torch.float32, device=dev)
-    if nearest_out is None:
-        nearest_out = torch.empty((n,), dtype=torch.int32, device=dev)
+    if weights_out is None or nearest_out is None:
+        n = kvcomm_weight_slots(model, seg_len, gran)
+        if weights_out is None:
+            weights_out = torch.empty((n, A), dtype=torch.float32, device=dev)
+        if nearest_out is None:
+            nearest_out = torch.empty((n,), dtype=torch.int32, device=dev)
     if selected_out is None:
         selected_out = torch.empty((A,), dtype=torch.int32, device=dev)
-    need = kvcomm_anchor_weights_workspace(model, seg_len, A, gran)
     if workspace is None:
+        need = kvcomm_anchor_weights_workspace(model, seg_len, A, gran)
         workspace = torch.empty((max(need, 1),), dtype=torch.uint8, device=dev)
     ptrs, layout, lens = _anchor_args(anchor_base_k, anchor_len, model.dtype, "anchor_base_k")
     _check(lib.kvcomm_anchor_weights(ctypes.byref(model.c()), gran, float(temperature),
@@ -260,7 +282,7 @@ def kvcomm_align_kv(model, base_k, base_v, anchor_dk, anchor_dv, weights, delta_
     if len(anchor_dv) != A:
         raise KVCommError(-1, "anchor_dk and anchor_dv differ in length")
     pk, layout, lens = _anchor_args(anchor_dk, anchor_len, model.dtype, "anchor_dk")
-    pv, layout_v, _ = _anchor_args(anchor_dv, anchor_len, model.dtype, "anchor_dv")
+    pv, layout_v = _anchor_ptrs(anchor_dv, model.dtype, "anchor_dv")
     if A and (layout.stride_layer, layout.stride_head, layout.stride_token) != (
             layout_v.stride_layer, layout_v.stride_head, layout_v.stride_token):
         raise KVCommError(-1, "anchor_dk and anchor_dv must share one layout")
@@ -290,8 +312,6 @@ def _attn_workspace(cmodel, n_ctx, tq, workspace, device, stream):
     """(pointer, bytes, tensor to keep until the call has returned) of the attention's scratch.  A workspace that is
     made here belongs to the stream the kernels run on, so the allocator does not hand it out under them."""
     if workspace is None:
-        if n_ctx + tq < ATTN_MIN_SPLIT_KEYS:
-            return None, 0, None
         need = load_library().kvcomm_suffix_attn_workspace(ctypes.byref(cmodel), n_ctx, tq)
         if not need:
             return None, 0, None
@@ -317,7 +337,9 @@ def kvcomm_suffix_attn(model, q, cache_k, cache_v, n_ctx, softmax_scale=0.0, out
     if want_lse and lse_out is None:
         lse_out = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device)
     cmodel = model.c()
-    ws, ws_bytes, _keep = _attn_workspace(cmodel, int(n_ctx), tq, workspace, q.device, stream)
+    ws, ws_bytes, _keep = None, 0, None
+    if workspace is not None or n_ctx + tq >= ATTN_MIN_SPLIT_KEYS:
+        ws, ws_bytes, _keep = _attn_workspace(cmodel, int(n_ctx), tq, workspace, q.device, stream)
     _check(lib.kvcomm_suffix_attn(ctypes.byref(cmodel), _desc(q, model.dtype, "q"),
                                   _desc(cache_k, model.dtype, "cache_k"), _desc(cache_v, model.dtype, "cache_v"),
                                   int(n_ctx), tq, float(softmax_scale), _desc(out, model.dtype, "out"),
@@ -345,7 +367,9 @@ def kvcomm_suffix_attn_confined_ws(model, q, cache_k, cache_v, n_ctx, max_blocks
     if want_lse and lse_out is None:
         lse_out = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device)
     cmodel = model.c()
-    ws, ws_bytes, _keep = _attn_workspace(cmodel, int(n_ctx), tq, workspace, q.device, stream)
+    ws, ws_bytes, _keep = None, 0, None
+    if workspace is not None or n_ctx + tq >= ATTN_MIN_SPLIT_KEYS:
+        ws, ws_bytes, _keep = _attn_workspace(cmodel, int(n_ctx), tq, workspace, q.device, stream)
     _check(lib.kvcomm_suffix_attn_confined_ws(ctypes.byref(cmodel), _desc(q, model.dtype, "q"),
                                               _desc(cache_k, model.dtype, "cache_k"),
                                               _desc(cache_v, model.dtype, "cache_v"), int(n_ctx), tq,
@@ -367,11 +391,12 @@ def kvcomm_anchor_weights_rule(model, rule, seg_base_k, anchor_base_k, anchor_le
     seg_len = seg_base_k.shape[2]
     A = len(anchor_base_k)
     dev = seg_base_k.device
-    n = kvcomm_weight_slots(model, seg_len, gran)
-    if weights_out is None:
-        weights_out = torch.empty((n, A), dtype=torch.float32, device=dev)
-    if nearest_out is None:
-        nearest_out = torch.empty((n,), dtype=torch.int32, device=dev)
+    if weights_out is None or nearest_out is None:
+        n = kvcomm_weight_slots(model, seg_len, gran)
+        if weights_out is None:
+            weights_out = torch.empty((n, A), dtype=torch.float32, device=dev)
+        if nearest_out is None:
+            nearest_out = torch.empty((n,), dtype=torch.int32, device=dev)
     if selected_out is None:
         selected_out = torch.empty((A,), dtype=torch.int32, device=dev)
     if workspace is None:
@@ -457,11 +482,11 @@ def kvcomm_anchor_weights_batch(model, jobs, temperature=1.0, gran=W_TOKEN, rule
     for j, jd in enumerate(jobs):
         seg = jd["seg_base_k"]
         S, A, dev = seg.shape[2], len(jd["anchor_base_k"]), seg.device
-        slots = kvcomm_weight_slots(model, S, gran)
-        w = jd.get("weights_out")
-        w = torch.empty((slots, A), dtype=torch.float32, device=dev) if w is None else w
-        nr = jd.get("nearest_out")
-        nr = torch.empty((slots,), dtype=torch.int32, device=dev) if nr is None else nr
+        w, nr = jd.get("weights_out"), jd.get("nearest_out")
+        if w is None or nr is None:
+            slots = kvcomm_weight_slots(model, S, gran)
+            w = torch.empty((slots, A), dtype=torch.float32, device=dev) if w is None else w
+            nr = torch.empty((slots,), dtype=torch.int32, device=dev) if nr is None else nr
         so = jd.get("selected_out")
         so = torch.empty((A,), dtype=torch.int32, device=dev) if so is None else so
         ptrs, lay, lens = _anchor_args(jd["anchor_base_k"], jd.get("anchor_len"), model.dtype, "anchor_base_k")
@@ -498,7 +523,7 @@ def kvcomm_align_kv_batch(model, jobs, gran=W_TOKEN, stream=None):
         if len(jd["anchor_dv"]) != A:
             raise KVCommError(-1, "anchor_dk and anchor_dv differ in length")
         pk, lay, lens = _anchor_args(jd["anchor_dk"], jd.get("anchor_len"), model.dtype, "anchor_dk")
-        pv, lay_v, _ = _anchor_args(jd["anchor_dv"], jd.get("anchor_len"), model.dtype, "anchor_dv")
+        pv, lay_v = _anchor_ptrs(jd["anchor_dv"], model.dtype, "anchor_dv")
         if A:
             if not _same_layout(lay, lay_v) or (layout is not None and not _same_layout(layout, lay)):
                 raise KVCommError(-1, "all anchors of a batched call must share one layout")
@@ -527,9 +552,23 @@ def kvcomm_align_kv_batch(model, jobs, gran=W_TOKEN, stream=None):
 
 def _desc_q8(t, what):
     """[layer, head, token, channel] uint8 tensor of E4M3 codes -> kvcomm_tensor (strides in bytes)."""
-    if t.dim() != 4 or t.dtype != torch.uint8 or not t.is_cuda or t.stride(3) != 1:
+    st = t.stride()
+    if t.dtype != torch.uint8 or len(st) != 4 or st[3] != 1 or not t.is_cuda:
         raise KVCommError(-1, f"{what}: expected a 4-d uint8 device tensor with contiguous channels")
-    return _CTensor(t.data_ptr(), t.stride(0), t.stride(1), t.stride(2))
+    return _CTensor(t.data_ptr(), st[0], st[1], st[2])
+
+
+def _anchor_ptrs_q8(dk8, dv8):
+    """Compressed deviations (at least one anchor) -> (key pointers, value pointers, their common layout)."""
+    n = len(dk8)
+    layout = _desc_q8(dk8[0], "anchor_dk8")
+    st = dk8[0].stride()
+    for anchors in (dk8, dv8):
+        for a in anchors:
+            if a.stride() != st or a.dtype != torch.uint8 or not a.is_cuda:
+                _desc_q8(a, "anchor deviations")
+                raise KVCommError(-1, "all compressed anchors must share one layout")
+    return (ctypes.c_void_p * n)(*[a.data_ptr() for a in dk8]), (ctypes.c_void_p * n)(*[a.data_ptr() for a in dv8]), layout
 
 
 def kvcomm_quantize_deltas(model, x, scale, out=None, stream=None):
@@ -551,12 +590,7 @@ def kvcomm_align_kv_q8(model, base_k, base_v, anchor_dk8, anchor_dv8, scale_k, s
     if len(anchor_dv8) != A or len(scale_k) != A or len(scale_v) != A:
         raise KVCommError(-1, "anchor lists and scales differ in length")
     if A:
-        layout = _desc_q8(anchor_dk8[0], "anchor_dk8")
-        for a in list(anchor_dk8) + list(anchor_dv8):
-            if not _same_layout(layout, _desc_q8(a, "anchor deviations")):
-                raise KVCommError(-1, "all compressed anchors must share one layout")
-        pk = (ctypes.c_void_p * A)(*[a.data_ptr() for a in anchor_dk8])
-        pv = (ctypes.c_void_p * A)(*[a.data_ptr() for a in anchor_dv8])
+        pk, pv, layout = _anchor_ptrs_q8(anchor_dk8, anchor_dv8)
         lens = (ctypes.c_int32 * A)(*[int(x) for x in (anchor_len if anchor_len is not None
                                                         else [a.shape[2] for a in anchor_dk8])])
         sk = (ctypes.c_float * A)(*[float(x) for x in scale_k])
@@ -594,15 +628,10 @@ def kvcomm_align_kv_q8_batch(model, jobs, gran=W_TOKEN, stream=None):
             raise KVCommError(-1, "anchor lists and scales differ in length")
         pk = pv = lens = sk = sv = adp = None
         if A:
-            lay = _desc_q8(dk8[0], "anchor_dk8")
-            for a in list(dk8) + list(dv8):
-                if not _same_layout(lay, _desc_q8(a, "anchor deviations")):
-                    raise KVCommError(-1, "all compressed anchors must share one layout")
+            pk, pv, lay = _anchor_ptrs_q8(dk8, dv8)
             if layout is not None and not _same_layout(layout, lay):
                 raise KVCommError(-1, "all anchors of a batched call must share one layout")
             layout = lay
-            pk = (ctypes.c_void_p * A)(*[a.data_ptr() for a in dk8])
-            pv = (ctypes.c_void_p * A)(*[a.data_ptr() for a in dv8])
             al = jd.get("anchor_len")
             lens = (ctypes.c_int32 * A)(*[int(x) for x in (al if al is not None else [a.shape[2] for a in dk8])])
             sk = (ctypes.c_float * A)(*[float(x) for x in jd["scale_k"]])

@@ -137,8 +137,7 @@ int plan_align(const kvcomm_model *model, int gran, const kvcomm_tensor &anchor_
     p.LH = model->n_layers * model->n_kv_heads;
     p.gran = gran;
     p.n_jobs = n_jobs;
-    for (int i = 0; i < model->head_dim / 2; ++i)
-        p.inv_freq[i] = pow(model->rope_theta, -2.0 * (double)i / (double)model->head_dim);
+    fill_inv_freq(p.inv_freq, model->rope_theta, model->head_dim);
 
     const int es = elem_size(dt);
     const int lpr = model->head_dim / (2 * (16 / es));

@@ -255,8 +255,7 @@ extern "C" int kvcomm_capture_offsets(const kvcomm_model *model, kvcomm_tensor b
     p.S = seg_len;
     p.LH = model->n_layers * model->n_kv_heads;
     p.delta = delta_pos;
-    for (int i = 0; i < model->head_dim / 2; ++i)
-        p.inv_freq[i] = pow(model->rope_theta, -2.0 * (double)i / (double)model->head_dim);
+    fill_inv_freq(p.inv_freq, model->rope_theta, model->head_dim);
 
     const int es = elem_size(dt);
     const int lpr = model->head_dim / (2 * (16 / es));

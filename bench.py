@@ -30,9 +30,9 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA, TFLOP/s
 # runs of this script, each scaled by the same counter's reading for a plain 1 GiB copy
 # (profiles/bench_llama8b_5agents_hbm_traffic.md; tests/test_bench_constants.py holds the two together).
 # Not measured live: counters need the profiler.
-HBM_TRAFFIC_READ_WRITTEN = {"align_kv": (2416182477, 268435456),                           # align_kernel
-                            "anchor_weights": (1208184422 + 8502272, 8390349 + 82022),     # dist_partial_kernel + finalize_kernel
-                            "suffix_attn": (537208422, 136314880)}                         # attn_mfma_kernel
+HBM_TRAFFIC_READ_WRITTEN = {"align_kv": (2416172237, 268435456),                           # align_kernel
+                            "anchor_weights": (1208103936 + 2206925, 2101965 + 82022),     # dist_partial_kernel + finalize_kernel
+                            "suffix_attn": (537216205, 136314880)}                         # attn_mfma_kernel
 HBM_TRAFFIC_BYTES = {k: r + w for k, (r, w) in HBM_TRAFFIC_READ_WRITTEN.items()}
 # Share of the kernel's cycles in which a SIMD's matrix pipe is busy (SQ_VALU_MFMA_BUSY_CYCLES per SIMD over
 # GRBM_GUI_ACTIVE per XCD, profiles/suffix_attn_llama8b_5agents_mfma_counters.md); not measured live either.

@@ -50,10 +50,11 @@ struct AlignParams {
 static_assert(sizeof(AlignParams) <= 4096, "kernel arguments are limited to 4 KB");
 
 // INFLIGHT: anchors whose rows are requested together (twice as many 16-byte loads per lane); WPE: wavefronts per SIMD the
-// register budget is sized for.  Four anchors at three wavefronts for pools of four and more, two at four wavefronts for
-// smaller ones.  us per launch, (2, 4) against (4, 3): 4 x 512 tokens, 8 anchors 483 / 460, 16 anchors, 2 x 1024 tokens 845 /
-// 803, weights per (layer, head, token) 478 / 466; 3 x 300 tokens, 2 anchors 89 / 98.  (A vector load of the rotation-table
-// index, whose wait drained every row in flight, used to hold the keys' blocks back: 466 / 820 / 488 us then.)
+// register budget is sized for.  Four anchors at three wavefronts for pools of seven and more, two at four wavefronts for
+// smaller ones.  us per launch of 4 x 512 tokens, (2, 4) against (4, 3): 8 anchors 471 / 449, 7 anchors 414 / 411, 6 anchors
+// 362 / 361, 5 anchors 309 / 328, 4 anchors 264 / 284; 3 x 300 tokens, 2 anchors 89 / 98; 2 x 1024 tokens, 16 anchors 845 /
+// 803.  (A vector load of the rotation-table index, whose wait drained every row in flight, used to hold the keys' blocks
+// back; the 8-anchor launch took 466 us then.)
 template <typename T, int LPR, int INFLIGHT, int WPE>
 __global__ __launch_bounds__(kBlock, WPE) void align_kernel(const AlignParams p)
 {
@@ -191,7 +192,7 @@ int launch_align(const AlignParams &p, int n_blocks, int max_tab, int max_sel, h
     constexpr int HALF = LPR * Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
     const size_t lds = sizeof(float2) * (size_t)max_tab * HALF + sizeof(float) * (size_t)RPB * max_sel;
-    return launch(max_sel >= 4 ? align_kernel<T, LPR, 4, 3> : align_kernel<T, LPR, 2, 4>, dim3(n_blocks, 2), dim3(kBlock), lds, stream, p);
+    return launch(max_sel >= 7 ? align_kernel<T, LPR, 4, 3> : align_kernel<T, LPR, 2, 4>, dim3(n_blocks, 2), dim3(kBlock), lds, stream, p);
 }
 
 }  // namespace

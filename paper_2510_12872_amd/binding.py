@@ -318,7 +318,8 @@ def _attn_workspace(cmodel, n_ctx, tq, workspace, device, stream):
         if stream is None:
             workspace = torch.empty((need,), dtype=torch.uint8, device=device)
         else:
-            with torch.cuda.stream(stream):
+            own = stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream)
+            with torch.cuda.stream(own):
                 workspace = torch.empty((need,), dtype=torch.uint8, device=device)
     return workspace.data_ptr(), workspace.numel() * workspace.element_size(), workspace
 

@@ -97,7 +97,7 @@ __device__ __forceinline__ void dma16_sbase_at(const unsigned char *base, uint32
 __host__ __device__ __forceinline__ int split_bound(int s, int n_splits, int units, int first_hidden)
 {
     if (s >= n_splits) return units;
-    const int b = s * units / n_splits;   // n_splits <= 64, units < 2^25: no overflow
+    const int b = s * units / n_splits;   // n_splits <= 16, units <= 2^26: no overflow
     return b < first_hidden ? b : (s == 0 ? 0 : units);
 }
 

@@ -92,6 +92,38 @@ def test_split_on_another_stream_and_large_scores():
     check_close(to_np(out), oracle.suffix_attn(to_np(q), to_np(k), to_np(v), n_ctx), torch.bfloat16, "large scores")
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_ctx,tq", [(3100, 1), (1500, 330)])
+def test_split_launches_in_a_graph(n_ctx, tq):
+    """Both kinds of split launch, their scratch made during the capture: every replay, with new inputs in place and eager
+    calls (which use scratch of their own) between the replays, equals the eager result bit for bit."""
+    print(f"attn split in a graph: n_ctx{n_ctx} tq{tq}", flush=True)
+    m = _model(1, 8, 4, 128)
+    assert kv.kvcomm_suffix_attn_workspace(m, n_ctx, tq) > 0
+    g = torch.Generator(device=DEV)
+    g.manual_seed(tq)
+    mk = lambda h, n: torch.randn((1, h, n, 128), generator=g, device=DEV).to(torch.bfloat16)
+    q, k, v = mk(32, tq), mk(8, n_ctx + tq), mk(8, n_ctx + tq)
+    out, eager = torch.empty_like(q), torch.empty_like(q)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        kv.kvcomm_suffix_attn(m, q, k, v, n_ctx, out=out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        kv.kvcomm_suffix_attn(m, q, k, v, n_ctx, out=out)
+    for _ in range(3):
+        for t, h, n in ((q, 32, tq), (k, 8, n_ctx + tq), (v, 8, n_ctx + tq)):
+            t.copy_(mk(h, n))
+        kv.kvcomm_suffix_attn(m, q, k, v, n_ctx, out=eager)
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
+
+
 def test_workspace_query():
     lib = binding.load_library()
     q = lambda m, n_ctx, tq: lib.kvcomm_suffix_attn_workspace(ctypes.byref(m.c()), n_ctx, tq)

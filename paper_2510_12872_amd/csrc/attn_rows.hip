@@ -216,7 +216,8 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             const float mw = ml[0][w][n];
-            ltot += mw == -INFINITY ? 0.f : ml[1][w][n] * __builtin_amdgcn_exp2f((mw - M) * p.scale_log2);
+            // reference -inf: no key seen and sum 0, or nothing but NaN scores and a sum that says so
+            ltot += mw == -INFINITY ? ml[1][w][n] : ml[1][w][n] * __builtin_amdgcn_exp2f((mw - M) * p.scale_log2);
         }
         const float f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - M) * p.scale_log2);
         f32x4 *join = reinterpret_cast<f32x4 *>(smem);
@@ -300,10 +301,13 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const AttnParams p)
                 const int s = min(s0 + i, p.n_splits - 1);
                 ms[i] = pm[s * 64];
                 ls[i] = pm[s * 64 + 32];
-                os[i] = po[(int64_t)s * (8 * D)];   // not used, and possibly never written, where m_s is -inf
+                os[i] = po[(int64_t)s * (8 * D)];   // not used, and possibly never written, where m_s is -inf and the sum 0
             }
 #pragma unroll
-            for (int i = 1; i < U; ++i) ms[i] = s0 + i < p.n_splits ? ms[i] : -INFINITY;
+            for (int i = 1; i < U; ++i) {
+                ms[i] = s0 + i < p.n_splits ? ms[i] : -INFINITY;
+                ls[i] = s0 + i < p.n_splits ? ls[i] : 0.f;
+            }
             float mx = M;
 #pragma unroll
             for (int i = 0; i < U; ++i) mx = fmaxf(mx, ms[i]);
@@ -315,7 +319,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const AttnParams p)
             }
 #pragma unroll
             for (int i = 0; i < U; ++i) {
-                if (ms[i] != -INFINITY) {
+                if (ms[i] != -INFINITY || ls[i] != 0.f) {   // a run of NaN scores has reference -inf and sum NaN
                     const float f = __builtin_amdgcn_exp2f((ms[i] - M) * p.scale_log2);
                     L = fmaf(f, ls[i], L);
                     acc += f * os[i];

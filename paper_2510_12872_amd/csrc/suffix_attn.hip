@@ -814,7 +814,7 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void attn_f32_kernel(const AttnP
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
         const float mw = ml[0][w][n];
-        ltot += mw == -INFINITY ? 0.f : ml[1][w][n] * expf(mw - M);
+        ltot += mw == -INFINITY ? ml[1][w][n] : ml[1][w][n] * expf(mw - M);   // reference -inf: sum 0, or NaN from NaN scores
     }
     const float f = m == -INFINITY ? 0.f : expf(m - M);
     vecf *join = reinterpret_cast<vecf *>(smem);   // [wavefront][j][lane]

@@ -93,6 +93,34 @@ def test_split_on_another_stream_and_large_scores():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n_ctx,tq,dtype", [(3100, 1, torch.bfloat16), (1500, 330, torch.bfloat16), (900, 3, torch.float32)])
+def test_nan_reaches_every_query_that_sees_it(n_ctx, tq, dtype):
+    """NaN keys that fill whole runs (and whole wavefronts' sub-steps), and a NaN query: the affected outputs are NaN and
+    no others, as if one block had walked the keys."""
+    print(f"attn NaN: n_ctx{n_ctx} tq{tq} {dtype}", flush=True)
+    m = _model(1, 8, 4, 128, dtype)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(tq)
+    mk = lambda h, n: torch.randn((1, h, n, 128), generator=g, device=DEV).to(dtype)
+    q, k, v = mk(32, tq), mk(8, n_ctx + tq), mk(8, n_ctx + tq)
+    good = kv.kvcomm_suffix_attn(m, q, k, v, n_ctx)
+    kn, qn = k.clone(), q.clone()
+    kn[:, 3, 256:n_ctx - 200] = float("nan")     # kv head 3: query heads 12 ... 15
+    qn[:, 21, tq - 1] = float("nan")
+    got, lse = kv.kvcomm_suffix_attn(m, q, kn, v, n_ctx, want_lse=True)
+    got_q = kv.kvcomm_suffix_attn(m, qn, k, v, n_ctx)
+    torch.cuda.synchronize()
+    assert torch.isnan(got[:, 12:16]).all() and torch.isnan(lse[:, 12:16]).all()
+    assert torch.equal(got[:, :12], good[:, :12]) and torch.equal(got[:, 16:], good[:, 16:])
+    assert torch.isnan(got_q[:, 21, tq - 1]).all()
+    keep = torch.ones(good.shape[:3], dtype=torch.bool, device=DEV)
+    keep[:, 21, tq - 1] = False
+    # The 256-row kernel re-references all rows of the wavefront that holds the NaN query: its neighbours' probabilities
+    # round differently (relative 2^-9 each, |v| < 5: below 2^-8 * 5 = 2e-2).
+    assert float((got_q[keep].float() - good[keep].float()).abs().max()) < 2e-2
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n_ctx,tq", [(3100, 1), (1500, 330)])
 def test_split_launches_in_a_graph(n_ctx, tq):
     """Both kinds of split launch, their scratch made during the capture: every replay, with new inputs in place and eager

@@ -36,6 +36,8 @@
 //     tiles of one (layer, kv head) run on the same XCD and share its L2.
 // fp32 path (attn_f32_kernel): the same transposed products on fp32 MFMA with expf and an online softmax, fp32
 // throughout.
+#include <float.h>
+
 #include "attn_common.h"
 #include "attn_plan.h"
 
@@ -335,10 +337,12 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
         mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
         const float m_new = fmaxf(m, mx);
-        // m == -inf only in the first sub-step, where key 0 is visible to every query and nothing is accumulated yet
+        // m == -inf: nothing but exponentials of 0 so far (the first sub-step, or scores of -inf only)
         const float corr = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_new) * p.scale_log2);
         m = m_new;
-        mc = m_new * p.scale_log2;
+        // No score above -inf yet (key 0 of the block's keys is visible to every query, but its score may be -inf): a
+        // reference so low that scores of -inf still give 0 and the first finite one overflows, which brings it here.
+        mc = fmaxf(m_new * p.scale_log2, -FLT_MAX);
         lsum *= corr;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)

@@ -370,7 +370,8 @@ __global__ __launch_bounds__(kBlock) void dist_row_softmax_kernel(const DistPara
             }
             for (int c = lir; c < jb.n_anchors; c += LPR)
                 if (!((jb.sel_mask >> c) & 1)) wrow[c] = 0.f;
-            if (lir == 0 && jb.nearest) jb.nearest[slot] = p.col[jb.a0 + best];
+            // best == NA: no distance is finite; equal distances, so the lowest index, as in the two-stage form
+            if (lir == 0 && jb.nearest) jb.nearest[slot] = p.col[jb.a0 + (best < na ? best : 0)];
         }
     }
 }

@@ -97,3 +97,26 @@ def test_update_pool_sizes(gran, dtype, D):
             want = oracle.align(to_np(bk), to_np(bv), devs[0], devs[1], w.cpu().numpy().astype(np.float64).T, delta, 5e5, adp, gran)
             check_close(to_np(got[0]), want[0], dtype, "K^")
             check_close(to_np(got[1]), want[1], dtype, "V^")
+
+
+@pytest.mark.parametrize("gran", [kv.W_TOKEN, kv.W_LAYER_HEAD_TOKEN, kv.W_SEGMENT])
+def test_nearest_of_infinite_distances(gran):
+    """Every anchor infinitely far away: equal distances, so `nearest` is the lowest selected index of the segment's OWN pool
+    (pools of 3 and 4 in one launch; the first anchor of the second pool is too short)."""
+    print(f"infinite distances gran{gran}", flush=True)
+    L, H, D, S = 2, 2, 128, 21
+    m = kv.Model(L, H, H, D, torch.bfloat16, 5e5)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(4)
+    mk = lambda: torch.randn((L, H, S, D), generator=g, device=DEV).to(torch.bfloat16)
+    segs = [mk(), mk()]
+    for s in segs:
+        s[:, :, 7, 3] = float("inf")
+    jobs = [dict(seg_base_k=segs[0], anchor_base_k=[mk() for _ in range(3)]),
+            dict(seg_base_k=segs[1], anchor_base_k=[mk() for _ in range(4)], anchor_len=[S - 1, S, S, S])]
+    got = kv.kvcomm_anchor_weights_batch(m, jobs, 1.0, gran)
+    torch.cuda.synchronize()
+    for (w, near, sel), jd, first in zip(got, jobs, (0, 1)):
+        bad = near if gran == kv.W_SEGMENT else near.view(-1, S)[:, 7]
+        assert (bad == first).all(), bad
+        assert near.min() >= first and near.max() < len(jd["anchor_base_k"])

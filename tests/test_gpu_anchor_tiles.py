@@ -120,3 +120,39 @@ def test_nearest_of_infinite_distances(gran):
         bad = near if gran == kv.W_SEGMENT else near.view(-1, S)[:, 7]
         assert (bad == first).all(), bad
         assert near.min() >= first and near.max() < len(jd["anchor_base_k"])
+
+
+@pytest.mark.parametrize("dtype,D", [(torch.bfloat16, 128), (torch.bfloat16, 64), (torch.float32, 128), (torch.float32, 256)])
+@pytest.mark.parametrize("gran", [kv.W_TOKEN, kv.W_LAYER_HEAD_TOKEN])
+def test_update_batches_of_unequal_pools(gran, dtype, D):
+    """Pools on both sides of the line between the update's two forms in one launch (the largest pool of a launch chooses):
+    bit-identical to the separate calls, rotated and unrotated deviations mixed, plain and E4M3."""
+    L, H, S = 2, 3, 35
+    m = kv.Model(L, H, H, D, dtype, 5e5)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(D + gran)
+    mk = lambda s=1.0: (torch.randn((L, H, S, D), generator=g, device=DEV) * s).to(dtype)
+    n = kv.kvcomm_weight_slots(m, S, gran)
+    for pools in ((2, 9), (7, 1, 3), (6, 16, 5)):
+        print(f"update of unequal pools: D{D} {dtype} gran{gran} {pools}", flush=True)
+        jobs, jobs8 = [], []
+        for j, A in enumerate(pools):
+            w = torch.softmax(torch.randn((n, A), generator=g, device=DEV), 1).contiguous()
+            d = dict(base_k=mk(), base_v=mk(), weights=w, delta_pos=300 + 40 * j, out_k=torch.empty_like(mk()),
+                     out_v=torch.empty_like(mk()), anchor_delta_pos=[(300 + 40 * j, 77, 1024)[a % 3] for a in range(A)])
+            dk, dv = [mk(0.05) for _ in range(A)], [mk(0.05) for _ in range(A)]
+            q8 = lambda x: [kv.kvcomm_quantize_deltas(m, t, 2.0 ** -9) for t in x]
+            jobs.append(dict(d, anchor_dk=dk, anchor_dv=dv))
+            jobs8.append(dict(d, anchor_dk8=q8(dk), anchor_dv8=q8(dv), scale_k=[2.0 ** -9] * A, scale_v=[2.0 ** -9] * A,
+                              out_k=torch.empty_like(d["out_k"]), out_v=torch.empty_like(d["out_v"])))
+        kv.kvcomm_align_kv_batch(m, jobs, gran)
+        kv.kvcomm_align_kv_q8_batch(m, jobs8, gran)
+        for jd, j8 in zip(jobs, jobs8):
+            ok, ov = torch.empty_like(jd["out_k"]), torch.empty_like(jd["out_v"])
+            kv.kvcomm_align_kv(m, jd["base_k"], jd["base_v"], jd["anchor_dk"], jd["anchor_dv"], jd["weights"],
+                               jd["delta_pos"], ok, ov, None, jd["anchor_delta_pos"], gran)
+            assert torch.equal(ok, jd["out_k"]) and torch.equal(ov, jd["out_v"])
+            kv.kvcomm_align_kv_q8(m, jd["base_k"], jd["base_v"], j8["anchor_dk8"], j8["anchor_dv8"], j8["scale_k"],
+                                  j8["scale_v"], jd["weights"], jd["delta_pos"], ok, ov, None, jd["anchor_delta_pos"], gran)
+            torch.cuda.synchronize()
+            assert torch.equal(ok, j8["out_k"]) and torch.equal(ov, j8["out_v"])

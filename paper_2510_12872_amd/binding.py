@@ -310,17 +310,21 @@ def kvcomm_suffix_attn_workspace(model, n_ctx, tq):
 
 def _attn_workspace(cmodel, n_ctx, tq, workspace, device, stream):
     """(pointer, bytes, tensor to keep until the call has returned) of the attention's scratch.  A workspace that is
-    made here belongs to the stream the kernels run on, so the allocator does not hand it out under them."""
+    made here belongs to the stream the kernels run on, so the allocator does not hand it out under them.  Where there is
+    no memory for it the call does without (same result up to rounding, only slower)."""
     if workspace is None:
         need = load_library().kvcomm_suffix_attn_workspace(ctypes.byref(cmodel), n_ctx, tq)
         if not need:
             return None, 0, None
-        if stream is None:
-            workspace = torch.empty((need,), dtype=torch.uint8, device=device)
-        else:
-            own = stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream)
-            with torch.cuda.stream(own):
+        try:
+            if stream is None:
                 workspace = torch.empty((need,), dtype=torch.uint8, device=device)
+            else:
+                own = stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream)
+                with torch.cuda.stream(own):
+                    workspace = torch.empty((need,), dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            return None, 0, None
     return workspace.data_ptr(), workspace.numel() * workspace.element_size(), workspace
 
 

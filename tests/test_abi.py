@@ -429,3 +429,15 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode != 0
     assert "ONE GPU" in (r.stderr + r.stdout)
+
+
+def test_attention_without_memory_for_its_scratch(lib, monkeypatch):
+    """The scratch that the binding makes is optional: the call goes on without it where the allocation fails."""
+    model = kv.Model(1, 8, 32, 128, torch.bfloat16, 5e5)
+    assert kv.kvcomm_suffix_attn_workspace(model, 2560, 512) > 0
+
+    def no_memory(*a, **k):
+        raise torch.OutOfMemoryError("no memory")
+
+    monkeypatch.setattr(torch, "empty", no_memory)
+    assert binding._attn_workspace(model.c(), 2560, 512, None, "cuda", None) == (None, 0, None)

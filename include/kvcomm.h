@@ -249,8 +249,9 @@ int kvcomm_suffix_attn(const kvcomm_model *model, kvcomm_tensor q,
  * alignment of the next agent next to the matrix-core-bound attention of the current one.  (Under the chip's
  * power limit the attention loses less than its share of compute units: measured 0.82 ms on 160 of 256 against
  * 0.66 ms on all of them.)  max_blocks is spread over the 8 XCDs in launch order; values of at least the number
- * of work items give the plain launch.  f32 tensors ignore max_blocks (their kernel is small-block and never fills
- * the chip's registers).  The kernel that joins the partial results of a split launch is small-block too.
+ * of work items give the plain launch.  The same holds for f32 tensors; f32 caches of up to 64 tokens ignore max_blocks
+ * (their kernel is small-block and never fills a compute unit), and so does the kernel that joins the partial results
+ * of a split launch.
  * Errors: as kvcomm_suffix_attn; KVCOMM_EINVAL for max_blocks < 8 (one block per XCD is the minimum).          */
 int kvcomm_suffix_attn_confined(const kvcomm_model *model, kvcomm_tensor q,
                                 kvcomm_tensor cache_k, kvcomm_tensor cache_v,

@@ -658,7 +658,7 @@ __global__ __launch_bounds__(256) void attn_f32_row_kernel(const AttnParams p)
 constexpr int kF32Waves = 8;
 
 template <int D>
-__global__ __launch_bounds__(64 * kF32Waves, 2) void attn_f32_kernel(const AttnParams p)
+__device__ __forceinline__ void attn_f32_item(const AttnParams &p, int item)   // item: one row tile of a (layer, kv head)
 {
     constexpr int NW = kF32Waves;
     constexpr int HD = D / 2, NDB = D / 32;
@@ -672,7 +672,7 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void attn_f32_kernel(const AttnP
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, n = lane & 31, hg = lane >> 5;
-    const int rt = blockIdx.x % p.n_row_tiles, lh = blockIdx.x / p.n_row_tiles;
+    const int rt = item % p.n_row_tiles, lh = item / p.n_row_tiles;
     const int l = lh / p.Hkv, hkv = lh % p.Hkv;
     const int r_row = rt * 32 + n;
     const bool valid = r_row / p.G < p.tq;
@@ -868,6 +868,21 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void attn_f32_kernel(const AttnP
     }
 }
 
+// PERSIST: a grid of fewer blocks than items, each walking every gridDim.x-th one.  A block fills a CU (eight wavefronts of up to
+// 256 registers, 64 or 128 KB of LDS), so such a launch keeps to gridDim.x of them.
+template <int D, bool PERSIST>
+__global__ __launch_bounds__(64 * kF32Waves, 2) void attn_f32_kernel(const AttnParams p)
+{
+    if constexpr (!PERSIST) {
+        attn_f32_item<D>(p, blockIdx.x);
+    } else {
+        for (int item = blockIdx.x; item < p.n_items; item += gridDim.x) {
+            attn_f32_item<D>(p, item);
+            __syncthreads();   // the joined states have been read: LDS becomes the next item's
+        }
+    }
+}
+
 }  // namespace
 
 extern "C" size_t kvcomm_suffix_attn_workspace(const kvcomm_model *model, int32_t n_ctx, int32_t tq)
@@ -889,7 +904,8 @@ int launch_mfma(const AttnParams &p, unsigned n_blocks, bool persist, hipStream_
                    : launch(attn_mfma_kernel<D, NW, WPE, false, false>, grid, block, 0, s, p);
 }
 
-// max_blocks > 0: at most that many thread blocks (the bf16 kernels' persistent form when there are more items).
+// max_blocks > 0: at most that many thread blocks (the kernels' persistent form when there are more items; the fp32 kernel of
+// short caches is small-block and ignores it).
 // A workspace of at least kvcomm_suffix_attn_workspace() bytes lets a small launch split the key axis; without one
 // (or with one that is too small or not 16-byte aligned) the keys of a row tile stay in one block.
 int suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_k, kvcomm_tensor cache_v, int32_t n_ctx,
@@ -939,11 +955,13 @@ int suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_
         p.n_row_tiles = (int32_t)(((int64_t)p.G * tq + 31) / 32);
         const int64_t n_blocks = (int64_t)p.L * p.Hkv * p.n_row_tiles;
         if (n_blocks > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
-        const dim3 grid((unsigned)n_blocks), block(64 * kF32Waves);
+        p.n_items = (int32_t)n_blocks;
+        const bool persist = max_blocks > 0 && max_blocks < p.n_items;
+        const dim3 grid((unsigned)(persist ? max_blocks : p.n_items)), block(64 * kF32Waves);
         switch (D) {
-            case 64: return launch(attn_f32_kernel<64>, grid, block, 0, s, p);
-            case 128: return launch(attn_f32_kernel<128>, grid, block, 0, s, p);
-            case 256: return launch(attn_f32_kernel<256>, grid, block, 0, s, p);
+            case 64: return launch(persist ? attn_f32_kernel<64, true> : attn_f32_kernel<64, false>, grid, block, 0, s, p);
+            case 128: return launch(persist ? attn_f32_kernel<128, true> : attn_f32_kernel<128, false>, grid, block, 0, s, p);
+            case 256: return launch(persist ? attn_f32_kernel<256, true> : attn_f32_kernel<256, false>, grid, block, 0, s, p);
             default: return KVCOMM_EUNSUPPORTED;
         }
     }

@@ -308,10 +308,19 @@ def kvcomm_suffix_attn_workspace(model, n_ctx, tq):
     return int(load_library().kvcomm_suffix_attn_workspace(ctypes.byref(model.c()), int(n_ctx), int(tq)))
 
 
+def _in_private_pool(t):
+    """Does t lie in one of the allocator's private pools, as all that is allocated under torch.cuda.graph does?  (Slow, asked
+    during captures only.)"""
+    p = t.data_ptr()
+    return any(seg["address"] <= p < seg["address"] + seg["total_size"] and tuple(seg["segment_pool_id"]) != (0, 0)
+               for seg in torch.cuda.memory_snapshot())
+
+
 def _attn_workspace(cmodel, n_ctx, tq, workspace, device, stream):
     """(pointer, bytes, tensor to keep until the call has returned) of the attention's scratch.  A workspace that is
     made here belongs to the stream the kernels run on, so the allocator does not hand it out under them.  Where there is
-    no memory for it the call does without (same result up to rounding, only slower)."""
+    no memory for it, or a graph that torch does not manage is being captured (the allocator would hand the memory out
+    again while the graph's replays write to it), the call does without: same result up to rounding, only slower."""
     if workspace is None:
         need = load_library().kvcomm_suffix_attn_workspace(ctypes.byref(cmodel), n_ctx, tq)
         if not need:
@@ -319,11 +328,15 @@ def _attn_workspace(cmodel, n_ctx, tq, workspace, device, stream):
         try:
             if stream is None:
                 workspace = torch.empty((need,), dtype=torch.uint8, device=device)
+                capturing = torch.cuda.is_current_stream_capturing()
             else:
                 own = stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream)
                 with torch.cuda.stream(own):
                     workspace = torch.empty((need,), dtype=torch.uint8, device=device)
+                    capturing = torch.cuda.is_current_stream_capturing()
         except torch.OutOfMemoryError:
+            return None, 0, None
+        if capturing and not _in_private_pool(workspace):
             return None, 0, None
     return workspace.data_ptr(), workspace.numel() * workspace.element_size(), workspace
 

@@ -18,6 +18,7 @@
 // similarities).  Both reuse the two-stage structure and the finalize kernels.
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -32,19 +33,25 @@ namespace {
 
 using namespace kvc;
 
-#ifndef KVC_DIST_BLOCKS
-// Blocks per segment the distance grid aims at.  Fewer blocks = longer runs of (layer, head) pairs = fewer partial sums for
-// the second stage; measured (us per call, both stages, the same inputs call after call) with 256 / 512 / 1024 / 2048
-// blocks: 4 segments x 512 tokens, 8 anchors 200 / 185 / 186 / 201; 1024 tokens, 64 anchors (with the update) 2086 / 2094 /
-// 2106 / 2188; D = 64 100 / 101 / 104 / 119.
-#define KVC_DIST_BLOCKS 512
-#endif
-
 constexpr int kBlock = 256;
 constexpr int kFinalBlock = 512; // threads of a finalize_kernel block
 constexpr int kSegBlock = 1024;  // threads of a finalize_segment_kernel block
 constexpr int kFinalRun = 16;    // partials of one chunk that stay together in a finalize_kernel block
+constexpr int kFinalLanes = 16;  // threads that share the chunks of a (slot, anchor) pair: at most this many, or one per eight chunks
+constexpr int kGroupPairs = 32;  // (chunk, token tile) pairs of a group, a multiple of 8
+constexpr int kMaxGroups = 32768;  // extent of the grid in z (the hardware takes 65535)
 constexpr int kAnchorTile = 16;  // anchors whose accumulators one lane keeps in registers
+
+// Blocks per segment the distance grid aims at.  Fewer blocks = longer runs of (layer, head) pairs = fewer partial sums for the
+// second stage: 512 for short segments.  Three blocks per compute unit (768) where runs stay long, kLongRun pairs and more: small
+// pools then have enough loads in flight, and the runs of 512 blocks, a power of two of kFarApart bytes and more apart, meet in the
+// same memory channels.  Batches whose runs are closer together have blocks enough with 512 per segment.
+// us per call, both stages, input sets in no cache, with 512 / 768 / 1024 / 2048 blocks (H = 8, L = 8 ... 32):
+//   77 tokens, 12 anchors, cosine, D 64   21 / 27 / 27 / 27      200 tokens, 12 anchors, D 256         40 / 45 / 46 / 46
+//   512 tokens, 4 anchors, f32 D 128      40 / 34 / 34 / 33      1024 tokens, 1 anchor, D 256          61 / 50 / 53 / 52
+//   8 x 512 tokens, 5 anchors, f32 D 128  301 / 261 / 263 / 253  4 x 512 tokens, 8 anchors, D 128      188 / 193 / 187 / 194
+constexpr int kDistBlocks = 512, kDistBlocksLong = 768, kLongRun = 9;
+constexpr int64_t kFarApart = (int64_t)4 << 20;
 
 // How a launch is cut into blocks.  Rows of one (layer, head) are LPR lanes wide; a block owns RPB
 // consecutive tokens and a run of lh_per_block (layer, head) pairs ("chunk").
@@ -68,11 +75,15 @@ DistPlan make_plan(const kvcomm_model *m, const int32_t *seg_lens, int n_jobs, i
     } else {
         int64_t tiles = 0;
         for (int j = 0; j < n_jobs; ++j) tiles += (seg_lens[j] + pl.rpb - 1) / pl.rpb;
-        const int64_t target_blocks = (int64_t)KVC_DIST_BLOCKS * n_jobs;
-        int64_t n_chunks = (target_blocks + tiles - 1) / tiles;
-        if (n_chunks > LH) n_chunks = LH;
-        if (n_chunks < 1) n_chunks = 1;
-        pl.lh_per_block = (int)((LH + n_chunks - 1) / n_chunks);
+        auto run_of = [&](int64_t blocks) {   // (layer, head) pairs per block
+            const int64_t n_chunks = std::max<int64_t>(1, std::min<int64_t>(LH, (blocks * n_jobs + tiles - 1) / tiles));
+            return (int)((LH + n_chunks - 1) / n_chunks);
+        };
+        int64_t longest = 0;
+        for (int j = 0; j < n_jobs; ++j) longest = std::max<int64_t>(longest, seg_lens[j]);
+        pl.lh_per_block = run_of(kDistBlocksLong);
+        const int64_t run_bytes = run_of(kDistBlocks) * longest * m->head_dim * elem_size(m->dtype);
+        if (pl.lh_per_block < kLongRun || (n_jobs > 1 && run_bytes < kFarApart)) pl.lh_per_block = run_of(kDistBlocks);
     }
     pl.n_chunks = (LH + pl.lh_per_block - 1) / pl.lh_per_block;
     return pl;
@@ -98,10 +109,10 @@ struct DistParams {
     Strides s_anc;
     int32_t H, LH, lh_per_block, n_jobs;
     int32_t fused, rule;   // fused: a row's distances are complete inside its lanes; write the weights here
-    int32_t n_blocks, a_tiles;   // distance kernel: (chunk, token tile) pairs of all segments, anchor tiles of the largest pool
+    int32_t n_blocks, group_pairs, tile_anchors;   // distance kernel: (chunk, token tile) pairs of all segments and of a group, anchors of a tile
     int32_t per_segment;   // one weight set per segment: a block also adds up its rows (partial[chunk][tile][anchor])
     double tau;
-    const void *anc[KVCOMM_MAX_ANCHORS];  // selected anchors of all segments
+    const void *anc[KVCOMM_MAX_ANCHORS + kAnchorTile];  // selected anchors of all segments (a tile's pointers are read without a look at how many it has)
     uint8_t col[KVCOMM_MAX_ANCHORS];      // original index of a selected anchor
 };
 static_assert(sizeof(DistParams) <= 4096, "kernel arguments are limited to 4 KB");
@@ -114,6 +125,15 @@ __device__ __forceinline__ int job_of_block(const DistParams &p, int block)
         if (i < p.n_jobs && block >= p.job[i].block0) ji = i;
     return ji;
 }
+
+// The grid of the two-stage distance kernels is (pairs of a group, anchor tiles, groups) over the (chunk, token tile) pairs of
+// all segments.  With groups of a few pairs the anchor tiles of one pair run at about the same time on the same XCD (hardware
+// deals block ids, x fastest, round-robin to the 8 XCDs), so that the segment's rows come from HBM once and from the XCD's L2
+// after that.  Where the segments of a launch have different numbers of l2 tiles, one group holds all pairs: between each other
+// the tiles that a small pool does not have would leave the same compute units without work (pools of 20, 3 and 3 anchors, 512
+// tokens each, D = 256, 16 layers x 8 heads: 191 us in groups, 158 in one).  The cosine rule's narrower tiles gain more from
+// the L2 than they lose (the same pools, 32 layers: 309 us in groups, 354 in one).
+__device__ __forceinline__ int pair_of_block(const DistParams &p) { return blockIdx.z * p.group_pairs + blockIdx.x; }
 
 // Sum of squared differences of two 16-byte vectors, added to a double accumulator.
 template <typename T>
@@ -129,18 +149,19 @@ __device__ __forceinline__ void sqdiff_acc(double &acc, const float (&x)[Elem<T>
 }
 
 // Anchor pointers of a tile in scalar registers for the whole kernel.  (Read where they are used, each anchor's load waited
-// for a scalar load of its own pointer, in every (layer, head) pair.)
+// for a scalar load of its own pointer, in every (layer, head) pair.)  All NA are read in one go, also behind the tile's last
+// anchor (never followed): picked one by one they held up the first rows of blocks that walk one pair only (cosine, 1 anchor,
+// per-(layer, head, token) weights: 47 against 44 us).
 template <typename T, int NA>
 struct AnchorPtrs {
     typedef const __attribute__((address_space(1))) u32x4 gvec;
     uint64_t ptr[NA];
-    __device__ __forceinline__ AnchorPtrs(const DistParams &p, int first, int na)
+    __device__ __forceinline__ AnchorPtrs(const DistParams &p, int first)
     {
 #pragma unroll
-        for (int j = 0; j < NA; ++j) {
-            ptr[j] = reinterpret_cast<uint64_t>(p.anc[first + min(j, na - 1)]);
-            asm volatile("" : "+s"(ptr[j]));
-        }
+        for (int j = 0; j < NA; ++j) ptr[j] = reinterpret_cast<uint64_t>(p.anc[first + j]);
+#pragma unroll
+        for (int j = 0; j < NA; ++j) asm volatile("" : "+s"(ptr[j]));
     }
     __device__ __forceinline__ u32x4 load(int j, int64_t off) const   // off in elements
     {
@@ -159,10 +180,7 @@ __global__ __launch_bounds__(kBlock) void dist_partial_kernel(const DistParams p
 {
     constexpr int EPV = Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
-    // Anchor tiles of one (chunk, token tile): consecutive blocks of the same XCD (hardware deals block ids round-robin
-    // to the 8 XCDs), so that the segment's rows come from HBM once and from the XCD's L2 after that.
-    const int group = blockIdx.x / (8 * p.a_tiles), in_group = blockIdx.x % (8 * p.a_tiles);
-    const int block = group * 8 + in_group % 8;
+    const int block = pair_of_block(p);
     if (block >= p.n_blocks) return;
     const DistJob &jb = p.job[job_of_block(p, block)];
     const int tid = threadIdx.x;
@@ -170,8 +188,9 @@ __global__ __launch_bounds__(kBlock) void dist_partial_kernel(const DistParams p
     const int bx = block - jb.block0;
     const int tile = bx % jb.n_token_tiles;
     const int chunk = bx / jb.n_token_tiles;
-    const int a0 = in_group / 8 * NA;
-    const int na = min(NA, jb.n_sel - a0);
+    const int a0 = blockIdx.y * p.tile_anchors;
+    const int na = min(p.tile_anchors, jb.n_sel - a0);
+    __builtin_assume(na <= NA);   // (without it the 16-anchor kernel takes 132 registers: 3 wavefronts per SIMD, 8 % slower)
     if (na <= 0) return;  // the launch's anchor tiles cover the largest pool of the launch
     const int t = tile * RPB + row;
     const bool valid = t < jb.S;
@@ -182,7 +201,7 @@ __global__ __launch_bounds__(kBlock) void dist_partial_kernel(const DistParams p
 #pragma unroll
     for (int j = 0; j < NA; ++j) acc[j] = 0.0;
 
-    const AnchorPtrs<T, NA> anc(p, jb.a0 + a0, na);
+    const AnchorPtrs<T, NA> anc(p, jb.a0 + a0);
     const T *seg = static_cast<const T *>(jb.seg_k) + t * jb.s_seg.token + lir * EPV;
     const int64_t arow = t * p.s_anc.token + lir * EPV;
     auto walk = [&](auto full) __attribute__((always_inline)) {   // full: every anchor of the tile exists (no branches)
@@ -297,7 +316,7 @@ __global__ __launch_bounds__(kBlock) void dist_row_softmax_kernel(const DistPara
     const int lh1 = min(lh0 + p.lh_per_block, p.LH);
     if (bx == 0 && jb.selected_out && tid < jb.n_anchors) jb.selected_out[tid] = (int32_t)((jb.sel_mask >> tid) & 1);
 
-    const AnchorPtrs<T, NA> anc(p, jb.a0, na);
+    const AnchorPtrs<T, NA> anc(p, jb.a0);
     const T *seg = static_cast<const T *>(jb.seg_k) + t * jb.s_seg.token + lir * EPV;
     const int64_t arow = t * p.s_anc.token + lir * EPV;
     for (int lh = lh0; lh < lh1; ++lh) {
@@ -385,8 +404,7 @@ __global__ __launch_bounds__(kBlock) void cos_partial_kernel(const DistParams p)
 {
     constexpr int EPV = Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
-    const int group = blockIdx.x / (8 * p.a_tiles), in_group = blockIdx.x % (8 * p.a_tiles);   // as in dist_partial_kernel
-    const int block = group * 8 + in_group % 8;
+    const int block = pair_of_block(p);
     if (block >= p.n_blocks) return;
     const DistJob &jb = p.job[job_of_block(p, block)];
     const int tid = threadIdx.x;
@@ -394,8 +412,9 @@ __global__ __launch_bounds__(kBlock) void cos_partial_kernel(const DistParams p)
     const int bx = block - jb.block0;
     const int tile = bx % jb.n_token_tiles;
     const int chunk = bx / jb.n_token_tiles;
-    const int a0 = in_group / 8 * kCosTile;
-    const int na = min(kCosTile, jb.n_sel - a0);
+    const int a0 = blockIdx.y * p.tile_anchors;
+    const int na = min(p.tile_anchors, jb.n_sel - a0);
+    __builtin_assume(na <= kCosTile);
     if (na <= 0) return;
     const int t = tile * RPB + row;
     const bool valid = t < jb.S;
@@ -407,7 +426,7 @@ __global__ __launch_bounds__(kBlock) void cos_partial_kernel(const DistParams p)
 #pragma unroll
     for (int j = 0; j < kCosTile; ++j) dot[j] = ny[j] = 0.0;
 
-    const AnchorPtrs<T, kCosTile> anc(p, jb.a0 + a0, na);
+    const AnchorPtrs<T, kCosTile> anc(p, jb.a0 + a0);
     if (valid) {
         const T *seg = static_cast<const T *>(jb.seg_k) + t * jb.s_seg.token + lir * EPV;
         const int64_t arow = t * p.s_anc.token + lir * EPV;
@@ -540,9 +559,11 @@ __device__ __forceinline__ void slot_softmax(const FinalParams &p, const FinalJo
 // threads, so a wavefront reads runs of a chunk's row), the CL sums meet in LDS and are added in increasing c, so the
 // result does not depend on timing.
 // The kernel is a chain of latencies (chunk loads, LDS sums, a double-precision root and exponential), so the chunks are
-// spread over as many threads as keep runs of 16 partials (128 bytes) together, and every exponential is formed once:
-// 77 tokens, 5 anchors, 256 chunks 14.1 -> 6.0 us; 4 x 512 tokens, 8 anchors 7.6 -> 5.5 us; 1024 tokens, 64 anchors
-// 16.6 -> 10.2 us against eight threads per pair and n_sel exponentials in each.
+// spread over several threads, runs of 16 partials (128 bytes) stay together, and every exponential is formed once.  Up to 16
+// threads per pair (or one per eight chunks): with 32 the second chain, of LDS sums, takes longer than what the first one
+// saves (cosine, 2 anchors, 64 chunks: 6.4 us with 32, 5.3 with 16; 77 tokens, 5 anchors, l2, both stages: 18.6 and 17.8).
+// Against eight threads per pair and n_sel exponentials in each, with the chunk counts of that time: 77 tokens, 5 anchors 14.1 -> 6.0
+// us; 4 x 512 tokens, 8 anchors 7.6 -> 5.5; 1024 tokens, 64 anchors 16.6 -> 10.2.
 __global__ __launch_bounds__(kFinalBlock) void finalize_kernel(const FinalParams p)
 {
     __shared__ double dsh[kFinalBlock], esh[kFinalBlock];
@@ -617,7 +638,8 @@ __global__ __launch_bounds__(kFinalBlock) void finalize_kernel(const FinalParams
 }
 
 // Per-segment granularity: one block per segment.  The distance kernel has left one partial per (chunk, token
-// tile, anchor), n_rows = n_chunks * n_token_tiles rows of n_sel values (about 2048 whatever the segment).  Thread t adds
+// tile, anchor), n_rows = n_chunks * n_token_tiles rows of n_sel values (512 ... 768 by make_plan, fewer for small models and
+// short segments, which have layers * heads chunks per tile at most).  Thread t adds
 // the rows g, g + G, ... of anchor t % n_sel (g = t / n_sel, G = kSegBlock / n_sel groups: consecutive threads read
 // consecutive addresses; eight interleaved chains keep as many loads in flight); the groups' sums are added in LDS, 16
 // threads per anchor and then one, in a fixed order, so the result does not depend on timing.
@@ -677,7 +699,7 @@ __global__ __launch_bounds__(kSegBlock) void finalize_segment_kernel(const Final
 }
 
 template <typename T, int LPR>
-int launch_dist(const DistParams &p, int n_blocks, int max_sel, bool cosine, hipStream_t stream)
+int launch_dist(const DistParams &p, int n_blocks, int max_sel, int min_sel, bool cosine, hipStream_t stream)
 {
     const int na = cosine ? kCosTile : max_sel <= 4 ? 4 : max_sel <= 8 ? 8 : kAnchorTile;
     if (p.fused)
@@ -685,12 +707,21 @@ int launch_dist(const DistParams &p, int n_blocks, int max_sel, bool cosine, hip
                       dim3(n_blocks), dim3(kBlock), 0, stream, p);
     DistParams q = p;
     q.n_blocks = n_blocks;
-    q.a_tiles = (max_sel + na - 1) / na;
-    const int64_t grid = ((int64_t)n_blocks + 7) / 8 * 8 * q.a_tiles;
-    if (grid > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
+    const int a_tiles = (max_sel + na - 1) / na;
+    const bool same_tiles = cosine || (min_sel + na - 1) / na == a_tiles;
+    // Tiles of equal width (17 anchors: 9 + 8, not 16 + 1): with a narrow last tile every other block would have next to
+    // nothing to do, and so would the compute units they land on (17 anchors, 1024 tokens, per-(layer, head, token) weights,
+    // f32 D = 256: 341 -> 234 us; per-token weights, bf16 D = 128, 32 layers: 233 -> 195; 9 anchors, cosine: 285 -> 194).
+    q.tile_anchors = same_tiles ? (max_sel + a_tiles - 1) / a_tiles : na;
+    q.group_pairs = n_blocks;
+    if (same_tiles && a_tiles > 1) {   // at most kMaxGroups groups
+        q.group_pairs = kGroupPairs;
+        while ((n_blocks - 1) / q.group_pairs >= kMaxGroups) q.group_pairs *= 2;
+    }
+    const dim3 grid((unsigned)q.group_pairs, (unsigned)a_tiles, (unsigned)((n_blocks + q.group_pairs - 1) / q.group_pairs));
     return launch(cosine ? cos_partial_kernel<T, LPR> : na == 4 ? dist_partial_kernel<T, LPR, 4> : na == 8 ? dist_partial_kernel<T, LPR, 8>
                                                                                               : dist_partial_kernel<T, LPR, kAnchorTile>,
-                  dim3((unsigned)grid), dim3(kBlock), 0, stream, q);
+                  grid, dim3(kBlock), 0, stream, q);
 }
 
 int check_rule(int rule)
@@ -858,7 +889,7 @@ extern "C" int kvcomm_anchor_weights_batch(const kvcomm_model *model, int32_t gr
         if (gran == KVCOMM_W_TOKEN && dj.n_sel > 0) {
             const int slots = (kFinalRun + dj.n_sel - 1) / dj.n_sel;   // of a run
             cl = kFinalBlock / (slots * dj.n_sel);
-            if (cl > pl.n_chunks) cl = pl.n_chunks;
+            cl = std::min(cl, std::min(pl.n_chunks, std::max(kFinalLanes, pl.n_chunks / 8)));
         }
         fj.chunk_lanes = cl;
         const int spb = dj.n_sel > 0 ? kFinalBlock / (cl * dj.n_sel) : kFinalBlock;
@@ -872,15 +903,15 @@ extern "C" int kvcomm_anchor_weights_batch(const kvcomm_model *model, int32_t gr
         const int nb = (int)dist_blocks;
         if (dt == KVCOMM_BF16) {
             switch (pl.lpr) {
-                case 8: st = launch_dist<bf16_t, 8>(dp, nb, max_sel, cosine, s); break;
-                case 16: st = launch_dist<bf16_t, 16>(dp, nb, max_sel, cosine, s); break;
-                case 32: st = launch_dist<bf16_t, 32>(dp, nb, max_sel, cosine, s); break;
+                case 8: st = launch_dist<bf16_t, 8>(dp, nb, max_sel, min_sel, cosine, s); break;
+                case 16: st = launch_dist<bf16_t, 16>(dp, nb, max_sel, min_sel, cosine, s); break;
+                case 32: st = launch_dist<bf16_t, 32>(dp, nb, max_sel, min_sel, cosine, s); break;
             }
         } else {
             switch (pl.lpr) {
-                case 16: st = launch_dist<float, 16>(dp, nb, max_sel, cosine, s); break;
-                case 32: st = launch_dist<float, 32>(dp, nb, max_sel, cosine, s); break;
-                case 64: st = launch_dist<float, 64>(dp, nb, max_sel, cosine, s); break;
+                case 16: st = launch_dist<float, 16>(dp, nb, max_sel, min_sel, cosine, s); break;
+                case 32: st = launch_dist<float, 32>(dp, nb, max_sel, min_sel, cosine, s); break;
+                case 64: st = launch_dist<float, 64>(dp, nb, max_sel, min_sel, cosine, s); break;
             }
         }
         if (st) return st;

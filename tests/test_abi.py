@@ -441,3 +441,24 @@ def test_attention_without_memory_for_its_scratch(lib, monkeypatch):
 
     monkeypatch.setattr(torch, "empty", no_memory)
     assert binding._attn_workspace(model.c(), 2560, 512, None, "cuda", None) == (None, 0, None)
+
+
+def test_weights_workspace_serves_smaller_pools(lib):
+    """A workspace made for a pool is large enough for every smaller pool of the same segments, batched or not, and the
+    library's own array holds what its documentation says."""
+    import random
+    rng = random.Random(7)
+    for _ in range(300):
+        m = _model(n_layers=rng.choice([1, 2, 5, 32, 80]), n_kv_heads=rng.choice([1, 3, 8]), n_q_heads=24,
+                   head_dim=rng.choice([64, 128, 256]), dtype=rng.choice([0, 1]))
+        S, gran, rule = rng.choice([1, 9, 77, 512, 2000]), rng.choice([0, 1, 2]), rng.choice([0, 2])
+        need = [lib.kvcomm_anchor_weights_rule_workspace(ctypes.byref(m), S, a, gran, rule) for a in range(1, 65)]
+        assert need[0] > 0 and need == sorted(need)
+        n = rng.randint(1, 4)
+        lens = (ctypes.c_int32 * n)(*[rng.choice([5, 100, 513]) for _ in range(n)])
+        big = [rng.randint(1, 16) for _ in range(n)]
+        ask = lambda pools: lib.kvcomm_anchor_weights_batch_workspace(ctypes.byref(m), gran, rule, lens,
+                                                                      (ctypes.c_int32 * n)(*pools), n)
+        assert ask(big) >= ask([rng.randint(1, b) for b in big]) > 0
+        for S in (1, 500, 32768):
+            assert lib.kvcomm_anchor_weights_workspace(ctypes.byref(m), S, 64, rng.choice([0, 2])) <= 16 << 20

@@ -156,3 +156,22 @@ def test_update_batches_of_unequal_pools(gran, dtype, D):
                                   j8["scale_v"], jd["weights"], jd["delta_pos"], ok, ov, None, jd["anchor_delta_pos"], gran)
             torch.cuda.synchronize()
             assert torch.equal(ok, j8["out_k"]) and torch.equal(ov, j8["out_v"])
+
+
+def test_more_groups_than_the_grid_has_room_for_in_z():
+    """Two anchor tiles over more than 262144 (chunk, token tile) pairs: groups of more than eight pairs.  The last tokens equal
+    the same call on those tokens alone (per-(layer, head, token) weights: rows are independent)."""
+    L, H, D, S, A, last = 32, 8, 64, 33000, 17, 70
+    print(f"many groups: S{S} A{A}", flush=True)
+    m = kv.Model(L, H, H, D, torch.bfloat16, 5e5)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(9)
+    mk = lambda: torch.randn((L, H, S, D), generator=g, device=DEV, dtype=torch.bfloat16)
+    bk, two = mk(), [mk(), mk()]
+    anc = [two[a % 2] for a in range(A)]
+    w, near, _ = kv.kvcomm_anchor_weights(m, bk, anc, gran=kv.W_LAYER_HEAD_TOKEN)
+    part = lambda t, n: t.view(L * H, S, -1)[:, S - n:].reshape(L * H * n, -1)
+    tail = lambda t: t[:, :, S - last:]
+    wt, nt, _ = kv.kvcomm_anchor_weights(m, tail(bk), [tail(a) for a in anc], gran=kv.W_LAYER_HEAD_TOKEN)
+    torch.cuda.synchronize()
+    assert torch.equal(part(w, last), wt) and torch.equal(part(near, last).view(-1), nt)

@@ -11,6 +11,7 @@ constexpr int rows_waves(int D) { return D == 256 ? 4 : 8; }   // wavefronts of 
 constexpr int kChipCUs = 256;
 constexpr int kRowsMaxSplits = 16;  // attn_combine_kernel takes 4 us up to here, 6 us at 25, 11 us at 64
 constexpr int kTileMaxSplits = 8;
+constexpr int kMinRunTiles = 5;     // 64-key tiles of a run on average; 1200 keys, Tq 500, 64 row tiles: 35 us in four runs, 31.5 in two or uncut
 constexpr int kMinSplitKeys = KVCOMM_ATTN_MIN_SPLIT_KEYS;
 constexpr int64_t kLastLevelCache = (int64_t)256 << 20;
 
@@ -62,10 +63,13 @@ static inline AttnPlan attn_plan(const kvcomm_model &m, int n_ctx, int tq, bool 
     const int64_t tile_items = LH * ((rows + tile_rows - 1) / tile_rows), tiles = (N + 63) / 64;
     may_split = may_split && N >= kMinSplitKeys;
     int tile_ns = 1;
-    double tile_us = attn_tiles_us(m, tile_items, tile_rows, tiles, 1);
-    for (int ns = 2; may_split && tile_items <= 2 * kChipCUs && ns <= kTileMaxSplits && ns * 4 <= tiles; ++ns) {
+    const double one_run_us = attn_tiles_us(m, tile_items, tile_rows, tiles, 1);
+    double tile_us = one_run_us;
+    for (int ns = 2; may_split && tile_items <= 2 * kChipCUs && ns <= kTileMaxSplits && ns * kMinRunTiles <= tiles; ++ns) {
         const double t = attn_tiles_us(m, tile_items, tile_rows, tiles, ns);
-        if (t < 0.95 * tile_us) {
+        // The model is 7 ... 10 % (rms) off: near the line a cut has to promise more than that.  8 layers, Tq 64, 1000 keys, D = 64:
+        // 20.5 us uncut, 24.8 in four runs (modelled 0.94); 9000 keys, Tq 700, D = 256: 249 us uncut, 266 in two (0.94).
+        if (t < 0.95 * tile_us && t < (ns == 2 && D <= 128 ? 0.95 : 0.93) * one_run_us) {
             tile_us = t;
             tile_ns = ns;
         }

@@ -50,11 +50,14 @@ struct AlignParams {
 static_assert(sizeof(AlignParams) <= 4096, "kernel arguments are limited to 4 KB");
 
 // INFLIGHT: anchors whose rows are requested together (twice as many 16-byte loads per lane); WPE: wavefronts per SIMD the
-// register budget is sized for.  Four anchors at three wavefronts for pools of seven and more, two at four wavefronts for
-// smaller ones.  us per launch of 4 x 512 tokens, (2, 4) against (4, 3): 8 anchors 471 / 449, 7 anchors 414 / 411, 6 anchors
-// 362 / 361, 5 anchors 309 / 328, 4 anchors 264 / 284; 3 x 300 tokens, 2 anchors 89 / 98; 2 x 1024 tokens, 16 anchors 845 /
-// 803.  (A vector load of the rotation-table index, whose wait drained every row in flight, used to hold the keys' blocks
-// back; the 8-anchor launch took 466 us then.)
+// register budget is sized for.  us per launch of 512-token segments in no cache (L * H = 256 at D = 128 and 64 in bf16, the same
+// bytes elsewhere), (2, 4) against (4, 3), four_in_flight() draws the line:
+//   bf16 D 128   pools of 4: 66 / 71, 7: 99 / 100, 8: 113 / 111, 12: 161 / 156, 40: 483 / 473, four of 8: 467 / 441,
+//                8 and 2: 156 / 168, 7, 4 and 4: 238 / 245;   D 256  8: 113 / 112, four of 8: 472 / 439, 8 and 2: 143 / 146
+//   bf16 D 64    pools of 4: 39 / 43, 8: 64 / 68, 16: 117 / 122, 40: 268 / 273, four of 8: 248 / 263
+//   f32 D 128    pools of 4: 65 / 66, 8: 110 / 111, 16: 208 / 206, 40: 488 / 482, 8 and 2: 152 / 149, 7, 4 and 4: 255 / 248
+// (A vector load of the rotation-table index, whose wait drained every row in flight, used to hold the keys' blocks back: four
+// of 8 took 482 us then.)
 template <typename T, int LPR, int INFLIGHT, int WPE>
 __global__ __launch_bounds__(kBlock, WPE) void align_kernel(const AlignParams p)
 {
@@ -186,13 +189,23 @@ __global__ __launch_bounds__(kBlock, WPE) void align_kernel(const AlignParams p)
     }
 }
 
+// Four anchors in flight: f32 with seven anchors or more in some segment, bf16 rows of 128 channels and more with eight or more
+// in every segment (see align_kernel).
+bool four_in_flight(const AlignParams &p, bool f32, int head_dim, int max_sel)
+{
+    if (f32) return max_sel >= 7;
+    int min_sel = max_sel;
+    for (int j = 0; j < p.n_jobs; ++j) min_sel = std::min<int>(min_sel, p.job[j].n_sel);
+    return head_dim >= 128 && min_sel >= 8;
+}
+
 template <typename T, int LPR>
 int launch_align(const AlignParams &p, int n_blocks, int max_tab, int max_sel, hipStream_t stream)
 {
     constexpr int HALF = LPR * Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
     const size_t lds = sizeof(float2) * (size_t)max_tab * HALF + sizeof(float) * (size_t)RPB * max_sel;
-    return launch(max_sel >= 7 ? align_kernel<T, LPR, 4, 3> : align_kernel<T, LPR, 2, 4>, dim3(n_blocks, 2), dim3(kBlock), lds, stream, p);
+    return launch(four_in_flight(p, sizeof(T) == 4, 2 * HALF, max_sel) ? align_kernel<T, LPR, 4, 3> : align_kernel<T, LPR, 2, 4>, dim3(n_blocks, 2), dim3(kBlock), lds, stream, p);
 }
 
 }  // namespace

@@ -48,12 +48,17 @@ static inline double attn_tiles_us(const kvcomm_model &m, int64_t items, int til
 }
 
 // Which kernel, and into how many runs the keys of a row tile are cut (one if the caller has no workspace).
-// The rows kernel takes a launch whose blocks all fit the chip at once, and a larger one where it is clearly
-// faster (few rows, so that most of a 256-row tile would be empty).  rows kernel / 256-row kernel unsplit / with its
-// best split and combine launch, 8 kv heads, 3100 keys: 64 blocks 22 / 63 / 23 us, 256 blocks 26 / 65 / 30 us, 512 blocks
-// 50 / 67 / 40 us.  Above two rounds of rows-kernel blocks the 256-row kernel wins whenever rows fill its tiles.
-// Splits of the rows kernel pay when they take off more than the combine launch (4 us, its gap and its launch on the
-// host), and only up to one round of blocks.  One decoded token, 3100 keys, 8 kv heads: 20 us in 8 blocks, 8.7 + 4.1 us in 104.
+// Both kernels with their best cut (and its combine launch) are compared by the modelled times.  The rows kernel is kept up to
+// 1.2 times the other's time where its blocks all fit the chip at once (what the model is off, and fewer partial results), and
+// taken for larger launches where it is clearly faster (few rows, so that most of a 256-row tile would be empty).
+// Measured, one layer, 8 kv heads, G = 4, us: rows kernel (with its cut) / 256-row kernel (128 rows at D = 256) uncut / cut
+//   D 128  Tq 256: 2000 keys 20 / 44 / 29, 3100 25 / 63 / 33, 9000 58 / 165 / 47, 20000 115 / 356 / 83;
+//          Tq 512: 3100 keys 45 / 64 / 41;  Tq 200, 40000 keys: 186 / 701 / 146
+//   D 64   Tq 256: 3100 keys 18 / 47 / 24, 40000 135 / 523 / 98;  Tq 512: 3100 keys 30 / 47 / 31, 5000 42 / 72 / 38
+//   D 256  Tq 256: 3100 keys 65 / 90 / 46, 9000 147 / 241 / 91;  Tq 512: 3100 keys 119 / 94 / 70;  Tq 700, G = 1, 9000 keys: 149 / 241 / 74
+// Cuts of the rows kernel pay when they take off more than the combine launch (4 us, its gap and its launch on the
+// host), and only up to one round of blocks.  One decoded token, 3100 keys, in one run / 13: D 64 15.4 / 12.3 us, D 128 20 / 13,
+// D 256 55 / 19.
 static inline AttnPlan attn_plan(const kvcomm_model &m, int n_ctx, int tq, bool may_split)
 {
     const int G = m.n_q_heads / m.n_kv_heads, D = m.head_dim;
@@ -77,18 +82,24 @@ static inline AttnPlan attn_plan(const kvcomm_model &m, int n_ctx, int tq, bool 
 
     const int64_t rows_items = LH * ((rows + 31) / 32);
     const int64_t its = (N + 32 * rows_waves(D) - 1) / (32 * rows_waves(D));
-    AttnPlan pl{};
-    pl.rows_kernel = rows_items <= kChipCUs || attn_rows_us(m, rows_items, its) < 0.7 * tile_us;
-    pl.tile_rows = pl.rows_kernel ? 32 : tile_rows;
-    pl.n_row_tiles = (int)((rows + pl.tile_rows - 1) / pl.tile_rows);
-    pl.n_splits = pl.rows_kernel ? 1 : tile_ns;
-    if (pl.rows_kernel && may_split && rows_items <= kChipCUs / 2) {
+    const double rows_one_run_us = attn_rows_us(m, rows_items, its);
+    double rows_us = rows_one_run_us;
+    int rows_ns = 1;
+    if (may_split && rows_items <= kChipCUs / 2) {
         int64_t ns = std::min<int64_t>(std::min<int64_t>(kRowsMaxSplits, kChipCUs / rows_items), its);
         const int64_t split_its = (its + ns - 1) / ns;
         ns = (its + split_its - 1) / split_its;   // the fewest runs of that many iterations
-        const double gain = attn_rows_us(m, rows_items, its) - attn_rows_us(m, rows_items * ns, split_its);
-        if (ns > 1 && gain > 8.0) pl.n_splits = (int)ns;
+        const double t = attn_rows_us(m, rows_items * ns, split_its);
+        if (ns > 1 && rows_one_run_us - t > 8.0) {
+            rows_us = t + 4.0;
+            rows_ns = (int)ns;
+        }
     }
+    AttnPlan pl{};
+    pl.rows_kernel = (rows_items <= kChipCUs && rows_us < 1.2 * tile_us) || rows_one_run_us < 0.7 * tile_us;
+    pl.tile_rows = pl.rows_kernel ? 32 : tile_rows;
+    pl.n_row_tiles = (int)((rows + pl.tile_rows - 1) / pl.tile_rows);
+    pl.n_splits = pl.rows_kernel ? rows_ns : tile_ns;
     return pl;
 }
 

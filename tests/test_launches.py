@@ -32,3 +32,40 @@ def test_keys_are_cut_where_that_clearly_pays(tmp_path):
     # runs of five 64-key tiles at least: 64 row tiles over 1200 keys make 128 blocks, not 256
     short, = attention_launches(tmp_path, [(1, 8, 4, 128, BF16, 688, 512, 0, True)])
     assert short["launches"][0][1] == [128, 1, 1]
+
+
+# (L, Hkv, G, D, n_ctx, tq), kernel with scratch, kernel without, measured us of both (the other kernel's with its best cut)
+KERNELS = [((1, 8, 4, 256, 2844, 256), "mfma", "rows"),     # 46 against 65
+           ((1, 8, 4, 256, 8744, 256), "mfma", "rows"),     # 91 against 147
+           ((1, 8, 1, 256, 8300, 700), "mfma", "rows"),     # 74 against 149
+           ((1, 8, 4, 128, 19744, 256), "mfma", "rows"),    # 83 against 115
+           ((1, 8, 4, 128, 39800, 200), "mfma", "rows"),    # 146 against 186
+           ((1, 8, 4, 128, 2844, 256), "rows", "rows"),     # 25 against 33
+           ((1, 8, 4, 64, 2844, 256), "rows", "rows"),      # 18 against 24
+           ((1, 8, 4, 128, 3099, 1), "rows", "rows"),
+           ((32, 8, 4, 128, 3099, 1), "rows", "rows"),
+           ((1, 8, 4, 128, 2560, 512), "mfma", "rows"),
+           ((32, 8, 4, 128, 2560, 512), "mfma", "mfma"),
+           ((1, 2, 4, 128, 10, 2), "rows", "rows")]
+
+
+def test_the_faster_kernel_is_taken(tmp_path):
+    res = attention_launches(tmp_path, [k[0][:4] + (BF16,) + k[0][4:] + (0, ws) for k in KERNELS for ws in (True, False)])
+    for (shape, *want), with_ws, without in zip(KERNELS, res[::2], res[1::2]):
+        for r, kernel in zip((with_ws, without), want):
+            assert r["status"] == 0 and f"attn_{kernel}_kernel" in r["launches"][0][0], (shape, kernel, r)
+        assert len(without["launches"]) == 1
+
+
+def test_the_shapes_of_the_gpu_tests_reach_what_they_name(tmp_path):
+    from test_gpu_attn_kernels import TILES
+    from test_gpu_attn_split import SHAPES
+    rows = attention_launches(tmp_path, [s[:4] + (BF16,) + s[4:6] + (0, True) for s in SHAPES])
+    for s, r in zip(SHAPES, rows):
+        kernel = "attn_mfma_kernel" if "-row tiles" in s[6] else "attn_rows_kernel"
+        assert kernel in r["launches"][0][0], (s, r)
+    for s, r in zip(TILES, attention_launches(tmp_path, [s[:4] + (BF16,) + s[4:] + (0, True) for s in TILES])):
+        assert "attn_mfma_kernel" in r["launches"][0][0], (s, r)
+    for s, nt in (((32, 8, 4, 128, 3100, 1), True), ((1, 8, 4, 128, 3100, 1), False)):
+        r, = attention_launches(tmp_path, [s[:4] + (BF16,) + s[4:] + (0, True)])
+        assert ("ELb1E" in r["launches"][0][0]) == nt and "attn_rows_kernel" in r["launches"][0][0]

@@ -243,15 +243,20 @@ int kvcomm_suffix_attn(const kvcomm_model *model, kvcomm_tensor q,
                        void *workspace, size_t workspace_bytes, void *stream);
 
 /* The same attention (workflow step 4), same arguments, results bit-identical to kvcomm_suffix_attn without a
- * workspace (the _ws form: with the same workspace), launched as at most `max_blocks` thread blocks that each walk a fixed share of the (layer, kv head, query tile) work
- * items.  A block of the bf16 kernel fills a compute unit, so the launch occupies max_blocks of the GPU's 256
- * compute units and leaves the others to kernels that run beside it on another stream: the memory-bound
- * alignment of the next agent next to the matrix-core-bound attention of the current one.  (Under the chip's
- * power limit the attention loses less than its share of compute units: measured 0.82 ms on 160 of 256 against
- * 0.66 ms on all of them.)  max_blocks is spread over the 8 XCDs in launch order; values of at least the number
- * of work items give the plain launch.  The same holds for f32 tensors; f32 caches of up to 64 tokens ignore max_blocks
- * (their kernel is small-block and never fills a compute unit), and so does the kernel that joins the partial results
- * of a split launch.
+ * workspace (the _ws form: with the same workspace), launched as at most `max_blocks` thread blocks that each walk
+ * a fixed share of the work items.  A block of the bf16 kernels fills a compute unit, so the launch occupies
+ * max_blocks of the GPU's 256 compute units and leaves the others to kernels that run beside it on another stream:
+ * the memory-bound alignment of the next agent next to the matrix-core-bound attention of the current one.  (Under
+ * the chip's power limit the attention loses less than its share of compute units: measured 0.82 ms on 160 of 256
+ * against 0.66 ms on all of them.)  max_blocks is spread over the 8 XCDs in launch order; values of at least the
+ * number of work items give the plain launch.  The same holds for f32 tensors; f32 caches of up to 64 tokens ignore
+ * max_blocks (their kernel is small-block and never fills a compute unit), and so does the kernel that joins the
+ * partial results of a split launch.
+ * The same bits mean the same work items whatever max_blocks is.  A launch that is too small to fill the GPU is cut
+ * into many (32 rows each, or runs of keys), which costs more than it gives where max_blocks is a small part of
+ * them.  One layer, 8 kv heads, G = 4, D = 128, 3000 keys, us on 160 / 64 / 8 blocks (in brackets: whole 256-row tiles,
+ * which kvcomm_suffix_attn takes for launches that fill the GPU): Tq 64  26 / 43 / 279 (63 / 63 / 63), Tq 256
+ * 42 / 78 / 572 (66 / 67 / 250), Tq 512  53 / 87 / 564 (63 / 65 / 452).
  * Errors: as kvcomm_suffix_attn; KVCOMM_EINVAL for max_blocks < 8 (one block per XCD is the minimum).          */
 int kvcomm_suffix_attn_confined(const kvcomm_model *model, kvcomm_tensor q,
                                 kvcomm_tensor cache_k, kvcomm_tensor cache_v,

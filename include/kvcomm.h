@@ -256,7 +256,8 @@ int kvcomm_suffix_attn(const kvcomm_model *model, kvcomm_tensor q,
  * into many (32 rows each, or runs of keys), which costs more than it gives where max_blocks is a small part of
  * them.  One layer, 8 kv heads, G = 4, D = 128, 3000 keys, us on 160 / 64 / 8 blocks (in brackets: whole 256-row tiles,
  * which kvcomm_suffix_attn takes for launches that fill the GPU): Tq 64  26 / 43 / 279 (63 / 63 / 63), Tq 256
- * 42 / 78 / 572 (66 / 67 / 250), Tq 512  53 / 87 / 564 (63 / 65 / 452).
+ * 42 / 78 / 572 (66 / 67 / 250), Tq 512  53 / 87 / 564 (63 / 65 / 452); Tq 1000  95 / 167 / 1160 (83 / 152 / 1093): there
+ * the cut pieces of 128 ... 240 blocks cost 12 ... 23 % as well.
  * Errors: as kvcomm_suffix_attn; KVCOMM_EINVAL for max_blocks < 8 (one block per XCD is the minimum).          */
 int kvcomm_suffix_attn_confined(const kvcomm_model *model, kvcomm_tensor q,
                                 kvcomm_tensor cache_k, kvcomm_tensor cache_v,

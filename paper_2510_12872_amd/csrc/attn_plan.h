@@ -72,7 +72,7 @@ static inline AttnPlan attn_plan(const kvcomm_model &m, int n_ctx, int tq, bool 
     double tile_us = one_run_us;
     for (int ns = 2; may_split && tile_items <= 2 * kChipCUs && ns <= kTileMaxSplits && ns * kMinRunTiles <= tiles; ++ns) {
         const double t = attn_tiles_us(m, tile_items, tile_rows, tiles, ns);
-        // The model is 7 ... 10 % (rms) off: near the line a cut has to promise more than that.  8 layers, Tq 64, 1000 keys, D = 64:
+        // The model is 8 ... 10 % (rms) off: near the line a cut has to promise more than that.  8 layers, Tq 64, 1000 keys, D = 64:
         // 20.5 us uncut, 24.8 in four runs (modelled 0.94); 9000 keys, Tq 700, D = 256: 249 us uncut, 266 in two (0.94).
         if (t < 0.95 * tile_us && t < (ns == 2 && D <= 128 ? 0.95 : 0.93) * one_run_us) {
             tile_us = t;

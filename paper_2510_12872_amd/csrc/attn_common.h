@@ -101,9 +101,68 @@ __host__ __device__ __forceinline__ int split_bound(int s, int n_splits, int uni
     return b < first_hidden ? b : (s == 0 ? 0 : units);
 }
 
-// Output accumulators of a 32-row group travel as 16-byte slots in the order the MFMA leaves them: slot
-// (db, j4, hg, n) = channels 32 * db + 8 * j4 + 4 * hg ... + 3 of row n, rows fastest, so that a wavefront
-// writes and reads 1 KB runs.
-__device__ __forceinline__ int part_slot(int db, int j4, int hg, int n) { return ((db * 4 + j4) * 2 + hg) * 32 + n; }
+// Output accumulators of a 32-row group travel as 16-byte slots: slot (c4, n) = channels 4 * c4 ... + 3 of row n, rows
+// fastest, as the MFMAs leave them (256- and 512-byte runs).
+__device__ __forceinline__ int part_slot(int c4, int n) { return c4 * 32 + n; }
+
+// acc = A B and acc += A B, the accumulator in place (ACC: in the accumulation registers).  Through the builtin the compiler gives
+// the sum other registers than the addend and hands the addend's to the vector instructions that follow, each of which
+// then waits for the MFMA.  It inserts no wait states around inline assembly: no vector instruction may write an operand in the
+// two wait states before it (kGuarded waits for those itself) or touch `acc` in the eight after it (mfma_settle waits that long).
+// tests/test_mfma_hazards.py looks for such instructions in the built library.
+enum class Mfma { kBuiltin, kInPlace, kGuarded };
+
+template <Mfma HOW>
+__device__ __forceinline__ void mfma_first(f32x4 &acc, const bf16x8 a, const bf16x8 b)
+{
+    if constexpr (HOW == Mfma::kBuiltin)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    else if constexpr (HOW == Mfma::kInPlace)
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
+    else
+        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
+}
+template <Mfma HOW, bool ACC = false>
+__device__ __forceinline__ void mfma_next(f32x4 &acc, const bf16x8 a, const bf16x8 b)
+{
+    if constexpr (HOW == Mfma::kBuiltin)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+    else if constexpr (HOW == Mfma::kInPlace && !ACC)
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+    else if constexpr (HOW == Mfma::kInPlace)
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+    else if constexpr (!ACC)
+        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+    else
+        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+template <bool ACC, int N>
+__device__ __forceinline__ void mfma_settle(f32x4 (&o)[2][N])
+{
+    asm volatile("s_nop 7\n\ts_nop 7" : : : "memory");
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        if constexpr (ACC)
+            asm volatile("" : "+a"(o[0][i]), "+a"(o[1][i]));
+        else
+            asm volatile("" : "+v"(o[0][i]), "+v"(o[1][i]));
+    }
+}
+
+// 16x16x32 MFMAs leave a query column in the four lanes n, 16 + n, 32 + n, 48 + n: their maximum and their sum.
+__device__ __forceinline__ float query_max(float x)
+{
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float query_sum(float x)
+{
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
 
 }  // namespace kvc

@@ -230,7 +230,7 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
             for (int d = 0; d < CDB; ++d)
 #pragma unroll
                 for (int j4 = 0; j4 < 4; ++j4)
-                    join[wave * (CDB * 256) + part_slot(d, j4, hg, n)] =
+                    join[wave * (CDB * 256) + part_slot(8 * d + 2 * j4 + hg, n)] =
                         f32x4{o[c0 + d][4 * j4], o[c0 + d][4 * j4 + 1], o[c0 + d][4 * j4 + 2], o[c0 + d][4 * j4 + 3]} * f;
             __syncthreads();
             if (valid) {

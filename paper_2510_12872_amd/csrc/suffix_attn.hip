@@ -2,15 +2,21 @@
 // aligned cache (workflow step 4 of the paper; q, k, v as in Sec. 3.1).  Suffix query i sits
 // at cache position n_ctx + i and sees keys 0 .. n_ctx + i.
 //
-// bf16 path (attn_mfma_kernel): flash-style single pass on bf16 MFMA (32x32x16) with fp32
+// bf16 path (attn_mfma_kernel): flash-style single pass on bf16 MFMA (16x16x32) with fp32
 // accumulation and an fp32 online softmax, written for gfx950:
+//   * 16x16x32, not 32x32x16: the chip is power-limited under this kernel, and a stream of the small ones sustains
+//     1970-2080 TFLOP/s on N(0,1) data where a stream of the large ones sustains 1740-1800.  A wavefront still owns 32 queries,
+//     as two halves of 16 that share every K and V^T operand, so LDS reads and registers are what they were.  Twice as
+//     many matrix instructions to issue take a part of it back: the pipes are busy in 63 % of the cycles at 1.84 GHz instead of
+//     69 % at 1.64.  32 layers, Tq 512, 3072 keys: 654 -> 648 us; 64 heads, 8704 keys: 16 layers 1860 -> 1783 us, 80 layers
+//     9001 -> 8923 us; one layer, 3072 keys, four runs: 40.8 -> 39.4 us; D = 256, 8 layers, 3072 keys: 423 -> 408 us.
 //   * GQA packing: the G query heads that share a kv head are folded into the row axis of one
 //     tile (row r = i * G + g), so each K/V tile staged in LDS serves G heads at once.
-//   * Both products are computed transposed, S^T = K Q^T and O^T = V^T P^T.  In the 32x32
-//     accumulator layout a lane then owns ONE query column: row max and row sum of the softmax
-//     are in-register reductions plus one v_permlane32_swap, the rescale of O is a per-lane
+//   * Both products are computed transposed, S^T = K Q^T and O^T = V^T P^T.  In the 16x16
+//     accumulator layout a lane then owns one query column of each half: row max and row sum of the softmax
+//     are in-register reductions plus two lane swaps at the end, the rescale of O is a per-lane
 //     scalar, and the exponentiated scores are already laid out as the B operand of the second
-//     product (the key order inside a 16-key step is a fixed permutation, matched on the V side).
+//     product (the key order inside a 32-key step is a fixed permutation, matched on the V side).
 //   * K and V tiles travel global -> LDS with global_load_lds_dwordx4 (no registers, no LDS
 //     stores), issued through inline assembly with a scalar row base and a fixed per-lane offset;
 //     the XOR swizzle of 16-byte chunks that keeps operand reads bank-conflict free is
@@ -18,10 +24,10 @@
 //     ds_read_b128; V^T operands with ds_read_b64_tr_b16, which transposes on the way out of
 //     LDS, so V is never transposed by the vector ALU.
 //   * Work advances in 32-key sub-steps as a three-stage software pipeline inside each wavefront:
-//     in one step the matrix cores compute S(u+2) = K(u+2) Q^T and O += V(u) P(u), their MFMAs
-//     alternating (two independent accumulator chains), while the vector ALU turns S(u+1) into
-//     P(u+1).  The vector work is cut into one piece per MFMA and staggered so that no instruction
-//     reads what its own piece produced; every piece is pinned by a scheduling barrier.
+//     in one step the matrix cores compute S(u+2) = K(u+2) Q^T and O += V(u) P(u), pairs of MFMAs
+//     alternating, while the vector ALU turns S(u+1) into P(u+1).  The vector work is cut into one
+//     piece per MFMA and staggered so that no instruction reads what its own piece produced; every
+//     piece is pinned by a scheduling barrier.
 //   * The softmax reference is not tracked.  It is set from the first sub-step (key 0 is visible to
 //     every query) and a sub-step only checks that the row sum of its exponentials, which is needed
 //     anyway, stayed below 2^30; a row that did not is re-referenced to its true maximum (O and
@@ -66,8 +72,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     else
         p_ptr = &p_arg;
     ParamT &p0 = *p_ptr;
-    constexpr int NKS = D / 16;      // k-steps of S^T = K Q^T; also the MFMAs of O^T += V^T P^T per sub-step
-    constexpr int NDB = D / 32;      // 32-row blocks of O^T
+    constexpr int NF = D / 16;       // K operands of a sub-step (contraction step, key half), V^T operands (16 channels)
     constexpr int BM = 32 * NW;      // query rows per block (32 per wavefront)
     constexpr int RW = 64 / NW;      // key rows of a 64-key group that one wavefront loads
     constexpr int KCH = D / 8;       // 16-byte chunks per K / V row
@@ -76,8 +81,12 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     constexpr int TILEB = 64 * ROWB; // bytes of a 64-key tile
     constexpr int RPL = 64 / KCH;    // key rows filled by one wavefront-wide direct load
     constexpr int LPT = RW / RPL;    // direct loads per wavefront, tensor and 64-key group
-    constexpr int KSWZ = (KCH < 16 ? KCH : 16) - 1; // K chunk swizzle: c ^ (key & KSWZ)
-    constexpr int VSWZ = KCH - 1;                   // V chunk swizzle: c ^ ((4 * (key & 3)) & VSWZ)
+    // Chunk swizzles: chunk c of key `key` sits at position c ^ swz(key).  16 chunks span the 64 banks (two keys at D = 64).
+    // K: sixteen lanes read one chunk of sixteen keys.  V: a transposing read of 32 lanes takes two chunks of eight keys.
+    auto k_swz = [](int key) __attribute__((always_inline)) -> int { return D == 64 ? (key >> 1) & 7 : key & 15; };
+    auto v_swz = [](int key) __attribute__((always_inline)) -> int {
+        return D == 64 ? (2 * (key & 2)) | ((key >> 1) & 2) : 4 * (key & 3) | ((key >> 1) & 2);
+    };
 
     // K: ring of four 32-key halves (half h in slot h & 3); V: two 64-key tiles (tile t in buffer t & 1).
     // Rows are [key][D] with XOR-swizzled 16-byte chunks.
@@ -110,7 +119,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     }
     ParamT &p = *p_item;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lane = tid & 63, n = lane & 31, hg = lane >> 5;
+    const int lane = tid & 63, n = lane & 15, g4 = lane >> 4;
     const int split = SPLIT ? logical % p.n_splits : 0;
     if constexpr (SPLIT) logical /= p.n_splits;
     const int lh = logical / p.n_row_tiles;
@@ -130,10 +139,10 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     const int n_tiles = SPLIT ? split_bound(split + 1, p.n_splits, all_tiles, first_hidden) - tile0 : all_tiles;
     if constexpr (SPLIT) {
         if (n_tiles <= 0) {   // the whole block: this run is empty
-            if (hg == 0 && (rt * BM + wave * 32 + n) / p.G < p.tq) {
+            if (lane < 32 && (rt * BM + wave * 32 + lane) / p.G < p.tq) {
                 const int64_t part = ((int64_t)(lh * p.n_row_tiles + rt) * NW + wave) * p.n_splits + split;
-                p.part_ml[part * 64 + n] = -INFINITY;
-                p.part_ml[part * 64 + 32 + n] = 0.f;
+                p.part_ml[part * 64 + lane] = -INFINITY;
+                p.part_ml[part * 64 + 32 + lane] = 0.f;
             }
             if (!PERSIST) return;
             item += x_blocks;
@@ -149,11 +158,12 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     const int n_sub = 2 * n_tiles;
     const int sub_unmasked = (n_ctx_() + wg_imin + 1) / 32;  // sub-steps [0, sub_unmasked) are visible to all queries
 
-    f32x16 o[NDB];
+    f32x4 o[2][NF];   // [query half][16 channels]
+    constexpr bool kAccO = D == 256;   // O lives in the accumulation registers: the others have no room for it
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
+        for (int db = 0; db < NF; ++db) o[h][db] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // ---- global -> LDS direct loads (global_load_lds_dwordx4): lane i of a wavefront fills the
     // 16-byte LDS chunk (base + i); the swizzle is applied by choosing which global chunk it fetches.
@@ -162,11 +172,11 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     // In a 64-key group, wavefront w fills keys [RW*w, RW*w + RW); load `it` fills rows RW*w + it*RPL ...
     auto in_row_k = [&](int it) __attribute__((always_inline)) -> int {  // swizzled source chunk (bytes inside the row), K
         const int key = wave * RW + it * RPL + lane / KCH;   // only the row index modulo 16 matters
-        return ((lane % KCH) ^ (key & KSWZ)) * 16;
+        return ((lane % KCH) ^ k_swz(key)) * 16;
     };
-    auto in_row_v = [&](int it) __attribute__((always_inline)) -> int {  // same for V (identical for every `it` when RPL is a multiple of 4)
+    auto in_row_v = [&](int it) __attribute__((always_inline)) -> int {  // same for V
         const int key = wave * RW + it * RPL + lane / KCH;
-        return ((lane % KCH) ^ ((4 * (key & 3)) & VSWZ)) * 16;
+        return ((lane % KCH) ^ v_swz(key)) * 16;
     };
     uint32_t ld_koff[LPT], ld_voff[LPT];
 #pragma unroll
@@ -210,16 +220,17 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     load_k64(0);    // halves 0, 1
     load_k64(64);   // halves 2, 3
     load_v64(0);
-    // This lane's query column: row r = i * G + g of the (layer, kv head) group.
-    int qi;
-    bf16x8 qf[NKS];
-    {
-        const int r_row = rt * BM + wave * 32 + n;
-        qi = min(r_row / p.G, p.tq - 1);
-        const int hq = hkv * p.G + r_row % p.G;
-        const bf16_t *qrow = static_cast<const bf16_t *>(p.q) + l * p.s_q.layer + (int64_t)(uint32_t)hq * p.s_q.head + (int64_t)(uint32_t)qi * p.s_q.token;
+    // This lane's two query columns, n and 16 + n of the wavefront's 32: row r = i * G + g of the (layer, kv head) group.
+    int qi[2];
+    bf16x8 qf[2][NF / 2];
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) qf[ks] = as_bf16x8(load16(qrow + ks * 16 + hg * 8));
+    for (int h = 0; h < 2; ++h) {
+        const int r_row = rt * BM + wave * 32 + 16 * h + n;
+        qi[h] = min(r_row / p.G, p.tq - 1);
+        const int hq = hkv * p.G + r_row % p.G;
+        const bf16_t *qrow = static_cast<const bf16_t *>(p.q) + l * p.s_q.layer + (int64_t)(uint32_t)hq * p.s_q.head + (int64_t)(uint32_t)qi[h] * p.s_q.token;
+#pragma unroll
+        for (int ks = 0; ks < NF / 2; ++ks) qf[h][ks] = as_bf16x8(load16(qrow + ks * 32 + g4 * 8));
     }
 
     // Steady state (all rows exist, no half is skipped): the same loads from two running row pointers,
@@ -253,161 +264,162 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     };
 
     // ---- per-lane LDS read offsets
-    // K operand (rows = keys): lane (n, hg) reads chunk 2*ks + hg of key n of the half.
-    int k_off[NKS];
+    // K operand (rows = keys): lane (n, g4) reads chunk 4 * ks + g4 of key n or 16 + n of the half.
+    int k_off[NF / 2];
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) k_off[ks] = n * ROWB + (((2 * ks + hg) ^ (n & KSWZ)) * 16);
+    for (int ks = 0; ks < NF / 2; ++ks) k_off[ks] = n * ROWB + (((4 * ks + g4) ^ k_swz(n)) * 16);
     // V^T operand through transposing reads: lane i of a 16-lane group supplies the address of
-    // 4 channels [32*db + 16*gi + 4*(i%4), +4) of key 16*ks + 4*hg + i/4 (second read: + 8 keys).
-    int v_off[NDB];
+    // 4 channels [16 * db + 4 * (i % 4), + 4) of key 4 * g4 + i / 4 (second read: + 16 keys).
+    int v_off[NF];
     {
-        const int i16 = lane & 15, gi = (lane >> 4) & 1;
-        const int row = 4 * hg + (i16 >> 2);
+        const int row = 4 * g4 + (n >> 2);
 #pragma unroll
-        for (int db = 0; db < NDB; ++db) {
-            const int col = 32 * db + 16 * gi + 4 * (i16 & 3);
-            const int pc = (col >> 3) ^ ((4 * (row & 3)) & VSWZ);
-            v_off[db] = row * ROWB + pc * 16 + (col & 7) * 2;
+        for (int db = 0; db < NF; ++db) {
+            const int col = 16 * db + 4 * (n & 3);
+            v_off[db] = row * ROWB + ((col >> 3) ^ v_swz(row)) * 16 + (col & 7) * 2;
         }
     }
-    auto read_k = [&](const lds_byte *kl, int ks) __attribute__((always_inline)) -> bf16x8 {
-        return as_bf16x8(*(const __attribute__((address_space(3))) u32x4 *)(kl + k_off[ks]));
+    auto read_k = [&](const lds_byte *kl, int i) __attribute__((always_inline)) -> bf16x8 {  // i = 2 * ks + key half
+        return as_bf16x8(*(const __attribute__((address_space(3))) u32x4 *)(kl + (i & 1) * 16 * ROWB + k_off[i >> 1]));
     };
-    auto read_v = [&](const lds_byte *vl, int i) __attribute__((always_inline)) -> bf16x8 {  // i = ks * NDB + db
-        const lds_byte *va = vl + (i / NDB) * 16 * ROWB + v_off[i % NDB];
-        return lds_read_tr_pair(va, va + 8 * ROWB);
+    auto read_v = [&](const lds_byte *vl, int db) __attribute__((always_inline)) -> bf16x8 {
+        const lds_byte *va = vl + v_off[db];
+        return lds_read_tr_pair(va, va + 16 * ROWB);
     };
 
-    // ---- softmax state of this lane's query.
+    // ---- softmax state of this lane's two queries.
     // m is the REFERENCE the exponentials are taken against (raw score units), mc = m * scale * log2(e).  It is
     // a true maximum when it is set, but it is not tracked: a sub-step only checks that its exponentials stayed
-    // in range (their row sum, which is needed anyway, below kOverflow) and re-references the row when they did
+    // in range (their row sums, which are needed anyway, below kOverflow) and re-references the rows when they did
     // not.  Numerator and denominator share the reference, so the result is that of the usual online softmax;
     // exponentials beyond 1 cost no accuracy in floating point.
-    float m = -INFINITY, mc = 0.f, lsum = 0.f;
-    f32x16 sbuf[2];   // scores of sub-step u live in sbuf[u & 1]
-    u32x4 pbuf[2][2]; // packed bf16 probabilities of sub-step u live in pbuf[u & 1]
+    float m[2] = {-INFINITY, -INFINITY}, mc[2] = {0.f, 0.f}, lsum[2] = {0.f, 0.f};
+    f32x4 sbuf[2][2][2]; // scores of sub-step u live in sbuf[u & 1][key half][query half]
+    u32x4 pbuf[2][2];    // packed bf16 probabilities of sub-step u live in pbuf[u & 1][query half]
 
-    // P = exp2(s * scale * log2(e) - mc) for the 16 scores of this lane, as packed bf16 B operands, and their sum.
-    // The work is cut into the 2 * NKS MFMA slots of a pipeline step and staggered so that no instruction reads
+    // P = exp2(s * scale * log2(e) - mc) for the 16 scores of this lane, as packed bf16 B operands, and their sums.
+    // The work is cut into the MFMA slots of a pipeline step and staggered so that no instruction reads
     // what its own slot produced: element j is scaled in slot b-2, exponentiated in slot b-1 and
     // summed / packed in slot b = j * NS / 16 (slots -2 and -1 precede the first MFMA).  A wavefront issues in
     // order, so a dependent chain inside one slot would hold back the next MFMA for its whole latency.
-    // Lane (n, hg) holds key rows 8*(j/4) + 4*hg + j%4 of the sub-step; `limit` is its last visible key.
-    // Row sums are plain fp32 additions of the unrounded exponentials (two chains): v_dot2 on the rounded pairs
+    // Element j is key row 16 * kh + 4 * g4 + r of the sub-step for query half j / 8, kh = j / 4 % 2, r = j % 4; `limit`
+    // plus the query's index is its last visible key.
+    // Row sums are plain fp32 additions of the unrounded exponentials: v_dot2 on the rounded pairs
     // would agree with the numerator to the last bit, but it shares a pipeline with the MFMAs and costs four
     // times as much next to them; the difference is a relative 2^-9 / sqrt(keys) of the denominator.
     struct ExpState {
-        float x[16], e[16], rs_even, rs_odd;
+        float x[16], e[16], rs[2];
     };
-    auto exp_slot = [&](const f32x16 &s, u32x4 (&pk)[2], ExpState &st, int limit, bool masked, int t, int NS)
+    typedef f32x4 Scores[2][2];
+    auto score = [&](const Scores &s, int j, int limit, bool masked) __attribute__((always_inline)) -> float {
+        const int h = j >> 3, kh = (j >> 2) & 1, r = j & 3;
+        return masked && 16 * kh + 4 * g4 + r > limit + qi[h] ? -INFINITY : s[kh][h][r];
+    };
+    auto exp_slot = [&](const Scores &s, u32x4 (&pk)[2], ExpState &st, int limit, bool masked, int t, int NS)
                         __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
-            const int b = j * NS / 16;
-            if (b - 2 == t) {
-                float v = s[j];
-                if (masked) v = 8 * (j >> 2) + 4 * hg + (j & 3) > limit ? -INFINITY : v;
-                st.x[j] = __builtin_fmaf(v, p.scale_log2, -mc);
-            }
+            const int b = j * NS / 16, h = j >> 3;
+            if (b - 2 == t) st.x[j] = __builtin_fmaf(score(s, j, limit, masked), p.scale_log2, -mc[h]);
             if (b - 1 == t) st.e[j] = __builtin_amdgcn_exp2f(st.x[j]);
             if (b == t) {
                 if (j & 1) {
                     uint32_t pr = pack_bf16x2(st.e[j - 1], st.e[j]);
                     asm volatile("" : "+v"(pr));  // keeps the conversion in this slot (it would sink to its use, a step later)
-                    pk[j >> 3][(j & 7) >> 1] = pr;
-                    st.rs_odd += st.e[j];
-                } else {
-                    st.rs_even += st.e[j];
+                    pk[h][(j & 7) >> 1] = pr;
                 }
+                st.rs[h] = (j & 7) == 0 ? st.e[j] : st.rs[h] + st.e[j];
             }
         }
     };
     // A row whose exponentials left the safe range (or the first sub-step, whose reference is still -inf): take
     // the true maximum of the sub-step as the new reference if it is larger, rescale what has been accumulated,
     // and form the exponentials again.  Rare: the reference only ever moves by more than log2(kOverflow).
-    auto rereference = [&](const f32x16 &s, u32x4 (&pk)[2], int limit, bool masked) __attribute__((always_inline)) -> float {
-        float mx = -INFINITY;
+    auto rereference = [&](const Scores &s, u32x4 (&pk)[2], ExpState &st, int limit, bool masked) __attribute__((always_inline)) {
+        if (kAccO || !masked) mfma_settle<kAccO>(o);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            float v = s[j];
-            if (masked) v = 8 * (j >> 2) + 4 * hg + (j & 3) > limit ? -INFINITY : v;
-            mx = fmaxf(mx, v);
+        for (int h = 0; h < 2; ++h) {
+            float mx = -INFINITY;
+#pragma unroll
+            for (int j = 8 * h; j < 8 * h + 8; ++j) mx = fmaxf(mx, score(s, j, limit, masked));
+            const float m_new = fmaxf(m[h], query_max(mx));
+            // m == -inf: nothing but exponentials of 0 so far (the first sub-step, or scores of -inf only)
+            const float corr = m[h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m[h] - m_new) * p.scale_log2);
+            m[h] = m_new;
+            // No score above -inf yet (key 0 of the block's keys is visible to every query, but its score may be -inf): a
+            // reference so low that scores of -inf still give 0 and the first finite one overflows, which brings it here.
+            mc[h] = fmaxf(m_new * p.scale_log2, -FLT_MAX);
+            lsum[h] *= corr;
+#pragma unroll
+            for (int db = 0; db < NF; ++db) o[h][db] *= corr;
         }
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-        const float m_new = fmaxf(m, mx);
-        // m == -inf: nothing but exponentials of 0 so far (the first sub-step, or scores of -inf only)
-        const float corr = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_new) * p.scale_log2);
-        m = m_new;
-        // No score above -inf yet (key 0 of the block's keys is visible to every query, but its score may be -inf): a
-        // reference so low that scores of -inf still give 0 and the first finite one overflows, which brings it here.
-        mc = fmaxf(m_new * p.scale_log2, -FLT_MAX);
-        lsum *= corr;
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) o[db][j] *= corr;
-        ExpState st;
-        st.rs_even = st.rs_odd = 0.f;
 #pragma unroll
         for (int t = -2; t < 16; ++t) exp_slot(s, pk, st, limit, masked, t, 16);
-        return st.rs_even + st.rs_odd;
     };
     constexpr float kOverflow = 1073741824.f;  // 2^30
 
     // One pipeline step for sub-step u (U4 = u & 3, a literal at every call site, fixes every ring slot and buffer):
-    //   matrix cores:  S(u+2) = K(u+2) Q^T  and  O += V(u) P(u), their MFMAs alternating (two independent chains);
+    //   matrix cores:  S(u+2) = K(u+2) Q^T  and  O += V(u) P(u), pairs of MFMAs that share the K or V^T operand alternating;
     //   vector ALU:    P(u+1) = exp2(S(u+1) - reference), spread evenly over the MFMAs.
-    // DO_QK / DO_EXP are false only in the last two sub-steps.  LDS operands are fetched two MFMAs of their own
+    // DO_QK / DO_EXP are false only in the last two sub-steps.  LDS operands are fetched two pairs of their own
     // product ahead; every MFMA + vector chunk is pinned by a scheduling barrier.
     auto step = [&](int u, auto u4c, auto do_qk_c, auto do_exp_c, auto masked_c) __attribute__((always_inline)) {
         constexpr int U4 = decltype(u4c)::value;
         constexpr bool DO_QK = decltype(do_qk_c)::value, DO_EXP = decltype(do_exp_c)::value, MASKED = decltype(masked_c)::value;
-        f32x16 &s_acc = sbuf[U4 & 1];
-        const f32x16 &s_exp = sbuf[(U4 + 1) & 1];
+        constexpr int NS = 4 * NF;   // slots: the MFMAs of both products
+        // The compiler copies operands right before the MFMAs of masked sub-steps, and moves scores of D = 256 between register files.
+        constexpr Mfma HOW_S = !MASKED && !kAccO ? Mfma::kInPlace : Mfma::kBuiltin;
+        constexpr Mfma HOW_O = !MASKED ? Mfma::kInPlace : kAccO ? Mfma::kGuarded : Mfma::kBuiltin;
+        Scores &s_acc = sbuf[U4 & 1];
+        const Scores &s_exp = sbuf[(U4 + 1) & 1];
         const lds_byte *kl = kring + ((U4 + 2) & 3) * HALFB;
         const lds_byte *vl = vbuf + ((U4 >> 1) & 1) * TILEB + (U4 & 1) * HALFB;
-        const int limit = n_ctx_() + qi - 32 * (u + 1);  // last visible key of S(u+1), relative to its sub-step
-        bf16x8 ka[NKS], va[NKS], pf[2];
+        const int limit = n_ctx_() - 32 * (u + 1);  // last key of S(u+1), relative to its sub-step, that query 0 sees
+        bf16x8 ka[NF], va[NF], pf[2];
         pf[0] = as_bf16x8(pbuf[U4 & 1][0]);
         pf[1] = as_bf16x8(pbuf[U4 & 1][1]);
-        if (DO_QK) {
-            ka[0] = read_k(kl, 0);
-            ka[1] = read_k(kl, 1);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            if (DO_QK) ka[i] = read_k(kl, i);
+            va[i] = read_v(vl, i);
         }
-        va[0] = read_v(vl, 0);
-        va[1] = read_v(vl, 1);
         ExpState st;
-        st.rs_even = st.rs_odd = 0.f;
-        if (DO_EXP) {
-            exp_slot(s_exp, pbuf[(U4 + 1) & 1], st, limit, MASKED, -2, 2 * NKS);
-            exp_slot(s_exp, pbuf[(U4 + 1) & 1], st, limit, MASKED, -1, 2 * NKS);
-        }
+        auto vec = [&](int t) __attribute__((always_inline)) {
+            if (DO_EXP) exp_slot(s_exp, pbuf[(U4 + 1) & 1], st, limit, MASKED, t, NS);
+        };
+        vec(-2);
+        vec(-1);
 #pragma unroll
-        for (int i = 0; i < NKS; ++i) {
-            if (DO_QK) {
-                if (i == 0) {
-                    f32x16 z;
+        for (int i = 0; i < NF; ++i) {
 #pragma unroll
-                    for (int j = 0; j < 16; ++j) z[j] = 0.f;
-                    s_acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[0], qf[0], z, 0, 0, 0);
-                } else {
-                    s_acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i], qf[i], s_acc, 0, 0, 0);
+            for (int h = 0; h < 2; ++h) {
+                if (DO_QK) {
+                    if (i < 2)
+                        mfma_first<HOW_S>(s_acc[i & 1][h], ka[i], qf[h][i >> 1]);
+                    else
+                        mfma_next<HOW_S>(s_acc[i & 1][h], ka[i], qf[h][i >> 1]);
                 }
-                if (i + 2 < NKS) ka[i + 2] = read_k(kl, i + 2);
+                __builtin_amdgcn_sched_barrier(0);
+                if (h == 0 && i + 2 < NF) {
+                    if (DO_QK) ka[i + 2] = read_k(kl, i + 2);
+                    va[i + 2] = read_v(vl, i + 2);
+                }
+                vec(4 * i + h);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            if (DO_EXP) exp_slot(s_exp, pbuf[(U4 + 1) & 1], st, limit, MASKED, 2 * i, 2 * NKS);
-            __builtin_amdgcn_sched_barrier(0);
-            o[i % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i], pf[i / NDB], o[i % NDB], 0, 0, 0);
-            if (i + 2 < NKS) va[i + 2] = read_v(vl, i + 2);
-            if (DO_EXP) exp_slot(s_exp, pbuf[(U4 + 1) & 1], st, limit, MASKED, 2 * i + 1, 2 * NKS);
-            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                mfma_next<HOW_O, kAccO>(o[h][i], va[i], pf[h]);
+                __builtin_amdgcn_sched_barrier(0);
+                vec(4 * i + 2 + h);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
         if (DO_EXP) {
-            float rs = st.rs_even + st.rs_odd;
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(rs < kOverflow)) != 0, 0)) rs = rereference(s_exp, pbuf[(U4 + 1) & 1], limit, MASKED);
-            lsum += rs;
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(st.rs[0] + st.rs[1] < kOverflow)) != 0, 0))
+                rereference(s_exp, pbuf[(U4 + 1) & 1], st, limit, MASKED);
+            lsum[0] += st.rs[0];
+            lsum[1] += st.rs[1];
         }
     };
     const auto tile_barrier = [&]() __attribute__((always_inline)) {
@@ -429,17 +441,23 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
         for (int h = 0; h < 2; ++h) {
             const lds_byte *kl = kring + h * HALFB;
 #pragma unroll
-            for (int j = 0; j < 16; ++j) sbuf[h][j] = 0.f;
+            for (int i = 0; i < NF; ++i) {
+                const bf16x8 ka = read_k(kl, i);
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks)
-                sbuf[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k(kl, ks), qf[ks], sbuf[h], 0, 0, 0);
+                for (int c = 0; c < 2; ++c)
+                    sbuf[h][i & 1][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qf[c][i >> 1], i < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : sbuf[h][i & 1][c], 0, 0, 0);
+            }
         }
-        lsum = rereference(sbuf[0], pbuf[0], n_ctx_() + qi, true);
+        ExpState st;
+        rereference(sbuf[0], pbuf[0], st, n_ctx_(), true);
+        lsum[0] = st.rs[0];
+        lsum[1] = st.rs[1];
     }
     // Halves 0 and 1 have no tile before them: every wavefront must have read them before the loads of the
     // first tile (halves 4 and 5 share their slots) are issued.
     __syncthreads();
 
+    if (kAccO) mfma_settle<kAccO>(o);   // (the zeros)
     const int t_last = n_tiles - 1;
     // Leading tiles whose exponentials need no mask and whose look-ahead loads stay inside the cache: a tile pair
     // starting at t forms the exponentials of sub-steps up to 2t+4 and loads keys up to 64t + 255.
@@ -470,6 +488,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     };
     int t = 0;
     for (; t + 2 <= t_plain; t += 2) tile_pair(t, T_{});
+    mfma_settle<kAccO>(o);
     for (; t + 2 <= t_last; t += 2) tile_pair(t, F_{});
     if (t < t_last) {  // two tiles left (t is even): a whole one, then the last
         load_k64(64 * t + 128);
@@ -485,65 +504,62 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
         step(2 * t + 1, u1, F_{}, F_{}, T_{});
     }
 
+    if (kAccO) mfma_settle<kAccO>(o);
     if constexpr (SPLIT) {
         // ---- epilogue of a split: accumulators as they are (1 KB runs per store), reference and row sum.
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum), false, false);
-        const float ltot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
         const int64_t part = ((int64_t)(lh * p.n_row_tiles + rt) * NW + wave) * p.n_splits + split;
         const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-        const int n_e = lane_e & 31, hg_e = lane_e >> 5;
-        if ((rt * BM + wave * 32 + n_e) / p.G < p.tq) {
-            f32x4 *po = reinterpret_cast<f32x4 *>(p.part_o + part * (32 * D));
+        const int n_e = lane_e & 15, g_e = lane_e >> 4;
+        f32x4 *po = reinterpret_cast<f32x4 *>(p.part_o + part * (32 * D));
 #pragma unroll
-            for (int db = 0; db < NDB; ++db)
+        for (int h = 0; h < 2; ++h) {
+            const float ltot = query_sum(lsum[h]);
+            const int row = 16 * h + n_e;
+            if ((rt * BM + wave * 32 + row) / p.G < p.tq) {
 #pragma unroll
-                for (int j4 = 0; j4 < 4; ++j4)
-                    po[part_slot(db, j4, hg_e, n_e)] = f32x4{o[db][4 * j4], o[db][4 * j4 + 1], o[db][4 * j4 + 2], o[db][4 * j4 + 3]};
-            p.part_ml[part * 64 + 32 * hg_e + n_e] = hg_e ? ltot : m;
+                for (int db = 0; db < NF; ++db) po[part_slot(4 * db + g_e, row)] = o[h][db];
+                if (g_e < 2) p.part_ml[part * 64 + 32 * g_e + row] = g_e ? ltot : m[h];
+            }
         }
         if (!PERSIST) return;
         __syncthreads();   // every wavefront has read its last tiles: the buffers become those of the next item
         item += x_blocks;
         continue;
     }
-    // ---- epilogue: normalise and store; lane (n, hg) holds channels 32*db + 8*(j/4) + 4*hg + j%4 of query row n.
-    // Stored straight from these registers a store instruction would scatter 16-byte pieces over 32 rows (8 K
+    // ---- epilogue: normalise and store; lane (n, g4) holds channels 16 * db + 4 * g4 ... + 3 of query rows n and 16 + n.
+    // Stored straight from these registers a store instruction would scatter 8-byte pieces over 16 rows (16 K
     // partial-line writes per block, several microseconds of back-pressure).  Instead each wavefront passes its
     // 32 rows through LDS (8-byte slots XOR-swizzled with the row number so that neither side conflicts much) and
     // writes them out as whole rows, 16 bytes per lane.
     {
-        float ltot;
-        {
-            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum), false, false);
-            ltot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-        }
         // Row coordinates again, from a freshly read lane id: the compiler then keeps none of the
         // prologue's address terms alive across the tile loops.
         const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-        const int n_e = lane_e & 31, hg_e = lane_e >> 5;
-        const int r_row = rt * BM + wave * 32 + n_e;
-        const bool valid = r_row / p.G < p.tq;
-        const uint32_t qi_e = (uint32_t)(r_row / p.G), hq_e = (uint32_t)(hkv * p.G + r_row % p.G);
-        bf16_t *orow = static_cast<bf16_t *>(p.out) + l * p.s_o.layer + (int64_t)hq_e * p.s_o.head + (int64_t)qi_e * p.s_o.token;
+        const int n_e = lane_e & 15, g_e = lane_e >> 4;
         constexpr int SLOTS = 2 * KCH;                       // 8-byte slots per row
         constexpr int FM = (SLOTS < 32 ? SLOTS : 32) - 1;    // swizzle mask
         __syncthreads();  // every wavefront has finished reading K and V (and no direct load is outstanding)
         unsigned char *stage = smem + wave * (32 * ROWB);
         uint64_t *ptab = reinterpret_cast<uint64_t *>(smem + 4 * HALFB + 2 * TILEB) + wave * 32;
-        if (hg_e == 0) ptab[n_e] = valid ? (uint64_t)(uintptr_t)orow : 0;
-        const float inv = 1.f / ltot;
 #pragma unroll
-        for (int db = 0; db < NDB; ++db)
+        for (int h = 0; h < 2; ++h) {
+            const int row = 16 * h + n_e, r_row = rt * BM + wave * 32 + row;
+            const bool valid = r_row / p.G < p.tq;
+            const uint32_t qi_e = (uint32_t)(r_row / p.G), hq_e = (uint32_t)(hkv * p.G + r_row % p.G);
+            bf16_t *orow = static_cast<bf16_t *>(p.out) + l * p.s_o.layer + (int64_t)hq_e * p.s_o.head + (int64_t)qi_e * p.s_o.token;
+            const float ltot = query_sum(lsum[h]);
+            if (g_e == 0) ptab[row] = valid ? (uint64_t)(uintptr_t)orow : 0;
+            const float inv = 1.f / ltot;
 #pragma unroll
-            for (int j4 = 0; j4 < 4; ++j4) {
+            for (int db = 0; db < NF; ++db) {
                 u32x2 w;
-                w[0] = pack_bf16x2(o[db][4 * j4] * inv, o[db][4 * j4 + 1] * inv);
-                w[1] = pack_bf16x2(o[db][4 * j4 + 2] * inv, o[db][4 * j4 + 3] * inv);
-                const int slot = (8 * db + 2 * j4 + hg_e) ^ (n_e & FM);
-                *reinterpret_cast<u32x2 *>(stage + n_e * ROWB + slot * 8) = w;
+                w[0] = pack_bf16x2(o[h][db][0] * inv, o[h][db][1] * inv);
+                w[1] = pack_bf16x2(o[h][db][2] * inv, o[h][db][3] * inv);
+                *reinterpret_cast<u32x2 *>(stage + row * ROWB + ((4 * db + g_e) ^ (row & FM)) * 8) = w;
             }
-        if (p.lse && hg_e == 0 && valid)
-            p.lse[((int64_t)l * p.Hkv * p.G + hq_e) * p.tq + qi_e] = m * p.scale + logf(ltot);
+            if (p.lse && g_e == 0 && valid)
+                p.lse[((int64_t)l * p.Hkv * p.G + hq_e) * p.tq + qi_e] = m[h] * p.scale + logf(ltot);
+        }
         // the reads below touch what other lanes of this wavefront wrote: LDS operations of a wavefront complete in order
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();

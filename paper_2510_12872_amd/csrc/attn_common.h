@@ -9,6 +9,18 @@
 
 namespace kvc {
 
+// Division by a launch constant d >= 1 of 0 <= n < 2^31 as a multiplication: with L = ceil(log2 d) and mul = floor(2^(31 + L) / d) + 1,
+// n * mul / 2^(31 + L) exceeds n / d by less than 1 / d.  The hardware has no integer division, and a block
+// starts with eight, one behind the other: one layer, one token, 3100 keys 13.5 -> 13.0 us without them, Tq 512 38.1 -> 37.8.
+typedef uint64_t divisor_t;   // mul, shift << 32
+static inline divisor_t make_divisor(uint32_t d)
+{
+    uint32_t L = 0;
+    while (((uint64_t)1 << L) < d) ++L;
+    return ((uint64_t)1 << (31 + L)) / d + 1 + ((uint64_t)(31 + L) << 32);
+}
+__host__ __device__ __forceinline__ int div_by(int n, divisor_t d) { return (int)(((uint64_t)(uint32_t)n * (uint32_t)d) >> (uint32_t)(d >> 32)); }
+
 struct AttnParams {
     const void *q, *k, *v;
     void *out;
@@ -25,7 +37,16 @@ struct AttnParams {
     float *part_ml;    // [group][split][2][32]: reference m (raw score units), row sum
     int32_t n_splits;  // 1: results go straight to `out`
     int32_t groups_per_tile;  // 32-row groups of a row tile (= wavefronts that own rows)
+    divisor_t by_G, by_Hkv, by_row_tiles, by_splits, by_groups;   // set_divisors()
 };
+static inline void set_divisors(AttnParams &p)
+{
+    p.by_G = make_divisor((uint32_t)p.G);
+    p.by_Hkv = make_divisor((uint32_t)p.Hkv);
+    p.by_row_tiles = make_divisor((uint32_t)p.n_row_tiles);
+    p.by_splits = make_divisor((uint32_t)p.n_splits);
+    p.by_groups = make_divisor((uint32_t)p.groups_per_tile);
+}
 
 __device__ __forceinline__ bf16x8 as_bf16x8(const u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 

@@ -49,18 +49,17 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
     const int x_count = (p.n_items >> 3) + (x_id < (p.n_items & 7) ? 1 : 0);
     const int x_blocks = ((int)gridDim.x - x_id + 7) >> 3;
     for (int item = blockIdx.x >> 3; item < x_count; item += x_blocks) {
-        int logical = x_first + item;
-        const int rt = logical % p.n_row_tiles;   // the row tiles of a key run are neighbours: they share its L2 lines
-        logical /= p.n_row_tiles;
-        const int split = logical % p.n_splits;
-        const int lh = logical / p.n_splits;
-        const int l = lh / p.Hkv, hkv = lh % p.Hkv;
+        const int logical = x_first + item;
+        const int run = div_by(logical, p.by_row_tiles);
+        const int rt = logical - run * p.n_row_tiles;   // the row tiles of a key run are neighbours: they share its L2 lines
+        const int lh = div_by(run, p.by_splits), split = run - lh * p.n_splits;
+        const int l = div_by(lh, p.by_Hkv), hkv = lh - l * p.Hkv;
 
-        const int r_row = rt * 32 + n;
-        const bool valid = r_row / p.G < p.tq;
-        const int qi = min(r_row / p.G, p.tq - 1);
-        const int hq = hkv * p.G + r_row % p.G;
-        const int imax = min(p.tq - 1, (rt * 32 + 31) / p.G), imin = min(p.tq - 1, rt * 32 / p.G);
+        const int r_row = rt * 32 + n, i_row = div_by(r_row, p.by_G);
+        const bool valid = i_row < p.tq;
+        const int qi = min(i_row, p.tq - 1);
+        const int hq = hkv * p.G + r_row - i_row * p.G;
+        const int imax = min(p.tq - 1, div_by(rt * 32 + 31, p.by_G)), imin = min(p.tq - 1, div_by(rt * 32, p.by_G));
         const int units = (p.n_ctx + imax + 32) / 32;   // sub-steps that some query of the tile sees
         const int u0 = split_bound(split, p.n_splits, units, units), u1 = split_bound(split + 1, p.n_splits, units, units);
 
@@ -273,15 +272,15 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const AttnParams p)
     const int n = tid & 31, hg = (tid >> 5) & 1, j4 = tid >> 6;
     const int db = blockIdx.y;
     const int group = blockIdx.x;
-    const int tile = group / p.groups_per_tile, w = group % p.groups_per_tile;
-    const int lh = tile / p.n_row_tiles, rt = tile % p.n_row_tiles;
-    const int l = lh / p.Hkv, hkv = lh % p.Hkv;
+    const int tile = div_by(group, p.by_groups), w = group - tile * p.groups_per_tile;
+    const int lh = div_by(tile, p.by_row_tiles), rt = tile - lh * p.n_row_tiles;
+    const int l = div_by(lh, p.by_Hkv), hkv = lh - l * p.Hkv;
     const int bm = 32 * p.groups_per_tile;
     auto row_of = [&](int nn, bool &ok, int64_t &q_i, int64_t &h_q) {
         const int r = rt * bm + w * 32 + nn;
-        ok = r / p.G < p.tq;
-        q_i = r / p.G;
-        h_q = hkv * p.G + r % p.G;
+        q_i = div_by(r, p.by_G);
+        ok = q_i < p.tq;
+        h_q = hkv * p.G + r - q_i * p.G;
     };
     bool valid;
     int64_t qi, hq;

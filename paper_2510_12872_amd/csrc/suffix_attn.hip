@@ -120,26 +120,30 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     ParamT &p = *p_item;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, n = lane & 15, g4 = lane >> 4;
-    const int split = SPLIT ? logical % p.n_splits : 0;
-    if constexpr (SPLIT) logical /= p.n_splits;
-    const int lh = logical / p.n_row_tiles;
-    const int rt = p.n_row_tiles - 1 - logical % p.n_row_tiles;  // longest rows first
-    const int l = lh / p.Hkv, hkv = lh % p.Hkv;
+    int split = 0;
+    if constexpr (SPLIT) {
+        const int rest = div_by(logical, p.by_splits);
+        split = logical - rest * p.n_splits;
+        logical = rest;
+    }
+    const int lh = div_by(logical, p.by_row_tiles);
+    const int rt = p.n_row_tiles - 1 - (logical - lh * p.n_row_tiles);  // longest rows first
+    const int l = div_by(lh, p.by_Hkv), hkv = lh - l * p.Hkv;
 
     const bf16_t *kb_ = static_cast<const bf16_t *>(p.k) + l * p.s_k.layer + hkv * p.s_k.head;
     const bf16_t *vb_ = static_cast<const bf16_t *>(p.v) + l * p.s_v.layer + hkv * p.s_v.head;
 
     // Every wavefront of the block walks the same tiles (one barrier per 64-key tile); the causal
     // mask is applied from the first 32-key sub-step that is partly hidden from some query of the block.
-    const int wg_imax = min(p.tq - 1, (rt * BM + BM - 1) / p.G);
-    const int wg_imin = min(p.tq - 1, (rt * BM) / p.G);
+    const int wg_imax = min(p.tq - 1, div_by(rt * BM + BM - 1, p.by_G));
+    const int wg_imin = min(p.tq - 1, div_by(rt * BM, p.by_G));
     const int all_tiles = (p.n_ctx + wg_imax + 1 + 63) / 64;
     const int first_hidden = (p.n_ctx + wg_imin) / 64 + 1;
     const int tile0 = SPLIT ? split_bound(split, p.n_splits, all_tiles, first_hidden) : 0;
     const int n_tiles = SPLIT ? split_bound(split + 1, p.n_splits, all_tiles, first_hidden) - tile0 : all_tiles;
     if constexpr (SPLIT) {
         if (n_tiles <= 0) {   // the whole block: this run is empty
-            if (lane < 32 && (rt * BM + wave * 32 + lane) / p.G < p.tq) {
+            if (lane < 32 && div_by(rt * BM + wave * 32 + lane, p.by_G) < p.tq) {
                 const int64_t part = ((int64_t)(lh * p.n_row_tiles + rt) * NW + wave) * p.n_splits + split;
                 p.part_ml[part * 64 + lane] = -INFINITY;
                 p.part_ml[part * 64 + 32 + lane] = 0.f;
@@ -226,8 +230,9 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int r_row = rt * BM + wave * 32 + 16 * h + n;
-        qi[h] = min(r_row / p.G, p.tq - 1);
-        const int hq = hkv * p.G + r_row % p.G;
+        const int i_row = div_by(r_row, p.by_G);
+        qi[h] = min(i_row, p.tq - 1);
+        const int hq = hkv * p.G + r_row - i_row * p.G;
         const bf16_t *qrow = static_cast<const bf16_t *>(p.q) + l * p.s_q.layer + (int64_t)(uint32_t)hq * p.s_q.head + (int64_t)(uint32_t)qi[h] * p.s_q.token;
 #pragma unroll
         for (int ks = 0; ks < NF / 2; ++ks) qf[h][ks] = as_bf16x8(load16(qrow + ks * 32 + g4 * 8));
@@ -515,7 +520,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
         for (int h = 0; h < 2; ++h) {
             const float ltot = query_sum(lsum[h]);
             const int row = 16 * h + n_e;
-            if ((rt * BM + wave * 32 + row) / p.G < p.tq) {
+            if (div_by(rt * BM + wave * 32 + row, p.by_G) < p.tq) {
 #pragma unroll
                 for (int db = 0; db < NF; ++db) po[part_slot(4 * db + g_e, row)] = o[h][db];
                 if (g_e < 2) p.part_ml[part * 64 + 32 * g_e + row] = g_e ? ltot : m[h];
@@ -544,8 +549,8 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int row = 16 * h + n_e, r_row = rt * BM + wave * 32 + row;
-            const bool valid = r_row / p.G < p.tq;
-            const uint32_t qi_e = (uint32_t)(r_row / p.G), hq_e = (uint32_t)(hkv * p.G + r_row % p.G);
+            const uint32_t qi_e = (uint32_t)div_by(r_row, p.by_G), hq_e = (uint32_t)(hkv * p.G + r_row) - qi_e * (uint32_t)p.G;
+            const bool valid = qi_e < (uint32_t)p.tq;
             bf16_t *orow = static_cast<bf16_t *>(p.out) + l * p.s_o.layer + (int64_t)hq_e * p.s_o.head + (int64_t)qi_e * p.s_o.token;
             const float ltot = query_sum(lsum[h]);
             if (g_e == 0) ptab[row] = valid ? (uint64_t)(uintptr_t)orow : 0;
@@ -688,13 +693,13 @@ __device__ __forceinline__ void attn_f32_item(const AttnParams &p, int item)   /
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, n = lane & 31, hg = lane >> 5;
-    const int rt = item % p.n_row_tiles, lh = item / p.n_row_tiles;
-    const int l = lh / p.Hkv, hkv = lh % p.Hkv;
-    const int r_row = rt * 32 + n;
-    const bool valid = r_row / p.G < p.tq;
-    const int qi = min(r_row / p.G, p.tq - 1);
-    const int hq = hkv * p.G + r_row % p.G;
-    const int imax = min(p.tq - 1, (rt * 32 + 31) / p.G), imin = min(p.tq - 1, rt * 32 / p.G);
+    const int lh = div_by(item, p.by_row_tiles), rt = item - lh * p.n_row_tiles;
+    const int l = div_by(lh, p.by_Hkv), hkv = lh - l * p.Hkv;
+    const int r_row = rt * 32 + n, i_row = div_by(r_row, p.by_G);
+    const bool valid = i_row < p.tq;
+    const int qi = min(i_row, p.tq - 1);
+    const int hq = hkv * p.G + r_row - i_row * p.G;
+    const int imax = min(p.tq - 1, div_by(rt * 32 + 31, p.by_G)), imin = min(p.tq - 1, div_by(rt * 32, p.by_G));
     const int units = (p.n_ctx + imax + 32) / 32;   // sub-steps that some query of the tile sees
 
     const float *kb = static_cast<const float *>(p.k) + l * p.s_k.layer + hkv * p.s_k.head;
@@ -955,6 +960,7 @@ int suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_
     p.scale = softmax_scale > 0.f ? softmax_scale : (float)(1.0 / sqrt((double)model->head_dim));
     p.scale_log2 = (float)((double)p.scale * 1.4426950408889634);
     p.n_splits = 1;
+    p.groups_per_tile = 1;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int D = model->head_dim;
 
@@ -972,6 +978,7 @@ int suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_
         const int64_t n_blocks = (int64_t)p.L * p.Hkv * p.n_row_tiles;
         if (n_blocks > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
         p.n_items = (int32_t)n_blocks;
+        set_divisors(p);
         const bool persist = max_blocks > 0 && max_blocks < p.n_items;
         const dim3 grid((unsigned)(persist ? max_blocks : p.n_items)), block(64 * kF32Waves);
         switch (D) {
@@ -1002,6 +1009,7 @@ int suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_
         p.part_o = static_cast<float *>(workspace);
         p.part_ml = p.part_o + attn_parts(*model, plan) * (size_t)(32 * D);
     }
+    set_divisors(p);
     const bool persist = max_blocks > 0 && max_blocks < p.n_items;
     const unsigned n_blocks = persist ? (unsigned)max_blocks : (unsigned)p.n_items;
     if (plan.rows_kernel) {

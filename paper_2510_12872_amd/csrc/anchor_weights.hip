@@ -9,6 +9,8 @@
 //      (layer, head) pairs: partial[chunk][token][anchor] in double.
 //   2. finalize_kernel adds the chunks in a fixed order, takes the square root and the
 //      softmax in double, and writes fp32 weights, the nearest anchor and the selection.
+// Per-token weights of pools that fit a block's anchor tiles take one launch instead where there are tokens enough to fill the chip
+// (token_weights_kernel), and so do per-(layer, head, token) weights (dist_row_softmax_kernel): same sums, another fixed order.
 // Squared differences are accumulated in double so that fp32 inputs keep ~1e-7 relative
 // accuracy in the weights and the arg-min is decided in the precision the definition uses.
 //
@@ -110,8 +112,10 @@ struct DistParams {
     int32_t H, LH, lh_per_block, n_jobs;
     int32_t fused, rule;   // fused: a row's distances are complete inside its lanes; write the weights here
     int32_t n_blocks, group_pairs, tile_anchors;   // distance kernel: (chunk, token tile) pairs of all segments and of a group, anchors of a tile
+    int32_t tok_shift;     // token_weights_kernel: log2 of the tokens of a block
     int32_t per_segment;   // one weight set per segment: a block also adds up its rows (partial[chunk][tile][anchor])
     double tau;
+    divisor_t by_H;
     const void *anc[KVCOMM_MAX_ANCHORS + kAnchorTile];  // selected anchors of all segments (a tile's pointers are read without a look at how many it has)
     uint8_t col[KVCOMM_MAX_ANCHORS];      // original index of a selected anchor
 };
@@ -511,9 +515,9 @@ struct FinalParams {
 
 // Score whose softmax across anchors gives the weights: minus the l2 distance, or the cosine
 // similarity <x,y> / (|x| |y|) (0 when a norm is 0).
-__device__ __forceinline__ double score_of(const FinalParams &p, double s0, double s1, double s2)
+__device__ __forceinline__ double score_of(int rule, double s0, double s1, double s2)
 {
-    if (p.rule != KVCOMM_RULE_COSINE_SOFTMAX) return -sqrt(s0);
+    if (rule != KVCOMM_RULE_COSINE_SOFTMAX) return -sqrt(s0);
     const double den = sqrt(s1) * sqrt(s2);
     return den > 0.0 ? s0 / den : 0.0;
 }
@@ -522,8 +526,9 @@ __device__ __forceinline__ double score_of(const FinalParams &p, double s0, doub
 // by each of the slot's threads, so all agree bit for bit; every thread forms the exponential of its own anchor only and
 // the denominator is the sum of the n_sel exponentials in `ex` (LDS) in index order.  `act`: this thread owns anchor
 // `a` of `slot`.  Called by whole blocks (it synchronises them once).
-__device__ __forceinline__ void slot_softmax(const FinalParams &p, const FinalJob &jb, const double *sc, double *ex, int a,
-                                             int64_t slot, bool act)
+template <class Params, class Job>
+__device__ __forceinline__ void slot_softmax(const Params &p, const Job &jb, const double *sc, double *ex, int a, int64_t slot,
+                                             bool act)
 {
     int best = 0;
     double w = 0.0;
@@ -632,7 +637,7 @@ __global__ __launch_bounds__(kFinalBlock) void finalize_kernel(const FinalParams
         }
     }
     const bool act = active && cl == 0;
-    if (act) dsh[tid] = score_of(p, s0, s1, s2);   // tid = sl * n_sel + a
+    if (act) dsh[tid] = score_of(p.rule, s0, s1, s2);   // tid = sl * n_sel + a
     __syncthreads();
     slot_softmax(p, jb, dsh + sl * jb.n_sel, esh + sl * jb.n_sel, a, slot, act);
 }
@@ -692,10 +697,184 @@ __global__ __launch_bounds__(kSegBlock) void finalize_segment_kernel(const Final
         for (int c = 0; c < n_comp; ++c)
 #pragma unroll
             for (int f = 0; f < NF; ++f) tot[c] += fin[c][f * n_sel + tid];
-        dsh[tid] = score_of(p, tot[0], tot[1], tot[2]);
+        dsh[tid] = score_of(p.rule, tot[0], tot[1], tot[2]);
     }
     __syncthreads();
     slot_softmax(p, jb, dsh, esh, tid, 0, tid < n_sel);
+}
+
+// Per-token granularity in one launch: a block walks ALL (layer, head) pairs of 1, 2, 4 or 8 consecutive tokens, adds up
+// its wavefronts in LDS in a fixed order and finishes the softmax itself: no partial sums in memory and no second launch (5 us,
+// its gap, and 3 us on the host).  A wavefront reads 64 / LPR rows at a time, the block's tokens of one or more (layer, head)
+// pairs, so with 64 / LPR tokens per block every access is 1 KB long; pools of several anchor tiles share the wavefronts out.
+// HBM bound where its blocks fill the chip, else bound by what one compute unit can have in flight (35 GB/s): token_shift() weighs
+// that against the two-stage kernels.  us per call, two stages -> one, input sets in no cache, D = 128, 32 layers x 8 heads:
+//   4 x 512 tokens, 8 anchors 180.9 -> 175.3 (cosine 189.7 -> 176.9); 512 tokens, 8 anchors 54.8 -> 48.2; 200, 12 anchors 38.0 -> 33.3;
+//   130, 8 anchors 22.2 -> 18.7; 1024, 4 anchors 56.7 -> 53.4; 2 layers x 4 heads, f32, D = 64, 128 tokens, 4 anchors 12.7 -> 10.2.
+// Fewer tokens than compute units (77 tokens, 6 anchors: 15.7 -> 17.4) and pools of many tiles (64 anchors, 1024 tokens: 651 -> 687)
+// stay with the two stages.
+constexpr int kTokBlock = 512;
+
+template <typename T, int LPR, int NA, bool COS>
+__global__ __launch_bounds__(kTokBlock, COS ? 2 : 4) void token_weights_kernel(const DistParams p)
+{
+    constexpr int EPV = Elem<T>::EPV;
+    constexpr int NW = kTokBlock / 64, RPW = 64 / LPR;   // wavefronts, rows that one reads at a time
+    constexpr int KEEP = NA > LPR ? NA / LPR : 1;         // anchors of a lane after the sums over a row
+    constexpr int NC = COS ? 3 : 1;
+    __shared__ double red[NC][NW][RPW][NA];
+    __shared__ double sc[RPW * KVCOMM_MAX_ANCHORS], ex[RPW * KVCOMM_MAX_ANCHORS];
+    const DistJob &jb = p.job[job_of_block(p, blockIdx.x)];
+    const int tid = threadIdx.x, bx = blockIdx.x - jb.block0;
+    const int tpb = 1 << p.tok_shift, t0 = bx << p.tok_shift;   // tpb <= RPW
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rw = (tid & 63) / LPR, lir = tid % LPR;
+    if (bx == 0 && jb.selected_out && tid < jb.n_anchors) jb.selected_out[tid] = (int32_t)((jb.sel_mask >> tid) & 1);
+    if (jb.n_sel == 0) {   // nothing selected: all weights 0, nearest -1
+        if (tid < tpb && t0 + tid < jb.S) {
+            for (int c = 0; c < jb.n_anchors; ++c) jb.weights[(int64_t)(t0 + tid) * jb.n_anchors + c] = 0.f;
+            if (jb.nearest) jb.nearest[t0 + tid] = -1;
+        }
+        return;
+    }
+    const int tiles = (jb.n_sel + NA - 1) / NA, width = (jb.n_sel + tiles - 1) / tiles;   // tiles <= NW
+    const int phases = NW / tiles, tile = wave % tiles, phase = wave / tiles;
+    const int a0 = tile * width, na = phase < phases ? min(width, jb.n_sel - a0) : 0;
+    __builtin_assume(na <= NA);
+    const int t = t0 + (rw & (tpb - 1));
+    const int lh_step = phases * (RPW >> p.tok_shift);
+
+    double acc[NA], ny[COS ? NA : 1], nx = 0.0;
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
+        acc[j] = 0.0;
+        if (COS) ny[j] = 0.0;
+    }
+    const AnchorPtrs<T, NA> anc(p, jb.a0 + a0);
+    const T *seg = static_cast<const T *>(jb.seg_k) + t * jb.s_seg.token + lir * EPV;
+    const int64_t arow = t * p.s_anc.token + lir * EPV;
+    auto walk = [&](auto full) __attribute__((always_inline)) {   // full: every anchor of the tile exists (no branches)
+        for (int lh = phase * (RPW >> p.tok_shift) + (rw >> p.tok_shift); lh < p.LH; lh += lh_step) {
+            const int l = div_by(lh, p.by_H), h = lh - l * p.H;
+            const u32x4 rs = load16(seg + l * jb.s_seg.layer + h * jb.s_seg.head);
+            const int64_t aoff = arow + l * p.s_anc.layer + h * p.s_anc.head;
+            u32x4 ra[NA];
+#pragma unroll
+            for (int j = 0; j < NA; ++j)
+                if (decltype(full)::value || j < na) ra[j] = anc.load(j, aoff);
+            float x[EPV];
+            unpack<T>(rs, x);
+            if (COS)
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) nx = fma((double)x[e], (double)x[e], nx);
+#pragma unroll
+            for (int j = 0; j < NA; ++j)
+                if (decltype(full)::value || j < na) {
+                    if constexpr (COS) {
+                        float y[EPV];
+                        unpack<T>(ra[j], y);
+#pragma unroll
+                        for (int e = 0; e < EPV; ++e) {
+                            acc[j] = fma((double)x[e], (double)y[e], acc[j]);
+                            ny[j] = fma((double)y[e], (double)y[e], ny[j]);
+                        }
+                    } else {
+                        sqdiff_acc<T>(acc[j], x, ra[j]);
+                    }
+                }
+        }
+    };
+    if (t < jb.S && na > 0) {
+        if (na == NA)
+            walk(std::true_type{});
+        else
+            walk(std::false_type{});
+    }
+    // Sums over the lanes of a row, then over the rows of the same token in the wavefront, then over the wavefronts.
+    auto sum_rows = [&](double v) __attribute__((always_inline)) {
+        for (int off = LPR << p.tok_shift; off < 64; off <<= 1) v += __shfl_xor(v, off);
+        return v;
+    };
+    row_reduce_scatter<LPR, NA>(acc, lir);
+    if constexpr (COS) {
+        row_reduce_scatter<LPR, NA>(ny, lir);
+#pragma unroll
+        for (int off = LPR / 2; off >= 1; off >>= 1) nx += __shfl_xor(nx, off, LPR);
+        nx = sum_rows(nx);
+    }
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k) {
+        const int j = anchor_of_lane<LPR, NA>(lir, k);
+        const double v = sum_rows(acc[k]);
+        double y = 0.0;
+        if constexpr (COS) y = sum_rows(ny[k]);
+        if (rw < tpb && j < na) {
+            red[0][wave][rw][j] = v;
+            if constexpr (COS) {
+                red[1][wave][rw][j] = nx;
+                red[2][wave][rw][j] = y;
+            }
+        }
+    }
+    __syncthreads();
+    const int tok = tid / jb.n_sel, a = tid % jb.n_sel;   // tpb * n_sel <= kTokBlock
+    const bool act = tok < tpb && t0 + tok < jb.S;
+    if (act) {
+        double s[3] = {0.0, 0.0, 0.0};
+        const int at = a / width, aj = a - at * width;
+        for (int ph = 0; ph < phases; ++ph)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) s[c] += red[c][ph * tiles + at][tok][aj];
+        sc[tid] = score_of(p.rule, s[0], s[1], s[2]);
+    }
+    __syncthreads();
+    slot_softmax(p, jb, sc + tok * jb.n_sel, ex + tok * jb.n_sel, a, t0 + tok, act);
+}
+
+// log2 of the tokens of a token_weights_kernel block, or -1 where the two-stage kernels are taken.  A step of a block (one row of
+// every anchor per wavefront and row slot) takes 0.8 us of latency (cosine: 1.7 with its arithmetic), or its bytes at the
+// 35 GB/s that a compute unit reaches; two blocks share a unit (cosine: one, by its registers).  The kernel is taken where that, or
+// the whole chip's time for the bytes, is at most the chip's time plus the 7 us of partial sums and second launch; of equal sizes the
+// larger (longer accesses).  Pools of more than 8 anchors only up to 150 us, where that second launch still weighs: 512 tokens, 16
+// anchors, 32 layers x 8 heads 98.8 -> 91.0, but 2048 tokens 343 -> 362 (16 wavefronts of 17 rows each on every unit).
+// The modelled line holds to 2 % over 60 shapes: 300 tokens, 8 anchors 36.6 (two stages) and 36.8; 17 tokens, f32, 4 anchors 13.1 and 13.3.
+int token_shift(const kvcomm_model &m, const kvcomm_weights_job *jobs, const DistJob *dist, int n_jobs, int max_sel, bool cosine)
+{
+    if (max_sel > kAnchorTile) return -1;
+    const double row = (double)m.head_dim * elem_size(m.dtype);
+    const int LH = m.n_layers * m.n_kv_heads, rpw = 1024 / (int)row, nw = kTokBlock / 64;   // rows of a wavefront, wavefronts
+    double bytes = 0.0;
+    for (int j = 0; j < n_jobs; ++j) bytes += (double)LH * row * (dist[j].n_sel + 1) * jobs[j].seg_len;
+    const double chip_us = bytes / 6.4e6;
+    if (max_sel > 8 && chip_us > 150.0) return -1;
+    const int tile = cosine ? kCosTile : kAnchorTile;
+    const int tiles = std::max(1, (max_sel + tile - 1) / tile), width = (max_sel + tiles - 1) / tiles;
+    int best = -1;
+    double best_us = chip_us + 7.0;
+    for (int shift = 0; 1 << shift <= rpw; ++shift) {
+        int64_t blocks = 0;
+        for (int j = 0; j < n_jobs; ++j) blocks += ((int64_t)jobs[j].seg_len + (1 << shift) - 1) >> shift;
+        const int per_cu = cosine ? 1 : blocks > 256 ? 2 : 1, lh_step = (nw / tiles) * (rpw >> shift);
+        const double rounds = (double)((blocks + 256 * per_cu - 1) / (256 * per_cu));
+        const double step_us = std::max(cosine ? 1.7 : 0.8, per_cu * nw * 1024.0 * (width + 1) / 35e3);
+        const double us = std::max(chip_us, rounds * (2.0 + step_us * ((LH + lh_step - 1) / lh_step)));
+        if (us <= best_us) {
+            best_us = us;
+            best = shift;
+        }
+    }
+    return best;
+}
+
+template <typename T, int LPR>
+int launch_tokens(const DistParams &p, int n_blocks, int max_sel, bool cosine, hipStream_t stream)
+{
+    const dim3 grid(n_blocks), block(kTokBlock);
+    if (cosine)
+        return launch(token_weights_kernel<T, LPR, kCosTile, true>, grid, block, 0, stream, p);
+    return launch(max_sel <= 4 ? token_weights_kernel<T, LPR, 4, false> : max_sel <= 8 ? token_weights_kernel<T, LPR, 8, false>
+                                                                           : token_weights_kernel<T, LPR, kAnchorTile, false>,
+                  grid, block, 0, stream, p);
 }
 
 template <typename T, int LPR>
@@ -837,6 +1016,7 @@ extern "C" int kvcomm_anchor_weights_batch(const kvcomm_model *model, int32_t gr
     hipStream_t s = static_cast<hipStream_t>(stream);
     dp.s_anc = strides_of(anchor_layout);
     dp.H = model->n_kv_heads;
+    dp.by_H = make_divisor((uint32_t)dp.H);
     dp.LH = model->n_layers * model->n_kv_heads;
     dp.lh_per_block = pl.lh_per_block;
     dp.n_jobs = n_jobs;
@@ -897,6 +1077,33 @@ extern "C" int kvcomm_anchor_weights_batch(const kvcomm_model *model, int32_t gr
         final_blocks += (fj.n_slots + spb - 1) / spb;
     }
     if (dist_blocks > 0x7fffffff || final_blocks > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
+
+    const int shift = gran == KVCOMM_W_TOKEN ? token_shift(*model, jobs, dp.job, n_jobs, max_sel, cosine) : -1;
+    if (shift >= 0) {
+        dp.tok_shift = shift;
+        int64_t blocks = 0;   // <= the sum of the segments' tokens
+        for (int j = 0; j < n_jobs; ++j) {
+            dp.job[j].block0 = (int32_t)blocks;
+            blocks += ((int64_t)jobs[j].seg_len + (1 << shift) - 1) >> shift;
+        }
+        if (blocks > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
+        st = KVCOMM_EUNSUPPORTED;
+        const int nb = (int)blocks;
+        if (dt == KVCOMM_BF16) {
+            switch (pl.lpr) {
+                case 8: return launch_tokens<bf16_t, 8>(dp, nb, max_sel, cosine, s);
+                case 16: return launch_tokens<bf16_t, 16>(dp, nb, max_sel, cosine, s);
+                case 32: return launch_tokens<bf16_t, 32>(dp, nb, max_sel, cosine, s);
+            }
+        } else {
+            switch (pl.lpr) {
+                case 16: return launch_tokens<float, 16>(dp, nb, max_sel, cosine, s);
+                case 32: return launch_tokens<float, 32>(dp, nb, max_sel, cosine, s);
+                case 64: return launch_tokens<float, 64>(dp, nb, max_sel, cosine, s);
+            }
+        }
+        return st;
+    }
 
     if (max_sel > 0) {
         st = KVCOMM_EUNSUPPORTED;

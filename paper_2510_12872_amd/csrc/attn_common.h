@@ -9,18 +9,6 @@
 
 namespace kvc {
 
-// Division by a launch constant d >= 1 of 0 <= n < 2^31 as a multiplication: with L = ceil(log2 d) and mul = floor(2^(31 + L) / d) + 1,
-// n * mul / 2^(31 + L) exceeds n / d by less than 1 / d.  The hardware has no integer division, and a block
-// starts with eight, one behind the other: one layer, one token, 3100 keys 13.5 -> 13.0 us without them, Tq 512 38.1 -> 37.8.
-typedef uint64_t divisor_t;   // mul, shift << 32
-static inline divisor_t make_divisor(uint32_t d)
-{
-    uint32_t L = 0;
-    while (((uint64_t)1 << L) < d) ++L;
-    return ((uint64_t)1 << (31 + L)) / d + 1 + ((uint64_t)(31 + L) << 32);
-}
-__host__ __device__ __forceinline__ int div_by(int n, divisor_t d) { return (int)(((uint64_t)(uint32_t)n * (uint32_t)d) >> (uint32_t)(d >> 32)); }
-
 struct AttnParams {
     const void *q, *k, *v;
     void *out;

@@ -1,0 +1,147 @@
+"""Per-token weights in one launch (token_weights_kernel) and in two (partial sums, softmax): which calls take which, and both
+against the float64 oracle (1e-5 as for all weights; arg-min and selection exact) where a block's tokens, the wavefronts' share
+of (layer, head) pairs or the anchor tiles do not come out even."""
+import json
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2510_12872_amd as kv
+from paper_2510_12872_amd import build
+
+from launches import RECORDER
+from parity import check_weights, to_np
+
+DEV = "cuda"
+BF, F32 = torch.bfloat16, torch.float32
+RULES = (kv.RULE_L2_SOFTMAX, kv.RULE_NEAREST, kv.RULE_COSINE_SOFTMAX)
+
+# L, H, D, dtype, segment lengths, anchors per segment; one launch for the l2 rules
+ONE = [(1, 1, 64, BF, [1], [1]),              # one token, seven of eight wavefronts without a pair
+       (3, 3, 64, BF, [9, 17], [5, 2]),       # eight rows per wavefront, ragged last block
+       (5, 5, 128, BF, [130], [16]),          # a full tile
+       (7, 5, 128, BF, [11, 3, 6], [9, 1, 4]),
+       (3, 7, 256, BF, [5, 8], [4, 8]),
+       (2, 3, 64, F32, [33], [7]),
+       (3, 5, 128, F32, [21, 4], [3, 12]),
+       (9, 1, 256, F32, [7], [6])]            # one row per wavefront
+TWO = [(32, 8, 64, BF, [7], [8]), (32, 8, 128, BF, [19], [3]), (40, 4, 128, F32, [9], [13]), (2, 2, 128, BF, [12], [17])]
+
+
+def _jobs(L, H, D, dtype, lens, pools, seed=0):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed + L + D)
+    # (strided views: tokens of a longer cache, heads before layers)
+    view = lambda n: torch.randn((H, L, n + 5, D), generator=g, device=DEV).to(dtype).permute(1, 0, 2, 3)[:, :, 2:2 + n]
+    cap = max(lens) + 2
+    pool = torch.randn((sum(pools), H, L, cap, D), generator=g, device=DEV).to(dtype)
+    anc, i = [], 0
+    for n in pools:
+        anc.append([pool[i + a].permute(1, 0, 2, 3) for a in range(n)])
+        i += n
+    return [dict(seg_base_k=view(S), anchor_base_k=a) for S, a in zip(lens, anc)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,H,D,dtype,lens,pools", ONE + TWO)
+def test_against_the_oracle(L, H, D, dtype, lens, pools):
+    m = kv.Model(L, H, H, D, dtype, 5e5)
+    jobs = _jobs(L, H, D, dtype, lens, pools)
+    for rule in RULES:
+        print(f"token weights: L{L} H{H} D{D} {dtype} {lens} {pools} rule{rule}", flush=True)
+        got = kv.kvcomm_anchor_weights_batch(m, jobs, 1.0, kv.W_TOKEN, rule)
+        torch.cuda.synchronize()
+        for (w, near, sel), jd, S in zip(got, jobs, lens):
+            bk, anc = to_np(jd["seg_base_k"]), [to_np(a[:, :, :S]) for a in jd["anchor_base_k"]]
+            if rule == kv.RULE_COSINE_SOFTMAX:
+                want, want_near = oracle.weights_from_sim(*oracle.cosine(bk, anc, kv.W_TOKEN), 1.0)
+            elif rule == kv.RULE_NEAREST:
+                want, want_near = oracle.weights_nearest(*oracle.distances(bk, anc, kv.W_TOKEN))
+            else:
+                want, want_near = oracle.weights(*oracle.distances(bk, anc, kv.W_TOKEN), 1.0)
+            check_weights(w.cpu().numpy(), want.T)
+            assert np.array_equal(near.cpu().numpy(), want_near) and sel.all()
+
+
+@pytest.mark.gpu
+def test_short_anchors_and_empty_pools():
+    """A pool none of whose anchors is long enough beside pools that have some; rows behind a short anchor are never read as weights."""
+    L, H, D = 3, 2, 128
+    m = kv.Model(L, H, H, D, BF, 5e5)
+    jobs = _jobs(L, H, D, BF, [13, 7, 10], [4, 3, 2], seed=5)
+    lens = [[15, 12, 15, 3], [6, 2, 0], [10, 9]]
+    for jd, n in zip(jobs, lens):
+        jd["anchor_len"] = n
+        for a, k in zip(jd["anchor_base_k"], n):
+            a[:, :, k:] = float("nan")
+    print("token weights: short anchors", flush=True)
+    got = kv.kvcomm_anchor_weights_batch(m, jobs, 1.0, kv.W_TOKEN)
+    torch.cuda.synchronize()
+    for (w, near, sel), jd, n in zip(got, jobs, lens):
+        S = jd["seg_base_k"].shape[2]
+        live = [a for a, k in enumerate(n) if k >= S]
+        assert [i for i, s in enumerate(sel.tolist()) if s] == live
+        want = np.zeros((S, len(n)))
+        if live:
+            dist, ok = oracle.distances(to_np(jd["seg_base_k"]), [to_np(jd["anchor_base_k"][a][:, :, :S]) for a in live], kv.W_TOKEN)
+            lw, ln = oracle.weights(dist, ok, 1.0)
+            want[:, live] = lw.T
+            assert near.tolist() == [live[i] for i in ln]
+        else:
+            assert (near == -1).all()
+        check_weights(w.cpu().numpy(), want)
+
+
+DRIVER = r"""
+import ctypes, json, sys
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+i32, i64, vp, sz = ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p, ctypes.c_size_t
+class Model(ctypes.Structure):
+    _fields_ = [(n, i32) for n in ("L", "hkv", "hq", "D", "dtype")] + [("theta", ctypes.c_double)]
+class Tensor(ctypes.Structure):
+    _fields_ = [("ptr", vp), ("sl", i64), ("sh", i64), ("st", i64)]
+class Job(ctypes.Structure):
+    _fields_ = [("seg", Tensor), ("S", i32), ("anc", vp), ("len", vp), ("n", i32), ("w", vp), ("near", vp), ("sel", vp)]
+shim.rec_name.restype = ctypes.c_char_p
+shim.rec_grid.restype = ctypes.c_uint
+f = lib.kvcomm_anchor_weights_batch
+f.argtypes = [vp, i32, i32, ctypes.c_float, Tensor, vp, i32, vp, sz, vp]
+res = []
+for L, H, D, dtype, lens, pools, rule in json.load(sys.stdin):
+    keep, jobs = [], (Job * len(lens))()
+    for j, (S, n) in enumerate(zip(lens, pools)):
+        anc, ln = (vp * n)(*[0x1000] * n), (i32 * n)(*[S] * n)
+        keep += [anc, ln]
+        jobs[j] = Job(Tensor(0x1000, H * S * D, S * D, D), S, ctypes.addressof(anc), ctypes.addressof(ln), n, 0x1000, 0x1000, 0x1000)
+    shim.rec_clear()
+    cap = max(lens)
+    st = f(ctypes.byref(Model(L, H, H, D, dtype, 1e4)), 0, rule, 1.0, Tensor(0x1000, H * cap * D, cap * D, D), jobs, len(lens), 0x1000, 1 << 40, None)
+    res.append(dict(status=st, names=[shim.rec_name(i).decode() for i in range(shim.rec_count())], grid=shim.rec_grid(0, 0)))
+json.dump(res, sys.stdout)
+"""
+
+
+def test_which_calls_take_one_launch(tmp_path):
+    src, shim = tmp_path / "rec.c", tmp_path / "librec.so"
+    src.write_text(RECORDER)
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-o", str(shim), str(src)], check=True)
+    # 4 x 512 tokens: four tokens per block; one segment of 512: two; 200: one; fewer tokens than half the chip and many pairs: two launches
+    sized = [((32, 8, 128, BF, [512] * 4, [8] * 4), 512), ((32, 8, 128, BF, [512], [8]), 256), ((32, 8, 128, BF, [200], [12]), 200)]
+    two = TWO + [(32, 8, 128, BF, [77], [6]), (32, 8, 128, BF, [1024], [64]), (32, 8, 128, BF, [2048], [16])]
+    calls = [(c, 0) for c in ONE + [c for c, _ in sized] + two]
+    arg = [[c[0], c[1], c[2], 0 if c[3] == F32 else 1, c[4], c[5], rule] for c, rule in calls]
+    lib = os.environ.get("KVCOMM_LIBRARY") or build.LIB
+    ran = subprocess.run([sys.executable, "-c", DRIVER, str(shim), lib], input=json.dumps(arg), capture_output=True, text=True)
+    assert ran.returncode == 0, ran.stderr[-2000:]
+    for (c, _), r in zip(calls, json.loads(ran.stdout)):
+        one = len(r["names"]) == 1 and "token_weights_kernel" in r["names"][0]
+        assert r["status"] == 0 and one == (c not in two), (c, r)
+        assert one or ("partial_kernel" in r["names"][0] and "finalize_kernel" in r["names"][1])
+        for s, grid in sized:
+            assert c != s or r["grid"] == grid

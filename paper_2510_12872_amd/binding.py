@@ -1,9 +1,12 @@
-"""ctypes binding of libkvcomm.so: argument marshalling only.
+"""Binding of libkvcomm.so: argument marshalling only.
 
 Every function here has the name of the C entry point it calls (include/kvcomm.h) and does
 nothing but turn torch tensors into (pointer, strides) descriptors, allocate outputs that
 the caller did not pass, and raise on a non-zero status.  All arithmetic of the reuse step
 runs inside the library's HIP kernels.  torch is used for device memory and streams only.
+
+Calls whose arguments are plain (device tensors, lists, numbers) are marshalled by the native module _marshal
+(csrc/marshal.cpp), which declines all others; those take the ctypes code below, which converts or refuses them.
 """
 import ctypes
 import os
@@ -86,6 +89,13 @@ class Model:
 
 
 _lib = None
+_native = None   # the module _marshal, set with _lib
+
+
+_NATIVE_CALLS = ("kvcomm_weight_slots", "kvcomm_suffix_attn_workspace", "kvcomm_anchor_weights_rule",
+                 "kvcomm_anchor_weights_batch", "kvcomm_align_kv_batch", "kvcomm_align_kv_q8_batch", "kvcomm_align_kv",
+                 "kvcomm_align_kv_q8", "kvcomm_suffix_attn", "kvcomm_suffix_attn_confined_ws", "kvcomm_anchor_predict",
+                 "kvcomm_capture_offsets", "kvcomm_quantize_deltas")
 
 
 def library_path():
@@ -94,7 +104,7 @@ def library_path():
 
 def load_library():
     """Load libkvcomm.so (built by paper_2510_12872_amd.build); raises if it is missing."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -159,6 +169,13 @@ def load_library():
     lib.kvcomm_status_string.restype = ctypes.c_char_p
     lib.kvcomm_version.argtypes = []
     lib.kvcomm_version.restype = ctypes.c_int
+    try:
+        from . import _marshal
+    except ImportError as e:
+        raise RuntimeError("the native module _marshal cannot be loaded: build it with `python -m paper_2510_12872_amd.build`") from e
+    _marshal.bind({n: ctypes.cast(getattr(lib, n), vp).value for n in _NATIVE_CALLS}, Model, torch.cuda.current_device,
+                  _raw_current_stream)
+    _native = _marshal
     _lib = lib
     return lib
 
@@ -166,6 +183,15 @@ def load_library():
 def _check(status):
     if status != 0:
         raise KVCommError(status, load_library().kvcomm_status_string(status).decode())
+
+
+def _done(status):
+    """Status of a call of the native module: False if it declined (nothing has been enqueued), else the call is made."""
+    if status is None:
+        return False
+    if status != 0:
+        _check(status)
+    return True
 
 
 def _not_a_tensor(what, dtype):
@@ -245,6 +271,9 @@ def kvcomm_anchor_weights(model, seg_base_k, anchor_base_k, anchor_len=None, tem
     if workspace is None:
         need = kvcomm_anchor_weights_workspace(model, seg_len, A, gran)
         workspace = torch.empty((max(need, 1),), dtype=torch.uint8, device=dev)
+    if _done(_native.anchor_weights(model, gran, RULE_L2_SOFTMAX, temperature, seg_base_k, anchor_base_k, anchor_len, weights_out,
+                                    nearest_out, selected_out, workspace, stream)):
+        return weights_out, nearest_out, selected_out
     ptrs, layout, lens = _anchor_args(anchor_base_k, anchor_len, model.dtype, "anchor_base_k")
     _check(lib.kvcomm_anchor_weights(ctypes.byref(model.c()), gran, float(temperature),
                                      _desc(seg_base_k, model.dtype, "seg_base_k"), seg_len, ptrs, layout, lens, A,
@@ -277,6 +306,9 @@ def kvcomm_align_kv(model, base_k, base_v, anchor_dk, anchor_dv, weights, delta_
                     anchor_len=None, anchor_delta_pos=None, gran=W_TOKEN, stream=None):
     """Positional alignment + offset approximation into out_k / out_v (views of the agent cache)."""
     lib = load_library()
+    if _done(_native.align_kv(model, gran, base_k, base_v, anchor_dk, anchor_dv, weights, delta_pos, out_k, out_v, anchor_len,
+                              anchor_delta_pos, stream)):
+        return out_k, out_v
     seg_len = base_k.shape[2]
     A = len(anchor_dk)
     if len(anchor_dv) != A:
@@ -316,36 +348,37 @@ def _in_private_pool(t):
                for seg in torch.cuda.memory_snapshot())
 
 
-def _attn_workspace(cmodel, n_ctx, tq, workspace, device, stream):
-    """(pointer, bytes, tensor to keep until the call has returned) of the attention's scratch.  A workspace that is
-    made here belongs to the stream the kernels run on, so the allocator does not hand it out under them.  Where there is
-    no memory for it, or a graph that torch does not manage is being captured (the allocator would hand the memory out
-    again while the graph's replays write to it), the call does without: same result up to rounding, only slower."""
-    if workspace is None:
-        need = load_library().kvcomm_suffix_attn_workspace(ctypes.byref(cmodel), n_ctx, tq)
-        if not need:
-            return None, 0, None
-        try:
-            if stream is None:
+def _attn_scratch(need, device, stream):
+    """Scratch of the attention, `need` bytes, or None.  It belongs to the stream the kernels run on, so the allocator does not
+    hand it out under them.  Where there is no memory for it, or a graph that torch does not manage is being captured (the
+    allocator would hand the memory out again while the graph's replays write to it), the call does without: same result
+    up to rounding, only slower."""
+    try:
+        if stream is None:
+            workspace = torch.empty((need,), dtype=torch.uint8, device=device)
+            capturing = torch.cuda.is_current_stream_capturing()
+        else:
+            own = stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream)
+            with torch.cuda.stream(own):
                 workspace = torch.empty((need,), dtype=torch.uint8, device=device)
                 capturing = torch.cuda.is_current_stream_capturing()
-            else:
-                own = stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream)
-                with torch.cuda.stream(own):
-                    workspace = torch.empty((need,), dtype=torch.uint8, device=device)
-                    capturing = torch.cuda.is_current_stream_capturing()
-        except torch.OutOfMemoryError:
-            return None, 0, None
-        if capturing and not _in_private_pool(workspace):
+    except torch.OutOfMemoryError:
+        return None
+    return None if capturing and not _in_private_pool(workspace) else workspace
+
+
+def _attn_workspace(cmodel, n_ctx, tq, workspace, device, stream):
+    """(pointer, bytes, tensor to keep until the call has returned) of the attention's scratch, made here if not given."""
+    if workspace is None:
+        need = load_library().kvcomm_suffix_attn_workspace(ctypes.byref(cmodel), n_ctx, tq)
+        workspace = _attn_scratch(need, device, stream) if need else None
+        if workspace is None:
             return None, 0, None
     return workspace.data_ptr(), workspace.numel() * workspace.element_size(), workspace
 
 
-def kvcomm_suffix_attn(model, q, cache_k, cache_v, n_ctx, softmax_scale=0.0, out=None, lse_out=None,
-                       want_lse=False, stream=None, workspace=None):
-    """Causal attention of the suffix queries q [L,Hq,Tq,D] over cache_k/v [L,Hkv,n_ctx+Tq,D].
-
-    workspace: kvcomm_suffix_attn_workspace() bytes on the device (made here if not given)."""
+def _suffix_attn(model, q, cache_k, cache_v, n_ctx, max_blocks, softmax_scale, out, lse_out, want_lse, stream, workspace):
+    """Both attention calls; max_blocks None: the plain launch."""
     lib = load_library()
     tq = q.shape[2]
     if cache_k.shape[2] != n_ctx + tq or cache_v.shape[2] != n_ctx + tq:
@@ -354,15 +387,34 @@ def kvcomm_suffix_attn(model, q, cache_k, cache_v, n_ctx, softmax_scale=0.0, out
         out = torch.empty_like(q)
     if want_lse and lse_out is None:
         lse_out = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device)
+    need = 0   # bytes of scratch to be made here; None: not asked yet
+    if workspace is None and n_ctx + tq >= ATTN_MIN_SPLIT_KEYS:
+        need = _native.suffix_attn_workspace(model, n_ctx, tq)
+    if need:
+        workspace = _attn_scratch(need, q.device, stream)
+    if need is not None and _done(_native.suffix_attn(model, q, cache_k, cache_v, n_ctx, softmax_scale, out, lse_out, max_blocks,
+                                                      workspace, stream)):
+        return (out, lse_out) if want_lse else out
     cmodel = model.c()
     ws, ws_bytes, _keep = None, 0, None
-    if workspace is not None or n_ctx + tq >= ATTN_MIN_SPLIT_KEYS:
+    if workspace is not None or need is None:
         ws, ws_bytes, _keep = _attn_workspace(cmodel, int(n_ctx), tq, workspace, q.device, stream)
-    _check(lib.kvcomm_suffix_attn(ctypes.byref(cmodel), _desc(q, model.dtype, "q"),
-                                  _desc(cache_k, model.dtype, "cache_k"), _desc(cache_v, model.dtype, "cache_v"),
-                                  int(n_ctx), tq, float(softmax_scale), _desc(out, model.dtype, "out"),
-                                  None if lse_out is None else lse_out.data_ptr(), ws, ws_bytes, _stream_ptr(stream)))
+    args = (ctypes.byref(cmodel), _desc(q, model.dtype, "q"), _desc(cache_k, model.dtype, "cache_k"),
+            _desc(cache_v, model.dtype, "cache_v"), int(n_ctx), tq, float(softmax_scale), _desc(out, model.dtype, "out"),
+            None if lse_out is None else lse_out.data_ptr())
+    if max_blocks is None:
+        _check(lib.kvcomm_suffix_attn(*args, ws, ws_bytes, _stream_ptr(stream)))
+    else:
+        _check(lib.kvcomm_suffix_attn_confined_ws(*args, int(max_blocks), ws, ws_bytes, _stream_ptr(stream)))
     return (out, lse_out) if want_lse else out
+
+
+def kvcomm_suffix_attn(model, q, cache_k, cache_v, n_ctx, softmax_scale=0.0, out=None, lse_out=None,
+                       want_lse=False, stream=None, workspace=None):
+    """Causal attention of the suffix queries q [L,Hq,Tq,D] over cache_k/v [L,Hkv,n_ctx+Tq,D].
+
+    workspace: kvcomm_suffix_attn_workspace() bytes on the device (made here if not given)."""
+    return _suffix_attn(model, q, cache_k, cache_v, n_ctx, None, softmax_scale, out, lse_out, want_lse, stream, workspace)
 
 
 def kvcomm_suffix_attn_confined(model, q, cache_k, cache_v, n_ctx, max_blocks, softmax_scale=0.0, out=None,
@@ -376,25 +428,8 @@ def kvcomm_suffix_attn_confined_ws(model, q, cache_k, cache_v, n_ctx, max_blocks
                                    lse_out=None, want_lse=False, stream=None, workspace=None):
     """kvcomm_suffix_attn_confined with the scratch of kvcomm_suffix_attn (made here if not given): the same bits as
     kvcomm_suffix_attn with a workspace."""
-    lib = load_library()
-    tq = q.shape[2]
-    if cache_k.shape[2] != n_ctx + tq or cache_v.shape[2] != n_ctx + tq:
-        raise KVCommError(-1, "cache_k / cache_v must hold n_ctx + tq tokens")
-    if out is None:
-        out = torch.empty_like(q)
-    if want_lse and lse_out is None:
-        lse_out = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device)
-    cmodel = model.c()
-    ws, ws_bytes, _keep = None, 0, None
-    if workspace is not None or n_ctx + tq >= ATTN_MIN_SPLIT_KEYS:
-        ws, ws_bytes, _keep = _attn_workspace(cmodel, int(n_ctx), tq, workspace, q.device, stream)
-    _check(lib.kvcomm_suffix_attn_confined_ws(ctypes.byref(cmodel), _desc(q, model.dtype, "q"),
-                                              _desc(cache_k, model.dtype, "cache_k"),
-                                              _desc(cache_v, model.dtype, "cache_v"), int(n_ctx), tq,
-                                              float(softmax_scale), _desc(out, model.dtype, "out"),
-                                              None if lse_out is None else lse_out.data_ptr(), int(max_blocks), ws,
-                                              ws_bytes, _stream_ptr(stream)))
-    return (out, lse_out) if want_lse else out
+    return _suffix_attn(model, q, cache_k, cache_v, n_ctx, int(max_blocks), softmax_scale, out, lse_out, want_lse, stream,
+                        workspace)
 
 
 def kvcomm_anchor_weights_rule_workspace(model, seg_len, n_anchors, gran=W_TOKEN, rule=RULE_L2_SOFTMAX):
@@ -420,6 +455,9 @@ def kvcomm_anchor_weights_rule(model, rule, seg_base_k, anchor_base_k, anchor_le
     if workspace is None:
         need = kvcomm_anchor_weights_rule_workspace(model, seg_len, A, gran, rule)
         workspace = torch.empty((max(need, 1),), dtype=torch.uint8, device=dev)
+    if _done(_native.anchor_weights(model, gran, rule, temperature, seg_base_k, anchor_base_k, anchor_len, weights_out, nearest_out,
+                                    selected_out, workspace, stream)):
+        return weights_out, nearest_out, selected_out
     ptrs, layout, lens = _anchor_args(anchor_base_k, anchor_len, model.dtype, "anchor_base_k")
     _check(lib.kvcomm_anchor_weights_rule(ctypes.byref(model.c()), gran, int(rule), float(temperature),
                                           _desc(seg_base_k, model.dtype, "seg_base_k"), seg_len, ptrs, layout, lens,
@@ -450,6 +488,8 @@ def kvcomm_anchor_predict(weights, anchor_len, seg_len, gamma, entropy_out=None,
         result_out = torch.empty((2,), dtype=torch.float32, device=dev)
     if workspace is None:
         workspace = torch.empty((max(kvcomm_anchor_predict_workspace(n), 8),), dtype=torch.uint8, device=dev)
+    if _done(_native.anchor_predict(weights, anchor_len, seg_len, gamma, entropy_out, result_out, workspace, stream)):
+        return (result_out, entropy_out) if want_entropy else result_out
     lens = (ctypes.c_int32 * max(A, 1))(*[int(x) for x in anchor_len])
     _check(lib.kvcomm_anchor_predict(weights.data_ptr(), n, lens, A, int(seg_len), float(gamma),
                                      None if entropy_out is None else entropy_out.data_ptr(), result_out.data_ptr(),
@@ -469,6 +509,8 @@ def kvcomm_capture_offsets(model, base_k, base_v, real_k, real_v, delta_pos, out
         out_dk = torch.empty(base_k.shape, dtype=model.dtype, device=base_k.device)
     if out_dv is None:
         out_dv = torch.empty(base_k.shape, dtype=model.dtype, device=base_k.device)
+    if _done(_native.capture_offsets(model, base_k, base_v, real_k, real_v, delta_pos, out_dk, out_dv, stream)):
+        return out_dk, out_dv
     d = lambda t, what: _desc(t, model.dtype, what)
     _check(lib.kvcomm_capture_offsets(ctypes.byref(model.c()), d(base_k, "base_k"), d(base_v, "base_v"),
                                       d(real_k, "real_k"), d(real_v, "real_v"), seg_len, int(delta_pos),
@@ -495,18 +537,28 @@ def kvcomm_anchor_weights_batch(model, jobs, temperature=1.0, gran=W_TOKEN, rule
     weights_out, nearest_out, selected_out.  Returns a list of (weights, nearest, selected)."""
     lib = load_library()
     n = len(jobs)
+    outs = []
+    for jd in jobs:
+        w, nr, so = jd.get("weights_out"), jd.get("nearest_out"), jd.get("selected_out")
+        if w is None or nr is None or so is None:
+            seg, A = jd["seg_base_k"], len(jd["anchor_base_k"])
+            if w is None or nr is None:
+                slots = kvcomm_weight_slots(model, seg.shape[2], gran)
+                w = torch.empty((slots, A), dtype=torch.float32, device=seg.device) if w is None else w
+                nr = torch.empty((slots,), dtype=torch.int32, device=seg.device) if nr is None else nr
+            so = torch.empty((A,), dtype=torch.int32, device=seg.device) if so is None else so
+        outs.append((w, nr, so))
+    if workspace is None:
+        need = kvcomm_anchor_weights_batch_workspace(model, [jd["seg_base_k"].shape[2] for jd in jobs],
+                                                     [len(jd["anchor_base_k"]) for jd in jobs], gran, rule)
+        workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=jobs[0]["seg_base_k"].device)
+    if _done(_native.anchor_weights_batch(model, gran, rule, temperature, jobs, outs, workspace, stream)):
+        return outs
     cjobs = (_CWeightsJob * max(n, 1))()
-    keep, outs, layout = [], [], None
-    for j, jd in enumerate(jobs):
+    keep, layout = [], None
+    for j, (jd, (w, nr, so)) in enumerate(zip(jobs, outs)):
         seg = jd["seg_base_k"]
-        S, A, dev = seg.shape[2], len(jd["anchor_base_k"]), seg.device
-        w, nr = jd.get("weights_out"), jd.get("nearest_out")
-        if w is None or nr is None:
-            slots = kvcomm_weight_slots(model, S, gran)
-            w = torch.empty((slots, A), dtype=torch.float32, device=dev) if w is None else w
-            nr = torch.empty((slots,), dtype=torch.int32, device=dev) if nr is None else nr
-        so = jd.get("selected_out")
-        so = torch.empty((A,), dtype=torch.int32, device=dev) if so is None else so
+        S, A = seg.shape[2], len(jd["anchor_base_k"])
         ptrs, lay, lens = _anchor_args(jd["anchor_base_k"], jd.get("anchor_len"), model.dtype, "anchor_base_k")
         if layout is None:
             layout = lay
@@ -515,11 +567,6 @@ def kvcomm_anchor_weights_batch(model, jobs, temperature=1.0, gran=W_TOKEN, rule
         keep.append((ptrs, lens))
         cjobs[j] = _CWeightsJob(_desc(seg, model.dtype, "seg_base_k"), S, ptrs, lens, A, w.data_ptr(), nr.data_ptr(),
                                 so.data_ptr())
-        outs.append((w, nr, so))
-    if workspace is None:
-        need = kvcomm_anchor_weights_batch_workspace(model, [jd["seg_base_k"].shape[2] for jd in jobs],
-                                                     [len(jd["anchor_base_k"]) for jd in jobs], gran, rule)
-        workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=jobs[0]["seg_base_k"].device)
     _check(lib.kvcomm_anchor_weights_batch(ctypes.byref(model.c()), gran, int(rule), float(temperature),
                                            layout if layout is not None else _CTensor(None, 0, 0, 0), cjobs, n,
                                            workspace.data_ptr(), workspace.numel() * workspace.element_size(),
@@ -533,6 +580,8 @@ def kvcomm_align_kv_batch(model, jobs, gran=W_TOKEN, stream=None):
     jobs: list of dicts with base_k, base_v, anchor_dk, anchor_dv (lists of tensors), weights, delta_pos,
     out_k, out_v and optionally anchor_len, anchor_delta_pos."""
     lib = load_library()
+    if _done(_native.align_kv_batch(model, gran, jobs, stream)):
+        return
     n = len(jobs)
     cjobs = (_CAlignJob * max(n, 1))()
     keep, layout = [], None
@@ -594,6 +643,8 @@ def kvcomm_quantize_deltas(model, x, scale, out=None, stream=None):
     lib = load_library()
     if out is None:
         out = torch.empty(x.shape, dtype=torch.uint8, device=x.device)
+    if _done(_native.quantize_deltas(model, x, scale, out, stream)):
+        return out
     _check(lib.kvcomm_quantize_deltas(ctypes.byref(model.c()), _desc(x, model.dtype, "x"), x.shape[2], float(scale),
                                       _desc_q8(out, "out"), _stream_ptr(stream)))
     return out
@@ -603,6 +654,9 @@ def kvcomm_align_kv_q8(model, base_k, base_v, anchor_dk8, anchor_dv8, scale_k, s
                        out_v, anchor_len=None, anchor_delta_pos=None, gran=W_TOKEN, stream=None):
     """kvcomm_align_kv with E4M3-compressed deviations (uint8 tensors) and their per-anchor scales."""
     lib = load_library()
+    if _done(_native.align_kv_q8(model, gran, base_k, base_v, anchor_dk8, anchor_dv8, scale_k, scale_v, weights, delta_pos, out_k,
+                                 out_v, anchor_len, anchor_delta_pos, stream)):
+        return out_k, out_v
     seg_len = base_k.shape[2]
     A = len(anchor_dk8)
     if len(anchor_dv8) != A or len(scale_k) != A or len(scale_v) != A:
@@ -636,6 +690,8 @@ def kvcomm_align_kv_q8_batch(model, jobs, gran=W_TOKEN, stream=None):
     jobs: list of dicts with base_k, base_v, anchor_dk8, anchor_dv8 (lists of uint8 tensors), scale_k, scale_v
     (lists of floats), weights, delta_pos, out_k, out_v and optionally anchor_len, anchor_delta_pos."""
     lib = load_library()
+    if _done(_native.align_kv_q8_batch(model, gran, jobs, stream)):
+        return
     n = len(jobs)
     cjobs = (_CAlignQ8Job * max(n, 1))()
     keep, layout = [], None

@@ -1,5 +1,5 @@
-"""Build libkvcomm.so (the C-ABI library of include/kvcomm.h) for gfx950 with hipcc, and the stand-alone
-HBM streaming probe that bench.py --hbm-calibration runs.
+"""Build libkvcomm.so (the C-ABI library of include/kvcomm.h) for gfx950 with hipcc, the binding's native
+marshalling module, and the stand-alone HBM streaming probe that bench.py --hbm-calibration runs.
 
 hipcc cross-compiles without a GPU, so this runs anywhere the ROCm toolchain is installed.
 The library is written next to this file; tests, the smoke check and the benchmark load
@@ -8,11 +8,14 @@ that file and never compile anything themselves.
 import os
 import shutil
 import subprocess
+import sysconfig
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libkvcomm.so")
+MARSHAL_SRC = os.path.join(CSRC, "marshal.cpp")
+MARSHAL = os.path.join(_HERE, "_marshal.so")
 PROBE_SRC = os.path.join(_HERE, "tools", "hbm_stream_probe.hip")
 PROBE = os.path.join(_HERE, "tools", "hbm_stream_probe")
 SOURCES = ["align_kv.hip", "anchor_weights.hip", "anchor_update.hip", "delta_q8.hip", "suffix_attn.hip",
@@ -45,7 +48,22 @@ def build(verbose=False, extra_flags=()):
     if verbose:
         print(" ".join(probe))
     subprocess.run(probe, check=True)
+    build_marshal(verbose)
     return LIB
+
+
+def build_marshal(verbose=False):
+    """Compile the native marshalling module (host code only) against the installed torch."""
+    import torch
+    top = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(top, "include"),
+           "-isystem", os.path.join(top, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-o", MARSHAL, MARSHAL_SRC,
+           "-L", os.path.join(top, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.run(cmd, check=True)
 
 
 if __name__ == "__main__":

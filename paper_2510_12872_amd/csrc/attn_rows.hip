@@ -22,7 +22,7 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 // 6.4 TB/s): K and V of a sub-step go global -> LDS into the wavefront's own buffers (no block barrier in the loop),
 // K of the next sub-step is requested as soon as its operands are in registers and V likewise, so a wavefront
 // always has 8 ... 16 KB in flight (D = 128).  Eight wavefronts measured 10 % better than two blocks of four.
-template <int D, bool NT>
+template <int D, bool NT, bool PERSIST>
 __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_rows_kernel(const AttnParams p)
 {
     constexpr int NW = rows_waves(D);
@@ -33,9 +33,9 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
     constexpr int VSWZ = KCH - 1;
     constexpr int KD = (KSWZ + 1) / RPL > 1 ? (KSWZ + 1) / RPL : 1;  // loads after which the swizzle pattern of the rows repeats
     constexpr int VD = 4 / RPL > 1 ? 4 / RPL : 1;
-    constexpr int CDB = NDB < 4 ? NDB : 4;           // 32-channel blocks joined per round
-    constexpr int BUFB = NW * 2 * HALFB, JOINB = NW * CDB * 32 * 32 * 4;
-    __shared__ __align__(16) unsigned char smem[BUFB > JOINB ? BUFB : JOINB];
+    constexpr int JW = 2 * HALFB / 16;               // 16-byte slots of a wavefront's buffers: all its outputs at the end
+    static_assert(NDB * 256 == JW, "a wavefront's outputs fill its own buffers");
+    __shared__ __align__(16) unsigned char smem[NW * 2 * HALFB];
     __shared__ float ml[2][NW][32];
 
     const int tid = threadIdx.x;
@@ -47,8 +47,10 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
     const int x_id = blockIdx.x & 7;
     const int x_first = x_id * (p.n_items >> 3) + min(x_id, p.n_items & 7);
     const int x_count = (p.n_items >> 3) + (x_id < (p.n_items & 7) ? 1 : 0);
-    const int x_blocks = ((int)gridDim.x - x_id + 7) >> 3;
-    for (int item = blockIdx.x >> 3; item < x_count; item += x_blocks) {
+    const int x_blocks = PERSIST ? ((int)gridDim.x - x_id + 7) >> 3 : x_count;
+    int item = blockIdx.x >> 3;
+    if (PERSIST && item >= x_count) return;   // the whole block: more blocks than items on this XCD
+    do {
         const int logical = x_first + item;
         const int run = div_by(logical, p.by_row_tiles);
         const int rt = logical - run * p.n_row_tiles;   // the row tiles of a key run are neighbours: they share its L2 lines
@@ -61,7 +63,8 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
         const int hq = hkv * p.G + r_row - i_row * p.G;
         const int imax = min(p.tq - 1, div_by(rt * 32 + 31, p.by_G)), imin = min(p.tq - 1, div_by(rt * 32, p.by_G));
         const int units = (p.n_ctx + imax + 32) / 32;   // sub-steps that some query of the tile sees
-        const int u0 = split_bound(split, p.n_splits, units, units), u1 = split_bound(split + 1, p.n_splits, units, units);
+        // split_bound() without a causal edge: s * units / n_splits (<= 2^30: see there)
+        const int u0 = div_by(split * units, p.by_splits), u1 = div_by((split + 1) * units, p.by_splits);
 
         const unsigned char *kbytes = reinterpret_cast<const unsigned char *>(static_cast<const bf16_t *>(p.k) + l * p.s_k.layer + hkv * p.s_k.head);
         const unsigned char *vbytes = reinterpret_cast<const unsigned char *>(static_cast<const bf16_t *>(p.v) + l * p.s_v.layer + hkv * p.s_v.head);
@@ -197,8 +200,9 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
             for (int i = 0; i < 2 * NDB; ++i) o[i % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i], pf[i / NDB], o[i % NDB], 0, 0, 0);
         }
 
-        // ---- join the wavefronts' states: factors against the common maximum, then sums over the wavefronts of 128
-        // channels at a time; a thread owns whole slots (its own n and hg).
+        // ---- join the wavefronts' states: outputs as they are go over the wavefront's own K / V buffers (no other wavefront
+        // reads those), so one barrier does; a thread then owns whole slots (its own n and hg) and sums them over
+        // the wavefronts with their factors against the common maximum.
         {
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum), false, false);
             lsum = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
@@ -207,44 +211,39 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
             ml[0][wave][n] = m;
             ml[1][wave][n] = lsum;
         }
-        __syncthreads();   // also: every wavefront is done with its K / V buffers
+        f32x4 *join = reinterpret_cast<f32x4 *>(smem);
+        if (valid) {
+#pragma unroll
+            for (int d = 0; d < NDB; ++d)
+#pragma unroll
+                for (int j4 = 0; j4 < 4; ++j4)
+                    join[wave * JW + part_slot(8 * d + 2 * j4 + hg, n)] = f32x4{o[d][4 * j4], o[d][4 * j4 + 1], o[d][4 * j4 + 2], o[d][4 * j4 + 3]};
+        }
+        __syncthreads();
         float M = ml[0][0][n];
 #pragma unroll
         for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[0][w][n]);
-        float ltot = 0.f;
+        float f[NW], ltot = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const float mw = ml[0][w][n];
-            // reference -inf: no key seen and sum 0, or nothing but NaN scores and a sum that says so
-            ltot += mw == -INFINITY ? ml[1][w][n] : ml[1][w][n] * __builtin_amdgcn_exp2f((mw - M) * p.scale_log2);
+            const float mw = ml[0][w][n], lw = ml[1][w][n];
+            f[w] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mw - M) * p.scale_log2);
+            ltot += mw == -INFINITY ? lw : lw * f[w];   // reference -inf: no key seen and sum 0, or nothing but NaN scores and a sum that says so
         }
-        const float f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - M) * p.scale_log2);
-        f32x4 *join = reinterpret_cast<f32x4 *>(smem);
         const int64_t part = (int64_t)(lh * p.n_row_tiles + rt) * p.n_splits + split;
-        const float inv = 1.f / ltot;
+        if (valid) {
+            const float inv = 1.f / ltot;
 #pragma unroll
-        for (int c0 = 0; c0 < NDB; c0 += CDB) {
-            if (c0) __syncthreads();
+            for (int i = 0; i < NDB * 256; i += 64 * NW) {
+                f32x4 a = join[i + tid] * f[0];
 #pragma unroll
-            for (int d = 0; d < CDB; ++d)
-#pragma unroll
-                for (int j4 = 0; j4 < 4; ++j4)
-                    join[wave * (CDB * 256) + part_slot(8 * d + 2 * j4 + hg, n)] =
-                        f32x4{o[c0 + d][4 * j4], o[c0 + d][4 * j4 + 1], o[c0 + d][4 * j4 + 2], o[c0 + d][4 * j4 + 3]} * f;
-            __syncthreads();
-            if (valid) {
-#pragma unroll
-                for (int i = 0; i < CDB * 256; i += 64 * NW) {
-                    f32x4 a = join[i + tid];
-#pragma unroll
-                    for (int w = 1; w < NW; ++w) a += join[w * (CDB * 256) + i + tid];
-                    if (p.n_splits > 1) {
-                        reinterpret_cast<f32x4 *>(p.part_o + part * (32 * D))[c0 * 256 + i + tid] = a;
-                    } else {
-                        bf16_t *orow = static_cast<bf16_t *>(p.out) + l * p.s_o.layer + (int64_t)hq * p.s_o.head + (int64_t)qi * p.s_o.token;
-                        const u32x2 w2 = {pack_bf16x2(a[0] * inv, a[1] * inv), pack_bf16x2(a[2] * inv, a[3] * inv)};
-                        *reinterpret_cast<u32x2 *>(orow + 32 * c0 + (i / 64 + wave) / 4 * 32 + 8 * (wave & 3) + 4 * hg) = w2;
-                    }
+                for (int w = 1; w < NW; ++w) a += join[w * JW + i + tid] * f[w];
+                if (p.n_splits > 1) {
+                    reinterpret_cast<f32x4 *>(p.part_o + part * (32 * D))[i + tid] = a;
+                } else {
+                    bf16_t *orow = static_cast<bf16_t *>(p.out) + l * p.s_o.layer + (int64_t)hq * p.s_o.head + (int64_t)qi * p.s_o.token;
+                    const u32x2 w2 = {pack_bf16x2(a[0] * inv, a[1] * inv), pack_bf16x2(a[2] * inv, a[3] * inv)};
+                    *reinterpret_cast<u32x2 *>(orow + i / 8 + 8 * wave + 4 * hg) = w2;
                 }
             }
         }
@@ -256,24 +255,28 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
                 p.lse[((int64_t)l * p.Hkv * p.G + hq) * p.tq + qi] = M * p.scale + logf(ltot);
             }
         }
+        if (!PERSIST) break;
         __syncthreads();   // the joined states have been read: LDS becomes the next item's buffers
-    }
+        item += x_blocks;
+    } while (item < x_count);
 }
 
 // attn_combine_kernel: one block per (32-row group, 32 channels).  out = sum_s f_s O_s / sum_s f_s l_s with
-// f_s = exp2((m_s - max m) * scale * log2 e), splits in increasing order.  Every load of a run of 8 splits is in
+// f_s = exp2((m_s - max m) * scale * log2 e), splits in increasing order.  All loads of the U >= n_splits partial results are in
 // flight at once (the launch is a few microseconds of latency); rows leave as 64-byte pieces through LDS.
-template <int D>
+template <int D, int U>
 __global__ __launch_bounds__(256) void attn_combine_kernel(const AttnParams p)
 {
-    constexpr int U = 8;
     __shared__ __align__(16) u32x2 stage[32][9];   // 8 pieces of 4 channels a row (+1: bank spread)
     const int tid = threadIdx.x;
     const int n = tid & 31, hg = (tid >> 5) & 1, j4 = tid >> 6;
-    const int db = blockIdx.y;
-    const int group = blockIdx.x;
-    const int tile = div_by(group, p.by_groups), w = group - tile * p.groups_per_tile;
-    const int lh = div_by(tile, p.by_row_tiles), rt = tile - lh * p.n_row_tiles;
+    // XCD x takes one contiguous range of the (row tile, group, channels) triples, in the order of attn_mfma_kernel's items
+    const int x_id = blockIdx.x & 7, n_blocks = gridDim.x;
+    const int logical = x_id * (n_blocks >> 3) + min(x_id, n_blocks & 7) + (blockIdx.x >> 3);
+    const int db = logical % (D / 32), item = logical / (D / 32);
+    const int row_tile = div_by(item, p.by_groups), w = item - row_tile * p.groups_per_tile;
+    const int lh = div_by(row_tile, p.by_row_tiles), rt = p.n_row_tiles - 1 - (row_tile - lh * p.n_row_tiles);
+    const int group = (lh * p.n_row_tiles + rt) * p.groups_per_tile + w;
     const int l = div_by(lh, p.by_Hkv), hkv = lh - l * p.Hkv;
     const int bm = 32 * p.groups_per_tile;
     auto row_of = [&](int nn, bool &ok, int64_t &q_i, int64_t &h_q) {
@@ -290,39 +293,30 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const AttnParams p)
         const int64_t part0 = (int64_t)group * p.n_splits;
         const f32x4 *po = reinterpret_cast<const f32x4 *>(p.part_o) + part0 * (8 * D) + db * 256 + tid;
         const float *pm = p.part_ml + part0 * 64 + n;
-        float M = -INFINITY, L = 0.f;
+        float ms[U], ls[U];
+        f32x4 os[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int s = min(i, p.n_splits - 1);
+            ms[i] = pm[s * 64];
+            ls[i] = pm[s * 64 + 32];
+            os[i] = po[(int64_t)s * (8 * D)];   // not used, and possibly never written, where m_s is -inf and the sum 0
+        }
+#pragma unroll
+        for (int i = 1; i < U; ++i) {
+            ms[i] = i < p.n_splits ? ms[i] : -INFINITY;
+            ls[i] = i < p.n_splits ? ls[i] : 0.f;
+        }
+        float M = ms[0], L = 0.f;
+#pragma unroll
+        for (int i = 1; i < U; ++i) M = fmaxf(M, ms[i]);
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int s0 = 0; s0 < p.n_splits; s0 += U) {
-            float ms[U], ls[U];
-            f32x4 os[U];
 #pragma unroll
-            for (int i = 0; i < U; ++i) {
-                const int s = min(s0 + i, p.n_splits - 1);
-                ms[i] = pm[s * 64];
-                ls[i] = pm[s * 64 + 32];
-                os[i] = po[(int64_t)s * (8 * D)];   // not used, and possibly never written, where m_s is -inf and the sum 0
-            }
-#pragma unroll
-            for (int i = 1; i < U; ++i) {
-                ms[i] = s0 + i < p.n_splits ? ms[i] : -INFINITY;
-                ls[i] = s0 + i < p.n_splits ? ls[i] : 0.f;
-            }
-            float mx = M;
-#pragma unroll
-            for (int i = 0; i < U; ++i) mx = fmaxf(mx, ms[i]);
-            if (mx > M) {
-                const float corr = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((M - mx) * p.scale_log2);
-                L *= corr;
-                acc *= corr;
-                M = mx;
-            }
-#pragma unroll
-            for (int i = 0; i < U; ++i) {
-                if (ms[i] != -INFINITY || ls[i] != 0.f) {   // a run of NaN scores has reference -inf and sum NaN
-                    const float f = __builtin_amdgcn_exp2f((ms[i] - M) * p.scale_log2);
-                    L = fmaf(f, ls[i], L);
-                    acc += f * os[i];
-                }
+        for (int i = 0; i < U; ++i) {
+            if (ms[i] != -INFINITY || ls[i] != 0.f) {   // a run of NaN scores has reference -inf and sum NaN
+                const float f = __builtin_amdgcn_exp2f((ms[i] - M) * p.scale_log2);
+                L = fmaf(f, ls[i], L);
+                acc += f * os[i];
             }
         }
         const float inv = 1.f / L;
@@ -341,6 +335,24 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const AttnParams p)
     }
 }
 
+template <int D>
+int launch_combine(const AttnParams &p, hipStream_t stream)
+{
+    static_assert(kRowsMaxSplits <= 16 && kTileMaxSplits <= 16, "attn_combine_kernel takes all partial results of a row at once");
+    const dim3 grid((unsigned)(p.L * p.Hkv * p.n_row_tiles * p.groups_per_tile * (D / 32))), block(256);
+    return launch(p.n_splits <= 4 ? attn_combine_kernel<D, 4> : p.n_splits <= 8 ? attn_combine_kernel<D, 8> : attn_combine_kernel<D, 16>, grid, block, 0,
+                  stream, p);
+}
+
+template <int D>
+int launch_rows(const AttnParams &p, bool nt, bool persist, unsigned n_blocks, hipStream_t stream)
+{
+    const dim3 grid(n_blocks), block(64 * rows_waves(D));
+    if (persist)
+        return launch(nt ? attn_rows_kernel<D, true, true> : attn_rows_kernel<D, false, true>, grid, block, 0, stream, p);
+    return launch(nt ? attn_rows_kernel<D, true, false> : attn_rows_kernel<D, false, false>, grid, block, 0, stream, p);
+}
+
 }  // namespace
 
 namespace kvc {
@@ -350,22 +362,21 @@ int launch_attn_rows(const AttnParams &p, int D, unsigned n_blocks, hipStream_t 
     // Non-temporal K / V only where they cannot stay in the last-level cache and no other block reads them: 32 layers
     // of 3100 keys (407 MB) take 64 us with it and 72 us without, 4 layers (51 MB, read again for the next token) 33 and 26.
     const bool nt = p.n_row_tiles == 1 && (int64_t)p.L * p.Hkv * p.N * D * 4 > kLastLevelCache;
-    const dim3 grid(n_blocks), block(64 * rows_waves(D));
+    const bool persist = n_blocks < (unsigned)p.n_items;
     switch (D) {
-        case 64: return launch(nt ? attn_rows_kernel<64, true> : attn_rows_kernel<64, false>, grid, block, 0, stream, p);
-        case 128: return launch(nt ? attn_rows_kernel<128, true> : attn_rows_kernel<128, false>, grid, block, 0, stream, p);
-        case 256: return launch(nt ? attn_rows_kernel<256, true> : attn_rows_kernel<256, false>, grid, block, 0, stream, p);
+        case 64: return launch_rows<64>(p, nt, persist, n_blocks, stream);
+        case 128: return launch_rows<128>(p, nt, persist, n_blocks, stream);
+        case 256: return launch_rows<256>(p, nt, persist, n_blocks, stream);
         default: return KVCOMM_EUNSUPPORTED;
     }
 }
 
 int launch_attn_combine(const AttnParams &p, int D, hipStream_t stream)
 {
-    const dim3 grid((unsigned)(p.L * p.Hkv * p.n_row_tiles * p.groups_per_tile), (unsigned)(D / 32)), block(256);
     switch (D) {
-        case 64: return launch(attn_combine_kernel<64>, grid, block, 0, stream, p);
-        case 128: return launch(attn_combine_kernel<128>, grid, block, 0, stream, p);
-        case 256: return launch(attn_combine_kernel<256>, grid, block, 0, stream, p);
+        case 64: return launch_combine<64>(p, stream);
+        case 128: return launch_combine<128>(p, stream);
+        case 256: return launch_combine<256>(p, stream);
         default: return KVCOMM_EUNSUPPORTED;
     }
 }

@@ -12,25 +12,18 @@
 // the rotation needs no cross-lane traffic and the kernel may run in place.  A block of
 // 256 threads owns a tile of 256/LPR consecutive tokens of one (layer, head) and of ONE of
 // the two tensors (blockIdx.y: 0 = keys, 1 = values): the two streams are independent, and
-// splitting them halves the registers per lane so that many wavefronts per CU keep loads in
-// flight.  Every access to a tensor is a run of whole 128-byte lines; deviations and outputs are marked
+// splitting them halves the registers per lane.  Every access to a tensor is a run of whole 128-byte lines; deviations and outputs are marked
 // non-temporal (they are not read again soon: 466 us per launch of 4 x 512 tokens with 8 anchors, 500 us with plain
 // stores).  The base rows are plain loads: anchor matching has just read the base keys, and a shared segment's base
 // cache serves the next agent as well (matching and update of a placeholder of 512 and a prefix segment of 173 tokens,
 // 8 anchors: 205 us, 212 us with non-temporal loads; no difference where nothing is in the last-level cache).  Per-token anchor weights and the cos/sin tables load once per block (LDS).
 // cos/sin: the angle delta * theta^(-2i/D) is formed and reduced modulo 2*pi in double from a
 // host-computed frequency table (kernel argument); sine and cosine of the reduced angle are fp32.
-#include <type_traits>
-
 #include "align_common.h"
 
 namespace {
 
 using namespace kvc;
-
-#ifndef KVC_ALIGN_BLOCKS
-#define KVC_ALIGN_BLOCKS 32768  // blocks per tensor the grid aims at (measured best on MI355X)
-#endif
 
 constexpr int kBlock = kAlignBlock;
 
@@ -39,8 +32,10 @@ struct AlignParams {
     Strides s_anc;
     int32_t H, LH;             // kv heads, layers*heads
     int32_t gran, n_jobs;
-    int32_t lh_per_block;
+    int32_t lh_per_block;      // 1
     int32_t tiles_total;       // token tiles of all segments
+    divisor_t by_tiles, by_H, by_pitch[KVCOMM_MAX_BATCH];
+    uint64_t sel_mask[KVCOMM_MAX_BATCH];        // bit a = anchor a of the segment is selected
     int32_t tab_delta[kMaxTab];                 // position delta of each rotation table
     const void *anc[2][KVCOMM_MAX_ANCHORS];     // [0] dK, [1] dV of the selected anchors of all segments
     alignas(4) uint8_t col[KVCOMM_MAX_ANCHORS];            // weight column of a selected anchor
@@ -49,32 +44,28 @@ struct AlignParams {
 };
 static_assert(sizeof(AlignParams) <= 4096, "kernel arguments are limited to 4 KB");
 
-// INFLIGHT: anchors whose rows are requested together (twice as many 16-byte loads per lane); WPE: wavefronts per SIMD the
-// register budget is sized for.  us per launch of 512-token segments in no cache (L * H = 256 at D = 128 and 64 in bf16, the same
-// bytes elsewhere), (2, 4) against (4, 3), four_in_flight() draws the line:
-//   bf16 D 128   pools of 4: 66 / 71, 7: 99 / 100, 8: 113 / 111, 12: 161 / 156, 40: 483 / 473, four of 8: 467 / 441,
-//                8 and 2: 156 / 168, 7, 4 and 4: 238 / 245;   D 256  8: 113 / 112, four of 8: 472 / 439, 8 and 2: 143 / 146
-//   bf16 D 64    pools of 4: 39 / 43, 8: 64 / 68, 16: 117 / 122, 40: 268 / 273, four of 8: 248 / 263
-//   f32 D 128    pools of 4: 65 / 66, 8: 110 / 111, 16: 208 / 206, 40: 488 / 482, 8 and 2: 152 / 149, 7, 4 and 4: 255 / 248
-// (A vector load of the rotation-table index, whose wait drained every row in flight, used to hold the keys' blocks back: four
-// of 8 took 482 us then.)
-template <typename T, int LPR, int INFLIGHT, int WPE>
-__global__ __launch_bounds__(kBlock, WPE) void align_kernel(const AlignParams p)
+// Two anchors' rows (four 16-byte loads per lane) are requested together, the first two under the block's set-up.  What bounds the kernel is
+// HBM, and past about 64 KB in flight per compute unit more requests cost: pages are opened and closed out of order.  So the
+// launch reserves LDS that keeps the number of blocks per compute unit at what measured best (lds_reserve()).
+template <typename T, int LPR>
+__global__ __launch_bounds__(kBlock, 4) void align_kernel(const AlignParams p)
 {
+    constexpr int INFLIGHT = 2;
     constexpr int EPV = Elem<T>::EPV;
     constexpr int HALF = LPR * EPV;  // D / 2
     constexpr int RPB = kBlock / LPR;
 
     // Block order: (layer, head) chunk, then segment, then token tile, so that the blocks in flight
     // write neighbouring slices of the same cache rows when the segments of a launch are adjacent.
-    const int chunk = blockIdx.x / p.tiles_total;
-    const int r = blockIdx.x % p.tiles_total;
-    const AlignJob &jb = p.job[job_of_tile(p, r)];
+    const int lh = div_by(blockIdx.x, p.by_tiles);
+    const int r = blockIdx.x - lh * p.tiles_total;
+    const int ji = job_of_tile(p, r);
+    const AlignJob &jb = p.job[ji];
     const int n_sel = jb.n_sel, a0 = jb.a0;
 
     extern __shared__ __align__(16) unsigned char smem_raw[];
     float2 *cs = reinterpret_cast<float2 *>(smem_raw);                          // [n_tab][HALF] (cos, sin)
-    float *w_lds = reinterpret_cast<float *>(smem_raw) + 2 * jb.n_tab * HALF;   // [RPB][n_sel]
+    float *w_lds = reinterpret_cast<float *>(smem_raw) + 2 * jb.n_tab * HALF;   // [RPB or 1][n_sel]
 
     const int tid = threadIdx.x;
     const int row = tid / LPR;
@@ -84,8 +75,42 @@ __global__ __launch_bounds__(kBlock, WPE) void align_kernel(const AlignParams p)
     const bool is_k = which == 0;
     const int t = tile * RPB + row;
     const bool valid = t < jb.S;
-    const int lh0 = chunk * p.lh_per_block;
-    const int lh1 = min(lh0 + p.lh_per_block, p.LH);
+    const T *bp = static_cast<const T *>(jb.base[which]);
+    T *op = static_cast<T *>(jb.out[which]);
+    const Strides sb = jb.s_base[which], so = jb.s_out[which];
+    const int64_t col0 = (int64_t)lir * EPV;
+
+    // What the block's set-up reads, its weight rows (as they are, unselected anchors included), is requested first, then the rows of
+    // its first (layer, head) pair: they arrive under the rotation tables and the barrier.
+    const uint64_t sel = p.sel_mask[ji];
+    const int n_w = sel == 0 ? 0 : (p.gran == KVCOMM_W_SEGMENT ? 1 : min(RPB, jb.S - tile * RPB)) * jb.w_pitch;
+    const float *wsrc = jb.weights;
+    if (p.gran != KVCOMM_W_SEGMENT)
+        wsrc += ((int64_t)(p.gran == KVCOMM_W_LAYER_HEAD_TOKEN ? lh : 0) * jb.S + tile * RPB) * jb.w_pitch;
+    float w_first = 0.f;
+    if (tid < n_w) w_first = wsrc[tid];
+    auto keep_weight = [&](int idx, float w) __attribute__((always_inline)) {
+        const int r = div_by(idx, p.by_pitch[ji]), c = idx - r * jb.w_pitch;
+        if ((sel >> c) & 1) w_lds[r * n_sel + __popcll(sel & (((uint64_t)1 << c) - 1))] = w;
+    };
+
+    const int l = div_by(lh, p.by_H), h = lh - l * p.H;
+    const T *xp = bp + l * sb.layer + h * sb.head + t * sb.token + col0;
+    const int64_t aoff = l * p.s_anc.layer + h * p.s_anc.head + t * p.s_anc.token + col0;
+    u32x4 rlo, rhi, rows[INFLIGHT][2];
+    auto request_group = [&](int a) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < INFLIGHT; ++u) {
+            const T *d = static_cast<const T *>(p.anc[which][a0 + a + u]) + aoff;
+            rows[u][0] = load16_stream(d);
+            rows[u][1] = load16_stream(d + HALF);
+        }
+    };
+    if (valid) {
+        rlo = load16(xp);   // plain: see the header
+        rhi = load16(xp + HALF);
+        if (n_sel >= INFLIGHT) request_group(0);
+    }
 
     if (is_k) {
         // cos/sin of delta * theta^(-2i/D): product and reduction modulo 2*pi in double.
@@ -94,14 +119,8 @@ __global__ __launch_bounds__(kBlock, WPE) void align_kernel(const AlignParams p)
             cs[idx] = rope_cos_sin(p.tab_delta[jb.t0 + r], p.inv_freq[i]);
         }
     }
-    if (p.gran != KVCOMM_W_LAYER_HEAD_TOKEN) {
-        for (int idx = tid; idx < RPB * n_sel; idx += kBlock) {
-            const int r = idx / n_sel, a = idx % n_sel;
-            const int tt = tile * RPB + r;
-            const int64_t slot = p.gran == KVCOMM_W_TOKEN ? tt : 0;
-            w_lds[idx] = tt < jb.S ? jb.weights[slot * jb.w_pitch + p.col[a0 + a]] : 0.f;
-        }
-    }
+    if (tid < n_w) keep_weight(tid, w_first);
+    for (int idx = tid + kBlock; idx < n_w; idx += kBlock) keep_weight(idx, wsrc[idx]);
     __syncthreads();
     if (!valid) return;
 
@@ -116,87 +135,79 @@ __global__ __launch_bounds__(kBlock, WPE) void align_kernel(const AlignParams p)
         }
     }
 
-    const T *bp = static_cast<const T *>(jb.base[which]);
-    T *op = static_cast<T *>(jb.out[which]);
-    const Strides sb = jb.s_base[which], so = jb.s_out[which];
-    const int64_t col0 = (int64_t)lir * EPV;
+    const float *wrow = w_lds + (p.gran == KVCOMM_W_SEGMENT ? 0 : row * n_sel);
 
-    for (int lh = lh0; lh < lh1; ++lh) {
-        const int l = lh / p.H, h = lh % p.H;
-        const T *xp = bp + l * sb.layer + h * sb.head + t * sb.token + col0;
-        const u32x4 rlo = load16(xp), rhi = load16(xp + HALF);   // plain: see the header
-        const int64_t aoff = l * p.s_anc.layer + h * p.s_anc.head + t * p.s_anc.token + col0;
-        const float *wrow = p.gran == KVCOMM_W_LAYER_HEAD_TOKEN
-                                ? jb.weights + ((int64_t)lh * jb.S + t) * jb.w_pitch
-                                : nullptr;
+    float lo[EPV], hi[EPV];
+    unpack<T>(rlo, lo);
+    unpack<T>(rhi, hi);
+    if (rot_base) {
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) {
+            const float a = lo[e], b = hi[e];
+            lo[e] = a * bc[e] - b * bs[e];
+            hi[e] = b * bc[e] + a * bs[e];
+        }
+    }
 
-        float lo[EPV], hi[EPV];
-        unpack<T>(rlo, lo);
-        unpack<T>(rhi, hi);
-        if (rot_base) {
+    auto accumulate = [&](int a, const u32x4 &rdlo, const u32x4 &rdhi) {
+        const float w = wrow[a];
+        float dlo[EPV], dhi[EPV];
+        unpack<T>(rdlo, dlo);
+        unpack<T>(rdhi, dhi);
+        const int tb = is_k ? arg_byte(p.tab, a0 + a) : 0;
+        if (tb) {
+            const float2 *tcs = cs + (tb - 1) * HALF + lir * EPV;
 #pragma unroll
             for (int e = 0; e < EPV; ++e) {
-                const float a = lo[e], b = hi[e];
-                lo[e] = a * bc[e] - b * bs[e];
-                hi[e] = b * bc[e] + a * bs[e];
+                const float2 v = tcs[e];
+                const float x = dlo[e], y = dhi[e];
+                dlo[e] = x * v.x - y * v.y;
+                dhi[e] = y * v.x + x * v.y;
             }
         }
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) {
+            lo[e] += w * dlo[e];
+            hi[e] += w * dhi[e];
+        }
+    };
 
-        auto accumulate = [&](int a, const u32x4 &rdlo, const u32x4 &rdhi) {
-            const float w = wrow ? wrow[arg_byte(p.col, a0 + a)] : w_lds[row * n_sel + a];
-            float dlo[EPV], dhi[EPV];
-            unpack<T>(rdlo, dlo);
-            unpack<T>(rdhi, dhi);
-            const int tb = is_k ? arg_byte(p.tab, a0 + a) : 0;
-            if (tb) {
-                const float2 *tcs = cs + (tb - 1) * HALF + lir * EPV;
+    int a = 0;
+    while (a + INFLIGHT <= n_sel) {
 #pragma unroll
-                for (int e = 0; e < EPV; ++e) {
-                    const float2 v = tcs[e];
-                    const float x = dlo[e], y = dhi[e];
-                    dlo[e] = x * v.x - y * v.y;
-                    dhi[e] = y * v.x + x * v.y;
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) {
-                lo[e] += w * dlo[e];
-                hi[e] += w * dhi[e];
-            }
-        };
-
-        int a = 0;
-        auto group = [&](auto count) __attribute__((always_inline)) {
-            constexpr int U = decltype(count)::value;
-            u32x4 x[U][2];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const T *d = static_cast<const T *>(p.anc[which][a0 + a + u]) + aoff;
-                x[u][0] = load16_stream(d);
-                x[u][1] = load16_stream(d + HALF);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) accumulate(a + u, x[u][0], x[u][1]);
-            a += U;
-        };
-        while (a + INFLIGHT <= n_sel) group(std::integral_constant<int, INFLIGHT>{});
-        if (INFLIGHT > 2 && a + 2 <= n_sel) group(std::integral_constant<int, 2>{});
-        while (a < n_sel) group(std::integral_constant<int, 1>{});
-
-        T *yp = op + l * so.layer + h * so.head + t * so.token + col0;
-        store16_stream(yp, pack<T>(lo));
-        store16_stream(yp + HALF, pack<T>(hi));
+        for (int u = 0; u < INFLIGHT; ++u) accumulate(a + u, rows[u][0], rows[u][1]);
+        a += INFLIGHT;
+        if (a + INFLIGHT <= n_sel) request_group(a);
     }
+    if (a < n_sel) {
+        const T *d = static_cast<const T *>(p.anc[which][a0 + a]) + aoff;
+        accumulate(a, load16_stream(d), load16_stream(d + HALF));
+    }
+
+    T *yp = op + l * so.layer + h * so.head + t * so.token + col0;
+    store16_stream(yp, pack<T>(lo));
+    store16_stream(yp + HALF, pack<T>(hi));
 }
 
-// Four anchors in flight: f32 with seven anchors or more in some segment, bf16 rows of 128 channels and more with eight or more
-// in every segment (see align_kernel).
-bool four_in_flight(const AlignParams &p, bool f32, int head_dim, int max_sel)
+// LDS that a launch asks for beyond its tables, so that two or three blocks share a compute unit instead of the five that the
+// registers allow (160 KB: three do not fit at 54 KB, four not at 40.5).  A block moves 8 KB per tensor row set, so `bytes` is the
+// whole launch.  us per launch with five / three / two blocks per unit, inputs in no cache (32 layers x 8 heads, bf16, D = 128 unless said):
+//   up to 450 MB the launch is too short to care, and wants every request early: 77 tokens, 5 anchors 30.4 / 32.1 / 33.8 (with the matching);
+//     300 tokens, 5 anchors 46.1 / 48.6 / 53.3; 512, 4 anchors 63.0 / 63.7 / 70.2; above it 400, 8 anchors 87.5 / 84.8 / 89.2;
+//   two blocks from six anchors and 0.95 GB on: 4 x 512 tokens, 6 anchors 392 / 365 / 354, 8: 494 / 465 / 443; 2 x 1024, 16 anchors 891 / 857 / 807;
+//     f32 D 128 8 anchors 494 / 471 / 438; 768 tokens, 8 anchors 181 / 176 / 170; 128 tokens, 64 anchors 193 / 191 / 186;
+//     80 layers, 2048 tokens, 16 anchors 2200 / 2133 / 2037; but 4 anchors 288 / 261 / 279, 5: 341 / 312 / 327; 685 tokens, 8 anchors
+//     (with the matching) 199 / 198 / 203;
+//   bf16 rows of 64 channels (half a line per lane group) never gain from two: 8 anchors 258 / 257 / 272, 16: 489 / 480 / 491.
+// (Four anchors in flight at three blocks, which pools of eight took before, and two at four for smaller ones: 4 x 512 tokens, 8 anchors
+// 445, 2 x 1024 tokens, 16 anchors 840, f32 490, 80 layers 2182; 2 anchors 179, now 172.)
+size_t lds_reserve(const AlignParams &p, int n_blocks, int lpr)
 {
-    if (f32) return max_sel >= 7;
-    int min_sel = max_sel;
-    for (int j = 0; j < p.n_jobs; ++j) min_sel = std::min<int>(min_sel, p.job[j].n_sel);
-    return head_dim >= 128 && min_sel >= 8;
+    double anchors = 0.0;   // of a block, on average
+    for (int j = 0; j < p.n_jobs; ++j) anchors += (double)p.job[j].n_token_tiles * p.job[j].n_sel / p.tiles_total;
+    const double bytes = 2.0 * n_blocks * 32 * kBlock * (anchors + 2.0);
+    if (bytes < 0.45e9) return 0;
+    return anchors >= 6.0 && bytes >= 0.95e9 && lpr > 4 ? 54 << 10 : 81 << 9;
 }
 
 template <typename T, int LPR>
@@ -205,7 +216,7 @@ int launch_align(const AlignParams &p, int n_blocks, int max_tab, int max_sel, h
     constexpr int HALF = LPR * Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
     const size_t lds = sizeof(float2) * (size_t)max_tab * HALF + sizeof(float) * (size_t)RPB * max_sel;
-    return launch(four_in_flight(p, sizeof(T) == 4, 2 * HALF, max_sel) ? align_kernel<T, LPR, 4, 3> : align_kernel<T, LPR, 2, 4>, dim3(n_blocks, 2), dim3(kBlock), lds, stream, p);
+    return launch(align_kernel<T, LPR>, dim3(n_blocks, 2), dim3(kBlock), std::max(lds, lds_reserve(p, n_blocks, LPR)), stream, p);
 }
 
 }  // namespace
@@ -216,9 +227,16 @@ extern "C" int kvcomm_align_kv_batch(const kvcomm_model *model, int32_t gran, kv
     AlignParams p{};
     AlignLaunch pl{};
     const int es = model ? elem_size(model->dtype) : 2;
-    int st = plan_align(model, gran, anchor_layout, es, jobs, n_jobs, KVC_ALIGN_BLOCKS, p, pl,
+    int st = plan_align(model, gran, anchor_layout, es, jobs, n_jobs, 0x7fffffff, p, pl,
                         [](int, const kvcomm_align_job &, int) { return (int)KVCOMM_OK; });
     if (st) return st;
+    p.by_tiles = make_divisor((uint32_t)p.tiles_total);
+    p.by_H = make_divisor((uint32_t)p.H);
+    for (int j = 0; j < n_jobs; ++j) {
+        p.by_pitch[j] = make_divisor((uint32_t)std::max(1, jobs[j].n_anchors));
+        for (int a = 0; a < jobs[j].n_anchors; ++a) p.sel_mask[j] |= (uint64_t)(jobs[j].anchor_len[a] >= jobs[j].seg_len) << a;
+    }
+    if (p.lh_per_block != 1) return KVCOMM_EUNSUPPORTED;   // more than 2^31 blocks
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int nb = (int)pl.n_blocks;
     if (model->dtype == KVCOMM_BF16) {

@@ -101,16 +101,22 @@ __device__ __forceinline__ u32x4 pack<bf16_t>(const float (&in)[8])
     return r;
 }
 
-// cos / sin of the RoPE angle delta * inv_freq: product and reduction modulo 2*pi in double
-// (inv_freq = theta^(-2i/D) comes from the host in double), sine and cosine of the reduced angle in fp32.
+// cos / sin of the RoPE angle delta * inv_freq (inv_freq = theta^(-2i/D) comes from the host in double): product, reduction to
+// the nearest quarter turn and the Taylor series about it in double, rounded to fp32 at the end (what is left out of the series is
+// below 2e-10 of the result).  The library's sinf and cosf carry a path for large arguments that no reduced angle takes, 1.5 KB of code
+// that every block fetched.
 __device__ __forceinline__ float2 rope_cos_sin(int32_t delta, double inv_freq)
 {
     const double x = (double)delta * inv_freq;
-    const double k = rint(x * 0.15915494309189535);  // 1 / (2 pi)
-    double red = fma(-k, 6.283185307179586, x);      // 2 pi, high part
-    red = fma(-k, 2.4492935982947064e-16, red);      // 2 pi, low part
-    const float rf = (float)red;
-    return make_float2(cosf(rf), sinf(rf));
+    const double k = rint(x * 0.6366197723675814);   // 2 / pi
+    double r = fma(-k, 1.5707963267948966, x);       // pi / 2, high part
+    r = fma(-k, 6.123233995736766e-17, r);           // pi / 2, low part
+    const double z = r * r;
+    const double s = r * fma(z, fma(z, fma(z, fma(z, fma(z, -1.0 / 39916800, 1.0 / 362880), -1.0 / 5040), 1.0 / 120), -1.0 / 6), 1.0);
+    const double c = fma(z, fma(z, fma(z, fma(z, fma(z, -1.0 / 3628800, 1.0 / 40320), -1.0 / 720), 1.0 / 24), -0.5), 1.0);
+    const int q = (int)(long long)k & 3;
+    const float fs = (float)((q & 1) ? c : s), fc = (float)((q & 1) ? s : c);
+    return make_float2(((q + 1) & 2) ? -fc : fc, (q & 2) ? -fs : fs);
 }
 
 // ------------------------------------------------------------------------- host-side checks

@@ -38,7 +38,7 @@ struct AlignParams {
     uint64_t sel_mask[KVCOMM_MAX_BATCH];        // bit a = anchor a of the segment is selected
     int32_t tab_delta[kMaxTab];                 // position delta of each rotation table
     const void *anc[2][KVCOMM_MAX_ANCHORS];     // [0] dK, [1] dV of the selected anchors of all segments
-    alignas(4) uint8_t col[KVCOMM_MAX_ANCHORS];            // weight column of a selected anchor
+    alignas(4) uint8_t col[KVCOMM_MAX_ANCHORS];            // weight column of a selected anchor (the kernel has it from sel_mask)
     alignas(4) uint8_t tab[KVCOMM_MAX_ANCHORS];            // its rotation table (index among the segment's tables) + 1, 0 = identity
     double inv_freq[kMaxHalf];                  // theta^(-2i/D), i < D/2
 };

@@ -17,7 +17,7 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 // attn_mfma_kernel), which the wavefronts SHARE: each takes every NW-th 32-key sub-step of the block's key
 // run with its own softmax state, and the states are joined through LDS at the end.  The 256-row kernel would leave
 // seven of eight wavefronts without rows and walk the keys one 64-key tile after the other (one layer, one token,
-// 3100 keys: 62 us; here 20 us in one block per kv head, 9 + 4 us with the keys cut into runs).
+// 3100 keys: 62 us; here 20 us in one block per kv head, 8.4 + 4.3 us with the keys cut into runs).
 // What bounds it is the latency of the K / V stream, and HBM where every layer is in one launch (32 layers: 64 us =
 // 6.4 TB/s): K and V of a sub-step go global -> LDS into the wavefront's own buffers (no block barrier in the loop),
 // K of the next sub-step is requested as soon as its operands are in registers and V likewise, so a wavefront

@@ -13,6 +13,8 @@
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <cxxabi.h>
+
 #include <climits>
 
 #include "kvcomm.h"
@@ -244,21 +246,24 @@ PyObject *entry(PyObject *const *a, Py_ssize_t n, F &&f)
     }
     try {
         return PyLong_FromLongLong(f(a));
+    } catch (abi::__forced_unwind &) {   // the thread is being ended (see unlocked())
+        throw;
     } catch (...) {
         PyErr_Clear();
         Py_RETURN_NONE;
     }
 }
 
-// The library's call, without the interpreter lock: a launch waits where the queue is full.
+// The library's call, without the interpreter lock: a launch waits where the queue is full.  A daemon thread that asks for the lock
+// again while the interpreter shuts down is ended there, by an unwinding that no destructor, noexcept or catch may stop.  The
+// library itself throws nothing.
 template <class F>
 long long unlocked(F &&f)
 {
-    struct Release {
-        PyThreadState *st = PyEval_SaveThread();
-        ~Release() { PyEval_RestoreThread(st); }
-    } released;
-    return f();
+    PyThreadState *st = PyEval_SaveThread();
+    const long long status = f();
+    PyEval_RestoreThread(st);
+    return status;
 }
 
 // -------------------------------------------------------------------------------------------- entry points

@@ -1,6 +1,10 @@
 """The native marshalling module against the ctypes code that it stands in for: the same bits from every entry point for every
 form of arguments that it takes, and no call for those that it does not."""
 import copy
+import os
+import subprocess
+import sys
+import sysconfig
 
 import pytest
 import torch
@@ -186,3 +190,60 @@ def test_host_tensors_and_wrappers_are_declined():
         assert native.suffix_attn_workspace(*bad) is None
     with pytest.raises(TypeError):
         native.suffix_attn_workspace(m, 1)
+
+
+# A module that makes tensors which say that they lie in device memory (their address is never used), and a library call that
+# takes a while.
+FAKE_DEVICE = r"""
+#include <torch/csrc/autograd/python_variable.h>
+#include <unistd.h>
+extern "C" int slow_call(...) { usleep(300000); return 0; }
+static PyObject *tensor(PyObject *, PyObject *)
+{
+    const c10::Device dev(c10::DeviceType::CUDA, 0);
+    c10::Storage st(c10::Storage::use_byte_size_t(), 1 << 20, c10::DataPtr((void *)0x100000, dev), nullptr, false);
+    at::Tensor t = at::detail::make_tensor<c10::TensorImpl>(std::move(st), c10::DispatchKeySet(c10::DispatchKey::CUDA), caffe2::TypeMeta::Make<float>());
+    t.unsafeGetTensorImpl()->set_sizes_contiguous({4, 4});
+    return THPVariable_Wrap(t);
+}
+static PyObject *address(PyObject *, PyObject *) { return PyLong_FromVoidPtr((void *)&slow_call); }
+static PyMethodDef methods[] = {{"tensor", tensor, METH_NOARGS, nullptr}, {"address", address, METH_NOARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
+static PyModuleDef module = {PyModuleDef_HEAD_INIT, "fake_device", nullptr, -1, methods};
+PyMODINIT_FUNC PyInit_fake_device(void) { return PyModule_Create(&module); }
+"""
+
+EXIT = r"""
+import sys, threading, time
+sys.path[:0] = sys.argv[1:3]
+import torch, fake_device
+import paper_2510_12872_amd as kv
+from paper_2510_12872_amd import binding
+kv.load_library()
+binding._native.bind({n: fake_device.address() for n in binding._NATIVE_CALLS}, binding.Model, lambda: 0, lambda d: 0)
+t, entered = fake_device.tensor(), threading.Event()
+def work():
+    entered.set()
+    binding._native.anchor_predict(t, [1, 1, 1, 1], 1, 0.5, None, t, None, None)
+    raise SystemError("the call was declined")
+threading.Thread(target=work, daemon=True).start()
+entered.wait()
+time.sleep(0.1)      # the thread is inside the call, without the interpreter lock
+class Late:
+    def __del__(self, sleep=time.sleep):
+        sleep(0.6)   # ... and comes back during the shutdown
+late = Late()
+"""
+
+
+def test_a_call_that_outlives_the_interpreter_ends_its_thread_only(tmp_path):
+    """A daemon thread whose call returns while the interpreter shuts down is ended where it asks for the lock again; that must not
+    reach std::terminate, nor be taken for a call that was declined."""
+    top = os.path.dirname(torch.__file__)
+    (tmp_path / "fake.cpp").write_text(FAKE_DEVICE)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                    "-isystem", os.path.join(top, "include"), "-isystem", os.path.join(top, "include", "torch", "csrc", "api", "include"),
+                    "-isystem", sysconfig.get_paths()["include"], "-o", str(tmp_path / "fake_device.so"), str(tmp_path / "fake.cpp"),
+                    "-L", os.path.join(top, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"], check=True)
+    ran = subprocess.run([sys.executable, "-c", EXIT, str(tmp_path),
+                          os.path.dirname(os.path.dirname(os.path.abspath(kv.__file__)))], capture_output=True, text=True, timeout=120)
+    assert ran.returncode == 0, (ran.returncode, ran.stderr[-2000:])

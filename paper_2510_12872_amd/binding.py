@@ -6,10 +6,13 @@ the caller did not pass, and raise on a non-zero status.  All arithmetic of the 
 runs inside the library's HIP kernels.  torch is used for device memory and streams only.
 
 Calls whose arguments are plain (device tensors, lists, numbers) are marshalled by the native module _marshal
-(csrc/marshal.cpp), which declines all others; those take the ctypes code below, which converts or refuses them.
+(csrc/marshal.cpp), which declines all others; those take the ctypes code below, which converts or refuses them.  Without
+a _marshal built for this torch and Python every call does (a warning says so: small calls then take longer on the host).
 """
 import ctypes
 import os
+import sys
+import warnings
 from dataclasses import dataclass
 
 import torch
@@ -89,7 +92,31 @@ class Model:
 
 
 _lib = None
-_native = None   # the module _marshal, set with _lib
+_native = None   # the module _marshal or _Declines, set with _lib
+
+# What _marshal is built against: it reads torch's and Python's objects through their internal layout
+MARSHAL_FOR = f"torch {torch.__version__}, Python {sys.version_info[0]}.{sys.version_info[1]}"
+
+
+class _Declines:
+    """In the place of _marshal: takes no call."""
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_native(lib):
+    try:
+        from . import _marshal
+        built_for = getattr(_marshal, "built_for", None)
+        if built_for != MARSHAL_FOR:
+            raise ImportError(f"built for {built_for}, this is {MARSHAL_FOR}")
+    except ImportError as e:
+        warnings.warn(f"the native module _marshal is not used ({e}): build it with `python -m paper_2510_12872_amd.build`; small "
+                      "calls take longer on the host without it", RuntimeWarning, stacklevel=3)
+        return _Declines()
+    _marshal.bind({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _NATIVE_CALLS}, Model, torch.cuda.current_device,
+                  _raw_current_stream)
+    return _marshal
 
 
 _NATIVE_CALLS = ("kvcomm_weight_slots", "kvcomm_suffix_attn_workspace", "kvcomm_anchor_weights_rule",
@@ -169,13 +196,7 @@ def load_library():
     lib.kvcomm_status_string.restype = ctypes.c_char_p
     lib.kvcomm_version.argtypes = []
     lib.kvcomm_version.restype = ctypes.c_int
-    try:
-        from . import _marshal
-    except ImportError as e:
-        raise RuntimeError("the native module _marshal cannot be loaded: build it with `python -m paper_2510_12872_amd.build`") from e
-    _marshal.bind({n: ctypes.cast(getattr(lib, n), vp).value for n in _NATIVE_CALLS}, Model, torch.cuda.current_device,
-                  _raw_current_stream)
-    _native = _marshal
+    _native = _load_native(lib)
     _lib = lib
     return lib
 

@@ -55,8 +55,11 @@ def build(verbose=False, extra_flags=()):
 def build_marshal(verbose=False):
     """Compile the native marshalling module (host code only) against the installed torch."""
     import torch
+
+    from .binding import MARSHAL_FOR
     top = os.path.dirname(torch.__file__)
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DKVC_BUILT_FOR="{MARSHAL_FOR}"',
            "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(top, "include"),
            "-isystem", os.path.join(top, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], "-o", MARSHAL, MARSHAL_SRC,

@@ -572,5 +572,10 @@ PyMODINIT_FUNC PyInit__marshal(void)
     NAME(anchor_dk8); NAME(anchor_dv8); NAME(scale_k); NAME(scale_v); NAME(weights); NAME(delta_pos); NAME(anchor_delta_pos);
     NAME(out_k); NAME(out_v);
 #undef NAME
-    return PyModule_Create(&module);
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", KVC_BUILT_FOR) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
 }

@@ -192,6 +192,27 @@ def test_host_tensors_and_wrappers_are_declined():
         native.suffix_attn_workspace(m, 1)
 
 
+@pytest.mark.parametrize("why", ["missing", "another torch"])
+def test_the_library_works_without_the_module(monkeypatch, why):
+    """No _marshal, or one built against another torch: a warning, and every call through ctypes."""
+    m = kv.Model(L, H, H * G, D, torch.bfloat16, 1e4)
+    want = kv.kvcomm_suffix_attn_workspace(m, 2560, 512)
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_native", None)
+    if why == "missing":
+        monkeypatch.delattr(kv, "_marshal", raising=False)
+        monkeypatch.setitem(sys.modules, kv.__name__ + "._marshal", None)
+    else:
+        monkeypatch.setattr(binding, "MARSHAL_FOR", "torch 1.0, Python 3.0")
+    with pytest.warns(RuntimeWarning, match="_marshal"):
+        binding.load_library()
+    assert kv.kvcomm_suffix_attn_workspace(m, 2560, 512) == want
+    assert binding._native.suffix_attn_workspace(m, 2560, 512) is None and binding._native.align_kv() is None
+    x = torch.zeros((L, H, 12, D), dtype=torch.bfloat16)
+    with pytest.raises(kv.KVCommError, match="device tensor"):     # refused by the ctypes code, as with the module
+        kv.kvcomm_quantize_deltas(m, x, 1.0)
+
+
 # A module that makes tensors which say that they lie in device memory (their address is never used), and a library call that
 # takes a while.
 FAKE_DEVICE = r"""

@@ -5,6 +5,8 @@
 
 #include <math.h>
 
+#include <algorithm>
+
 #include "kvcomm_device.h"
 
 namespace kvc {
@@ -50,8 +52,10 @@ __device__ __forceinline__ int job_of_tile(const P &p, int r)
 
 struct AlignLaunch {
     int max_tab, max_sel, lpr;
+    int lh_per_block;      // (layer, head) pairs that a block walks
     int64_t n_blocks;
 };
+constexpr int kOnePairPerBlock = 0;   // in the place of plan_align()'s target
 
 // What a launch writes must not be something it also reads or writes elsewhere: an output may be exactly its
 // own base tensor (in place: a lane owns both members of every rotation pair it touches), anything else that
@@ -98,8 +102,9 @@ int check_align_aliasing(const kvcomm_model *model, int gran, const kvcomm_tenso
 }
 
 // Validates the jobs of a batched update and fills the launch parameters P (fields job, s_anc, H, LH, gran,
-// n_jobs, lh_per_block, tiles_total, tab_delta, anc, col, tab, inv_freq).  `on_anchor(slot, job, a)` is called
-// for every selected anchor with its launch-wide slot and may return an error status.
+// n_jobs, tiles_total, tab_delta, anc, tab, inv_freq).  `on_anchor(slot, job, a)` is called for every selected anchor with its
+// launch-wide slot and may return an error status.  The blocks are cut so that there are about target_blocks_per_job * n_jobs, or
+// one per (layer, head) pair and token tile.
 template <class P, class JobT, class OnAnchor>
 int plan_align(const kvcomm_model *model, int gran, const kvcomm_tensor &anchor_layout, int anchor_es, const JobT *jobs,
                int n_jobs, int target_blocks_per_job, P &p, AlignLaunch &plan, OnAnchor &&on_anchor)
@@ -186,7 +191,6 @@ int plan_align(const kvcomm_model *model, int gran, const kvcomm_tensor &anchor_
             const int s = n_sel_total + n_sel++;
             p.anc[0][s] = jd.anchor_dk[a];
             p.anc[1][s] = jd.anchor_dv[a];
-            p.col[s] = (uint8_t)a;
             p.tab[s] = (uint8_t)(jd.anchor_delta_pos ? table_of(jd.delta_pos - jd.anchor_delta_pos[a]) : 0);
             if ((st = on_anchor(s, jd, a))) return st;
         }
@@ -201,14 +205,17 @@ int plan_align(const kvcomm_model *model, int gran, const kvcomm_tensor &anchor_
         tiles_total += jb.n_token_tiles;
     }
 
-    // Many small blocks: the memory system delivers more with more wavefronts in flight, and the
-    // per-block set-up (weights, cos/sin) is a few dozen instructions.
-    const int64_t target_blocks = (int64_t)target_blocks_per_job * n_jobs;
-    int64_t n_chunks = (target_blocks + tiles_total - 1) / tiles_total;
-    if (n_chunks > p.LH) n_chunks = p.LH;
-    if (n_chunks < 1) n_chunks = 1;
-    p.lh_per_block = (int32_t)((p.LH + n_chunks - 1) / n_chunks);
-    n_chunks = (p.LH + p.lh_per_block - 1) / p.lh_per_block;
+    if (tiles_total > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
+    int64_t n_chunks = p.LH;
+    plan.lh_per_block = 1;
+    if (target_blocks_per_job != kOnePairPerBlock) {
+        // Many small blocks: the memory system delivers more with more wavefronts in flight, and the
+        // per-block set-up (weights, cos/sin) is a few dozen instructions.
+        const int64_t target_blocks = (int64_t)target_blocks_per_job * n_jobs;
+        n_chunks = std::max<int64_t>(1, std::min<int64_t>(p.LH, (target_blocks + tiles_total - 1) / tiles_total));
+        plan.lh_per_block = (int)((p.LH + n_chunks - 1) / n_chunks);
+        n_chunks = (p.LH + plan.lh_per_block - 1) / plan.lh_per_block;
+    }
     int32_t tile0 = 0;
     for (int j = 0; j < n_jobs; ++j) {
         p.job[j].tile0 = tile0;
@@ -219,7 +226,6 @@ int plan_align(const kvcomm_model *model, int gran, const kvcomm_tensor &anchor_
     plan.max_tab = max_tab;
     plan.max_sel = max_sel;
     plan.lpr = lpr;
-    if (plan.n_blocks > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
     return KVCOMM_OK;
 }
 

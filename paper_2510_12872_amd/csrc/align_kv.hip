@@ -11,7 +11,7 @@
 // same channels of the second half, i.e. both members of each RoPE pair (i, i + D/2), so
 // the rotation needs no cross-lane traffic and the kernel may run in place.  A block of
 // 256 threads owns a tile of 256/LPR consecutive tokens of one (layer, head) and of ONE of
-// the two tensors (blockIdx.y: 0 = keys, 1 = values): the two streams are independent, and
+// the two tensors (blockIdx.y even: keys, odd: values): the two streams are independent, and
 // splitting them halves the registers per lane.  Every access to a tensor is a run of whole 128-byte lines; deviations and outputs are marked
 // non-temporal (they are not read again soon: 466 us per launch of 4 x 512 tokens with 8 anchors, 500 us with plain
 // stores).  The base rows are plain loads: anchor matching has just read the base keys, and a shared segment's base
@@ -32,13 +32,12 @@ struct AlignParams {
     Strides s_anc;
     int32_t H, LH;             // kv heads, layers*heads
     int32_t gran, n_jobs;
-    int32_t lh_per_block;      // 1
     int32_t tiles_total;       // token tiles of all segments
+    int32_t lh_range;          // (layer, head) pairs along the grid's first axis
     divisor_t by_tiles, by_H, by_pitch[KVCOMM_MAX_BATCH];
     uint64_t sel_mask[KVCOMM_MAX_BATCH];        // bit a = anchor a of the segment is selected
     int32_t tab_delta[kMaxTab];                 // position delta of each rotation table
     const void *anc[2][KVCOMM_MAX_ANCHORS];     // [0] dK, [1] dV of the selected anchors of all segments
-    alignas(4) uint8_t col[KVCOMM_MAX_ANCHORS];            // weight column of a selected anchor (the kernel has it from sel_mask)
     alignas(4) uint8_t tab[KVCOMM_MAX_ANCHORS];            // its rotation table (index among the segment's tables) + 1, 0 = identity
     double inv_freq[kMaxHalf];                  // theta^(-2i/D), i < D/2
 };
@@ -57,8 +56,10 @@ __global__ __launch_bounds__(kBlock, 4) void align_kernel(const AlignParams p)
 
     // Block order: (layer, head) chunk, then segment, then token tile, so that the blocks in flight
     // write neighbouring slices of the same cache rows when the segments of a launch are adjacent.
-    const int lh = div_by(blockIdx.x, p.by_tiles);
-    const int r = blockIdx.x - lh * p.tiles_total;
+    const int q = div_by(blockIdx.x, p.by_tiles);
+    const int r = blockIdx.x - q * p.tiles_total;
+    const int lh = (blockIdx.y >> 1) * p.lh_range + q;
+    if (lh >= p.LH) return;   // the whole block: the last range of pairs is not full
     const int ji = job_of_tile(p, r);
     const AlignJob &jb = p.job[ji];
     const int n_sel = jb.n_sel, a0 = jb.a0;
@@ -71,7 +72,7 @@ __global__ __launch_bounds__(kBlock, 4) void align_kernel(const AlignParams p)
     const int row = tid / LPR;
     const int lir = tid % LPR;
     const int tile = r - jb.tile0;
-    const int which = blockIdx.y;          // 0 = keys (rotated), 1 = values
+    const int which = blockIdx.y & 1;      // 0 = keys (rotated), 1 = values
     const bool is_k = which == 0;
     const int t = tile * RPB + row;
     const bool valid = t < jb.S;
@@ -201,22 +202,23 @@ __global__ __launch_bounds__(kBlock, 4) void align_kernel(const AlignParams p)
 //   bf16 rows of 64 channels (half a line per lane group) never gain from two: 8 anchors 258 / 257 / 272, 16: 489 / 480 / 491.
 // (Four anchors in flight at three blocks, which pools of eight took before, and two at four for smaller ones: 4 x 512 tokens, 8 anchors
 // 445, 2 x 1024 tokens, 16 anchors 840, f32 490, 80 layers 2182; 2 anchors 179, now 172.)
-size_t lds_reserve(const AlignParams &p, int n_blocks, int lpr)
+size_t lds_reserve(const AlignParams &p, int64_t n_blocks, int lpr)
 {
     double anchors = 0.0;   // of a block, on average
     for (int j = 0; j < p.n_jobs; ++j) anchors += (double)p.job[j].n_token_tiles * p.job[j].n_sel / p.tiles_total;
-    const double bytes = 2.0 * n_blocks * 32 * kBlock * (anchors + 2.0);
+    const double bytes = 2.0 * (double)n_blocks * 32 * kBlock * (anchors + 2.0);
     if (bytes < 0.45e9) return 0;
     return anchors >= 6.0 && bytes >= 0.95e9 && lpr > 4 ? 54 << 10 : 81 << 9;
 }
 
 template <typename T, int LPR>
-int launch_align(const AlignParams &p, int n_blocks, int max_tab, int max_sel, hipStream_t stream)
+int launch_align(const AlignParams &p, const AlignLaunch &pl, hipStream_t stream)
 {
     constexpr int HALF = LPR * Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
-    const size_t lds = sizeof(float2) * (size_t)max_tab * HALF + sizeof(float) * (size_t)RPB * max_sel;
-    return launch(align_kernel<T, LPR>, dim3(n_blocks, 2), dim3(kBlock), std::max(lds, lds_reserve(p, n_blocks, LPR)), stream, p);
+    const size_t lds = sizeof(float2) * (size_t)pl.max_tab * HALF + sizeof(float) * (size_t)RPB * pl.max_sel;
+    const dim3 grid((unsigned)(p.lh_range * p.tiles_total), (unsigned)(2 * ((p.LH + p.lh_range - 1) / p.lh_range)));
+    return launch(align_kernel<T, LPR>, grid, dim3(kBlock), std::max(lds, lds_reserve(p, pl.n_blocks, LPR)), stream, p);
 }
 
 }  // namespace
@@ -227,7 +229,7 @@ extern "C" int kvcomm_align_kv_batch(const kvcomm_model *model, int32_t gran, kv
     AlignParams p{};
     AlignLaunch pl{};
     const int es = model ? elem_size(model->dtype) : 2;
-    int st = plan_align(model, gran, anchor_layout, es, jobs, n_jobs, 0x7fffffff, p, pl,
+    int st = plan_align(model, gran, anchor_layout, es, jobs, n_jobs, kOnePairPerBlock, p, pl,
                         [](int, const kvcomm_align_job &, int) { return (int)KVCOMM_OK; });
     if (st) return st;
     p.by_tiles = make_divisor((uint32_t)p.tiles_total);
@@ -236,20 +238,23 @@ extern "C" int kvcomm_align_kv_batch(const kvcomm_model *model, int32_t gran, kv
         p.by_pitch[j] = make_divisor((uint32_t)std::max(1, jobs[j].n_anchors));
         for (int a = 0; a < jobs[j].n_anchors; ++a) p.sel_mask[j] |= (uint64_t)(jobs[j].anchor_len[a] >= jobs[j].seg_len) << a;
     }
-    if (p.lh_per_block != 1) return KVCOMM_EUNSUPPORTED;   // more than 2^31 blocks
+    // A launch holds fewer than 2^32 threads along an axis, and 65535 blocks along the second: more (layer, head) pairs than go along the
+    // first come as further pairs (keys, values) along that one.
+    constexpr int64_t kMaxBlocks = ((int64_t)1 << 32) / kBlock - 1;
+    p.lh_range = (int32_t)std::min<int64_t>(p.LH, kMaxBlocks / p.tiles_total);
+    if (p.lh_range < 1 || (p.LH + p.lh_range - 1) / p.lh_range > 65535 / 2) return KVCOMM_EUNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int nb = (int)pl.n_blocks;
     if (model->dtype == KVCOMM_BF16) {
         switch (pl.lpr) {
-            case 4: return launch_align<bf16_t, 4>(p, nb, pl.max_tab, pl.max_sel, s);
-            case 8: return launch_align<bf16_t, 8>(p, nb, pl.max_tab, pl.max_sel, s);
-            case 16: return launch_align<bf16_t, 16>(p, nb, pl.max_tab, pl.max_sel, s);
+            case 4: return launch_align<bf16_t, 4>(p, pl, s);
+            case 8: return launch_align<bf16_t, 8>(p, pl, s);
+            case 16: return launch_align<bf16_t, 16>(p, pl, s);
         }
     } else {
         switch (pl.lpr) {
-            case 8: return launch_align<float, 8>(p, nb, pl.max_tab, pl.max_sel, s);
-            case 16: return launch_align<float, 16>(p, nb, pl.max_tab, pl.max_sel, s);
-            case 32: return launch_align<float, 32>(p, nb, pl.max_tab, pl.max_sel, s);
+            case 8: return launch_align<float, 8>(p, pl, s);
+            case 16: return launch_align<float, 16>(p, pl, s);
+            case 32: return launch_align<float, 32>(p, pl, s);
         }
     }
     return KVCOMM_EUNSUPPORTED;

@@ -407,11 +407,14 @@ extern "C" int kvcomm_align_kv_q8_batch(const kvcomm_model *model, int32_t gran,
                             int ek, ev;
                             if (!power_of_two(jd.anchor_scale_k[a], &ek) || !power_of_two(jd.anchor_scale_v[a], &ev))
                                 return (int)KVCOMM_EINVAL;
+                            p.col[slot] = (uint8_t)a;
                             p.scale_exp[0][slot] = (int8_t)ek;
                             p.scale_exp[1][slot] = (int8_t)ev;
                             return (int)KVCOMM_OK;
                         });
     if (st) return st;
+    if (pl.n_blocks > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
+    p.lh_per_block = pl.lh_per_block;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int nb = (int)pl.n_blocks;
     if (model->dtype == KVCOMM_BF16) {

@@ -45,3 +45,25 @@ def test_selected_columns(dtype, D, A, S):
         for got, want in ((out_k, want_k), (out_v, want_v)):
             tol = 1e-5 * want.abs().max() + (want.abs() * 2.0 ** -8 if dtype == torch.bfloat16 else 0.0)
             assert bool(((got.double() - want).abs() <= tol).all())
+
+
+@pytest.mark.gpu
+def test_more_blocks_than_one_axis_of_a_launch_holds():
+    """2^24 blocks and a few: the (layer, head) pairs past the grid's first axis.  One token per segment and no anchors (what fits
+    memory): keys rotated within half a unit in the last place and 1e-5, values copied."""
+    L, H, D, n, theta = 299600, 7, 64, 8, 1e4
+    m = kv.Model(L, H, H, D, torch.bfloat16, theta)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(11)
+    bk, bv = (torch.randn((L, H, n, D), generator=g, device=DEV, dtype=torch.bfloat16) for _ in range(2))
+    out_k, out_v = torch.zeros_like(bk), torch.zeros_like(bv)
+    at = lambda t, j: t[:, :, j:j + 1]
+    print(f"update blocks: L{L} H{H} {n} segments", flush=True)
+    kv.kvcomm_align_kv_batch(m, [dict(base_k=at(bk, j), base_v=at(bv, j), anchor_dk=[], anchor_dv=[], delta_pos=100 * j, out_k=at(out_k, j),
+                                      out_v=at(out_v, j)) for j in range(n)])
+    torch.cuda.synchronize()
+    assert torch.equal(out_v, bv)
+    for j in range(n):
+        for part in range(0, L, 50000):
+            want = _rotate(bk[part:part + 50000, :, j].double(), 100 * j, theta, D)
+            assert bool(((out_k[part:part + 50000, :, j].double() - want).abs() <= 1e-5 * want.abs().max() + want.abs() * 2.0 ** -8).all())

@@ -1,7 +1,7 @@
 """What the attention calls launch (CPU only, see launches.py)."""
 import pytest
 
-from launches import attention_launches
+from launches import align_launches, attention_launches
 
 F32, BF16 = 0, 1
 
@@ -69,3 +69,17 @@ def test_the_shapes_of_the_gpu_tests_reach_what_they_name(tmp_path):
     for s, nt in (((32, 8, 4, 128, 3100, 1), True), ((1, 8, 4, 128, 3100, 1), False)):
         r, = attention_launches(tmp_path, [s[:4] + (BF16,) + s[4:] + (0, True)])
         assert ("ELb1E" in r["launches"][0][0]) == nt and "attn_rows_kernel" in r["launches"][0][0]
+
+
+@pytest.mark.parametrize("L,H,D,dtype,lens,pools,rows", [(32, 8, 128, BF16, [512] * 4, [8] * 4, 32), (1, 1, 64, F32, [1], [0], 32),
+                                                         (80, 8, 128, BF16, [1 << 20], [1], 32), (257, 8, 256, F32, [300000], [1], 8),
+                                                         (4000, 8, 64, BF16, [1 << 17, 5], [1, 1], 64)])
+def test_updates_of_any_size_stay_within_a_launch(tmp_path, L, H, D, dtype, lens, pools, rows):
+    """A launch holds fewer than 2^32 threads along each axis.  Every (layer, head, token tile, tensor) has its block."""
+    r, = align_launches(tmp_path, [(L, H, D, dtype, lens, pools)])
+    assert r["status"] == 0 and len(r["launches"]) == 1
+    (x, y, z), (threads, _, _) = r["launches"][0]["grid"], r["launches"][0]["block"]
+    assert threads == 256 and x * threads < 1 << 32 and y <= 65535 and z == 1
+    tiles = sum(-(-S // rows) for S in lens)
+    pairs, left = divmod(x, tiles)
+    assert left == 0 and pairs * (y // 2 - 1) < L * H <= pairs * (y // 2) and y % 2 == 0

@@ -854,6 +854,7 @@ int token_shift(const kvcomm_model &m, const kvcomm_weights_job *jobs, const Dis
     for (int shift = 0; 1 << shift <= rpw; ++shift) {
         int64_t blocks = 0;
         for (int j = 0; j < n_jobs; ++j) blocks += ((int64_t)jobs[j].seg_len + (1 << shift) - 1) >> shift;
+        if (blocks * kTokBlock >= (int64_t)1 << 32) continue;   // more threads than a launch holds
         const int per_cu = cosine ? 1 : blocks > 256 ? 2 : 1, lh_step = (nw / tiles) * (rpw >> shift);
         const double rounds = (double)((blocks + 256 * per_cu - 1) / (256 * per_cu));
         const double step_us = std::max(cosine ? 1.7 : 0.8, per_cu * nw * 1024.0 * (width + 1) / 35e3);
@@ -1081,12 +1082,11 @@ extern "C" int kvcomm_anchor_weights_batch(const kvcomm_model *model, int32_t gr
     const int shift = gran == KVCOMM_W_TOKEN ? token_shift(*model, jobs, dp.job, n_jobs, max_sel, cosine) : -1;
     if (shift >= 0) {
         dp.tok_shift = shift;
-        int64_t blocks = 0;   // <= the sum of the segments' tokens
+        int64_t blocks = 0;
         for (int j = 0; j < n_jobs; ++j) {
             dp.job[j].block0 = (int32_t)blocks;
             blocks += ((int64_t)jobs[j].seg_len + (1 << shift) - 1) >> shift;
         }
-        if (blocks > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
         st = KVCOMM_EUNSUPPORTED;
         const int nb = (int)blocks;
         if (dt == KVCOMM_BF16) {

@@ -1,20 +1,14 @@
 """Per-token weights in one launch (token_weights_kernel) and in two (partial sums, softmax): which calls take which, and both
 against the float64 oracle (1e-5 as for all weights; arg-min and selection exact) where a block's tokens, the wavefronts' share
 of (layer, head) pairs or the anchor tiles do not come out even."""
-import json
-import os
-import subprocess
-import sys
-
 import numpy as np
 import pytest
 import torch
 
 import oracle
 import paper_2510_12872_amd as kv
-from paper_2510_12872_amd import build
 
-from launches import RECORDER
+from launches import record
 from parity import check_weights, to_np
 
 DEV = "cuda"
@@ -109,7 +103,7 @@ class Tensor(ctypes.Structure):
 class Job(ctypes.Structure):
     _fields_ = [("seg", Tensor), ("S", i32), ("anc", vp), ("len", vp), ("n", i32), ("w", vp), ("near", vp), ("sel", vp)]
 shim.rec_name.restype = ctypes.c_char_p
-shim.rec_grid.restype = ctypes.c_uint
+shim.rec_grid.restype = shim.rec_block.restype = ctypes.c_uint
 f = lib.kvcomm_anchor_weights_batch
 f.argtypes = [vp, i32, i32, ctypes.c_float, Tensor, vp, i32, vp, sz, vp]
 res = []
@@ -122,26 +116,31 @@ for L, H, D, dtype, lens, pools, rule in json.load(sys.stdin):
     shim.rec_clear()
     cap = max(lens)
     st = f(ctypes.byref(Model(L, H, H, D, dtype, 1e4)), 0, rule, 1.0, Tensor(0x1000, H * cap * D, cap * D, D), jobs, len(lens), 0x1000, 1 << 40, None)
-    res.append(dict(status=st, names=[shim.rec_name(i).decode() for i in range(shim.rec_count())], grid=shim.rec_grid(0, 0)))
+    res.append(dict(status=st, names=[shim.rec_name(i).decode() for i in range(shim.rec_count())], grid=shim.rec_grid(0, 0),
+                    threads=[shim.rec_grid(i, 0) * shim.rec_block(i, 0) for i in range(shim.rec_count())]))
 json.dump(res, sys.stdout)
 """
 
 
+def _launches(tmp_path, calls):
+    return record(tmp_path, DRIVER, [[c[0], c[1], c[2], 0 if c[3] == F32 else 1, c[4], c[5], rule] for c, rule in calls])
+
+
 def test_which_calls_take_one_launch(tmp_path):
-    src, shim = tmp_path / "rec.c", tmp_path / "librec.so"
-    src.write_text(RECORDER)
-    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-o", str(shim), str(src)], check=True)
     # 4 x 512 tokens: four tokens per block; one segment of 512: two; 200: one; fewer tokens than half the chip and many pairs: two launches
     sized = [((32, 8, 128, BF, [512] * 4, [8] * 4), 512), ((32, 8, 128, BF, [512], [8]), 256), ((32, 8, 128, BF, [200], [12]), 200)]
     two = TWO + [(32, 8, 128, BF, [77], [6]), (32, 8, 128, BF, [1024], [64]), (32, 8, 128, BF, [2048], [16])]
     calls = [(c, 0) for c in ONE + [c for c, _ in sized] + two]
-    arg = [[c[0], c[1], c[2], 0 if c[3] == F32 else 1, c[4], c[5], rule] for c, rule in calls]
-    lib = os.environ.get("KVCOMM_LIBRARY") or build.LIB
-    ran = subprocess.run([sys.executable, "-c", DRIVER, str(shim), lib], input=json.dumps(arg), capture_output=True, text=True)
-    assert ran.returncode == 0, ran.stderr[-2000:]
-    for (c, _), r in zip(calls, json.loads(ran.stdout)):
+    for (c, _), r in zip(calls, _launches(tmp_path, calls)):
         one = len(r["names"]) == 1 and "token_weights_kernel" in r["names"][0]
         assert r["status"] == 0 and one == (c not in two), (c, r)
         assert one or ("partial_kernel" in r["names"][0] and "finalize_kernel" in r["names"][1])
         for s, grid in sized:
             assert c != s or r["grid"] == grid
+
+
+def test_more_tokens_than_a_launch_holds_blocks(tmp_path):
+    """A block per token and 2^23 tokens would be 2^32 threads, which no launch holds: the two stages."""
+    below, above = _launches(tmp_path, [((4, 4, 256, F32, [S], [8]), 0) for S in ((1 << 23) - 1, 1 << 23)])
+    for r, n in ((below, 1), (above, 2)):
+        assert r["status"] == 0 and len(r["names"]) == n and all(t < 1 << 32 for t in r["threads"]), r

@@ -210,6 +210,13 @@ typedef struct {
 int kvcomm_align_kv_batch(const kvcomm_model *model, int32_t gran, kvcomm_tensor anchor_layout,
                           const kvcomm_align_job *jobs, int32_t n_jobs, void *stream);
 
+/* kvcomm_align_kv_batch for a launch that runs beside other work, such as kvcomm_suffix_attn_confined on another stream, and has
+ * about `units` of the GPU's 256 compute units to itself (256 - max_blocks there).  A hint only: same arguments, results bit for
+ * bit and errors, plus KVCOMM_EINVAL for units <= 0.  A large update bounds its blocks per compute unit so that HBM has the
+ * requests in flight that suit it; on a part of the chip that bound lies higher.                       */
+int kvcomm_align_kv_batch_beside(const kvcomm_model *model, int32_t gran, kvcomm_tensor anchor_layout,
+                                 const kvcomm_align_job *jobs, int32_t n_jobs, int32_t units, void *stream);
+
 /* --------------------------------------------------------------------------------------
  * Causal attention of the tq non-shared suffix queries over the assembled cache (workflow
  * step 4; q, k, v as defined in Sec. 3.1).  Suffix query i sits at cache position

@@ -26,6 +26,7 @@ W_LAYER_HEAD_TOKEN = 1
 W_SEGMENT = 2
 MAX_ANCHORS = 64
 MAX_BATCH = 8
+COMPUTE_UNITS = 256
 ATTN_MIN_SPLIT_KEYS = 512   # shorter caches never use the attention's scratch
 RULE_L2_SOFTMAX = 0
 RULE_NEAREST = 1
@@ -120,7 +121,7 @@ def _load_native(lib):
 
 
 _NATIVE_CALLS = ("kvcomm_weight_slots", "kvcomm_suffix_attn_workspace", "kvcomm_anchor_weights_rule",
-                 "kvcomm_anchor_weights_batch", "kvcomm_align_kv_batch", "kvcomm_align_kv_q8_batch", "kvcomm_align_kv",
+                 "kvcomm_anchor_weights_batch", "kvcomm_align_kv_batch", "kvcomm_align_kv_batch_beside", "kvcomm_align_kv_q8_batch", "kvcomm_align_kv",
                  "kvcomm_align_kv_q8", "kvcomm_suffix_attn", "kvcomm_suffix_attn_confined_ws", "kvcomm_anchor_predict",
                  "kvcomm_capture_offsets", "kvcomm_quantize_deltas")
 
@@ -179,6 +180,8 @@ def load_library():
     lib.kvcomm_capture_offsets.restype = ctypes.c_int
     lib.kvcomm_align_kv_batch.argtypes = [mp, i32, _CTensor, ctypes.POINTER(_CAlignJob), i32, vp]
     lib.kvcomm_align_kv_batch.restype = ctypes.c_int
+    lib.kvcomm_align_kv_batch_beside.argtypes = [mp, i32, _CTensor, ctypes.POINTER(_CAlignJob), i32, i32, vp]
+    lib.kvcomm_align_kv_batch_beside.restype = ctypes.c_int
     lib.kvcomm_anchor_weights_batch_workspace.argtypes = [mp, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32), i32]
     lib.kvcomm_anchor_weights_batch_workspace.restype = sz
     lib.kvcomm_anchor_weights_batch.argtypes = [mp, i32, i32, f32, _CTensor, ctypes.POINTER(_CWeightsJob), i32, vp,
@@ -600,8 +603,18 @@ def kvcomm_align_kv_batch(model, jobs, gran=W_TOKEN, stream=None):
 
     jobs: list of dicts with base_k, base_v, anchor_dk, anchor_dv (lists of tensors), weights, delta_pos,
     out_k, out_v and optionally anchor_len, anchor_delta_pos."""
+    _align_kv_batch(model, jobs, None, gran, stream)
+
+
+def kvcomm_align_kv_batch_beside(model, jobs, units, gran=W_TOKEN, stream=None):
+    """kvcomm_align_kv_batch (the same bits) as a launch beside other work that leaves it about `units` of the COMPUTE_UNITS."""
+    _align_kv_batch(model, jobs, units, gran, stream)
+
+
+def _align_kv_batch(model, jobs, units, gran, stream):
+    """Both batched updates; units None: the plain launch."""
     lib = load_library()
-    if _done(_native.align_kv_batch(model, gran, jobs, stream)):
+    if _done(_native.align_kv_batch(model, gran, jobs, units, stream)):
         return
     n = len(jobs)
     cjobs = (_CAlignJob * max(n, 1))()
@@ -633,9 +646,11 @@ def kvcomm_align_kv_batch(model, jobs, gran=W_TOKEN, stream=None):
         cjobs[j] = _CAlignJob(d(jd["base_k"], "base_k"), d(jd["base_v"], "base_v"), d(jd["out_k"], "out_k"),
                               d(jd["out_v"], "out_v"), S, int(jd["delta_pos"]), pk, pv, lens, adp, A,
                               None if w is None else w.data_ptr(), 0 if (w is None or not A) else w.numel() // A)
-    _check(lib.kvcomm_align_kv_batch(ctypes.byref(model.c()), gran,
-                                     layout if layout is not None else _CTensor(None, 0, 0, 0), cjobs, n,
-                                     _stream_ptr(stream)))
+    args = (ctypes.byref(model.c()), gran, layout if layout is not None else _CTensor(None, 0, 0, 0), cjobs, n)
+    if units is None:
+        _check(lib.kvcomm_align_kv_batch(*args, _stream_ptr(stream)))
+    else:
+        _check(lib.kvcomm_align_kv_batch_beside(*args, int(units), _stream_ptr(stream)))
 
 
 def _desc_q8(t, what):
@@ -711,7 +726,7 @@ def kvcomm_align_kv_q8_batch(model, jobs, gran=W_TOKEN, stream=None):
     jobs: list of dicts with base_k, base_v, anchor_dk8, anchor_dv8 (lists of uint8 tensors), scale_k, scale_v
     (lists of floats), weights, delta_pos, out_k, out_v and optionally anchor_len, anchor_delta_pos."""
     lib = load_library()
-    if _done(_native.align_kv_q8_batch(model, gran, jobs, stream)):
+    if _done(_native.align_kv_q8_batch(model, gran, jobs, None, stream)):
         return
     n = len(jobs)
     cjobs = (_CAlignQ8Job * max(n, 1))()

@@ -26,6 +26,7 @@ namespace {
 using namespace kvc;
 
 constexpr int kBlock = kAlignBlock;
+constexpr int kComputeUnits = 256;
 
 struct AlignParams {
     AlignJob job[KVCOMM_MAX_BATCH];
@@ -202,29 +203,34 @@ __global__ __launch_bounds__(kBlock, 4) void align_kernel(const AlignParams p)
 //   bf16 rows of 64 channels (half a line per lane group) never gain from two: 8 anchors 258 / 257 / 272, 16: 489 / 480 / 491.
 // (Four anchors in flight at three blocks, which pools of eight took before, and two at four for smaller ones: 4 x 512 tokens, 8 anchors
 // 445, 2 x 1024 tokens, 16 anchors 840, f32 490, 80 layers 2182; 2 anchors 179, now 172.)
-size_t lds_reserve(const AlignParams &p, int64_t n_blocks, int lpr)
+// A launch that has only `units` of the chip's compute units (kvcomm_align_kv_batch_beside) must keep as many requests in flight on fewer
+// of them.  ms per two-stream step beside an attention of the other units, two / three / four / five blocks per unit (config: 5 agents of 4 x 512
+// tokens, 8 anchors, 32 layers; and 4 agents of 4 x 2048 tokens, 16 anchors, 80 layers), one box each:
+//   112 units 6.16 / 6.47 / 6.51 / 6.46 and 82.3 / 83.0 / 83.7 / 84.2;  104 units 5.85 / 5.66 / 5.91 / 5.94 and 79.4 / 77.5 / 78.8 / 78.3;
+//    96 units 5.86 / 5.54 / 5.95 / 5.94 and 79.1 / 76.1 / 77.0 / 77.1;   88 units 6.39 / 6.13 / 5.93 / 5.83 and 84.1 / 82.7 / 81.7 / 82.0;
+//    64 units 6.29 / 6.09 / 5.83 / 5.73 and 82.8 / 79.6 / 80.7 / 80.3.
+size_t lds_reserve(const AlignParams &p, int64_t n_blocks, int lpr, int units)
 {
+    constexpr size_t kThreeBlocks = 81 << 9, kTwoBlocks = 54 << 10;
     double anchors = 0.0;   // of a block, on average
     for (int j = 0; j < p.n_jobs; ++j) anchors += (double)p.job[j].n_token_tiles * p.job[j].n_sel / p.tiles_total;
     const double bytes = 2.0 * (double)n_blocks * 32 * kBlock * (anchors + 2.0);
-    if (bytes < 0.45e9) return 0;
-    return anchors >= 6.0 && bytes >= 0.95e9 && lpr > 4 ? 54 << 10 : 81 << 9;
+    if (bytes < 0.45e9 || units < 92) return 0;
+    return units >= 108 && anchors >= 6.0 && bytes >= 0.95e9 && lpr > 4 ? kTwoBlocks : kThreeBlocks;
 }
 
 template <typename T, int LPR>
-int launch_align(const AlignParams &p, const AlignLaunch &pl, hipStream_t stream)
+int launch_align(const AlignParams &p, const AlignLaunch &pl, int units, hipStream_t stream)
 {
     constexpr int HALF = LPR * Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
     const size_t lds = sizeof(float2) * (size_t)pl.max_tab * HALF + sizeof(float) * (size_t)RPB * pl.max_sel;
     const dim3 grid((unsigned)(p.lh_range * p.tiles_total), (unsigned)(2 * ((p.LH + p.lh_range - 1) / p.lh_range)));
-    return launch(align_kernel<T, LPR>, grid, dim3(kBlock), std::max(lds, lds_reserve(p, pl.n_blocks, LPR)), stream, p);
+    return launch(align_kernel<T, LPR>, grid, dim3(kBlock), std::max(lds, lds_reserve(p, pl.n_blocks, LPR, units)), stream, p);
 }
 
-}  // namespace
-
-extern "C" int kvcomm_align_kv_batch(const kvcomm_model *model, int32_t gran, kvcomm_tensor anchor_layout,
-                                     const kvcomm_align_job *jobs, int32_t n_jobs, void *stream)
+int align_kv_batch(const kvcomm_model *model, int32_t gran, kvcomm_tensor anchor_layout, const kvcomm_align_job *jobs, int32_t n_jobs,
+                   int32_t units, void *stream)
 {
     AlignParams p{};
     AlignLaunch pl{};
@@ -246,18 +252,33 @@ extern "C" int kvcomm_align_kv_batch(const kvcomm_model *model, int32_t gran, kv
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (model->dtype == KVCOMM_BF16) {
         switch (pl.lpr) {
-            case 4: return launch_align<bf16_t, 4>(p, pl, s);
-            case 8: return launch_align<bf16_t, 8>(p, pl, s);
-            case 16: return launch_align<bf16_t, 16>(p, pl, s);
+            case 4: return launch_align<bf16_t, 4>(p, pl, units, s);
+            case 8: return launch_align<bf16_t, 8>(p, pl, units, s);
+            case 16: return launch_align<bf16_t, 16>(p, pl, units, s);
         }
     } else {
         switch (pl.lpr) {
-            case 8: return launch_align<float, 8>(p, pl, s);
-            case 16: return launch_align<float, 16>(p, pl, s);
-            case 32: return launch_align<float, 32>(p, pl, s);
+            case 8: return launch_align<float, 8>(p, pl, units, s);
+            case 16: return launch_align<float, 16>(p, pl, units, s);
+            case 32: return launch_align<float, 32>(p, pl, units, s);
         }
     }
     return KVCOMM_EUNSUPPORTED;
+}
+
+}  // namespace
+
+extern "C" int kvcomm_align_kv_batch(const kvcomm_model *model, int32_t gran, kvcomm_tensor anchor_layout,
+                                     const kvcomm_align_job *jobs, int32_t n_jobs, void *stream)
+{
+    return align_kv_batch(model, gran, anchor_layout, jobs, n_jobs, kComputeUnits, stream);
+}
+
+extern "C" int kvcomm_align_kv_batch_beside(const kvcomm_model *model, int32_t gran, kvcomm_tensor anchor_layout,
+                                            const kvcomm_align_job *jobs, int32_t n_jobs, int32_t units, void *stream)
+{
+    if (units <= 0) return KVCOMM_EINVAL;
+    return align_kv_batch(model, gran, anchor_layout, jobs, n_jobs, units, stream);
 }
 
 extern "C" int kvcomm_align_kv(const kvcomm_model *model, int32_t gran, kvcomm_tensor base_k, kvcomm_tensor base_v,

@@ -32,6 +32,7 @@ struct Library {
     decltype(&kvcomm_anchor_weights_rule) anchor_weights_rule;
     decltype(&kvcomm_anchor_weights_batch) anchor_weights_batch;
     decltype(&kvcomm_align_kv_batch) align_kv_batch;
+    decltype(&kvcomm_align_kv_batch_beside) align_kv_batch_beside;
     decltype(&kvcomm_align_kv_q8_batch) align_kv_q8_batch;
     decltype(&kvcomm_align_kv) align_kv;
     decltype(&kvcomm_align_kv_q8) align_kv_q8;
@@ -404,14 +405,16 @@ PyObject *align_kv_q8(PyObject *, PyObject *const *args, Py_ssize_t n)
     });
 }
 
-// The batched updates: (model, gran, jobs, stream)
+// The batched updates: (model, gran, jobs, units or None, stream)
 template <bool Q8>
 PyObject *update_batch(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
-    return entry<4>(args, n, [](PyObject *const *a) {
+    return entry<5>(args, n, [](PyObject *const *a) {
         const Call c(a[0]);
         const int32_t gran = as_int(a[1]);
         const Items jobs(a[2], kMaxBatch);
+        const bool beside = a[3] != Py_None;
+        const int32_t units = beside ? as_int(a[3]) : 0;
         Anchors k[kMaxBatch], v[kMaxBatch];
         int32_t adp[kMaxBatch][kMaxAnchors];
         float sk[kMaxBatch][kMaxAnchors], sv[kMaxBatch][kMaxAnchors];
@@ -436,12 +439,13 @@ PyObject *update_batch(PyObject *, PyObject *const *args, Py_ssize_t n)
                 cj[j].anchor_scale_v = sv[j];
             }
         }
-        void *stream = stream_of(a[3]);
+        void *stream = stream_of(a[4]);
         return unlocked([&] {
             if constexpr (Q8)
                 return lib.align_kv_q8_batch(&c.m, gran, k[0].layout, cj, jobs.n, stream);
             else
-                return lib.align_kv_batch(&c.m, gran, k[0].layout, cj, jobs.n, stream);
+                return beside ? lib.align_kv_batch_beside(&c.m, gran, k[0].layout, cj, jobs.n, units, stream)
+                              : lib.align_kv_batch(&c.m, gran, k[0].layout, cj, jobs.n, stream);
         });
     });
 }
@@ -530,7 +534,8 @@ PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
     };
     if (!set(lib.weight_slots, "kvcomm_weight_slots") || !set(lib.attn_workspace, "kvcomm_suffix_attn_workspace") ||
         !set(lib.anchor_weights_rule, "kvcomm_anchor_weights_rule") || !set(lib.anchor_weights_batch, "kvcomm_anchor_weights_batch") ||
-        !set(lib.align_kv_batch, "kvcomm_align_kv_batch") || !set(lib.align_kv_q8_batch, "kvcomm_align_kv_q8_batch") ||
+        !set(lib.align_kv_batch, "kvcomm_align_kv_batch") || !set(lib.align_kv_batch_beside, "kvcomm_align_kv_batch_beside") ||
+        !set(lib.align_kv_q8_batch, "kvcomm_align_kv_q8_batch") ||
         !set(lib.align_kv, "kvcomm_align_kv") || !set(lib.align_kv_q8, "kvcomm_align_kv_q8") ||
         !set(lib.suffix_attn, "kvcomm_suffix_attn") || !set(lib.suffix_attn_confined_ws, "kvcomm_suffix_attn_confined_ws") ||
         !set(lib.anchor_predict, "kvcomm_anchor_predict") || !set(lib.capture_offsets, "kvcomm_capture_offsets") ||

@@ -142,6 +142,8 @@ class TwoStreamPipeline:
             kv.kvcomm_anchor_weights_batch(self.model, wjobs, self.temperature, self.gran, workspace=workspace)
             if q8:
                 kv.kvcomm_align_kv_q8_batch(self.model, ajobs, self.gran)
+            elif q is not None and 0 < self.attn_blocks < kv.COMPUTE_UNITS:
+                kv.kvcomm_align_kv_batch_beside(self.model, ajobs, kv.COMPUTE_UNITS - self.attn_blocks, self.gran)
             else:
                 kv.kvcomm_align_kv_batch(self.model, ajobs, self.gran)
             aligned = torch.cuda.Event()

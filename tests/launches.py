@@ -92,7 +92,7 @@ shim.rec_name.restype = ctypes.c_char_p
 shim.rec_grid.restype = shim.rec_block.restype = ctypes.c_uint
 shim.rec_lds.restype = ctypes.c_size_t
 res = []
-for L, H, D, dtype, lens, pools in json.load(sys.stdin):
+for L, H, D, dtype, lens, pools, units in json.load(sys.stdin):
     keep, jobs, at = [], (Job * len(lens))(), [1 << 44]
     def place():                      # tensors that share no bytes
         at[0] += 1 << 40
@@ -104,9 +104,10 @@ for L, H, D, dtype, lens, pools in json.load(sys.stdin):
         jobs[j] = Job(t(), t(), t(), t(), S, 3, ctypes.addressof(anc), ctypes.addressof(anc), ctypes.addressof(ln), None, n, place(), S)
     shim.rec_clear()
     cap = max(lens)
-    f = lib.kvcomm_align_kv_batch
-    f.argtypes = [vp, i32, Tensor, vp, i32, vp]
-    st = f(ctypes.byref(Model(L, H, H, D, dtype, 1e4)), 0, Tensor(None, H * cap * D, cap * D, D), jobs, len(lens), None)
+    lib.kvcomm_align_kv_batch.argtypes = [vp, i32, Tensor, vp, i32, vp]
+    lib.kvcomm_align_kv_batch_beside.argtypes = [vp, i32, Tensor, vp, i32, i32, vp]
+    a = (ctypes.byref(Model(L, H, H, D, dtype, 1e4)), 0, Tensor(None, H * cap * D, cap * D, D), jobs, len(lens))
+    st = lib.kvcomm_align_kv_batch(*a, None) if units is None else lib.kvcomm_align_kv_batch_beside(*a, units, None)
     res.append(dict(status=st, launches=[dict(name=shim.rec_name(i).decode(), grid=[shim.rec_grid(i, k) for k in range(3)],
                                               block=[shim.rec_block(i, k) for k in range(3)], lds=shim.rec_lds(i)) for i in range(shim.rec_count())]))
 json.dump(res, sys.stdout)
@@ -132,6 +133,6 @@ def attention_launches(tmp_path, calls):
 
 
 def align_launches(tmp_path, calls):
-    """Batched updates with per-token weights; calls: (L, Hkv, D, dtype code, segment lengths, anchors per segment) -> per call its status
-    and its launches."""
+    """Batched updates with per-token weights; calls: (L, Hkv, D, dtype code, segment lengths, anchors per segment, units or None) -> per call
+    its status and its launches."""
     return record(tmp_path, ALIGN_DRIVER, calls)

@@ -67,3 +67,28 @@ def test_more_blocks_than_one_axis_of_a_launch_holds():
         for part in range(0, L, 50000):
             want = _rotate(bk[part:part + 50000, :, j].double(), 100 * j, theta, D)
             assert bool(((out_k[part:part + 50000, :, j].double() - want).abs() <= 1e-5 * want.abs().max() + want.abs() * 2.0 ** -8).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_beside_other_work_the_same_bits(dtype):
+    """400 tokens, 8 anchors, 32 layers x 8 heads: large enough for the bound on the blocks per compute unit."""
+    L, H, S, D, A = 32, 8, 400, 128, 8
+    m = kv.Model(L, H, H, D, dtype, 1e4)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(4)
+    rnd = lambda: torch.randn((L, H, S, D), generator=g, device=DEV).to(dtype)
+    job = dict(base_k=rnd(), base_v=rnd(), anchor_dk=[rnd() for _ in range(A)], anchor_dv=[rnd() for _ in range(A)], delta_pos=70,
+               anchor_delta_pos=[70, 3] * 4, weights=torch.softmax(torch.randn((S, A), generator=g, device=DEV), 1))
+
+    def run(call):
+        out = dict(out_k=torch.zeros_like(job["base_k"]), out_v=torch.zeros_like(job["base_v"]))
+        call([{**job, **out}])
+        return out["out_k"], out["out_v"]
+    want = run(lambda j: kv.kvcomm_align_kv_batch(m, j))
+    for units in (1, 64, 96, 200, 1000):
+        print(f"update beside: {dtype} units{units}", flush=True)
+        got = run(lambda j: kv.kvcomm_align_kv_batch_beside(m, j, units))
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    with pytest.raises(kv.KVCommError):
+        run(lambda j: kv.kvcomm_align_kv_batch_beside(m, j, 0))

@@ -76,10 +76,23 @@ def test_the_shapes_of_the_gpu_tests_reach_what_they_name(tmp_path):
                                                          (4000, 8, 64, BF16, [1 << 17, 5], [1, 1], 64)])
 def test_updates_of_any_size_stay_within_a_launch(tmp_path, L, H, D, dtype, lens, pools, rows):
     """A launch holds fewer than 2^32 threads along each axis.  Every (layer, head, token tile, tensor) has its block."""
-    r, = align_launches(tmp_path, [(L, H, D, dtype, lens, pools)])
+    r, = align_launches(tmp_path, [(L, H, D, dtype, lens, pools, None)])
     assert r["status"] == 0 and len(r["launches"]) == 1
     (x, y, z), (threads, _, _) = r["launches"][0]["grid"], r["launches"][0]["block"]
     assert threads == 256 and x * threads < 1 << 32 and y <= 65535 and z == 1
     tiles = sum(-(-S // rows) for S in lens)
     pairs, left = divmod(x, tiles)
     assert left == 0 and pairs * (y // 2 - 1) < L * H <= pairs * (y // 2) and y % 2 == 0
+
+
+def test_blocks_per_unit_of_an_update(tmp_path):
+    """The LDS that a launch reserves bounds its blocks per compute unit (160 KB): two for large launches of large pools, three for
+    others from 0.45 GB on, no bound below; beside other work, on a part of the units, more of them, until the bound goes."""
+    big, few, mid, small, narrow = ((32, 8, 128, BF16, [512] * 4, [8] * 4), (32, 8, 128, BF16, [512] * 4, [4] * 4), (32, 8, 128, BF16, [512], [8]),
+                                    (32, 8, 128, BF16, [77], [6]), (32, 8, 64, BF16, [512] * 8, [8] * 8))
+    want = [(big, None, 2), (few, None, 3), (mid, None, 3), (small, None, 0), (narrow, None, 3), (big, 256, 2), (big, 112, 2), (big, 96, 3),
+            (mid, 96, 3), (big, 88, 0), (big, 1, 0), (small, 96, 0)]
+    for (shape, units, blocks), r in zip(want, align_launches(tmp_path, [s + (u,) for s, u, _ in want])):
+        lds = r["launches"][0]["lds"]
+        assert r["status"] == 0 and (lds < 32768 if blocks == 0 else 163840 // lds == blocks), (shape, units, lds)
+    assert [r["status"] for r in align_launches(tmp_path, [small + (u,) for u in (0, -3)])] == [-1, -1]

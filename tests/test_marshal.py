@@ -79,6 +79,8 @@ def _everything(dtype, order, seq, dev="cuda"):
                    out_v=cache_v[:, :, 3 + j * S:3 + j * S + S]) for j in range(2)]
         kv.kvcomm_align_kv_batch(m, aj, gran)
         outs += [got, cache_k.clone(), cache_v.clone()]
+        kv.kvcomm_align_kv_batch_beside(m, aj, 96, gran)
+        outs += [cache_k.clone(), cache_v.clone()]
         q8 = lambda x: kv.kvcomm_quantize_deltas(m, x, 2.0 ** -8)
         dk8, dv8 = seq(q8(t) for t in dk), seq(q8(t) for t in dv)
         sc = seq([2.0 ** -8, 2.0 ** -7, 1])

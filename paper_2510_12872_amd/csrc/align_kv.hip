@@ -193,14 +193,17 @@ __global__ __launch_bounds__(kBlock, 4) void align_kernel(const AlignParams p)
 
 // LDS that a launch asks for beyond its tables, so that two or three blocks share a compute unit instead of the five that the
 // registers allow (160 KB: three do not fit at 54 KB, four not at 40.5).  A block moves 8 KB per tensor row set, so `bytes` is the
-// whole launch.  us per launch with five / three / two blocks per unit, inputs in no cache (32 layers x 8 heads, bf16, D = 128 unless said):
-//   up to 450 MB the launch is too short to care, and wants every request early: 77 tokens, 5 anchors 30.4 / 32.1 / 33.8 (with the matching);
-//     300 tokens, 5 anchors 46.1 / 48.6 / 53.3; 512, 4 anchors 63.0 / 63.7 / 70.2; above it 400, 8 anchors 87.5 / 84.8 / 89.2;
-//   two blocks from six anchors and 0.95 GB on: 4 x 512 tokens, 6 anchors 392 / 365 / 354, 8: 494 / 465 / 443; 2 x 1024, 16 anchors 891 / 857 / 807;
-//     f32 D 128 8 anchors 494 / 471 / 438; 768 tokens, 8 anchors 181 / 176 / 170; 128 tokens, 64 anchors 193 / 191 / 186;
-//     80 layers, 2048 tokens, 16 anchors 2200 / 2133 / 2037; but 4 anchors 288 / 261 / 279, 5: 341 / 312 / 327; 685 tokens, 8 anchors
-//     (with the matching) 199 / 198 / 203;
-//   bf16 rows of 64 channels (half a line per lane group) never gain from two: 8 anchors 258 / 257 / 272, 16: 489 / 480 / 491.
+// whole launch.  us of the update alone with five / three / two blocks per unit, inputs in no cache (32 layers x 8 heads, bf16, D = 128 unless said):
+//   up to 0.45 GB the launch is too short to care, and wants every request early: 256 tokens, 8 anchors 54.4 / 58.1 / 58.1; 400, 4 anchors
+//     48.6 / 50.0 / 55.3; 600, 3 anchors 58.7 / 63.7 / 74.2.  To 0.75 GB five and three are even (by 2.5 % either way: 512, 8 anchors
+//     106.3 / 108.2 / 107.6; 530, 8 anchors 107.9 / 105.3 / 110.2), then three are better: 900, 5 anchors 139.2 / 131.2 / 145.9;
+//   two blocks from six anchors and 0.95 GB on.  Below, three: 685 tokens, 8 anchors (0.90 GB) 138.8 / 134.9 / 143.3; 512 + 173, 8 anchors
+//     139.3 / 138.1 / 143.3; 900, 6 anchors (0.94 GB) 160.2 / 150.9 / 156.7.  From 0.95 to 1.3 GB the two are even, 3 % either way in 15
+//     shapes: 768, 8 anchors 168.2 / 163.2 / 158.9; f32, 400, 8 anchors 178.3 / 175.1 / 167.8; 1000, 7 anchors 200.3 / 189.0 / 199.1; 600, 12 anchors
+//     175.0 / 167.8 / 171.6.  Above, two: 2 x 512, 8 anchors 239 / 233 / 213; 4 x 512, 6 anchors 388 / 367 / 347, 8: 492 / 465 / 425;
+//     2 x 1024, 16 anchors 871 / 840 / 786; f32, 1024, 8 anchors 474 / 452 / 419; 80 layers, 2048 tokens, 16 anchors 2154 / 2054 / 1976 (at worst
+//     1700, 8 anchors 378 / 356 / 364).  Pools of less than six never: 2048, 4 anchors 273 / 260 / 271; 1800, 5 anchors 278 / 257 / 285;
+//   bf16 rows of 64 channels (half a line per lane group) hardly gain from two: 2048, 8 anchors 240 / 239 / 257, 1024, 16 anchors 222 / 217 / 216.
 // (Four anchors in flight at three blocks, which pools of eight took before, and two at four for smaller ones: 4 x 512 tokens, 8 anchors
 // 445, 2 x 1024 tokens, 16 anchors 840, f32 490, 80 layers 2182; 2 anchors 179, now 172.)
 // A launch that has only `units` of the chip's compute units (kvcomm_align_kv_batch_beside) must keep as many requests in flight on fewer

@@ -1,6 +1,8 @@
-"""Per-token weights in one launch (token_weights_kernel) and in two (partial sums, softmax): which calls take which, and both
+"""Per-token weights in one launch (token_weights_kernel) and in two (partial sums, softmax), both
 against the float64 oracle (1e-5 as for all weights; arg-min and selection exact) where a block's tokens, the wavefronts' share
 of (layer, head) pairs or the anchor tiles do not come out even."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -15,7 +17,7 @@ DEV = "cuda"
 BF, F32 = torch.bfloat16, torch.float32
 RULES = (kv.RULE_L2_SOFTMAX, kv.RULE_NEAREST, kv.RULE_COSINE_SOFTMAX)
 
-# L, H, D, dtype, segment lengths, anchors per segment; one launch for the l2 rules
+# L, H, D, dtype, segment lengths, anchors per segment; one launch
 ONE = [(1, 1, 64, BF, [1], [1]),              # one token, seven of eight wavefronts without a pair
        (3, 3, 64, BF, [9, 17], [5, 2]),       # eight rows per wavefront, ragged last block
        (5, 5, 128, BF, [130], [16]),          # a full tile
@@ -126,17 +128,18 @@ def _launches(tmp_path, calls):
     return record(tmp_path, DRIVER, [[c[0], c[1], c[2], 0 if c[3] == F32 else 1, c[4], c[5], rule] for c, rule in calls])
 
 
-def test_which_calls_take_one_launch(tmp_path):
-    # 4 x 512 tokens: four tokens per block; one segment of 512: two; 200: one; fewer tokens than half the chip and many pairs: two launches
-    sized = [((32, 8, 128, BF, [512] * 4, [8] * 4), 512), ((32, 8, 128, BF, [512], [8]), 256), ((32, 8, 128, BF, [200], [12]), 200)]
-    two = TWO + [(32, 8, 128, BF, [77], [6]), (32, 8, 128, BF, [1024], [64]), (32, 8, 128, BF, [2048], [16])]
-    calls = [(c, 0) for c in ONE + [c for c, _ in sized] + two]
-    for (c, _), r in zip(calls, _launches(tmp_path, calls)):
+def test_the_shapes_of_the_oracle_test_reach_what_they_name(tmp_path):
+    """Under every rule; cosine has its own instantiations, one of whose pools takes two anchor tiles."""
+    calls = [(c, rule) for c in ONE + TWO for rule in RULES]
+    kernels = set()
+    for (c, rule), r in zip(calls, _launches(tmp_path, calls)):
         one = len(r["names"]) == 1 and "token_weights_kernel" in r["names"][0]
-        assert r["status"] == 0 and one == (c not in two), (c, r)
+        assert r["status"] == 0 and one == (c in ONE), (c, rule, r)
         assert one or ("partial_kernel" in r["names"][0] and "finalize_kernel" in r["names"][1])
-        for s, grid in sized:
-            assert c != s or r["grid"] == grid
+        if one:
+            assert ("ELb1E" in r["names"][0]) == (rule == kv.RULE_COSINE_SOFTMAX)
+            kernels.add((re.search(r"token_weights_kernelI(\w+?Li\d+E)Li\d+ELb", r["names"][0])[1], rule == kv.RULE_COSINE_SOFTMAX))
+    assert any(max(c[5]) > 8 for c in ONE) and len(kernels) == 12     # three row widths of two types
 
 
 def test_more_tokens_than_a_launch_holds_blocks(tmp_path):

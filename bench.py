@@ -231,9 +231,11 @@ def compressed_step(torch, kv, w, model, agents, outs, scratches, wjobs, steps=5
                              out_k=ag.cache_k[:, :, w.seg_offset(j):w.seg_offset(j) + w.seg_len],
                              out_v=ag.cache_v[:, :, w.seg_offset(j):w.seg_offset(j) + w.seg_len]))
         qjobs.append(jobs)
-    ev = []
+    ev, ev_step = [], []
 
     def step(record):
+        s0, s1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        s0.record()
         for ai, ag in enumerate(agents):
             kv.kvcomm_anchor_weights_batch(model, wjobs[ai], w.temperature, kv.W_TOKEN, workspace=scratches[ai].workspace)
             if record:
@@ -244,6 +246,9 @@ def compressed_step(torch, kv, w, model, agents, outs, scratches, wjobs, steps=5
                 e1.record()
                 ev.append((e0, e1))
             kv.kvcomm_suffix_attn(model, ag.q, ag.cache_k, ag.cache_v, w.n_ctx, out=outs[ai])
+        s1.record()
+        if record:
+            ev_step.append((s0, s1))
 
     for _ in range(warmup):
         step(False)
@@ -254,6 +259,7 @@ def compressed_step(torch, kv, w, model, agents, outs, scratches, wjobs, steps=5
     torch.cuda.synchronize()
     ms = (time.perf_counter() - t0) / steps * 1e3
     mean, med = _stats(ev)
+    step_med = _stats(ev_step)[1]   # beside the mean: a stall of one step then shows as one
     rows = w.n_layers * w.n_kv_heads * w.n_segments * w.seg_len          # per launch: the segments of one agent
     nbytes = rows * w.head_dim * (4 * 2 + 2 * w.n_anchors)
     two_stream, blocks = None, 192
@@ -273,7 +279,7 @@ def compressed_step(torch, kv, w, model, agents, outs, scratches, wjobs, steps=5
         run(10)
         torch.cuda.synchronize()
         two_stream = (time.perf_counter() - t1) / 10 * 1e3
-    return {"ms_per_step": ms, "tokens_per_s": w.aligned_tokens / (ms * 1e-3),
+    return {"ms_per_step": ms, "median_ms_per_step": step_med, "tokens_per_s": w.aligned_tokens / (ms * 1e-3),
             "two_stream_ms_per_step": two_stream, "two_stream_attn_blocks": blocks if two_stream else None,
             "align_kv_q8_batch": {"avg_call_ms": mean, "median_call_ms": med, "algorithmic_bytes": nbytes,
                                   "GBps": nbytes / mean / 1e6, "frac_of_hbm_peak": nbytes / mean / 1e6 / HBM_PEAK_GBS},

@@ -105,8 +105,8 @@ size_t kvcomm_weight_slots(const kvcomm_model *model, int32_t seg_len, int32_t g
  *   selected_out   DEVICE [n_anchors] int32 (0/1) or NULL.
  *   workspace      DEVICE scratch of at least kvcomm_anchor_weights_workspace() bytes,
  *                  256-byte aligned; contents are undefined afterwards.
- * Distances are accumulated in double precision in a fixed order (two deterministic
- * stages, no floating-point atomics), so results are reproducible run to run.
+ * Distances are accumulated in double precision in a fixed order (one or two launches, no
+ * floating-point atomics), so results are reproducible run to run.
  * Errors: KVCOMM_EINVAL for null/misaligned pointers, seg_len <= 0, n_anchors <= 0,
  * temperature <= 0 or NaN, negative anchor_len, bad granularity; KVCOMM_EWORKSPACE.     */
 size_t kvcomm_anchor_weights_workspace(const kvcomm_model *model, int32_t seg_len,
@@ -254,17 +254,17 @@ int kvcomm_suffix_attn(const kvcomm_model *model, kvcomm_tensor q,
  * a fixed share of the work items.  A block of the bf16 kernels fills a compute unit, so the launch occupies
  * max_blocks of the GPU's 256 compute units and leaves the others to kernels that run beside it on another stream:
  * the memory-bound alignment of the next agent next to the matrix-core-bound attention of the current one.  (Under
- * the chip's power limit the attention loses less than its share of compute units: measured 0.82 ms on 160 of 256
- * against 0.66 ms on all of them.)  max_blocks is spread over the 8 XCDs in launch order; values of at least the
+ * the chip's power limit the attention loses less than its share of compute units: measured 0.85-0.86 ms on 160 of 256
+ * against 0.67-0.70 ms on all of them.)  max_blocks is spread over the 8 XCDs in launch order; values of at least the
  * number of work items give the plain launch.  The same holds for f32 tensors; f32 caches of up to 64 tokens ignore
  * max_blocks (their kernel is small-block and never fills a compute unit), and so does the kernel that joins the
  * partial results of a split launch.
  * The same bits mean the same work items whatever max_blocks is.  A launch that is too small to fill the GPU is cut
  * into many (32 rows each, or runs of keys), which costs more than it gives where max_blocks is a small part of
  * them.  One layer, 8 kv heads, G = 4, D = 128, 3000 keys, us on 160 / 64 / 8 blocks (in brackets: whole 256-row tiles,
- * which kvcomm_suffix_attn takes for launches that fill the GPU): Tq 64  26 / 43 / 279 (63 / 63 / 63), Tq 256
- * 42 / 78 / 572 (66 / 67 / 250), Tq 512  53 / 87 / 564 (63 / 65 / 452); Tq 1000  95 / 167 / 1160 (83 / 152 / 1093): there
- * the cut pieces of 128 ... 240 blocks cost 12 ... 23 % as well.
+ * which kvcomm_suffix_attn takes for launches that fill the GPU): Tq 64  22 / 37 / 254 (66 / 66 / 66), Tq 256
+ * 38 / 70 / 532 (66 / 66 / 255), Tq 512  51 / 89 / 602 (66 / 67 / 488); Tq 1000  76 / 138 / 982 (67 / 125 / 919): there
+ * the cut pieces of 128 ... 240 blocks cost 12 ... 16 % as well.
  * Errors: as kvcomm_suffix_attn; KVCOMM_EINVAL for max_blocks < 8 (one block per XCD is the minimum).          */
 int kvcomm_suffix_attn_confined(const kvcomm_model *model, kvcomm_tensor q,
                                 kvcomm_tensor cache_k, kvcomm_tensor cache_v,

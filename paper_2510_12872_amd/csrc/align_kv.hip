@@ -17,8 +17,8 @@
 // stores).  The base rows are plain loads: anchor matching has just read the base keys, and a shared segment's base
 // cache serves the next agent as well (matching and update of a placeholder of 512 and a prefix segment of 173 tokens,
 // 8 anchors: 205 us, 212 us with non-temporal loads; no difference where nothing is in the last-level cache).  Per-token anchor weights and the cos/sin tables load once per block (LDS).
-// cos/sin: the angle delta * theta^(-2i/D) is formed and reduced modulo 2*pi in double from a
-// host-computed frequency table (kernel argument); sine and cosine of the reduced angle are fp32.
+// cos/sin: the angle delta * theta^(-2i/D) is formed in double from a host-computed frequency table (kernel argument), reduced
+// to the nearest quarter turn and put through short series in double, and rounded to fp32 (rope_cos_sin()).
 #include "align_common.h"
 
 namespace {
@@ -115,7 +115,6 @@ __global__ __launch_bounds__(kBlock, 4) void align_kernel(const AlignParams p)
     }
 
     if (is_k) {
-        // cos/sin of delta * theta^(-2i/D): product and reduction modulo 2*pi in double.
         for (int idx = tid; idx < jb.n_tab * HALF; idx += kBlock) {
             const int r = idx / HALF, i = idx % HALF;
             cs[idx] = rope_cos_sin(p.tab_delta[jb.t0 + r], p.inv_freq[i]);

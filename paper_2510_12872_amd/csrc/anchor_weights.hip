@@ -3,7 +3,7 @@
 // anchor dimension (Eq. "pred", Eq. "ph_update" and the weight step of Algorithm 1; the
 // appendix on long-context anchor matching gives the reduced shape [m,1,1,seq_len,1]).
 //
-// Two deterministic stages, no floating-point atomics:
+// Deterministic stages, no floating-point atomics:
 //   1. dist_partial_kernel streams the key rows once (HBM-bound: (A+1) rows per
 //      (layer, head, token)) and leaves, per block, the squared distance of its chunk of
 //      (layer, head) pairs: partial[chunk][token][anchor] in double.
@@ -711,8 +711,9 @@ __global__ __launch_bounds__(kSegBlock) void finalize_segment_kernel(const Final
 // that against the two-stage kernels.  us per call, two stages -> one, input sets in no cache, D = 128, 32 layers x 8 heads:
 //   4 x 512 tokens, 8 anchors 180.9 -> 175.3 (cosine 189.7 -> 176.9); 512 tokens, 8 anchors 54.8 -> 48.2; 200, 12 anchors 38.0 -> 33.3;
 //   130, 8 anchors 22.2 -> 18.7; 1024, 4 anchors 56.7 -> 53.4; 2 layers x 4 heads, f32, D = 64, 128 tokens, 4 anchors 12.7 -> 10.2.
-// Fewer tokens than compute units (77 tokens, 6 anchors: 15.7 -> 17.4) and pools of many tiles (64 anchors, 1024 tokens: 651 -> 687)
-// stay with the two stages.
+// Where the model says otherwise the two stages stay: 77 tokens with 6 anchors (in one launch 15.7 -> 17.4, while 77 with one anchor and 130
+// with 8 take it), and pools of many tiles (64 anchors, 1024 tokens: 651 -> 687).  Beside an attention on 160 of the 256 units the
+// choice makes no difference (two-stream step of 5 agents 5.49 ms, 5.56 with two stages; on 192 units 5.48 and 5.47).
 constexpr int kTokBlock = 512;
 
 template <typename T, int LPR, int NA, bool COS>

@@ -29,7 +29,7 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
     constexpr int NKS = D / 16, NDB = D / 32, KCH = D / 8, ROWB = D * 2, HALFB = 32 * ROWB;
     constexpr int RPL = 64 / KCH;    // key rows filled by one wavefront-wide direct load
     constexpr int LPT = 32 / RPL;    // direct loads of a 32-key half
-    constexpr int KSWZ = (KCH < 16 ? KCH : 16) - 1;  // chunk swizzles as in attn_mfma_kernel
+    constexpr int KSWZ = (KCH < 16 ? KCH : 16) - 1;  // chunk c of key k sits at c ^ (k & KSWZ) (K), c ^ (4 * (k & 3) & VSWZ) (V)
     constexpr int VSWZ = KCH - 1;
     constexpr int KD = (KSWZ + 1) / RPL > 1 ? (KSWZ + 1) / RPL : 1;  // loads after which the swizzle pattern of the rows repeats
     constexpr int VD = 4 / RPL > 1 ? 4 / RPL : 1;

@@ -5,10 +5,11 @@
 // bf16 path (attn_mfma_kernel): flash-style single pass on bf16 MFMA (16x16x32) with fp32
 // accumulation and an fp32 online softmax, written for gfx950:
 //   * 16x16x32, not 32x32x16: the chip is power-limited under this kernel, and a stream of the small ones sustains
-//     1970-2080 TFLOP/s on N(0,1) data where a stream of the large ones sustains 1740-1800.  A wavefront still owns 32 queries,
+//     1930-1940 TFLOP/s on N(0,1) data where a stream of the large ones sustains 1660-1710.  A wavefront still owns 32 queries,
 //     as two halves of 16 that share every K and V^T operand, so LDS reads and registers are what they were.  Twice as
-//     many matrix instructions to issue take a part of it back: the pipes are busy in 63 % of the cycles at 1.84 GHz instead of
-//     69 % at 1.64.  32 layers, Tq 512, 3072 keys: 654 -> 648 us; 64 heads, 8704 keys: 16 layers 1860 -> 1783 us, 80 layers
+//     many matrix instructions to issue take a part of it back: the pipes are busy in 56 % of the launch's cycles at 1.93 GHz instead of
+//     60 % at 1.80, and a launch on 160 of the 256 units, which leaves power to spare where nothing runs beside it, takes 0.85 ms
+//     instead of 0.81 (0.86 both on a slower chip; beside the update of another agent the step gains 1 %).  32 layers, Tq 512, 3072 keys: 654 -> 648 us; 64 heads, 8704 keys: 16 layers 1860 -> 1783 us, 80 layers
 //     9001 -> 8923 us; one layer, 3072 keys, four runs: 40.8 -> 39.4 us; D = 256, 8 layers, 3072 keys: 423 -> 408 us.
 //   * GQA packing: the G query heads that share a kv head are folded into the row axis of one
 //     tile (row r = i * G + g), so each K/V tile staged in LDS serves G heads at once.
@@ -511,7 +512,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
 
     if (kAccO) mfma_settle<kAccO>(o);
     if constexpr (SPLIT) {
-        // ---- epilogue of a split: accumulators as they are (1 KB runs per store), reference and row sum.
+        // ---- epilogue of a split: accumulators as they are (256-byte runs per store), reference and row sum.
         const int64_t part = ((int64_t)(lh * p.n_row_tiles + rt) * NW + wave) * p.n_splits + split;
         const int lane_e = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
         const int n_e = lane_e & 15, g_e = lane_e >> 4;

@@ -1,4 +1,4 @@
-"""The divisions of the attention kernels' index arithmetic (div_by() of csrc/kvcomm_device.h), on the CPU: every quotient of 31-bit numbers,
+"""The divisions of the kernels' index arithmetic (div_by() of csrc/kvcomm_device.h), on the CPU: every quotient of 31-bit numbers,
 at the multiples of the divisor and next to them, where a multiplication in place of a division goes wrong first."""
 import subprocess
 

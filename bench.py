@@ -3,8 +3,8 @@
 
 A step is one pass of the whole hot path over the Llama-3-8B-shaped five-agent workload
 (workloads.LLAMA8B_5AGENTS): for each of the 5 agents, 4 peer segments of 512 tokens are
-matched against their 8-anchor pools (kvcomm_anchor_weights_batch, one launch per stage for the
-four segments), re-positioned and offset-corrected into the agent's cache (kvcomm_align_kv_batch,
+matched against their 8-anchor pools (kvcomm_anchor_weights_batch, one launch for the four
+segments), re-positioned and offset-corrected into the agent's cache (kvcomm_align_kv_batch,
 one launch), and the agent's 512 suffix queries then attend over the 3072-token cache
 (kvcomm_suffix_attn).  All inputs are synthetic, seeded and
 resident in HBM before the timed region starts.
@@ -30,13 +30,13 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 MFMA, TFLOP/s
 # runs of this script, each scaled by the same counter's reading for a plain 1 GiB copy
 # (profiles/bench_llama8b_5agents_hbm_traffic.md; tests/test_bench_constants.py holds the two together).
 # Not measured live: counters need the profiler.
-HBM_TRAFFIC_READ_WRITTEN = {"align_kv": (2416172237, 268435456),                           # align_kernel
-                            "anchor_weights": (1208103936 + 2206925, 2101965 + 82022),     # dist_partial_kernel + finalize_kernel
-                            "suffix_attn": (537216205, 136314880)}                         # attn_mfma_kernel
+HBM_TRAFFIC_READ_WRITTEN = {"align_kv": (2416109764, 268435456),          # align_kernel
+                            "anchor_weights": (1208103646, 82048),        # token_weights_kernel
+                            "suffix_attn": (537252198, 134217728)}        # attn_mfma_kernel
 HBM_TRAFFIC_BYTES = {k: r + w for k, (r, w) in HBM_TRAFFIC_READ_WRITTEN.items()}
 # Share of the kernel's cycles in which a SIMD's matrix pipe is busy (SQ_VALU_MFMA_BUSY_CYCLES per SIMD over
 # GRBM_GUI_ACTIVE per XCD, profiles/suffix_attn_llama8b_5agents_mfma_counters.md); not measured live either.
-SUFFIX_ATTN_MFMA_BUSY_FRAC = 0.599
+SUFFIX_ATTN_MFMA_BUSY_FRAC = 0.560
 
 
 def cpu_baseline(w):
@@ -681,7 +681,7 @@ def main():
         kernels["anchor_weights"] = {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                      "frac": ach / HBM_PEAK_GBS, "avg_launch_ms": t_weights, "median_launch_ms": med_ms("weights"),
                                      "bytes_per_launch": seg_w.distance_bytes(), "traffic": HBM_TRAFFIC_BYTES["anchor_weights"],
-                                     "note": "two kernels per call (partial distances + softmax finalize)"}
+                                     "note": "one kernel per call (token_weights_kernel: distances and softmax)"}
     if t_attn:
         ach = agent_w.attn_flops() / (t_attn * 1e-3) / 1e12
         kernels["suffix_attn"] = {"bound": "mfma", "achieved": ach, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",

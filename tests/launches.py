@@ -7,6 +7,8 @@ import sys
 
 from paper_2510_12872_amd import build
 
+F32, BF16 = 0, 1   # dtype codes
+
 RECORDER = r"""
 #include <stddef.h>
 #include <string.h>

@@ -7,7 +7,7 @@ import re
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROFILE = os.path.join(ROOT, "profiles", "bench_llama8b_5agents_hbm_traffic.md")
-KERNELS_OF_CALL = {"align_kv": ("align_kernel",), "anchor_weights": ("dist_partial_kernel", "finalize_kernel"),
+KERNELS_OF_CALL = {"align_kv": ("align_kernel",), "anchor_weights": ("token_weights_kernel",),
                    "suffix_attn": ("attn_mfma_kernel",)}
 
 
@@ -52,12 +52,12 @@ def test_bench_traffic_constants_equal_the_profile():
 
 
 def test_streaming_kernels_move_their_algorithmic_bytes():
-    """The align and distance kernels' measured traffic is within 1 % of the algorithmic bytes bench.py divides by."""
+    """The align and weights kernels' measured traffic is within 1 % of the algorithmic bytes bench.py divides by."""
     bench = load_bench()
     from paper_2510_12872_amd import workloads
     one = workloads.scaled(workloads.LLAMA8B_5AGENTS, n_agents=1)
     assert abs(bench.HBM_TRAFFIC_BYTES["align_kv"] / one.align_bytes() - 1) < 0.01
-    assert 0 <= bench.HBM_TRAFFIC_BYTES["anchor_weights"] / one.distance_bytes() - 1 < 0.02   # + partial sums
+    assert 0 <= bench.HBM_TRAFFIC_BYTES["anchor_weights"] / one.distance_bytes() - 1 < 0.02   # + the weights
 
 
 def test_mfma_busy_fraction_equals_the_profile():
@@ -65,3 +65,23 @@ def test_mfma_busy_fraction_equals_the_profile():
     text = open(os.path.join(ROOT, "profiles", "suffix_attn_llama8b_5agents_mfma_counters.md")).read()
     m = re.search(r"= ([0-9.]+) %: the matrix", text)
     assert m and abs(float(m.group(1)) / 100 - bench.SUFFIX_ATTN_MFMA_BUSY_FRAC) < 5e-4
+
+
+def test_the_profiles_are_of_the_kernels_that_the_benchmark_launches(tmp_path):
+    """Else the constants describe other kernels, and the counters have to be taken again."""
+    from launches import BF16, align_launches, attention_launches, record
+    from test_token_weights import DRIVER
+    from paper_2510_12872_amd import workloads
+    w = workloads.LLAMA8B_5AGENTS
+    shape, lens, pools = (w.n_layers, w.n_kv_heads, w.head_dim, BF16), [w.seg_len] * w.n_segments, [w.n_anchors] * w.n_segments
+    weights, = record(tmp_path, DRIVER, [[*shape, lens, pools, 0]])
+    align, = align_launches(tmp_path, [(*shape, lens, pools, None)])
+    attn, = attention_launches(tmp_path, [(w.n_layers, w.n_kv_heads, w.n_q_heads // w.n_kv_heads, w.head_dim, BF16, w.n_ctx, w.tq, 0, True)])
+    launched = {"anchor_weights": weights["names"], "align_kv": [x["name"] for x in align["launches"]],
+                "suffix_attn": [n for n, _ in attn["launches"]]}
+    for call, names in launched.items():
+        assert len(names) == len(KERNELS_OF_CALL[call]) and all(k in n for k, n in zip(KERNELS_OF_CALL[call], names)), (call, names)
+    text = open(os.path.join(ROOT, "profiles", "suffix_attn_llama8b_5agents_mfma_counters.md")).read()
+    args = re.search(r"attn_mfma_kernel<([^>]*)>", text)[1].split(", ")
+    mangled = "".join({"false": "Lb0E", "true": "Lb1E"}.get(a, f"Li{a}E") for a in args)
+    assert f"attn_mfma_kernelI{mangled}E" in launched["suffix_attn"][0]

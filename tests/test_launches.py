@@ -1,9 +1,7 @@
 """What the attention calls launch (CPU only, see launches.py)."""
 import pytest
 
-from launches import align_launches, attention_launches
-
-F32, BF16 = 0, 1
+from launches import BF16, F32, align_launches, attention_launches
 
 
 @pytest.mark.parametrize("dtype,kernel", [(F32, "attn_f32_kernel"), (BF16, "attn_mfma_kernel"), (BF16, "attn_rows_kernel")])

@@ -211,14 +211,17 @@ __global__ __launch_bounds__(kBlock, 4) void align_kernel(const AlignParams p)
 //   112 units 6.16 / 6.47 / 6.51 / 6.46 and 82.3 / 83.0 / 83.7 / 84.2;  104 units 5.85 / 5.66 / 5.91 / 5.94 and 79.4 / 77.5 / 78.8 / 78.3;
 //    96 units 5.86 / 5.54 / 5.95 / 5.94 and 79.1 / 76.1 / 77.0 / 77.1;   88 units 6.39 / 6.13 / 5.93 / 5.83 and 84.1 / 82.7 / 81.7 / 82.0;
 //    64 units 6.29 / 6.09 / 5.83 / 5.73 and 82.8 / 79.6 / 80.7 / 80.3.
-size_t lds_reserve(const AlignParams &p, int64_t n_blocks, int lpr, int units)
+size_t lds_reserve(const AlignParams &p, int64_t n_blocks, int lpr, int es, int units)
 {
     constexpr size_t kThreeBlocks = 81 << 9, kTwoBlocks = 54 << 10;
     double anchors = 0.0;   // of a block, on average
     for (int j = 0; j < p.n_jobs; ++j) anchors += (double)p.job[j].n_token_tiles * p.job[j].n_sel / p.tiles_total;
     const double bytes = 2.0 * (double)n_blocks * 32 * kBlock * (anchors + 2.0);
     if (bytes < 0.45e9 || units < 92) return 0;
-    return units >= 108 && anchors >= 6.0 && bytes >= 0.95e9 && lpr > 4 ? kTwoBlocks : kThreeBlocks;
+    // heads of the pool a multiple of 16 KB apart; rows of 512 bytes and more
+    const bool even = p.s_anc.head * es % 16384 == 0, wide = lpr > 8;
+    const bool two = lpr > 4 && bytes >= 0.95e9 && anchors >= 6.0 && (even || anchors >= 16.0 || (anchors >= 8.0 && (wide || bytes >= 1.8e9)));
+    return units >= 108 && two ? kTwoBlocks : kThreeBlocks;
 }
 
 template <typename T, int LPR>
@@ -228,7 +231,7 @@ int launch_align(const AlignParams &p, const AlignLaunch &pl, int units, hipStre
     constexpr int RPB = kBlock / LPR;
     const size_t lds = sizeof(float2) * (size_t)pl.max_tab * HALF + sizeof(float) * (size_t)RPB * pl.max_sel;
     const dim3 grid((unsigned)(p.lh_range * p.tiles_total), (unsigned)(2 * ((p.LH + p.lh_range - 1) / p.lh_range)));
-    return launch(align_kernel<T, LPR>, grid, dim3(kBlock), std::max(lds, lds_reserve(p, pl.n_blocks, LPR, units)), stream, p);
+    return launch(align_kernel<T, LPR>, grid, dim3(kBlock), std::max(lds, lds_reserve(p, pl.n_blocks, LPR, (int)sizeof(T), units)), stream, p);
 }
 
 int align_kv_batch(const kvcomm_model *model, int32_t gran, kvcomm_tensor anchor_layout, const kvcomm_align_job *jobs, int32_t n_jobs,

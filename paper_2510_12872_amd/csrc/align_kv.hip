@@ -47,10 +47,14 @@ static_assert(sizeof(AlignParams) <= 4096, "kernel arguments are limited to 4 KB
 // Two anchors' rows (four 16-byte loads per lane) are requested together, the first two under the block's set-up.  What bounds the kernel is
 // HBM, and past about 64 KB in flight per compute unit more requests cost: pages are opened and closed out of order.  So the
 // launch reserves LDS that keeps the number of blocks per compute unit at what measured best (lds_reserve()).
-template <typename T, int LPR>
-__global__ __launch_bounds__(kBlock, 4) void align_kernel(const AlignParams p)
+// SMALL (few_rows()): what bounds the launch is the latency of a block, one group of anchors behind the other.  Four are requested together
+// (all segments have as many), the set-up's own inputs before them, and the rows unconditionally (lanes behind the segment re-read its last
+// row): only then does the compiler wait for the set-up's loads alone while the rows stay in flight.  (Large launches gain nothing
+// from that: their other blocks fill the wait, and it moved them by -5 ... +5 %.)
+template <typename T, int LPR, bool SMALL>
+__global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const AlignParams p)
 {
-    constexpr int INFLIGHT = 2;
+    constexpr int INFLIGHT = SMALL ? 4 : 2;
     constexpr int EPV = Elem<T>::EPV;
     constexpr int HALF = LPR * EPV;  // D / 2
     constexpr int RPB = kBlock / LPR;
@@ -89,16 +93,26 @@ __global__ __launch_bounds__(kBlock, 4) void align_kernel(const AlignParams p)
     const float *wsrc = jb.weights;
     if (p.gran != KVCOMM_W_SEGMENT)
         wsrc += ((int64_t)(p.gran == KVCOMM_W_LAYER_HEAD_TOKEN ? lh : 0) * jb.S + tile * RPB) * jb.w_pitch;
-    float w_first = 0.f;
-    if (tid < n_w) w_first = wsrc[tid];
+    constexpr int W = !SMALL ? 1 : RPB / 4 < 4 ? RPB / 4 : 4;   // n_w <= RPB * 64 = RPB / 4 weights of every thread
+    float w_first[W] = {};
+#pragma unroll
+    for (int u = 0; u < W; ++u)
+        if (tid + u * kBlock < n_w) w_first[u] = wsrc[tid + u * kBlock];
+    double freq = 0.0;
+    int delta = 0;
+    if (SMALL && is_k && tid < jb.n_tab * HALF) {
+        freq = p.inv_freq[tid % HALF];
+        delta = p.tab_delta[jb.t0 + tid / HALF];
+    }
     auto keep_weight = [&](int idx, float w) __attribute__((always_inline)) {
         const int r = div_by(idx, p.by_pitch[ji]), c = idx - r * jb.w_pitch;
         if ((sel >> c) & 1) w_lds[r * n_sel + __popcll(sel & (((uint64_t)1 << c) - 1))] = w;
     };
 
     const int l = div_by(lh, p.by_H), h = lh - l * p.H;
-    const T *xp = bp + l * sb.layer + h * sb.head + t * sb.token + col0;
-    const int64_t aoff = l * p.s_anc.layer + h * p.s_anc.head + t * p.s_anc.token + col0;
+    const int tr = SMALL ? min(t, jb.S - 1) : t;
+    const T *xp = bp + l * sb.layer + h * sb.head + tr * sb.token + col0;
+    const int64_t aoff = l * p.s_anc.layer + h * p.s_anc.head + tr * p.s_anc.token + col0;
     u32x4 rlo, rhi, rows[INFLIGHT][2];
     auto request_group = [&](int a) __attribute__((always_inline)) {
 #pragma unroll
@@ -108,20 +122,26 @@ __global__ __launch_bounds__(kBlock, 4) void align_kernel(const AlignParams p)
             rows[u][1] = load16_stream(d + HALF);
         }
     };
-    if (valid) {
+    if (SMALL || valid) {
         rlo = load16(xp);   // plain: see the header
         rhi = load16(xp + HALF);
-        if (n_sel >= INFLIGHT) request_group(0);
+        if (SMALL || n_sel >= INFLIGHT) request_group(0);
     }
 
     if (is_k) {
-        for (int idx = tid; idx < jb.n_tab * HALF; idx += kBlock) {
+        if (SMALL && tid < jb.n_tab * HALF) {
+            asm volatile("" : "+v"(delta));   // (else its conversion, and the wait for it, moves up to its load)
+            cs[tid] = rope_cos_sin(delta, freq);
+        }
+        for (int idx = SMALL ? tid + kBlock : tid; idx < jb.n_tab * HALF; idx += kBlock) {
             const int r = idx / HALF, i = idx % HALF;
             cs[idx] = rope_cos_sin(p.tab_delta[jb.t0 + r], p.inv_freq[i]);
         }
     }
-    if (tid < n_w) keep_weight(tid, w_first);
-    for (int idx = tid + kBlock; idx < n_w; idx += kBlock) keep_weight(idx, wsrc[idx]);
+#pragma unroll
+    for (int u = 0; u < W; ++u)
+        if (tid + u * kBlock < n_w) keep_weight(tid + u * kBlock, w_first[u]);
+    for (int idx = tid + W * kBlock; idx < n_w; idx += kBlock) keep_weight(idx, wsrc[idx]);
     __syncthreads();
     if (!valid) return;
 
@@ -180,6 +200,13 @@ __global__ __launch_bounds__(kBlock, 4) void align_kernel(const AlignParams p)
         a += INFLIGHT;
         if (a + INFLIGHT <= n_sel) request_group(a);
     }
+    if (SMALL && a + 2 <= n_sel) {
+        const T *d0 = static_cast<const T *>(p.anc[which][a0 + a]) + aoff, *d1 = static_cast<const T *>(p.anc[which][a0 + a + 1]) + aoff;
+        const u32x4 r[4] = {load16_stream(d0), load16_stream(d0 + HALF), load16_stream(d1), load16_stream(d1 + HALF)};
+        accumulate(a, r[0], r[1]);
+        accumulate(a + 1, r[2], r[3]);
+        a += 2;
+    }
     if (a < n_sel) {
         const T *d = static_cast<const T *>(p.anc[which][a0 + a]) + aoff;
         accumulate(a, load16_stream(d), load16_stream(d + HALF));
@@ -224,6 +251,24 @@ size_t lds_reserve(const AlignParams &p, int64_t n_blocks, int lpr, int es, int 
     return units >= 108 && two ? kTwoBlocks : kThreeBlocks;
 }
 
+// Four anchors in flight (SMALL): pools of four and more (in every segment) whose rows are at most 2.7 MB per anchor, keys and values, where three
+// blocks per unit (what the registers of four allow) hold the launch or a pool has 32 anchors, long chains.  us with two / four (in brackets:
+// four, rows requested behind the set-up), 32 layers x 8 heads, bf16, D = 128 unless said:
+//   8 tokens, 8 anchors 6.6 / 5.9 (6.1), 64 anchors 25.6 / 18.9 (24.2); 16 tokens, 16 anchors 10.6 / 9.1 (10.0); f32, D = 64, 8 x 4, 77 tokens, 8 anchors
+//   6.7 / 5.8 (5.8), 16: 9.7 / 7.8 (8.1); 80 layers, 8 tokens, 64 anchors 49.0 / 35.3 (31.7); one token, f32, 8 anchors 5.4 / 5.2 (4.7);
+//   but 33 tokens, 8 anchors 12.2 / 13.3 (14.9); 64 tokens, 16 anchors 26.3 / 29.1 (31.1); 80 layers, one token, 8 anchors 6.2 / 7.4 (7.0).
+// Of 480 launches of pools from four on the rule's choice is 0.3 % slower on average than the faster one.
+bool few_rows(const AlignParams &p, int64_t n_blocks, int max_sel, int row_bytes)
+{
+    int64_t tokens = 0;
+    int min_sel = max_sel;
+    for (int j = 0; j < p.n_jobs; ++j) {
+        tokens += p.job[j].S;
+        min_sel = std::min<int>(min_sel, p.job[j].n_sel);
+    }
+    return min_sel >= 4 && 2 * tokens * p.LH * row_bytes <= 2700000 && (2 * n_blocks <= 3 * kComputeUnits || max_sel >= 32);
+}
+
 template <typename T, int LPR>
 int launch_align(const AlignParams &p, const AlignLaunch &pl, int units, hipStream_t stream)
 {
@@ -231,7 +276,8 @@ int launch_align(const AlignParams &p, const AlignLaunch &pl, int units, hipStre
     constexpr int RPB = kBlock / LPR;
     const size_t lds = sizeof(float2) * (size_t)pl.max_tab * HALF + sizeof(float) * (size_t)RPB * pl.max_sel;
     const dim3 grid((unsigned)(p.lh_range * p.tiles_total), (unsigned)(2 * ((p.LH + p.lh_range - 1) / p.lh_range)));
-    return launch(align_kernel<T, LPR>, grid, dim3(kBlock), std::max(lds, lds_reserve(p, pl.n_blocks, LPR, (int)sizeof(T), units)), stream, p);
+    const auto kernel = few_rows(p, pl.n_blocks, pl.max_sel, 32 * LPR) ? align_kernel<T, LPR, true> : align_kernel<T, LPR, false>;
+    return launch(kernel, grid, dim3(kBlock), std::max(lds, lds_reserve(p, pl.n_blocks, LPR, (int)sizeof(T), units)), stream, p);
 }
 
 int align_kv_batch(const kvcomm_model *model, int32_t gran, kvcomm_tensor anchor_layout, const kvcomm_align_job *jobs, int32_t n_jobs,

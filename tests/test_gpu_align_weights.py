@@ -19,7 +19,19 @@ def _rotate(x, pos, theta, D):
 @pytest.mark.parametrize("dtype,D", [(torch.bfloat16, 64), (torch.bfloat16, 128), (torch.bfloat16, 256), (torch.float32, 64), (torch.float32, 256)])
 @pytest.mark.parametrize("A,S", [(1, 1), (2, 31), (3, 33), (9, 65), (64, 70)])
 def test_selected_columns(dtype, D, A, S):
-    L, H, theta = 2, 3, 1e4
+    _check_columns(dtype, D, A, S, 2, 3)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,D,A,S,L,H", [(torch.bfloat16, 128, 4, 8, 32, 8), (torch.bfloat16, 128, 7, 77, 32, 8), (torch.float32, 128, 6, 33, 24, 8),
+                                             (torch.bfloat16, 64, 11, 65, 60, 8), (torch.bfloat16, 256, 33, 5, 80, 8), (torch.bfloat16, 128, 48, 3, 80, 8)])
+def test_selected_columns_of_larger_launches(dtype, D, A, S, L, H):
+    """On both sides of the lines between two and four anchors in flight."""
+    _check_columns(dtype, D, A, S, L, H)
+
+
+def _check_columns(dtype, D, A, S, L, H):
+    theta = 1e4
     m = kv.Model(L, H, H, D, dtype, theta)
     g = torch.Generator(device=DEV)
     g.manual_seed(A * 100 + S + D)
@@ -29,7 +41,7 @@ def test_selected_columns(dtype, D, A, S):
     lens = [S - 1 if a % 3 == 1 else S for a in range(A)]
     adp = [(7, 131071, 40)[a % 3] for a in range(A)]
     for gran, slots in ((kv.W_TOKEN, S), (kv.W_LAYER_HEAD_TOKEN, L * H * S), (kv.W_SEGMENT, 1)):
-        print(f"update weights: {dtype} D{D} A{A} S{S} gran{gran}", flush=True)
+        print(f"update weights: {dtype} D{D} A{A} S{S} L{L} H{H} gran{gran}", flush=True)
         w = torch.softmax(rnd(slots, A), 1)
         for a in range(A):
             if lens[a] < S:

@@ -94,3 +94,12 @@ def test_blocks_per_unit_of_an_update(tmp_path):
         lds = r["launches"][0]["lds"]
         assert r["status"] == 0 and (lds < 32768 if blocks == 0 else 163840 // lds == blocks), (shape, units, lds)
     assert [r["status"] for r in align_launches(tmp_path, [small + (u,) for u in (0, -3)])] == [-1, -1]
+
+
+def test_anchors_in_flight_of_an_update(tmp_path):
+    """Four where few rows are moved (by one round of blocks, or for pools of 32 and more) and every segment has four, two elsewhere."""
+    want = [((2, 3, 64, BF16, [70], [9]), True), ((2, 3, 64, BF16, [70], [3]), False), ((2, 3, 64, BF16, [70, 20], [9, 3]), False),
+            ((32, 8, 128, BF16, [8], [4]), True), ((32, 8, 128, BF16, [33], [8]), False), ((80, 8, 128, BF16, [3], [8]), False),
+            ((80, 8, 128, BF16, [3], [48]), True), ((80, 8, 128, BF16, [20], [48]), False), ((32, 8, 128, BF16, [512] * 4, [8] * 4), False)]
+    for (shape, four), r in zip(want, align_launches(tmp_path, [s + (None,) for s, _ in want])):
+        assert r["status"] == 0 and ("ELb1E" in r["launches"][0]["name"]) == four, (shape, r)

@@ -838,12 +838,18 @@ __global__ __launch_bounds__(kTokBlock, COS ? 2 : 4) void token_weights_kernel(c
 // the whole chip's time for the bytes, is at most the chip's time plus the 7 us of partial sums and second launch; of equal sizes the
 // larger (longer accesses).  Pools of more than 8 anchors only up to 150 us, where that second launch still weighs: 512 tokens, 16
 // anchors, 32 layers x 8 heads 98.8 -> 91.0, but 2048 tokens 343 -> 362 (16 wavefronts of 17 rows each on every unit).
-// The modelled line holds to 2 % over 60 shapes: 300 tokens, 8 anchors 36.6 (two stages) and 36.8; 17 tokens, f32, 4 anchors 13.1 and 13.3.
-int token_shift(const kvcomm_model &m, const kvcomm_weights_job *jobs, const DistJob *dist, int n_jobs, int max_sel, bool cosine)
+// The modelled line holds to 3 % over 300 shapes: 300 tokens, 8 anchors 36.6 (two stages) and 36.8; 17 tokens, f32, 4 anchors 13.1 and 13.3.
+// Heads that lie an odd multiple of 512 KB apart meet in the same memory channels, and the rows that a block has in flight are those of many
+// heads: from 128 pairs of layer and head and four anchors on, two stages (2048 tokens, D = 128, 6 anchors: 16 layers 77.5 and 84.9, 24 118.6 and 119.5,
+// 32 147 and 161; cosine, 8 anchors, 32 layers 190 and 216; f32, 1024 tokens, 8 anchors 183 and 197; but 12 layers 63.8 and 59.5, and at 32 layers
+// 2000 tokens 154 and 145, 1024 77.3 and 72.5); where the pools happen to lie matters too: another run had 16 layers, 8 anchors at 99 both ways.
+int token_shift(const kvcomm_model &m, const kvcomm_tensor &anchor_layout, const kvcomm_weights_job *jobs, const DistJob *dist, int n_jobs, int max_sel,
+                bool cosine)
 {
     if (max_sel > kAnchorTile) return -1;
     const double row = (double)m.head_dim * elem_size(m.dtype);
     const int LH = m.n_layers * m.n_kv_heads, rpw = 1024 / (int)row, nw = kTokBlock / 64;   // rows of a wavefront, wavefronts
+    if (max_sel >= 4 && LH >= 128 && anchor_layout.stride_head * elem_size(m.dtype) % (1 << 20) == 1 << 19) return -1;
     double bytes = 0.0;
     for (int j = 0; j < n_jobs; ++j) bytes += (double)LH * row * (dist[j].n_sel + 1) * jobs[j].seg_len;
     const double chip_us = bytes / 6.4e6;
@@ -1080,7 +1086,7 @@ extern "C" int kvcomm_anchor_weights_batch(const kvcomm_model *model, int32_t gr
     }
     if (dist_blocks > 0x7fffffff || final_blocks > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
 
-    const int shift = gran == KVCOMM_W_TOKEN ? token_shift(*model, jobs, dp.job, n_jobs, max_sel, cosine) : -1;
+    const int shift = gran == KVCOMM_W_TOKEN ? token_shift(*model, anchor_layout, jobs, dp.job, n_jobs, max_sel, cosine) : -1;
     if (shift >= 0) {
         dp.tok_shift = shift;
         int64_t blocks = 0;

@@ -147,3 +147,12 @@ def test_more_tokens_than_a_launch_holds_blocks(tmp_path):
     below, above = _launches(tmp_path, [((4, 4, 256, F32, [S], [8]), 0) for S in ((1 << 23) - 1, 1 << 23)])
     for r, n in ((below, 1), (above, 2)):
         assert r["status"] == 0 and len(r["names"]) == n and all(t < 1 << 32 for t in r["threads"]), r
+
+
+def test_rows_that_meet_in_the_same_memory_channels(tmp_path):
+    """Heads an odd multiple of 512 KB apart, many of them and four anchors or more: two stages, which do not have several heads in flight."""
+    f = lambda L, D, dtype, S, n: (L, 8, D, dtype, [S], [n])
+    two = [f(32, 128, BF, 2048, 4), f(16, 128, BF, 2048, 8), f(32, 128, F32, 1024, 8), f(32, 256, BF, 1024, 4), f(24, 64, F32, 2048, 6), f(32, 128, BF, 6144, 4)]
+    one = [f(32, 128, BF, 2048, 3), f(15, 128, BF, 2048, 8), f(32, 128, BF, 2000, 8), f(32, 128, BF, 1024, 8), f(32, 128, BF, 4096, 4), f(32, 128, F32, 512, 8)]
+    for c, r in zip(two + one, _launches(tmp_path, [(c, 0) for c in two + one])):
+        assert r["status"] == 0 and len(r["names"]) == (1 if c in one else 2), (c, r)

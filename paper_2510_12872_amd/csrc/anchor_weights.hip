@@ -839,6 +839,8 @@ __global__ __launch_bounds__(kTokBlock, COS ? 2 : 4) void token_weights_kernel(c
 // larger (longer accesses).  Pools of more than 8 anchors only up to 150 us, where that second launch still weighs: 512 tokens, 16
 // anchors, 32 layers x 8 heads 98.8 -> 91.0, but 2048 tokens 343 -> 362 (16 wavefronts of 17 rows each on every unit).
 // The modelled line holds to 3 % over 300 shapes: 300 tokens, 8 anchors 36.6 (two stages) and 36.8; 17 tokens, f32, 4 anchors 13.1 and 13.3.
+// Two and three anchors of bf16 rows of 256 channels take 15 % more a step where the blocks leave compute units empty (128 tokens, 3 anchors 18.2 in
+// two stages and 20.1, 140 tokens 19.6 and 20.4; 170 tokens 21.6 and 20.8; one anchor and four 14.2 and 20.4 either way).
 // Heads that lie an odd multiple of 512 KB apart meet in the same memory channels, and the rows that a block has in flight are those of many
 // heads: from 128 pairs of layer and head and four anchors on, two stages (2048 tokens, D = 128, 6 anchors: 16 layers 77.5 and 84.9, 24 118.6 and 119.5,
 // 32 147 and 161; cosine, 8 anchors, 32 layers 190 and 216; f32, 1024 tokens, 8 anchors 183 and 197; but 12 layers 63.8 and 59.5, and at 32 layers
@@ -850,6 +852,7 @@ int token_shift(const kvcomm_model &m, const kvcomm_tensor &anchor_layout, const
     const double row = (double)m.head_dim * elem_size(m.dtype);
     const int LH = m.n_layers * m.n_kv_heads, rpw = 1024 / (int)row, nw = kTokBlock / 64;   // rows of a wavefront, wavefronts
     if (max_sel >= 4 && LH >= 128 && anchor_layout.stride_head * elem_size(m.dtype) % (1 << 20) == 1 << 19) return -1;
+    const bool few_wide = m.dtype == KVCOMM_BF16 && m.head_dim == 256 && !cosine && (max_sel == 2 || max_sel == 3);
     double bytes = 0.0;
     for (int j = 0; j < n_jobs; ++j) bytes += (double)LH * row * (dist[j].n_sel + 1) * jobs[j].seg_len;
     const double chip_us = bytes / 6.4e6;
@@ -864,7 +867,7 @@ int token_shift(const kvcomm_model &m, const kvcomm_tensor &anchor_layout, const
         if (blocks * kTokBlock >= (int64_t)1 << 32) continue;   // more threads than a launch holds
         const int per_cu = cosine ? 1 : blocks > 256 ? 2 : 1, lh_step = (nw / tiles) * (rpw >> shift);
         const double rounds = (double)((blocks + 256 * per_cu - 1) / (256 * per_cu));
-        const double step_us = std::max(cosine ? 1.7 : 0.8, per_cu * nw * 1024.0 * (width + 1) / 35e3);
+        const double step_us = (few_wide && blocks <= 150 ? 1.15 : 1.0) * std::max(cosine ? 1.7 : 0.8, per_cu * nw * 1024.0 * (width + 1) / 35e3);
         const double us = std::max(chip_us, rounds * (2.0 + step_us * ((LH + lh_step - 1) / lh_step)));
         if (us <= best_us) {
             best_us = us;

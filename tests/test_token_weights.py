@@ -156,3 +156,9 @@ def test_rows_that_meet_in_the_same_memory_channels(tmp_path):
     one = [f(32, 128, BF, 2048, 3), f(15, 128, BF, 2048, 8), f(32, 128, BF, 2000, 8), f(32, 128, BF, 1024, 8), f(32, 128, BF, 4096, 4), f(32, 128, F32, 512, 8)]
     for c, r in zip(two + one, _launches(tmp_path, [(c, 0) for c in two + one])):
         assert r["status"] == 0 and len(r["names"]) == (1 if c in one else 2), (c, r)
+
+
+def test_few_wide_rows(tmp_path):
+    """Two and three anchors of 128 tokens of 256 bf16 channels leave half of the compute units empty: two stages; not for narrower rows or more tokens."""
+    calls = [((32, 8, 256, BF, [S], [n]), 0) for S, n in ((128, 2), (140, 3), (170, 2), (200, 3), (140, 4))] + [((32, 8, 128, F32, [140], [3]), 0)]
+    assert [len(r["names"]) for r in _launches(tmp_path, calls)] == [2, 2, 1, 1, 1, 1]

@@ -223,12 +223,14 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
 //   up to 0.45 GB the launch is too short to care, and wants every request early: 256 tokens, 8 anchors 54.4 / 58.1 / 58.1; 400, 4 anchors
 //     48.6 / 50.0 / 55.3; 600, 3 anchors 58.7 / 63.7 / 74.2.  To 0.75 GB five and three are even (by 2.5 % either way: 512, 8 anchors
 //     106.3 / 108.2 / 107.6; 530, 8 anchors 107.9 / 105.3 / 110.2), then three are better: 900, 5 anchors 139.2 / 131.2 / 145.9;
-//   two blocks from six anchors and 0.95 GB on.  Below, three: 685 tokens, 8 anchors (0.90 GB) 138.8 / 134.9 / 143.3; 512 + 173, 8 anchors
-//     139.3 / 138.1 / 143.3; 900, 6 anchors (0.94 GB) 160.2 / 150.9 / 156.7.  From 0.95 to 1.3 GB the two are even, 3 % either way in 15
-//     shapes: 768, 8 anchors 168.2 / 163.2 / 158.9; f32, 400, 8 anchors 178.3 / 175.1 / 167.8; 1000, 7 anchors 200.3 / 189.0 / 199.1; 600, 12 anchors
-//     175.0 / 167.8 / 171.6.  Above, two: 2 x 512, 8 anchors 239 / 233 / 213; 4 x 512, 6 anchors 388 / 367 / 347, 8: 492 / 465 / 425;
-//     2 x 1024, 16 anchors 871 / 840 / 786; f32, 1024, 8 anchors 474 / 452 / 419; 80 layers, 2048 tokens, 16 anchors 2154 / 2054 / 1976 (at worst
-//     1700, 8 anchors 378 / 356 / 364).  Pools of less than six never: 2048, 4 anchors 273 / 260 / 271; 1800, 5 anchors 278 / 257 / 285;
+//   two blocks from six anchors and 0.95 GB on where the heads of a pool lie a multiple of 16 KB apart.  Below, three: 685 tokens, 8 anchors
+//     (0.90 GB) 138.8 / 134.9 / 143.3; 512 + 173, 8 anchors 139.3 / 138.1 / 143.3; 900, 6 anchors (0.94 GB) 160.2 / 150.9 / 156.7.  Above: 768, 8 anchors
+//     168.2 / 163.2 / 158.9; 2 x 512, 8 anchors 239 / 233 / 213; 4 x 512, 6 anchors 388 / 367 / 347, 8: 492 / 465 / 425; f32, 1024, 8 anchors
+//     474 / 452 / 419.  Pools of less than six never: 2048, 4 anchors 273 / 260 / 271; 1800, 5 anchors 278 / 257 / 285;
+//   heads any other distance apart: two for 16 anchors and more (2 x 1024 871 / 840 / 786, 80 layers, 2048 tokens 2154 / 2054 / 1976), and for eight and more
+//     from 1.8 GB on or with rows of 512 bytes and more; else three: 1000 tokens, 7 anchors 200.3 / 189.0 / 199.1; 600, 12 anchors 175.0 / 167.8 /
+//     171.6; and three / two: 1000, 9 anchors 232 / 242; 4 x 500, 6 anchors 346 / 353; 3 x 300, 8 anchors 193 / 201; 80 layers of 300, 8 anchors 156 / 164
+//     (at worst, of 204 shapes: 1700, 8 anchors, 378 / 356 / 364);
 //   bf16 rows of 64 channels (half a line per lane group) hardly gain from two: 2048, 8 anchors 240 / 239 / 257, 1024, 16 anchors 222 / 217 / 216.
 // (Four anchors in flight at three blocks, which pools of eight took before, and two at four for smaller ones: 4 x 512 tokens, 8 anchors
 // 445, 2 x 1024 tokens, 16 anchors 840, f32 490, 80 layers 2182; 2 anchors 179, now 172.)

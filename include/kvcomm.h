@@ -256,7 +256,7 @@ int kvcomm_suffix_attn(const kvcomm_model *model, kvcomm_tensor q,
  * the memory-bound alignment of the next agent next to the matrix-core-bound attention of the current one.  (Under
  * the chip's power limit the attention loses less than its share of compute units: measured 0.85-0.86 ms on 160 of 256
  * against 0.67-0.70 ms on all of them.)  max_blocks is spread over the 8 XCDs in launch order; values of at least the
- * number of work items give the plain launch.  The same holds for f32 tensors; f32 caches of up to 64 tokens ignore
+ * number of work items give the plain launch.  The same holds for f32 tensors; f32 caches of up to 16 tokens may ignore
  * max_blocks (their kernel is small-block and never fills a compute unit), and so does the kernel that joins the
  * partial results of a split launch.
  * The same bits mean the same work items whatever max_blocks is.  A launch that is too small to fill the GPU is cut

@@ -19,7 +19,7 @@ MARSHAL = os.path.join(_HERE, "_marshal.so")
 PROBE_SRC = os.path.join(_HERE, "tools", "hbm_stream_probe.hip")
 PROBE = os.path.join(_HERE, "tools", "hbm_stream_probe")
 SOURCES = ["align_kv.hip", "anchor_weights.hip", "anchor_update.hip", "delta_q8.hip", "suffix_attn.hip",
-           "attn_rows.hip", "status.hip"]
+           "attn_rows.hip", "attn_f32.hip", "status.hip"]
 
 # -packed-fp32-ops: keep the compiler from forming packed fp32 instructions.
 HIPCC_FLAGS = [

@@ -114,7 +114,18 @@ static inline size_t attn_workspace(const kvcomm_model &m, const AttnPlan &pl)
     return pl.n_splits > 1 ? attn_parts(m, pl) * sizeof(float) * (32 * (size_t)m.head_dim + 64) : 0;
 }
 
+// Groups of 16 packed rows of an fp32 block: one as long as all blocks run at once, two above (they share what they load).  us with
+// one / two, 4 layers x 8 heads, G = 4: D = 128, 1056 keys, Tq 32 (256 blocks of one group) 44.5 / 49.8, 1088 keys, Tq 64 (512) 58.6 / 55.6; one
+// layer, 1152 keys, Tq 128 (256) 34.8 / 52.5; 2 layers, 400 keys, Tq 100 (400) 26.0 / 25.4; D = 64, 540 keys, Tq 40 (320) 21.0 / 18.7; D = 256,
+// 1056 keys, Tq 32 (256) 84 / 90, 1088 keys, Tq 64 (512) 118 / 97; but 128 keys, Tq 128, 4 layers x 4 heads, G = 8 (1024) 23.2 / 24.3.
+static inline int attn_f32_groups(const kvcomm_model &m, int tq)
+{
+    const int64_t rows = (int64_t)(m.n_q_heads / m.n_kv_heads) * tq;
+    return (int64_t)m.n_layers * m.n_kv_heads * ((rows + 15) / 16) <= kChipCUs ? 1 : 2;
+}
+
 int launch_attn_rows(const AttnParams &p, int D, unsigned n_blocks, hipStream_t stream);
+int launch_attn_f32(const AttnParams &p, int D, unsigned n_blocks, hipStream_t stream);
 int launch_attn_combine(const AttnParams &p, int D, hipStream_t stream);
 
 }  // namespace kvc

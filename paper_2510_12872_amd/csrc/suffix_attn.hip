@@ -41,8 +41,7 @@
 //     (query, head) axis = 64 queries of all four heads for G = 4; one block per CU.
 //   * Row tiles are ordered longest-first and the block index is remapped so that the row
 //     tiles of one (layer, kv head) run on the same XCD and share its L2.
-// fp32 path (attn_f32_kernel): the same transposed products on fp32 MFMA with expf and an online softmax, fp32
-// throughout.
+// fp32 path: attn_f32.hip.
 #include <float.h>
 
 #include "attn_common.h"
@@ -591,320 +590,6 @@ __global__ __launch_bounds__(64 * NW, WPE) void attn_mfma_kernel(const AttnParam
     } while (item < x_count);
 }
 
-// ------------------------------------------------------------------------------- fp32 path
-// Caches of up to kF32RowKeys tokens: one wavefront per query row, one key per lane, dot products on the vector ALU.  One
-// chunk of keys, about 5 us; the kernel below has 12 us of latency whatever the size (one layer, 32 heads, one key).
-constexpr int kF32RowKeys = 64;
-
-template <int D>
-__global__ __launch_bounds__(256) void attn_f32_row_kernel(const AttnParams p)
-{
-    constexpr int CPL = D / 64;  // output channels per lane
-    __shared__ float q_lds[4][D];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + wave;  // over (l, hq, i)
-    const int Hq = p.Hkv * p.G;
-    if (row >= (int64_t)p.L * Hq * p.tq) return;
-    const int i = (int)(row % p.tq);
-    const int hq = (int)((row / p.tq) % Hq);
-    const int l = (int)(row / ((int64_t)p.tq * Hq));
-    const int hkv = hq / p.G;
-    const float *q = static_cast<const float *>(p.q) + l * p.s_q.layer + (int64_t)hq * p.s_q.head + i * p.s_q.token;
-    const float *k = static_cast<const float *>(p.k) + l * p.s_k.layer + (int64_t)hkv * p.s_k.head;
-    const float *v = static_cast<const float *>(p.v) + l * p.s_v.layer + (int64_t)hkv * p.s_v.head;
-    for (int c = lane; c < D; c += 64) q_lds[wave][c] = q[c];
-    // only this wavefront reads q_lds[wave]; its writes are ordered before the reads below
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-    const int last = p.n_ctx + i;
-    float m = -INFINITY, lsum = 0.f;
-    float acc[CPL];
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
-
-    for (int j0 = 0; j0 <= last; j0 += 64) {
-        const int j = j0 + lane;
-        float sc = -INFINITY;
-        if (j <= last) {
-            const float *kr = k + (int64_t)j * p.s_k.token;
-            float dot = 0.f;
-#pragma unroll 4
-            for (int c = 0; c < D; c += 4) {
-                const f32x4 kv = *reinterpret_cast<const f32x4 *>(kr + c);
-                dot = fmaf(q_lds[wave][c], kv[0], dot);
-                dot = fmaf(q_lds[wave][c + 1], kv[1], dot);
-                dot = fmaf(q_lds[wave][c + 2], kv[2], dot);
-                dot = fmaf(q_lds[wave][c + 3], kv[3], dot);
-            }
-            sc = dot * p.scale;
-        }
-        float cmax = sc;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, off));
-        const float m_new = fmaxf(m, cmax);  // finite: lane 0 of every chunk is visible
-        const float corr = expf(m - m_new);
-        const float pj = j <= last ? expf(sc - m_new) : 0.f;
-        float psum = pj;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) psum += __shfl_xor(psum, off);
-        lsum = lsum * corr + psum;
-        m = m_new;
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c] *= corr;
-        const int cnt = min(64, last - j0 + 1);
-        for (int jj = 0; jj < cnt; ++jj) {
-            const float pv = __shfl(pj, jj);
-            const float *vr = v + (int64_t)(j0 + jj) * p.s_v.token;
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) acc[c] = fmaf(pv, vr[lane + 64 * c], acc[c]);
-        }
-    }
-    float *o = static_cast<float *>(p.out) + l * p.s_o.layer + (int64_t)hq * p.s_o.head + i * p.s_o.token;
-    const float inv = 1.f / lsum;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) o[lane + 64 * c] = acc[c] * inv;
-    if (p.lse && lane == 0) p.lse[row] = m + logf(lsum);
-}
-
-// Longer caches (attn_f32_kernel): 32 packed (query, head) rows per block on fp32 MFMA (32x32x2: exact fp32 products and sums); the wavefronts share the
-// rows and each takes every NW-th 32-key sub-step with its own softmax state, joined through LDS at the end (the same
-// work split as the bf16 rows kernel).  Both products are transposed, so a lane owns one query column, and every operand
-// comes straight from global memory in the layout the instruction wants: K and Q as 16-byte pieces of a lane's own
-// half of the channels (the contraction order is free as long as both agree), V as VEC consecutive channels of one key
-// (row r of accumulator c stands for channel VEC * r + c), P from the score registers.
-// What bounds it: matrix cores at large sizes (fp32 MFMA, 1/16 of the bf16 rate: 80 TFLOP/s at D = 128, Tq 512, 3072
-// keys), latency at small ones.  2 layers x 8 heads x 32 queries over 224 keys, D = 64: 11 us, 50 us with the row kernel;
-// 3 layers x 8 heads x 128 queries over 1152 keys, D = 128: 60 us, 443 us with the row kernel.
-constexpr int kF32Waves = 8;
-
-template <int D>
-__device__ __forceinline__ void attn_f32_item(const AttnParams &p, int item)   // item: one row tile of a (layer, kv head)
-{
-    constexpr int NW = kF32Waves;
-    constexpr int HD = D / 2, NDB = D / 32;
-    constexpr int VEC = NDB < 4 ? NDB : 4, SETS = NDB / VEC;   // channels of one V load, loads per key
-    constexpr int VJ = NDB == 2 ? 16 : NDB == 4 ? 8 : 4;      // V rows of a half wavefront in registers at a time
-    typedef float vecf __attribute__((ext_vector_type(VEC)));
-    __shared__ __align__(16) unsigned char smem[NW * 1024 * VEC * 4];   // Q, then the wavefronts' states
-    static_assert(D * 128 <= sizeof(smem), "Q must fit");
-    __shared__ float ml[2][NW][32];
-
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lane = tid & 63, n = lane & 31, hg = lane >> 5;
-    const int lh = div_by(item, p.by_row_tiles), rt = item - lh * p.n_row_tiles;
-    const int l = div_by(lh, p.by_Hkv), hkv = lh - l * p.Hkv;
-    const int r_row = rt * 32 + n, i_row = div_by(r_row, p.by_G);
-    const bool valid = i_row < p.tq;
-    const int qi = min(i_row, p.tq - 1);
-    const int hq = hkv * p.G + r_row - i_row * p.G;
-    const int imax = min(p.tq - 1, div_by(rt * 32 + 31, p.by_G)), imin = min(p.tq - 1, div_by(rt * 32, p.by_G));
-    const int units = (p.n_ctx + imax + 32) / 32;   // sub-steps that some query of the tile sees
-
-    const float *kb = static_cast<const float *>(p.k) + l * p.s_k.layer + hkv * p.s_k.head;
-    const float *vb = static_cast<const float *>(p.v) + l * p.s_v.layer + hkv * p.s_v.head;
-    const float *qrow = static_cast<const float *>(p.q) + l * p.s_q.layer + (int64_t)hq * p.s_q.head + (int64_t)qi * p.s_q.token;
-    // Q as operands, [piece c of the lane's half][lane]
-    f32x4 *q_lds = reinterpret_cast<f32x4 *>(smem);
-    for (int c = wave; c < HD / 4; c += NW) q_lds[c * 64 + lane] = *reinterpret_cast<const f32x4 *>(qrow + hg * HD + 4 * c);
-    __syncthreads();
-
-    f32x16 o[NDB];
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
-    float m = -INFINITY, lsum = 0.f;   // lsum: this lane's half of the row sum
-    bool odd = false;                  // left out a value that is not finite
-
-    for (int u = wave; u < units; u += NW) {
-        const int key0 = 32 * u;
-        const int limit = p.n_ctx + qi - key0;             // last visible key of this lane's query, relative to the sub-step
-        const bool edge = key0 + 31 > p.n_ctx + imin;      // some key is hidden from some query
-        const float *kr = kb + (int64_t)min(key0 + n, p.N - 1) * p.s_k.token + hg * HD;
-        // Accumulator row j of this lane is key 8 * (j / 4) + 4 * hg + j % 4; rows past the cache end re-read the last one.
-        const int row0 = min(key0 + 4 * hg, p.N - 1);
-        const float *v0 = vb + (int64_t)row0 * p.s_v.token + VEC * n;
-        vecf v[VJ][SETS];
-        auto load_v = [&](int j0) __attribute__((always_inline)) {
-#pragma unroll
-            for (int j = 0; j < VJ; ++j) {
-                const float *vr = v0 + (int64_t)min(8 * ((j0 + j) >> 2) + ((j0 + j) & 3), p.N - 1 - row0) * p.s_v.token;
-#pragma unroll
-                for (int t = 0; t < SETS; ++t) v[j][t] = *reinterpret_cast<const vecf *>(vr + t * 32 * VEC);
-            }
-        };
-        f32x16 s;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) s[j] = 0.f;
-        // 32 channels of the lane's half at a time: Q, K, V and O of a wide head together exceed the registers.  D = 128
-        // requests the second piece under the first one's products.
-        constexpr int NP = HD / 32;
-        f32x4 kv[2][8];
-        auto load_k = [&](f32x4 (&dst)[8], int c0) __attribute__((always_inline)) {
-#pragma unroll
-            for (int c = 0; c < 8; ++c) dst[c] = *reinterpret_cast<const f32x4 *>(kr + 4 * (c0 + c));
-        };
-        auto dot = [&](const f32x4 (&src)[8], int c0) __attribute__((always_inline)) {
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const f32x4 q = q_lds[(c0 + c) * 64 + lane];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(src[c][e], q[e], s, 0, 0, 0);
-            }
-        };
-        load_k(kv[0], 0);
-        if constexpr (NP == 2) load_k(kv[1], 8);
-        if constexpr (NP <= 2) load_v(0);
-        dot(kv[0], 0);
-        if constexpr (NP == 2) dot(kv[1], 8);
-        if constexpr (NP == 4) {
-#pragma unroll 1
-            for (int c0 = 8; c0 < 8 * NP; c0 += 8) {
-                load_k(kv[0], c0);
-                dot(kv[0], c0);
-            }
-            load_v(0);
-        }
-        float mx = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            s[j] *= p.scale;
-            if (edge && 8 * (j >> 2) + 4 * hg + (j & 3) > limit) s[j] = -INFINITY;
-            mx = fmaxf(mx, s[j]);
-        }
-        {
-            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-            mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-        }
-        if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
-            const float m_new = fmaxf(m, mx);
-            const float corr = m == -INFINITY ? 0.f : expf(m - m_new);
-            lsum *= corr;
-#pragma unroll
-            for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                for (int j = 0; j < 16; ++j) o[db][j] *= corr;
-            m = m_new;
-        }
-        const float mref = m == -INFINITY ? 0.f : m;   // a row that sees no key yet: exponentials 0
-        float rs = 0.f;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            s[j] = expf(s[j] - mref);
-            rs += s[j];
-        }
-        lsum += rs;
-
-        // A hidden key must not reach the result, not even as 0 * inf: at the causal edge values that are not finite are
-        // left out here and added behind the loop to the queries that do see them.
-#pragma unroll
-        for (int j0 = 0; j0 < 16; j0 += VJ) {
-            if (j0) load_v(j0);
-            if (edge) {
-#pragma unroll
-                for (int j = 0; j < VJ; ++j)
-#pragma unroll
-                    for (int t = 0; t < SETS; ++t)
-#pragma unroll
-                        for (int c = 0; c < VEC; ++c) {
-                            const bool fin = fabsf(v[j][t][c]) < INFINITY;
-                            odd |= !fin;
-                            v[j][t][c] = fin ? v[j][t][c] : 0.f;
-                        }
-            }
-#pragma unroll
-            for (int j = 0; j < VJ; ++j)
-#pragma unroll
-                for (int db = 0; db < NDB; ++db)
-                    o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[j][db / VEC][db % VEC], s[j0 + j], o[db], 0, 0, 0);
-        }
-    }
-
-    // ---- join the wavefronts' states and store
-    {
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum), false, false);
-        lsum = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-    }
-    if (hg == 0) {
-        ml[0][wave][n] = m;
-        ml[1][wave][n] = lsum;
-    }
-    __syncthreads();   // also: every wavefront is done with its part of smem
-    float M = ml[0][0][n];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[0][w][n]);
-    float ltot = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const float mw = ml[0][w][n];
-        ltot += mw == -INFINITY ? ml[1][w][n] : ml[1][w][n] * expf(mw - M);   // reference -inf: sum 0, or NaN from NaN scores
-    }
-    const float f = m == -INFINITY ? 0.f : expf(m - M);
-    vecf *join = reinterpret_cast<vecf *>(smem);   // [wavefront][j][lane]
-    float *orow = static_cast<float *>(p.out) + l * p.s_o.layer + (int64_t)hq * p.s_o.head + (int64_t)qi * p.s_o.token;
-    const float inv = 1.f / ltot;
-#pragma unroll
-    for (int t = 0; t < SETS; ++t) {
-        if (t) __syncthreads();
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            vecf x;
-#pragma unroll
-            for (int c = 0; c < VEC; ++c) x[c] = o[t * VEC + c][j] * f;
-            join[wave * 1024 + j * 64 + lane] = x;
-        }
-        __syncthreads();
-        if (valid) {
-#pragma unroll
-            for (int i = 0; i < 16 / NW; ++i) {
-                const int j = wave + NW * i;
-                vecf a = join[j * 64 + lane];
-#pragma unroll
-                for (int w = 1; w < NW; ++w) a += join[w * 1024 + j * 64 + lane];
-                *reinterpret_cast<vecf *>(orow + t * 32 * VEC + VEC * (8 * (j >> 2) + 4 * hg + (j & 3))) = a * inv;
-            }
-        }
-    }
-    if (p.lse && wave == 0 && hg == 0 && valid) p.lse[((int64_t)l * p.Hkv * p.G + hq) * p.tq + qi] = M + logf(ltot);
-
-    // Rare: values left out at the causal edge, for the queries that see them (thread: one query, every 2 * NW-th channel).
-    if (__syncthreads_or(odd) && valid) {
-        for (int key = (p.n_ctx + imin + 1) & ~31; key <= p.n_ctx + qi; ++key) {
-            const float *vr = vb + (int64_t)key * p.s_v.token;
-            float pk = -1.f;
-            for (int c = 2 * wave + hg; c < D; c += 2 * NW) {
-                const float x = vr[c];
-                if (fabsf(x) < INFINITY) continue;
-                if (pk < 0.f) {
-                    const float *kr = kb + (int64_t)key * p.s_k.token;
-                    float dot = 0.f;
-                    for (int i = 0; i < D; ++i) dot = fmaf(qrow[i], kr[i], dot);
-                    pk = expf(dot * p.scale - M) * inv;
-                }
-                orow[c] += pk * x;
-            }
-        }
-    }
-}
-
-// PERSIST: a grid of fewer blocks than items, each walking every gridDim.x-th one.  A block fills a CU (eight wavefronts of up to
-// 256 registers, 64 or 128 KB of LDS), so such a launch keeps to gridDim.x of them.
-template <int D, bool PERSIST>
-__global__ __launch_bounds__(64 * kF32Waves, 2) void attn_f32_kernel(const AttnParams p)
-{
-    if constexpr (!PERSIST) {
-        attn_f32_item<D>(p, blockIdx.x);
-    } else {
-        for (int item = blockIdx.x; item < p.n_items; item += gridDim.x) {
-            attn_f32_item<D>(p, item);
-            __syncthreads();   // the joined states have been read: LDS becomes the next item's
-        }
-    }
-}
-
 }  // namespace
 
 extern "C" size_t kvcomm_suffix_attn_workspace(const kvcomm_model *model, int32_t n_ctx, int32_t tq)
@@ -966,28 +651,14 @@ int suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_
     const int D = model->head_dim;
 
     if (dt == KVCOMM_F32) {
-        if (p.N <= kF32RowKeys) {
-            const dim3 grid((unsigned)(((int64_t)p.L * model->n_q_heads * tq + 3) / 4)), block(256);
-            switch (D) {
-                case 64: return launch(attn_f32_row_kernel<64>, grid, block, 0, s, p);
-                case 128: return launch(attn_f32_row_kernel<128>, grid, block, 0, s, p);
-                case 256: return launch(attn_f32_row_kernel<256>, grid, block, 0, s, p);
-                default: return KVCOMM_EUNSUPPORTED;
-            }
-        }
-        p.n_row_tiles = (int32_t)(((int64_t)p.G * tq + 31) / 32);
-        const int64_t n_blocks = (int64_t)p.L * p.Hkv * p.n_row_tiles;
-        if (n_blocks > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
-        p.n_items = (int32_t)n_blocks;
+        p.groups_per_tile = attn_f32_groups(*model, tq);
+        const int rows = 16 * p.groups_per_tile;
+        p.n_row_tiles = (int32_t)(((int64_t)p.G * tq + rows - 1) / rows);
+        const int64_t n_items = (int64_t)p.L * p.Hkv * p.n_row_tiles;
+        if (n_items > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
+        p.n_items = (int32_t)n_items;
         set_divisors(p);
-        const bool persist = max_blocks > 0 && max_blocks < p.n_items;
-        const dim3 grid((unsigned)(persist ? max_blocks : p.n_items)), block(64 * kF32Waves);
-        switch (D) {
-            case 64: return launch(persist ? attn_f32_kernel<64, true> : attn_f32_kernel<64, false>, grid, block, 0, s, p);
-            case 128: return launch(persist ? attn_f32_kernel<128, true> : attn_f32_kernel<128, false>, grid, block, 0, s, p);
-            case 256: return launch(persist ? attn_f32_kernel<256, true> : attn_f32_kernel<256, false>, grid, block, 0, s, p);
-            default: return KVCOMM_EUNSUPPORTED;
-        }
+        return launch_attn_f32(p, D, (unsigned)(max_blocks > 0 ? std::min(max_blocks, p.n_items) : p.n_items), s);
     }
 
     // The direct loads address a row group as a 64-bit scalar base plus an unsigned 32-bit per-lane byte

@@ -20,6 +20,7 @@ struct AttnPlan {
     int tile_rows;      // packed (query, head) rows of a row tile
     int n_row_tiles;
     int n_splits;
+    int group_rows;     // rows whose partial results lie together
 };
 
 // Rounds that `x` chips full of blocks take (a last round that is not full costs less than a whole one).
@@ -97,21 +98,37 @@ static inline AttnPlan attn_plan(const kvcomm_model &m, int n_ctx, int tq, bool 
     }
     AttnPlan pl{};
     pl.rows_kernel = (rows_items <= kChipCUs && rows_us < 1.2 * tile_us) || rows_one_run_us < 0.7 * tile_us;
-    pl.tile_rows = pl.rows_kernel ? 32 : tile_rows;
+    // 16 rows per block where a tile has no more, and where those blocks, in the runs found for 32, all run at once.  Of 304 launches of 17 to 340
+    // rows those of up to one round took 0.67 ... 0.94 of the time with 16 rows (one layer, 2064 keys, Tq 64 16.4 -> 13.4 us; 2 layers, 364 keys,
+    // Tq 64 8.6 -> 6.9), all others 0.99 ... 1.65 (one layer, 3116 keys, Tq 16 11.5 and 13.4).
+    const int64_t items16 = LH * ((rows + 15) / 16);
+    const bool half = rows <= 16 || items16 * rows_ns <= kChipCUs;
+    if (pl.rows_kernel && half && rows_ns == 1 && may_split && items16 <= kChipCUs / 4) {
+        // Their cuts pay earlier: an iteration takes 0.9 us (D = 64: 0.6), the combine launch 3.3.  8 blocks, G = 4, D = 128, one run / the cut: 520
+        // keys (3 iterations) 7.3 / 7.7 us, 1000 (4) 9.1 / 8.1, 2000 (8) 12.8 / 8.2; 64 blocks, 1250 keys (5, in runs of two) 12.6 / 13.6, 2000 (in
+        // runs of two) 16.9 / 16.2; D = 64, 8 blocks, 1000 keys 6.7 / 6.7, 1250 7.2 / 6.7; 64 blocks, 1250 keys 7.4 / 7.7, 1500 7.9 / 7.8.  More blocks
+        // have the memory's rate already: 128 blocks, G = 2, 2000 keys, D = 128 22.0 / 26.0, D = 64 13.0 / 15.6.
+        int64_t ns = std::min<int64_t>(std::min<int64_t>(kRowsMaxSplits, kChipCUs / items16), its);
+        const int64_t split_its = (its + ns - 1) / ns;
+        ns = (its + split_its - 1) / split_its;
+        if (its - split_its >= 4 || (D == 128 && its == 4 && split_its == 1)) rows_ns = (int)ns;
+    }
+    pl.tile_rows = !pl.rows_kernel ? tile_rows : half ? 16 : 32;
+    pl.group_rows = std::min(pl.tile_rows, 32);
     pl.n_row_tiles = (int)((rows + pl.tile_rows - 1) / pl.tile_rows);
     pl.n_splits = pl.rows_kernel ? rows_ns : tile_ns;
     return pl;
 }
 
-// (32-row group, split) pairs of a launch.
+// (row group, split) pairs of a launch.
 static inline size_t attn_parts(const kvcomm_model &m, const AttnPlan &pl)
 {
-    return (size_t)m.n_layers * m.n_kv_heads * pl.n_row_tiles * (pl.tile_rows / 32) * pl.n_splits;
+    return (size_t)m.n_layers * m.n_kv_heads * pl.n_row_tiles * (pl.tile_rows / pl.group_rows) * pl.n_splits;
 }
 
 static inline size_t attn_workspace(const kvcomm_model &m, const AttnPlan &pl)
 {
-    return pl.n_splits > 1 ? attn_parts(m, pl) * sizeof(float) * (32 * (size_t)m.head_dim + 64) : 0;
+    return pl.n_splits > 1 ? attn_parts(m, pl) * sizeof(float) * (size_t)pl.group_rows * ((size_t)m.head_dim + 2) : 0;
 }
 
 // Groups of 16 packed rows of an fp32 block: one as long as all blocks run at once, two above (they share what they load).  us with
@@ -124,8 +141,8 @@ static inline int attn_f32_groups(const kvcomm_model &m, int tq)
     return (int64_t)m.n_layers * m.n_kv_heads * ((rows + 15) / 16) <= kChipCUs ? 1 : 2;
 }
 
-int launch_attn_rows(const AttnParams &p, int D, unsigned n_blocks, hipStream_t stream);
+int launch_attn_rows(const AttnParams &p, int D, int rows, unsigned n_blocks, hipStream_t stream);
 int launch_attn_f32(const AttnParams &p, int D, unsigned n_blocks, hipStream_t stream);
-int launch_attn_combine(const AttnParams &p, int D, hipStream_t stream);
+int launch_attn_combine(const AttnParams &p, int D, int rows, hipStream_t stream);   // rows: of a group of partial results
 
 }  // namespace kvc

@@ -17,7 +17,7 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 // attn_mfma_kernel), which the wavefronts SHARE: each takes every NW-th 32-key sub-step of the block's key
 // run with its own softmax state, and the states are joined through LDS at the end.  The 256-row kernel would leave
 // seven of eight wavefronts without rows and walk the keys one 64-key tile after the other (one layer, one token,
-// 3100 keys: 62 us; here 20 us in one block per kv head, 8.4 + 4.3 us with the keys cut into runs).
+// 3100 keys: 62 us; here 20 us in one block per kv head, 8.4 + 4.3 us with the keys cut into runs, and less with 16 rows, see below).
 // What bounds it is the latency of the K / V stream, and HBM where every layer is in one launch (32 layers: 64 us =
 // 6.4 TB/s): K and V of a sub-step go global -> LDS into the wavefront's own buffers (no block barrier in the loop),
 // K of the next sub-step is requested as soon as its operands are in registers and V likewise, so a wavefront
@@ -261,11 +261,247 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
     } while (item < x_count);
 }
 
-// attn_combine_kernel: one block per (32-row group, 32 channels).  out = sum_s f_s O_s / sum_s f_s l_s with
+// Direct loads of 32 rows from key0 on into a wavefront's buffer, chunk c of row `key` at position c ^ swz(key): a wavefront-uniform row
+// pointer plus per-lane offsets that do not change from one sub-step to the next (lane_offsets(); the pattern repeats after
+// NIN loads).  Rows past the cache end (last sub-step only) re-read the last row; they are always masked.
+template <int D, int NIN, class Swz>
+__device__ __forceinline__ void lane_offsets(uint32_t (&in)[NIN], int lane, int64_t tok, Swz swz)
+{
+    constexpr int KCH = D / 8, RPL = 64 / KCH;
+    const int lq = lane / KCH;
+#pragma unroll
+    for (int i = 0; i < NIN; ++i) in[i] = (uint32_t)lq * (uint32_t)(tok * 2) + (uint32_t)(((lane % KCH) ^ swz(i * RPL + lq)) * 16);
+}
+template <int D, bool NT, int NIN, class Swz>
+__device__ __forceinline__ void load_half(const unsigned char *bytes, int64_t tok, int key0, int n_keys, const uint32_t (&in)[NIN], int lane, Swz swz,
+                                          lds_byte *dst)
+{
+    constexpr int KCH = D / 8, ROWB = D * 2, RPL = 64 / KCH, LPT = 32 / RPL;   // chunks and bytes of a row, rows of a load, loads
+    if (key0 + 32 <= n_keys) {   // wavefront-uniform
+        const unsigned char *row = bytes + (int64_t)key0 * tok * 2;
+#pragma unroll
+        for (int it = 0; it < LPT; ++it, row += (int64_t)RPL * tok * 2) dma16_sbase<NT>(row, in[it % NIN], dst + it * RPL * ROWB);
+    } else {
+        const int lq = lane / KCH;
+#pragma unroll 1
+        for (int it = 0; it < LPT; ++it) {
+            const int row0 = min(key0 + it * RPL, n_keys - 1);
+            const int row = min(lq, n_keys - 1 - row0);   // steps back by whole rows where the cache ends
+            dma16_sbase<NT>(bytes + (int64_t)row0 * tok * 2,
+                            (uint32_t)row * (uint32_t)(tok * 2) + (uint32_t)(((lane % KCH) ^ swz(it * RPL + lq)) * 16), dst + it * RPL * ROWB);
+        }
+    }
+}
+
+// attn_rows_kernel16: the same split of the keys for 16 packed rows per block, on 16x16x32 MFMAs in the operand layout of attn_mfma_kernel.  What
+// bounds a small launch is the number of instructions on a wavefront's way (a lone one issues one per 8 cycles), and with half the rows
+// every part of it is half as long: products, exponentials, rescaling, join.  Taken where its blocks all run at once (attn_plan()).
+// us per launch (HIP graph, with the combine launch where keys are cut), 32 rows -> 16: one layer, 8 kv heads, G = 4, one token: 1 key 6.3 -> 4.8,
+// 701 keys 10.2 -> 8.2, 3101 keys 12.1 -> 8.4 (D = 64 9.7 -> 7.0, G = 2, D = 256 15.9 -> 11.3; 9.6, 8.0 and 13.3 with the combine kernel of 32 rows);
+// 4 layers x 8 heads, Tq 16, 516 keys 9.4 -> 7.5; 32 layers, one token, 3101 keys 73.2 -> 70.8.
+template <int D, bool NT, bool PERSIST>
+__global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_rows_kernel16(const AttnParams p)
+{
+    constexpr int NW = rows_waves(D), ROWS = 16;
+    constexpr int NF = D / 16, KCH = D / 8, ROWB = D * 2, HALFB = 32 * ROWB;
+    constexpr int RPL = 64 / KCH;                    // key rows filled by one wavefront-wide direct load
+    constexpr int LPT = 32 / RPL;                    // direct loads of a 32-key half
+    constexpr int KD = 16 / RPL, VD = RPL < 8 ? 8 / RPL : 1;   // loads after which the swizzle pattern of the rows repeats
+    constexpr int JW = D * ROWS / 4;                 // 16-byte slots of a wavefront's outputs
+    constexpr int JP = 2 * HALFB / 16;               // 16-byte slots of its buffers
+    static_assert(JW <= JP, "a wavefront's outputs fit its own buffers");
+    // Chunk c of key `key` sits at position c ^ swz(key), as in attn_mfma_kernel.
+    auto k_swz = [](int key) __attribute__((always_inline)) -> int { return D == 64 ? (key >> 1) & 7 : key & 15; };
+    auto v_swz = [](int key) __attribute__((always_inline)) -> int {
+        return D == 64 ? (2 * (key & 2)) | ((key >> 1) & 2) : 4 * (key & 3) | ((key >> 1) & 2);
+    };
+    __shared__ __align__(16) unsigned char smem[NW * 2 * HALFB];
+    __shared__ float ml[2][NW][ROWS];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, n = lane & 15, g = lane >> 4;
+    lds_byte *kbuf = (lds_byte *)smem + wave * 2 * HALFB;
+    lds_byte *vbuf = kbuf + HALFB;
+
+    const int x_id = blockIdx.x & 7;
+    const int x_first = x_id * (p.n_items >> 3) + min(x_id, p.n_items & 7);
+    const int x_count = (p.n_items >> 3) + (x_id < (p.n_items & 7) ? 1 : 0);
+    const int x_blocks = PERSIST ? ((int)gridDim.x - x_id + 7) >> 3 : x_count;
+    int item = blockIdx.x >> 3;
+    if (PERSIST && item >= x_count) return;   // the whole block: more blocks than items on this XCD
+    do {
+        const int logical = x_first + item;
+        const int run = div_by(logical, p.by_row_tiles);
+        const int rt = logical - run * p.n_row_tiles;   // the row tiles of a key run are neighbours: they share its L2 lines
+        const int lh = div_by(run, p.by_splits), split = run - lh * p.n_splits;
+        const int l = div_by(lh, p.by_Hkv), hkv = lh - l * p.Hkv;
+
+        const int r_row = rt * ROWS + n, i_row = div_by(r_row, p.by_G);   // (also the row that this thread joins: tid % ROWS == n)
+        const bool valid = i_row < p.tq;
+        const int qi = min(i_row, p.tq - 1);
+        const int hq = hkv * p.G + r_row - i_row * p.G;
+        const int imax = min(p.tq - 1, div_by(rt * ROWS + ROWS - 1, p.by_G)), imin = min(p.tq - 1, div_by(rt * ROWS, p.by_G));
+        const int units = (p.n_ctx + imax + 32) / 32;   // sub-steps that some query of the tile sees
+        // split_bound() without a causal edge: s * units / n_splits (<= 2^30: see there)
+        const int u0 = div_by(split * units, p.by_splits), u1 = div_by((split + 1) * units, p.by_splits);
+
+        const unsigned char *kbytes = reinterpret_cast<const unsigned char *>(static_cast<const bf16_t *>(p.k) + l * p.s_k.layer + hkv * p.s_k.head);
+        const unsigned char *vbytes = reinterpret_cast<const unsigned char *>(static_cast<const bf16_t *>(p.v) + l * p.s_v.layer + hkv * p.s_v.head);
+        uint32_t k_in[KD], v_in[VD];
+        lane_offsets<D>(k_in, lane, p.s_k.token, k_swz);
+        lane_offsets<D>(v_in, lane, p.s_v.token, v_swz);
+        auto load_k = [&](int u) __attribute__((always_inline)) { load_half<D, NT>(kbytes, p.s_k.token, 32 * u, p.N, k_in, lane, k_swz, kbuf); };
+        auto load_v = [&](int u) __attribute__((always_inline)) { load_half<D, NT>(vbytes, p.s_v.token, 32 * u, p.N, v_in, lane, v_swz, vbuf); };
+        int u = u0 + wave;
+        bf16x8 qf[NF / 2];
+        const bf16_t *qrow = static_cast<const bf16_t *>(p.q) + l * p.s_q.layer + (int64_t)hq * p.s_q.head + (int64_t)qi * p.s_q.token;
+#pragma unroll
+        for (int ks = 0; ks < NF / 2; ++ks) qf[ks] = as_bf16x8(load16(qrow + ks * 32 + g * 8));
+        if (u < u1) {
+            load_k(u);
+            load_v(u);
+        }
+
+        // Operand addresses: K chunk 4 * ks + g of key n (and 16 + n); V^T is transposed on the way out of LDS.
+        int k_off[NF / 2], v_off[NF];
+#pragma unroll
+        for (int ks = 0; ks < NF / 2; ++ks) k_off[ks] = n * ROWB + (((4 * ks + g) ^ k_swz(n)) * 16);
+        {
+            const int row = 4 * g + (n >> 2);
+#pragma unroll
+            for (int db = 0; db < NF; ++db) {
+                const int col = 16 * db + 4 * (n & 3);
+                v_off[db] = row * ROWB + ((col >> 3) ^ v_swz(row)) * 16 + (col & 7) * 2;
+            }
+        }
+
+        f32x4 o[NF];
+#pragma unroll
+        for (int db = 0; db < NF; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        float m = -INFINITY, mc = 0.f, lsum = 0.f;   // lsum: this lane's quarter of the row sum
+        __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0), seen by the compiler: it puts no wait for the queries into the loop
+
+        for (; u < u1; u += NW) {
+            const bool more = u + NW < u1;   // wavefront-uniform
+            wait_loads<LPT>();               // K(u) has landed (V(u) may be outstanding)
+            bf16x8 ka[NF];                   // all operand reads in flight at once: ks = i / 2, keys 16 * (i & 1) ...
+#pragma unroll
+            for (int i = 0; i < NF; ++i)
+                ka[i] = as_bf16x8(*(const __attribute__((address_space(3))) u32x4 *)(kbuf + (i & 1) * 16 * ROWB + k_off[i >> 1]));
+            wait_lds();                      // K(u) has been read: its buffer is free
+            if (more) load_k(u + NW);
+            f32x4 s[2];                      // score j of this lane: key 16 * (j / 4) + 4 * g + j % 4
+#pragma unroll
+            for (int i = 0; i < NF; ++i)
+                s[i & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[i], qf[i >> 1], i < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[i & 1], 0, 0, 0);
+
+            if (32 * u + 31 > p.n_ctx + imin) {   // some key is hidden from some query
+                const int limit = p.n_ctx + qi - 32 * u - 4 * g;
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (16 * (j >> 2) + (j & 3) > limit) s[j >> 2][j & 3] = -INFINITY;
+            }
+            float mx = s[0][0];
+#pragma unroll
+            for (int j = 1; j < 8; ++j) mx = fmaxf(mx, s[j >> 2][j & 3]);
+            mx = query_max(mx);
+            if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
+                const float m_new = fmaxf(m, mx);
+                const float corr = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_new) * p.scale_log2);
+                lsum *= corr;
+#pragma unroll
+                for (int db = 0; db < NF; ++db) o[db] *= corr;
+                m = m_new;
+                mc = m == -INFINITY ? 0.f : m * p.scale_log2;   // a row that sees no key of this run yet: exponentials 0
+            }
+            u32x4 pk;
+            float rs0 = 0.f, rs1 = 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j >> 1][2 * (j & 1)], p.scale_log2, -mc));
+                const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j >> 1][2 * (j & 1) + 1], p.scale_log2, -mc));
+                rs0 += e0;
+                rs1 += e1;
+                pk[j] = pack_bf16x2(e0, e1);
+            }
+            const bf16x8 pf = as_bf16x8(pk);
+            lsum += rs0 + rs1;
+
+            if (more)
+                wait_loads<LPT>();   // V(u) has landed (K of the next sub-step may be outstanding)
+            else
+                wait_loads<0>();
+            bf16x8 va[NF];
+#pragma unroll
+            for (int db = 0; db < NF; ++db) va[db] = lds_read_tr_pair(vbuf + v_off[db], vbuf + v_off[db] + 16 * ROWB);
+            wait_lds();                      // V(u) has been read
+            if (more) load_v(u + NW);
+#pragma unroll
+            for (int db = 0; db < NF; ++db) o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[db], pf, o[db], 0, 0, 0);
+        }
+
+        // ---- join the wavefronts' states as in attn_rows_kernel.  Lane (n, g) holds channels 16 * db + 4 * g ... + 3 of row n: slot
+        // (4 * db + g, n).
+        lsum = query_sum(lsum);
+        if (g == 0) {
+            ml[0][wave][n] = m;
+            ml[1][wave][n] = lsum;
+        }
+        f32x4 *join = reinterpret_cast<f32x4 *>(smem);
+        if (valid) {
+#pragma unroll
+            for (int db = 0; db < NF; ++db) join[wave * JP + 64 * db + lane] = o[db];
+        }
+        __syncthreads();
+        float M = ml[0][0][n];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[0][w][n]);
+        float f[NW], ltot = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float mw = ml[0][w][n], lw = ml[1][w][n];
+            f[w] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mw - M) * p.scale_log2);
+            ltot += mw == -INFINITY ? lw : lw * f[w];   // reference -inf: no key seen and sum 0, or nothing but NaN scores and a sum that says so
+        }
+        const int64_t part = (int64_t)(lh * p.n_row_tiles + rt) * p.n_splits + split;
+        if (valid) {
+            const float inv = 1.f / ltot;
+#pragma unroll
+            for (int i = 0; i < JW; i += 64 * NW) {
+                const int slot = i + tid;
+                if (JW % (64 * NW) && slot >= JW) break;
+                f32x4 a = join[slot] * f[0];
+#pragma unroll
+                for (int w = 1; w < NW; ++w) a += join[w * JP + slot] * f[w];
+                if (p.n_splits > 1) {
+                    reinterpret_cast<f32x4 *>(p.part_o + part * (ROWS * D))[slot] = a;
+                } else {
+                    bf16_t *orow = static_cast<bf16_t *>(p.out) + l * p.s_o.layer + (int64_t)hq * p.s_o.head + (int64_t)qi * p.s_o.token;
+                    const u32x2 w2 = {pack_bf16x2(a[0] * inv, a[1] * inv), pack_bf16x2(a[2] * inv, a[3] * inv)};
+                    *reinterpret_cast<u32x2 *>(orow + slot / ROWS * 4) = w2;
+                }
+            }
+        }
+        if (tid < ROWS && valid) {
+            if (p.n_splits > 1) {
+                p.part_ml[part * 2 * ROWS + n] = M;
+                p.part_ml[part * 2 * ROWS + ROWS + n] = ltot;
+            } else if (p.lse) {
+                p.lse[((int64_t)l * p.Hkv * p.G + hq) * p.tq + qi] = M * p.scale + logf(ltot);
+            }
+        }
+        if (!PERSIST) break;
+        __syncthreads();   // the joined states have been read: LDS becomes the next item's buffers
+        item += x_blocks;
+    } while (item < x_count);
+}
+
+// attn_combine_kernel, groups of 32 rows: one block per (group, 32 channels).  out = sum_s f_s O_s / sum_s f_s l_s with
 // f_s = exp2((m_s - max m) * scale * log2 e), splits in increasing order.  All loads of the U >= n_splits partial results are in
 // flight at once (the launch is a few microseconds of latency); rows leave as 64-byte pieces through LDS.
 template <int D, int U>
-__global__ __launch_bounds__(256) void attn_combine_kernel(const AttnParams p)
+__device__ __forceinline__ void combine32(const AttnParams &p)
 {
     __shared__ __align__(16) u32x2 stage[32][9];   // 8 pieces of 4 channels a row (+1: bank spread)
     const int tid = threadIdx.x;
@@ -335,48 +571,140 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const AttnParams p)
     }
 }
 
-template <int D>
-int launch_combine(const AttnParams &p, hipStream_t stream)
+// Groups of 16 rows (attn_rows_kernel16): one block per (group, 16 channels); the four wavefronts share the runs (wavefront w takes
+// w, w + 4, ...) and their states are joined through LDS, in a fixed order.  With few rows the launch is the chain of one wavefront's
+// instructions: one token, 13 runs, both launches 9.6 us with all runs in every thread, 8.4 so.
+template <int D, int U>
+__device__ __forceinline__ void combine16(const AttnParams &p)
 {
-    static_assert(kRowsMaxSplits <= 16 && kTileMaxSplits <= 16, "attn_combine_kernel takes all partial results of a row at once");
-    const dim3 grid((unsigned)(p.L * p.Hkv * p.n_row_tiles * p.groups_per_tile * (D / 32))), block(256);
-    return launch(p.n_splits <= 4 ? attn_combine_kernel<D, 4> : p.n_splits <= 8 ? attn_combine_kernel<D, 8> : attn_combine_kernel<D, 16>, grid, block, 0,
-                  stream, p);
+    constexpr int ROWS = 16, UW = U / 4;
+    __shared__ f32x4 accs[4][64];
+    __shared__ float ml[2][4][ROWS];
+    const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, c4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int x_id = blockIdx.x & 7, n_blocks = gridDim.x;   // (the order of combine32())
+    const int logical = x_id * (n_blocks >> 3) + min(x_id, n_blocks & 7) + (blockIdx.x >> 3);
+    const int db = logical % (D / 16), item = logical / (D / 16);
+    const int lh = div_by(item, p.by_row_tiles), rt = p.n_row_tiles - 1 - (item - lh * p.n_row_tiles);
+    const int l = div_by(lh, p.by_Hkv), hkv = lh - l * p.Hkv;
+    const int r = rt * ROWS + n, qi = div_by(r, p.by_G), hq = hkv * p.G + r - qi * p.G;
+    const bool valid = qi < p.tq;
+
+    if (valid) {
+        const int64_t part0 = (int64_t)(lh * p.n_row_tiles + rt) * p.n_splits;
+        const f32x4 *po = reinterpret_cast<const f32x4 *>(p.part_o) + part0 * (ROWS * D / 4) + db * 64 + lane;
+        const float *pm = p.part_ml + part0 * 2 * ROWS + n;
+        float ms[UW], ls[UW];
+        f32x4 os[UW];
+#pragma unroll
+        for (int i = 0; i < UW; ++i) {
+            const int s = min(wave + 4 * i, p.n_splits - 1);
+            ms[i] = pm[s * 2 * ROWS];
+            ls[i] = pm[s * 2 * ROWS + ROWS];
+            os[i] = po[(int64_t)s * (ROWS * D / 4)];   // not used, and possibly never written, where m_s is -inf and the sum 0
+        }
+        float M = -INFINITY, L = 0.f;
+#pragma unroll
+        for (int i = 0; i < UW; ++i) {
+            ms[i] = wave + 4 * i < p.n_splits ? ms[i] : -INFINITY;
+            ls[i] = wave + 4 * i < p.n_splits ? ls[i] : 0.f;
+            M = fmaxf(M, ms[i]);
+        }
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < UW; ++i) {
+            if (ms[i] != -INFINITY || ls[i] != 0.f) {   // a run of NaN scores has reference -inf and sum NaN
+                const float f = __builtin_amdgcn_exp2f((ms[i] - M) * p.scale_log2);
+                L = fmaf(f, ls[i], L);
+                acc += f * os[i];
+            }
+        }
+        accs[wave][lane] = acc;
+        if (c4 == 0) {
+            ml[0][wave][n] = M;
+            ml[1][wave][n] = L;
+        }
+    }
+    __syncthreads();
+    if (wave == 0 && valid) {
+        float ms[4], M = -INFINITY, L = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            ms[w] = ml[0][w][n];
+            M = fmaxf(M, ms[w]);
+        }
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float lw = ml[1][w][n];
+            if (ms[w] != -INFINITY || lw != 0.f) {
+                const float f = __builtin_amdgcn_exp2f((ms[w] - M) * p.scale_log2);
+                L = fmaf(f, lw, L);
+                acc += f * accs[w][lane];
+            }
+        }
+        const float inv = 1.f / L;
+        bf16_t *dst = static_cast<bf16_t *>(p.out) + l * p.s_o.layer + (int64_t)hq * p.s_o.head + (int64_t)qi * p.s_o.token + 16 * db + 4 * c4;
+        *reinterpret_cast<u32x2 *>(dst) = u32x2{pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv)};
+        if (p.lse && db == 0 && c4 == 0) p.lse[((int64_t)l * p.Hkv * p.G + hq) * p.tq + qi] = M * p.scale + logf(L);
+    }
+}
+
+template <int D, int U, int ROWS>
+__global__ __launch_bounds__(256) void attn_combine_kernel(const AttnParams p)
+{
+    if constexpr (ROWS == 16)
+        combine16<D, U>(p);
+    else
+        combine32<D, U>(p);
 }
 
 template <int D>
-int launch_rows(const AttnParams &p, bool nt, bool persist, unsigned n_blocks, hipStream_t stream)
+int launch_combine(const AttnParams &p, int rows, hipStream_t stream)
+{
+    static_assert(kRowsMaxSplits <= 16 && kTileMaxSplits <= 16, "the combine kernels take all partial results of a row at once");
+    const int64_t groups = (int64_t)p.L * p.Hkv * p.n_row_tiles * p.groups_per_tile;
+    const dim3 grid((unsigned)(groups * (rows == 16 ? D / 16 : D / 32))), block(256);
+    const auto of16 = p.n_splits <= 4 ? attn_combine_kernel<D, 4, 16> : p.n_splits <= 8 ? attn_combine_kernel<D, 8, 16> : attn_combine_kernel<D, 16, 16>;
+    const auto of32 = p.n_splits <= 4 ? attn_combine_kernel<D, 4, 32> : p.n_splits <= 8 ? attn_combine_kernel<D, 8, 32> : attn_combine_kernel<D, 16, 32>;
+    return launch(rows == 16 ? of16 : of32, grid, block, 0, stream, p);
+}
+
+template <int D>
+int launch_rows(const AttnParams &p, int rows, bool nt, bool persist, unsigned n_blocks, hipStream_t stream)
 {
     const dim3 grid(n_blocks), block(64 * rows_waves(D));
-    if (persist)
-        return launch(nt ? attn_rows_kernel<D, true, true> : attn_rows_kernel<D, false, true>, grid, block, 0, stream, p);
-    return launch(nt ? attn_rows_kernel<D, true, false> : attn_rows_kernel<D, false, false>, grid, block, 0, stream, p);
+    const auto rows16 = persist ? (nt ? attn_rows_kernel16<D, true, true> : attn_rows_kernel16<D, false, true>)
+                                : (nt ? attn_rows_kernel16<D, true, false> : attn_rows_kernel16<D, false, false>);
+    const auto rows32 = persist ? (nt ? attn_rows_kernel<D, true, true> : attn_rows_kernel<D, false, true>)
+                                : (nt ? attn_rows_kernel<D, true, false> : attn_rows_kernel<D, false, false>);
+    return launch(rows == 16 ? rows16 : rows32, grid, block, 0, stream, p);
 }
 
 }  // namespace
 
 namespace kvc {
 
-int launch_attn_rows(const AttnParams &p, int D, unsigned n_blocks, hipStream_t stream)
+int launch_attn_rows(const AttnParams &p, int D, int rows, unsigned n_blocks, hipStream_t stream)
 {
     // Non-temporal K / V only where they cannot stay in the last-level cache and no other block reads them: 32 layers
     // of 3100 keys (407 MB) take 64 us with it and 72 us without, 4 layers (51 MB, read again for the next token) 33 and 26.
     const bool nt = p.n_row_tiles == 1 && (int64_t)p.L * p.Hkv * p.N * D * 4 > kLastLevelCache;
     const bool persist = n_blocks < (unsigned)p.n_items;
     switch (D) {
-        case 64: return launch_rows<64>(p, nt, persist, n_blocks, stream);
-        case 128: return launch_rows<128>(p, nt, persist, n_blocks, stream);
-        case 256: return launch_rows<256>(p, nt, persist, n_blocks, stream);
+        case 64: return launch_rows<64>(p, rows, nt, persist, n_blocks, stream);
+        case 128: return launch_rows<128>(p, rows, nt, persist, n_blocks, stream);
+        case 256: return launch_rows<256>(p, rows, nt, persist, n_blocks, stream);
         default: return KVCOMM_EUNSUPPORTED;
     }
 }
 
-int launch_attn_combine(const AttnParams &p, int D, hipStream_t stream)
+int launch_attn_combine(const AttnParams &p, int D, int rows, hipStream_t stream)
 {
     switch (D) {
-        case 64: return launch_combine<64>(p, stream);
-        case 128: return launch_combine<128>(p, stream);
-        case 256: return launch_combine<256>(p, stream);
+        case 64: return launch_combine<64>(p, rows, stream);
+        case 128: return launch_combine<128>(p, rows, stream);
+        case 256: return launch_combine<256>(p, rows, stream);
         default: return KVCOMM_EUNSUPPORTED;
     }
 }

@@ -675,17 +675,17 @@ int suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_
     }
     p.n_row_tiles = plan.n_row_tiles;
     p.n_splits = plan.n_splits;
-    p.groups_per_tile = plan.tile_rows / 32;
+    p.groups_per_tile = plan.tile_rows / plan.group_rows;
     p.n_items = p.L * p.Hkv * p.n_row_tiles * p.n_splits;
     if (p.n_splits > 1) {
         p.part_o = static_cast<float *>(workspace);
-        p.part_ml = p.part_o + attn_parts(*model, plan) * (size_t)(32 * D);
+        p.part_ml = p.part_o + attn_parts(*model, plan) * (size_t)(plan.group_rows * D);
     }
     set_divisors(p);
     const bool persist = max_blocks > 0 && max_blocks < p.n_items;
     const unsigned n_blocks = persist ? (unsigned)max_blocks : (unsigned)p.n_items;
     if (plan.rows_kernel) {
-        st = launch_attn_rows(p, D, n_blocks, s);
+        st = launch_attn_rows(p, D, plan.tile_rows, n_blocks, s);
     } else {
         switch (D) {
             case 64: st = launch_mfma<64, kAttnWaves, 2>(p, n_blocks, persist, s); break;
@@ -694,7 +694,7 @@ int suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_
         }
     }
     if (st || p.n_splits == 1) return st;
-    return launch_attn_combine(p, D, s);
+    return launch_attn_combine(p, D, plan.group_rows, s);
 }
 
 }  // namespace

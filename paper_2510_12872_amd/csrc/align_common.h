@@ -25,12 +25,24 @@ struct AlignJob {
     int32_t S;                 // tokens
     int32_t w_pitch;           // anchors per weight row (n_anchors of the segment)
     int32_t n_token_tiles;
-    int32_t tile0;             // first of the segment's tiles in the launch-wide tile list
     int16_t a0, n_sel;         // its selected anchors: entries [a0, a0 + n_sel) of anc / col / tab
     int16_t t0, n_tab;         // its rotation tables: entries [t0, t0 + n_tab) of tab_delta
     int16_t base_tab;          // table of the base keys' rotation (index among the segment's tables) + 1, 0 = identity
     int16_t pad_;
 };
+
+// What every block reads first: the line and a half that a launch's arguments begin with.  A segment's descriptor follows.
+struct AlignHead {
+    Strides s_anc;             // E4M3 deviations: in bytes
+    int32_t H, LH;             // kv heads, layers*heads
+    int32_t gran, n_jobs;
+    int32_t tiles_total;       // token tiles of all segments
+    int32_t lh_range;          // uncompressed: (layer, head) pairs along the grid's first axis; E4M3: pairs that a block walks
+    divisor_t by_tiles, by_H;
+    int32_t tile0[KVCOMM_MAX_BATCH];   // first of a segment's tiles in the launch-wide tile list
+    uint32_t pad_[8];
+};
+static_assert(sizeof(AlignHead) == 128, "two lines");
 
 // Entry i of a byte array in the kernel arguments, i wavefront-uniform: read as a dword on the scalar unit.  (There is no
 // scalar byte load; a plain access becomes a vector load whose wait also waits for every row in flight before it.)
@@ -46,7 +58,7 @@ __device__ __forceinline__ int job_of_tile(const P &p, int r)
     int ji = 0;
 #pragma unroll
     for (int i = 1; i < KVCOMM_MAX_BATCH; ++i)
-        if (i < p.n_jobs && r >= p.job[i].tile0) ji = i;
+        if (i < p.head.n_jobs && r >= p.head.tile0[i]) ji = i;
     return ji;
 }
 
@@ -101,8 +113,8 @@ int check_align_aliasing(const kvcomm_model *model, int gran, const kvcomm_tenso
     return KVCOMM_OK;
 }
 
-// Validates the jobs of a batched update and fills the launch parameters P (fields job, s_anc, H, LH, gran,
-// n_jobs, tiles_total, tab_delta, anc, tab, inv_freq).  `on_anchor(slot, job, a)` is called for every selected anchor with its
+// Validates the jobs of a batched update and fills the launch parameters P (fields head but for lh_range, job, tab_delta,
+// anc, tab, inv_freq).  `on_anchor(slot, job, a)` is called for every selected anchor with its
 // launch-wide slot and may return an error status.  The blocks are cut so that there are about target_blocks_per_job * n_jobs, or
 // one per (layer, head) pair and token tile.
 template <class P, class JobT, class OnAnchor>
@@ -137,11 +149,13 @@ int plan_align(const kvcomm_model *model, int gran, const kvcomm_tensor &anchor_
     }
     if ((st = check_align_aliasing(model, gran, anchor_layout, anchor_es, jobs, n_jobs))) return st;
 
-    p.s_anc = strides_of(anchor_layout);
-    p.H = model->n_kv_heads;
-    p.LH = model->n_layers * model->n_kv_heads;
-    p.gran = gran;
-    p.n_jobs = n_jobs;
+    AlignHead &head = p.head;
+    head.s_anc = strides_of(anchor_layout);
+    head.H = model->n_kv_heads;
+    head.LH = model->n_layers * model->n_kv_heads;
+    head.by_H = make_divisor((uint32_t)head.H);
+    head.gran = gran;
+    head.n_jobs = n_jobs;
     fill_inv_freq(p.inv_freq, model->rope_theta, model->head_dim);
 
     const int es = elem_size(dt);
@@ -206,22 +220,23 @@ int plan_align(const kvcomm_model *model, int gran, const kvcomm_tensor &anchor_
     }
 
     if (tiles_total > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
-    int64_t n_chunks = p.LH;
+    int64_t n_chunks = head.LH;
     plan.lh_per_block = 1;
     if (target_blocks_per_job != kOnePairPerBlock) {
         // Many small blocks: the memory system delivers more with more wavefronts in flight, and the
         // per-block set-up (weights, cos/sin) is a few dozen instructions.
         const int64_t target_blocks = (int64_t)target_blocks_per_job * n_jobs;
-        n_chunks = std::max<int64_t>(1, std::min<int64_t>(p.LH, (target_blocks + tiles_total - 1) / tiles_total));
-        plan.lh_per_block = (int)((p.LH + n_chunks - 1) / n_chunks);
-        n_chunks = (p.LH + plan.lh_per_block - 1) / plan.lh_per_block;
+        n_chunks = std::max<int64_t>(1, std::min<int64_t>(head.LH, (target_blocks + tiles_total - 1) / tiles_total));
+        plan.lh_per_block = (int)((head.LH + n_chunks - 1) / n_chunks);
+        n_chunks = (head.LH + plan.lh_per_block - 1) / plan.lh_per_block;
     }
     int32_t tile0 = 0;
     for (int j = 0; j < n_jobs; ++j) {
-        p.job[j].tile0 = tile0;
+        head.tile0[j] = tile0;
         tile0 += p.job[j].n_token_tiles;
     }
-    p.tiles_total = (int32_t)tiles_total;
+    head.tiles_total = (int32_t)tiles_total;
+    head.by_tiles = make_divisor((uint32_t)tiles_total);
     plan.n_blocks = n_chunks * tiles_total;
     plan.max_tab = max_tab;
     plan.max_sel = max_sel;

@@ -28,15 +28,14 @@ using namespace kvc;
 constexpr int kBlock = kAlignBlock;
 constexpr int kComputeUnits = 256;
 
+struct AlignKvJob : AlignJob {
+    uint64_t sel_mask;     // bit a = anchor a of the segment is selected
+    divisor_t by_pitch;    // of w_pitch
+};
+
 struct AlignParams {
-    AlignJob job[KVCOMM_MAX_BATCH];
-    Strides s_anc;
-    int32_t H, LH;             // kv heads, layers*heads
-    int32_t gran, n_jobs;
-    int32_t tiles_total;       // token tiles of all segments
-    int32_t lh_range;          // (layer, head) pairs along the grid's first axis
-    divisor_t by_tiles, by_H, by_pitch[KVCOMM_MAX_BATCH];
-    uint64_t sel_mask[KVCOMM_MAX_BATCH];        // bit a = anchor a of the segment is selected
+    AlignHead head;
+    AlignKvJob job[KVCOMM_MAX_BATCH];
     int32_t tab_delta[kMaxTab];                 // position delta of each rotation table
     const void *anc[2][KVCOMM_MAX_ANCHORS];     // [0] dK, [1] dV of the selected anchors of all segments
     alignas(4) uint8_t tab[KVCOMM_MAX_ANCHORS];            // its rotation table (index among the segment's tables) + 1, 0 = identity
@@ -61,12 +60,17 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
 
     // Block order: (layer, head) chunk, then segment, then token tile, so that the blocks in flight
     // write neighbouring slices of the same cache rows when the segments of a launch are adjacent.
-    const int q = div_by(blockIdx.x, p.by_tiles);
-    const int r = blockIdx.x - q * p.tiles_total;
-    const int lh = (blockIdx.y >> 1) * p.lh_range + q;
-    if (lh >= p.LH) return;   // the whole block: the last range of pairs is not full
+    const int which = blockIdx.y & 1;      // 0 = keys (rotated), 1 = values
+    const AlignHead &hd = p.head;
+    await_args(arg_word(&hd), arg_word(hd.tile0), arg_word(&p.job[0]), arg_word(&p.job[0].s_base[1]), arg_word(&p.job[0].S), arg_word(p.anc[which]),
+               arg_word(p.tab), arg_word(p.tab_delta));
+    const int q = div_by(blockIdx.x, hd.by_tiles);
+    const int r = blockIdx.x - q * hd.tiles_total;
+    const int lh = (blockIdx.y >> 1) * hd.lh_range + q;
+    if (lh >= hd.LH) return;   // the whole block: the last range of pairs is not full
     const int ji = job_of_tile(p, r);
-    const AlignJob &jb = p.job[ji];
+    const AlignKvJob &jb = p.job[ji];
+    if (ji > 0) await_args(arg_word(&jb), arg_word(&jb.s_base[1]), arg_word(&jb.s_out[1]), arg_word(&jb.S));
     const int n_sel = jb.n_sel, a0 = jb.a0;
 
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -76,8 +80,7 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
     const int tid = threadIdx.x;
     const int row = tid / LPR;
     const int lir = tid % LPR;
-    const int tile = r - jb.tile0;
-    const int which = blockIdx.y & 1;      // 0 = keys (rotated), 1 = values
+    const int tile = r - hd.tile0[ji];
     const bool is_k = which == 0;
     const int t = tile * RPB + row;
     const bool valid = t < jb.S;
@@ -88,11 +91,11 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
 
     // What the block's set-up reads, its weight rows (as they are, unselected anchors included), is requested first, then the rows of
     // its first (layer, head) pair: they arrive under the rotation tables and the barrier.
-    const uint64_t sel = p.sel_mask[ji];
-    const int n_w = sel == 0 ? 0 : (p.gran == KVCOMM_W_SEGMENT ? 1 : min(RPB, jb.S - tile * RPB)) * jb.w_pitch;
+    const uint64_t sel = jb.sel_mask;
+    const int n_w = sel == 0 ? 0 : (hd.gran == KVCOMM_W_SEGMENT ? 1 : min(RPB, jb.S - tile * RPB)) * jb.w_pitch;
     const float *wsrc = jb.weights;
-    if (p.gran != KVCOMM_W_SEGMENT)
-        wsrc += ((int64_t)(p.gran == KVCOMM_W_LAYER_HEAD_TOKEN ? lh : 0) * jb.S + tile * RPB) * jb.w_pitch;
+    if (hd.gran != KVCOMM_W_SEGMENT)
+        wsrc += ((int64_t)(hd.gran == KVCOMM_W_LAYER_HEAD_TOKEN ? lh : 0) * jb.S + tile * RPB) * jb.w_pitch;
     constexpr int W = !SMALL ? 1 : RPB / 4 < 4 ? RPB / 4 : 4;   // n_w <= RPB * 64 = RPB / 4 weights of every thread
     float w_first[W] = {};
 #pragma unroll
@@ -105,14 +108,14 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
         delta = p.tab_delta[jb.t0 + tid / HALF];
     }
     auto keep_weight = [&](int idx, float w) __attribute__((always_inline)) {
-        const int r = div_by(idx, p.by_pitch[ji]), c = idx - r * jb.w_pitch;
+        const int r = div_by(idx, jb.by_pitch), c = idx - r * jb.w_pitch;
         if ((sel >> c) & 1) w_lds[r * n_sel + __popcll(sel & (((uint64_t)1 << c) - 1))] = w;
     };
 
-    const int l = div_by(lh, p.by_H), h = lh - l * p.H;
+    const int l = div_by(lh, hd.by_H), h = lh - l * hd.H;
     const int tr = SMALL ? min(t, jb.S - 1) : t;
     const T *xp = bp + l * sb.layer + h * sb.head + tr * sb.token + col0;
-    const int64_t aoff = l * p.s_anc.layer + h * p.s_anc.head + tr * p.s_anc.token + col0;
+    const int64_t aoff = l * hd.s_anc.layer + h * hd.s_anc.head + tr * hd.s_anc.token + col0;
     u32x4 rlo, rhi, rows[INFLIGHT][2];
     auto request_group = [&](int a) __attribute__((always_inline)) {
 #pragma unroll
@@ -156,7 +159,7 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
         }
     }
 
-    const float *wrow = w_lds + (p.gran == KVCOMM_W_SEGMENT ? 0 : row * n_sel);
+    const float *wrow = w_lds + (hd.gran == KVCOMM_W_SEGMENT ? 0 : row * n_sel);
 
     float lo[EPV], hi[EPV];
     unpack<T>(rlo, lo);
@@ -244,11 +247,11 @@ size_t lds_reserve(const AlignParams &p, int64_t n_blocks, int lpr, int es, int 
 {
     constexpr size_t kThreeBlocks = 81 << 9, kTwoBlocks = 54 << 10;
     double anchors = 0.0;   // of a block, on average
-    for (int j = 0; j < p.n_jobs; ++j) anchors += (double)p.job[j].n_token_tiles * p.job[j].n_sel / p.tiles_total;
+    for (int j = 0; j < p.head.n_jobs; ++j) anchors += (double)p.job[j].n_token_tiles * p.job[j].n_sel / p.head.tiles_total;
     const double bytes = 2.0 * (double)n_blocks * 32 * kBlock * (anchors + 2.0);
     if (bytes < 0.45e9 || units < 92) return 0;
     // heads of the pool a multiple of 16 KB apart; rows of 512 bytes and more
-    const bool even = p.s_anc.head * es % 16384 == 0, wide = lpr > 8;
+    const bool even = p.head.s_anc.head * es % 16384 == 0, wide = lpr > 8;
     const bool two = lpr > 4 && bytes >= 0.95e9 && anchors >= 6.0 && (even || anchors >= 16.0 || (anchors >= 8.0 && (wide || bytes >= 1.8e9)));
     return units >= 108 && two ? kTwoBlocks : kThreeBlocks;
 }
@@ -264,11 +267,11 @@ bool few_rows(const AlignParams &p, int64_t n_blocks, int max_sel, int row_bytes
 {
     int64_t tokens = 0;
     int min_sel = max_sel;
-    for (int j = 0; j < p.n_jobs; ++j) {
+    for (int j = 0; j < p.head.n_jobs; ++j) {
         tokens += p.job[j].S;
         min_sel = std::min<int>(min_sel, p.job[j].n_sel);
     }
-    return min_sel >= 4 && 2 * tokens * p.LH * row_bytes <= 2700000 && (2 * n_blocks <= 3 * kComputeUnits || max_sel >= 32);
+    return min_sel >= 4 && 2 * tokens * p.head.LH * row_bytes <= 2700000 && (2 * n_blocks <= 3 * kComputeUnits || max_sel >= 32);
 }
 
 template <typename T, int LPR>
@@ -277,7 +280,8 @@ int launch_align(const AlignParams &p, const AlignLaunch &pl, int units, hipStre
     constexpr int HALF = LPR * Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
     const size_t lds = sizeof(float2) * (size_t)pl.max_tab * HALF + sizeof(float) * (size_t)RPB * pl.max_sel;
-    const dim3 grid((unsigned)(p.lh_range * p.tiles_total), (unsigned)(2 * ((p.LH + p.lh_range - 1) / p.lh_range)));
+    const AlignHead &hd = p.head;
+    const dim3 grid((unsigned)(hd.lh_range * hd.tiles_total), (unsigned)(2 * ((hd.LH + hd.lh_range - 1) / hd.lh_range)));
     const auto kernel = few_rows(p, pl.n_blocks, pl.max_sel, 32 * LPR) ? align_kernel<T, LPR, true> : align_kernel<T, LPR, false>;
     return launch(kernel, grid, dim3(kBlock), std::max(lds, lds_reserve(p, pl.n_blocks, LPR, (int)sizeof(T), units)), stream, p);
 }
@@ -291,17 +295,16 @@ int align_kv_batch(const kvcomm_model *model, int32_t gran, kvcomm_tensor anchor
     int st = plan_align(model, gran, anchor_layout, es, jobs, n_jobs, kOnePairPerBlock, p, pl,
                         [](int, const kvcomm_align_job &, int) { return (int)KVCOMM_OK; });
     if (st) return st;
-    p.by_tiles = make_divisor((uint32_t)p.tiles_total);
-    p.by_H = make_divisor((uint32_t)p.H);
     for (int j = 0; j < n_jobs; ++j) {
-        p.by_pitch[j] = make_divisor((uint32_t)std::max(1, jobs[j].n_anchors));
-        for (int a = 0; a < jobs[j].n_anchors; ++a) p.sel_mask[j] |= (uint64_t)(jobs[j].anchor_len[a] >= jobs[j].seg_len) << a;
+        p.job[j].by_pitch = make_divisor((uint32_t)std::max(1, jobs[j].n_anchors));
+        for (int a = 0; a < jobs[j].n_anchors; ++a) p.job[j].sel_mask |= (uint64_t)(jobs[j].anchor_len[a] >= jobs[j].seg_len) << a;
     }
     // A launch holds fewer than 2^32 threads along an axis, and 65535 blocks along the second: more (layer, head) pairs than go along the
     // first come as further pairs (keys, values) along that one.
     constexpr int64_t kMaxBlocks = ((int64_t)1 << 32) / kBlock - 1;
-    p.lh_range = (int32_t)std::min<int64_t>(p.LH, kMaxBlocks / p.tiles_total);
-    if (p.lh_range < 1 || (p.LH + p.lh_range - 1) / p.lh_range > 65535 / 2) return KVCOMM_EUNSUPPORTED;
+    AlignHead &hd = p.head;
+    hd.lh_range = (int32_t)std::min<int64_t>(hd.LH, kMaxBlocks / hd.tiles_total);
+    if (hd.lh_range < 1 || (hd.LH + hd.lh_range - 1) / hd.lh_range > 65535 / 2) return KVCOMM_EUNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (model->dtype == KVCOMM_BF16) {
         switch (pl.lpr) {

@@ -104,6 +104,7 @@ struct CaptureParams {
     void *out[2];
     Strides s_base[2], s_real[2], s_out[2];
     int32_t H, S, LH, lh_per_block, n_token_tiles, delta;
+    divisor_t by_tiles, by_H;
     double inv_freq[kMaxHalf];
 };
 
@@ -121,9 +122,10 @@ __global__ __launch_bounds__(kBlock) void capture_kernel(const CaptureParams p)
 
     const int tid = threadIdx.x;
     const int row = tid / LPR, lir = tid % LPR;
-    const int tile = blockIdx.x % p.n_token_tiles;
-    const int chunk = blockIdx.x / p.n_token_tiles;
     const int which = blockIdx.y;
+    await_args(arg_word(&p), arg_word(&p.s_base[which]), arg_word(&p.s_out[which]), arg_word(&p.by_tiles));
+    const int chunk = div_by(blockIdx.x, p.by_tiles);
+    const int tile = blockIdx.x - chunk * p.n_token_tiles;
     const bool rot = which == 0 && p.delta != 0;
     const int t = tile * RPB + row;
     if (rot)
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(kBlock) void capture_kernel(const CaptureParams p)
     const int64_t col0 = (int64_t)lir * EPV;
     const int lh1 = min((chunk + 1) * p.lh_per_block, p.LH);
     for (int lh = chunk * p.lh_per_block; lh < lh1; ++lh) {
-        const int l = lh / p.H, h = lh % p.H;
+        const int l = div_by(lh, p.by_H), h = lh - l * p.H;
         const T *xp = bp + l * sb.layer + h * sb.head + t * sb.token + col0;
         const T *yp = rp + l * sr.layer + h * sr.head + t * sr.token + col0;
         const u32x4 xlo = load16_stream(xp), xhi = load16_stream(xp + HALF);
@@ -261,6 +263,8 @@ extern "C" int kvcomm_capture_offsets(const kvcomm_model *model, kvcomm_tensor b
     const int lpr = model->head_dim / (2 * (16 / es));
     const int rpb = kBlock / lpr;
     p.n_token_tiles = (seg_len + rpb - 1) / rpb;
+    p.by_tiles = make_divisor((uint32_t)p.n_token_tiles);
+    p.by_H = make_divisor((uint32_t)p.H);
     const int target_blocks = 16384;
     int n_chunks = (target_blocks + p.n_token_tiles - 1) / p.n_token_tiles;
     if (n_chunks > p.LH) n_chunks = p.LH;

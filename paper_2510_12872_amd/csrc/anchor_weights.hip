@@ -96,18 +96,18 @@ struct DistJob {
     Strides s_seg;
     double *partial;       // [component][n_chunks][S][n_sel]
     int64_t comp_stride;   // elements between components (cosine rule)
-    int32_t S, n_token_tiles, block0;
+    int32_t S, n_token_tiles;
     int16_t a0, n_sel;     // its selected anchors: entries [a0, a0 + n_sel) of anc
     // outputs of the fused form (per-(layer, head, token) weights straight from the distance kernel)
     float *weights;
     int32_t *nearest;
     int32_t *selected_out;
     uint64_t sel_mask;     // bit a = anchor a is selected
+    divisor_t by_tiles;    // of n_token_tiles
     int32_t n_anchors;
 };
 
-struct DistParams {
-    DistJob job[KVCOMM_MAX_BATCH];
+struct DistParams {   // (begins with what every block reads first)
     Strides s_anc;
     int32_t H, LH, lh_per_block, n_jobs;
     int32_t fused, rule;   // fused: a row's distances are complete inside its lanes; write the weights here
@@ -116,17 +116,26 @@ struct DistParams {
     int32_t per_segment;   // one weight set per segment: a block also adds up its rows (partial[chunk][tile][anchor])
     double tau;
     divisor_t by_H;
+    int32_t block0[KVCOMM_MAX_BATCH];   // first block of a segment
+    DistJob job[KVCOMM_MAX_BATCH];
     const void *anc[KVCOMM_MAX_ANCHORS + kAnchorTile];  // selected anchors of all segments (a tile's pointers are read without a look at how many it has)
     uint8_t col[KVCOMM_MAX_ANCHORS];      // original index of a selected anchor
 };
 static_assert(sizeof(DistParams) <= 4096, "kernel arguments are limited to 4 KB");
 
-__device__ __forceinline__ int job_of_block(const DistParams &p, int block)
+__device__ __forceinline__ void await_dist_args(const DistParams &p)
+{
+    await_args(arg_word(&p), arg_word(&p.rule), arg_word(p.block0), arg_word(&p.job[0]), arg_word(&p.job[0].S), arg_word(p.anc), arg_word(p.anc + 8),
+               arg_word(p.col));
+}
+
+template <class P>
+__device__ __forceinline__ int job_of_block(const P &p, int block)
 {
     int ji = 0;
 #pragma unroll
     for (int i = 1; i < KVCOMM_MAX_BATCH; ++i)
-        if (i < p.n_jobs && block >= p.job[i].block0) ji = i;
+        if (i < p.n_jobs && block >= p.block0[i]) ji = i;
     return ji;
 }
 
@@ -184,14 +193,17 @@ __global__ __launch_bounds__(kBlock) void dist_partial_kernel(const DistParams p
 {
     constexpr int EPV = Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
+    await_dist_args(p);
     const int block = pair_of_block(p);
     if (block >= p.n_blocks) return;
-    const DistJob &jb = p.job[job_of_block(p, block)];
+    const int ji = job_of_block(p, block);
+    const DistJob &jb = p.job[ji];
+    if (ji > 0) await_args(arg_word(&jb), arg_word(&jb.sel_mask));
     const int tid = threadIdx.x;
     const int row = tid / LPR, lir = tid % LPR;
-    const int bx = block - jb.block0;
-    const int tile = bx % jb.n_token_tiles;
-    const int chunk = bx / jb.n_token_tiles;
+    const int bx = block - p.block0[ji];
+    const int chunk = div_by(bx, jb.by_tiles);
+    const int tile = bx - chunk * jb.n_token_tiles;
     const int a0 = blockIdx.y * p.tile_anchors;
     const int na = min(p.tile_anchors, jb.n_sel - a0);
     __builtin_assume(na <= NA);   // (without it the 16-anchor kernel takes 132 registers: 3 wavefronts per SIMD, 8 % slower)
@@ -210,7 +222,7 @@ __global__ __launch_bounds__(kBlock) void dist_partial_kernel(const DistParams p
     const int64_t arow = t * p.s_anc.token + lir * EPV;
     auto walk = [&](auto full) __attribute__((always_inline)) {   // full: every anchor of the tile exists (no branches)
         for (int lh = lh0; lh < lh1; ++lh) {
-            const int l = lh / p.H, h = lh % p.H;
+            const int l = div_by(lh, p.by_H), h = lh - l * p.H;
             const T *sp = seg + l * jb.s_seg.layer + h * jb.s_seg.head;
             const u32x4 rs = load16(sp);   // plain: see above
             const int64_t aoff = arow + l * p.s_anc.layer + h * p.s_anc.head;
@@ -307,12 +319,15 @@ __global__ __launch_bounds__(kBlock) void dist_row_softmax_kernel(const DistPara
     constexpr int EPV = Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
     constexpr int NPL = (NA + LPR - 1) / LPR;  // anchors per lane
-    const DistJob &jb = p.job[job_of_block(p, blockIdx.x)];
+    await_dist_args(p);
+    const int ji = job_of_block(p, blockIdx.x);
+    const DistJob &jb = p.job[ji];
+    if (ji > 0) await_args(arg_word(&jb), arg_word(&jb.sel_mask));
     const int tid = threadIdx.x;
     const int row = tid / LPR, lir = tid % LPR;
-    const int bx = blockIdx.x - jb.block0;
-    const int tile = bx % jb.n_token_tiles;
-    const int chunk = bx / jb.n_token_tiles;
+    const int bx = blockIdx.x - p.block0[ji];
+    const int chunk = div_by(bx, jb.by_tiles);
+    const int tile = bx - chunk * jb.n_token_tiles;
     const int na = jb.n_sel;  // 1 ... NA (checked by the host)
     const int t = tile * RPB + row;
     const bool valid = t < jb.S;
@@ -328,7 +343,7 @@ __global__ __launch_bounds__(kBlock) void dist_row_softmax_kernel(const DistPara
 #pragma unroll
         for (int j = 0; j < NA; ++j) acc[j] = 0.0;
         auto add_row = [&](auto full) __attribute__((always_inline)) {   // full: na == NA (no branches)
-            const int l = lh / p.H, h = lh % p.H;
+            const int l = div_by(lh, p.by_H), h = lh - l * p.H;
             const u32x4 rs = load16(seg + l * jb.s_seg.layer + h * jb.s_seg.head);
             const int64_t aoff = arow + l * p.s_anc.layer + h * p.s_anc.head;
             u32x4 ra[NA];
@@ -408,14 +423,17 @@ __global__ __launch_bounds__(kBlock) void cos_partial_kernel(const DistParams p)
 {
     constexpr int EPV = Elem<T>::EPV;
     constexpr int RPB = kBlock / LPR;
+    await_dist_args(p);
     const int block = pair_of_block(p);
     if (block >= p.n_blocks) return;
-    const DistJob &jb = p.job[job_of_block(p, block)];
+    const int ji = job_of_block(p, block);
+    const DistJob &jb = p.job[ji];
+    if (ji > 0) await_args(arg_word(&jb), arg_word(&jb.sel_mask));
     const int tid = threadIdx.x;
     const int row = tid / LPR, lir = tid % LPR;
-    const int bx = block - jb.block0;
-    const int tile = bx % jb.n_token_tiles;
-    const int chunk = bx / jb.n_token_tiles;
+    const int bx = block - p.block0[ji];
+    const int chunk = div_by(bx, jb.by_tiles);
+    const int tile = bx - chunk * jb.n_token_tiles;
     const int a0 = blockIdx.y * p.tile_anchors;
     const int na = min(p.tile_anchors, jb.n_sel - a0);
     __builtin_assume(na <= kCosTile);
@@ -435,7 +453,7 @@ __global__ __launch_bounds__(kBlock) void cos_partial_kernel(const DistParams p)
         const T *seg = static_cast<const T *>(jb.seg_k) + t * jb.s_seg.token + lir * EPV;
         const int64_t arow = t * p.s_anc.token + lir * EPV;
         for (int lh = lh0; lh < lh1; ++lh) {
-            const int l = lh / p.H, h = lh % p.H;
+            const int l = div_by(lh, p.by_H), h = lh - l * p.H;
             const u32x4 rs = load16(seg + l * jb.s_seg.layer + h * jb.s_seg.head);
             const int64_t aoff = arow + l * p.s_anc.layer + h * p.s_anc.head;
             u32x4 ra[kCosTile];
@@ -502,14 +520,16 @@ struct FinalJob {
     int32_t *selected_out;
     int64_t comp_stride;   // cosine rule: elements between the three partial components
     uint64_t sel_mask;     // bit a = anchor a is selected
-    int32_t S, n_slots, n_anchors, chunk_lanes, block0, n_token_tiles;
+    int32_t S, n_slots, n_anchors, chunk_lanes, n_token_tiles;
     int16_t a0, n_sel;     // its selected anchors: entries [a0, a0 + n_sel) of col
 };
 
-struct FinalParams {
-    FinalJob job[KVCOMM_MAX_BATCH];
+struct FinalParams {   // (begins with what every block reads first)
     int32_t n_chunks, gran, rule, n_jobs;
     double tau;
+    int32_t block0[KVCOMM_MAX_BATCH];  // first block of a segment
+    uint64_t pad_;
+    FinalJob job[KVCOMM_MAX_BATCH];
     uint8_t col[KVCOMM_MAX_ANCHORS];   // original index of a selected anchor
 };
 
@@ -573,12 +593,11 @@ __global__ __launch_bounds__(kFinalBlock) void finalize_kernel(const FinalParams
 {
     __shared__ double dsh[kFinalBlock], esh[kFinalBlock];
     __shared__ double red[3][kFinalBlock];
-    int ji = 0;
-#pragma unroll
-    for (int i = 1; i < KVCOMM_MAX_BATCH; ++i)
-        if (i < p.n_jobs && (int)blockIdx.x >= p.job[i].block0) ji = i;
+    await_args(arg_word(&p), arg_word(&p.job[0]), arg_word(&p.job[0].n_slots), arg_word(p.col));
+    const int ji = job_of_block(p, blockIdx.x);
     const FinalJob &jb = p.job[ji];
-    const int bx = blockIdx.x - jb.block0;
+    if (ji > 0) await_args(arg_word(&jb), arg_word(&jb.n_token_tiles));
+    const int bx = blockIdx.x - p.block0[ji];
     const int tid = threadIdx.x;
     if (bx == 0 && jb.selected_out && tid < jb.n_anchors) jb.selected_out[tid] = (int32_t)((jb.sel_mask >> tid) & 1);
     if (jb.n_sel == 0) {  // nothing selected: all weights 0, nearest -1
@@ -657,6 +676,7 @@ __global__ __launch_bounds__(kSegBlock) void finalize_segment_kernel(const Final
     __shared__ double fin[3][NF * KVCOMM_MAX_ANCHORS];
     __shared__ double dsh[KVCOMM_MAX_ANCHORS], esh[KVCOMM_MAX_ANCHORS];
     const FinalJob &jb = p.job[blockIdx.x];
+    await_args(arg_word(&p), arg_word(&jb), arg_word(&jb.n_slots), arg_word(p.col));
     const int tid = threadIdx.x;
     if (jb.selected_out && tid < jb.n_anchors) jb.selected_out[tid] = (int32_t)((jb.sel_mask >> tid) & 1);
     if (jb.n_sel == 0) {
@@ -725,8 +745,11 @@ __global__ __launch_bounds__(kTokBlock, COS ? 2 : 4) void token_weights_kernel(c
     constexpr int NC = COS ? 3 : 1;
     __shared__ double red[NC][NW][RPW][NA];
     __shared__ double sc[RPW * KVCOMM_MAX_ANCHORS], ex[RPW * KVCOMM_MAX_ANCHORS];
-    const DistJob &jb = p.job[job_of_block(p, blockIdx.x)];
-    const int tid = threadIdx.x, bx = blockIdx.x - jb.block0;
+    await_dist_args(p);
+    const int ji = job_of_block(p, blockIdx.x);
+    const DistJob &jb = p.job[ji];
+    if (ji > 0) await_args(arg_word(&jb), arg_word(&jb.sel_mask));
+    const int tid = threadIdx.x, bx = blockIdx.x - p.block0[ji];
     const int tpb = 1 << p.tok_shift, t0 = bx << p.tok_shift;   // tpb <= RPW
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rw = (tid & 63) / LPR, lir = tid % LPR;
@@ -1059,7 +1082,8 @@ extern "C" int kvcomm_anchor_weights_batch(const kvcomm_model *model, int32_t gr
         dj.comp_stride = (int64_t)pl.n_chunks * jd.seg_len * dj.n_sel;  // <= a third of the segment's partials
         dj.S = jd.seg_len;
         dj.n_token_tiles = (jd.seg_len + pl.rpb - 1) / pl.rpb;
-        dj.block0 = (int32_t)dist_blocks;
+        dj.by_tiles = make_divisor((uint32_t)dj.n_token_tiles);
+        dp.block0[j] = (int32_t)dist_blocks;
         dist_blocks += (int64_t)pl.n_chunks * dj.n_token_tiles;
 
         dj.weights = jd.weights_out;
@@ -1084,7 +1108,7 @@ extern "C" int kvcomm_anchor_weights_batch(const kvcomm_model *model, int32_t gr
         }
         fj.chunk_lanes = cl;
         const int spb = dj.n_sel > 0 ? kFinalBlock / (cl * dj.n_sel) : kFinalBlock;
-        fj.block0 = (int32_t)final_blocks;
+        fp.block0[j] = (int32_t)final_blocks;
         final_blocks += (fj.n_slots + spb - 1) / spb;
     }
     if (dist_blocks > 0x7fffffff || final_blocks > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
@@ -1094,7 +1118,7 @@ extern "C" int kvcomm_anchor_weights_batch(const kvcomm_model *model, int32_t gr
         dp.tok_shift = shift;
         int64_t blocks = 0;
         for (int j = 0; j < n_jobs; ++j) {
-            dp.job[j].block0 = (int32_t)blocks;
+            dp.block0[j] = (int32_t)blocks;
             blocks += ((int64_t)jobs[j].seg_len + (1 << shift) - 1) >> shift;
         }
         st = KVCOMM_EUNSUPPORTED;

@@ -27,6 +27,11 @@ struct AttnParams {
     int32_t groups_per_tile;  // 32-row groups of a row tile (= wavefronts that own rows)
     divisor_t by_G, by_Hkv, by_row_tiles, by_splits, by_groups;   // set_divisors()
 };
+__device__ __forceinline__ void await_attn_args(const AttnParams &p)
+{
+    await_args(arg_word(&p), arg_word(&p.s_q.token), arg_word(&p.s_v), arg_word(&p.L));
+    await_args(arg_word(&p.n_splits), arg_word(&p.by_groups));
+}
 static inline void set_divisors(AttnParams &p)
 {
     p.by_G = make_divisor((uint32_t)p.G);

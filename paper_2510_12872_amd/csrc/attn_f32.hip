@@ -354,6 +354,7 @@ __device__ __forceinline__ void attn_f32_item(const AttnParams &p, int item)   /
 template <int D, int RH, bool PERSIST>
 __global__ __launch_bounds__(64 * kF32Waves, D * RH <= 128 ? 4 : 2) void attn_f32_kernel(const AttnParams p)
 {
+    await_attn_args(p);
     if constexpr (!PERSIST) {
         attn_f32_item<D, RH>(p, blockIdx.x);
     } else {

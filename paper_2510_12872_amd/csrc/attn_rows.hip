@@ -38,6 +38,7 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
     __shared__ __align__(16) unsigned char smem[NW * 2 * HALFB];
     __shared__ float ml[2][NW][32];
 
+    await_attn_args(p);
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, n = lane & 31, hg = lane >> 5;
@@ -318,6 +319,7 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
     __shared__ __align__(16) unsigned char smem[NW * 2 * HALFB];
     __shared__ float ml[2][NW][ROWS];
 
+    await_attn_args(p);
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, n = lane & 15, g = lane >> 4;
@@ -653,6 +655,7 @@ __device__ __forceinline__ void combine16(const AttnParams &p)
 template <int D, int U, int ROWS>
 __global__ __launch_bounds__(256) void attn_combine_kernel(const AttnParams p)
 {
+    await_attn_args(p);
     if constexpr (ROWS == 16)
         combine16<D, U>(p);
     else

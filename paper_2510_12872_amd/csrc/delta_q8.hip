@@ -95,6 +95,7 @@ struct QuantParams {
     uint8_t *out;
     Strides s_in, s_out;
     int32_t H, S, LH, n_token_tiles;
+    divisor_t by_tiles, by_H;
     float inv_scale;
 };
 
@@ -109,9 +110,10 @@ __global__ __launch_bounds__(kBlock) void quantize_kernel(const QuantParams p)
     constexpr int RPB = kBlock / LPR;
     constexpr int U = KVC_QUANT_ROWS;
     const int row = threadIdx.x / LPR, lir = threadIdx.x % LPR;
-    const int tile = blockIdx.x % p.n_token_tiles;   // a tile is U * RPB consecutive tokens
-    const int lh = blockIdx.x / p.n_token_tiles;
-    const int l = lh / p.H, h = lh % p.H;
+    await_args(arg_word(&p), arg_word(&p.by_tiles));
+    const int lh = div_by(blockIdx.x, p.by_tiles);
+    const int tile = blockIdx.x - lh * p.n_token_tiles;   // a tile is U * RPB consecutive tokens
+    const int l = div_by(lh, p.by_H), h = lh - l * p.H;
     const T *xb = static_cast<const T *>(p.in) + l * p.s_in.layer + h * p.s_in.head + lir * EPV;
     uint8_t *yb = p.out + l * p.s_out.layer + h * p.s_out.head + lir * EPV;
     u32x4 raw[U];
@@ -158,12 +160,8 @@ __global__ __launch_bounds__(kBlock) void quantize_kernel(const QuantParams p)
 // Same launch-wide layout as the uncompressed update (per-segment descriptors, selected anchors and rotation
 // tables of all segments in the kernel arguments); a deviation's power-of-two scale travels as its exponent.
 struct AlignQ8Params {
+    AlignHead head;
     AlignJob job[KVCOMM_MAX_BATCH];
-    Strides s_anc;             // in bytes (= elements of the E4M3 tensors)
-    int32_t H, LH;
-    int32_t gran, n_jobs;
-    int32_t lh_per_block;
-    int32_t tiles_total;
     int32_t tab_delta[kMaxTab];
     const void *anc[2][KVCOMM_MAX_ANCHORS];
     alignas(4) int8_t scale_exp[2][KVCOMM_MAX_ANCHORS];   // [0] key, [1] value deviation scale = 2^scale_exp of a selected anchor
@@ -187,9 +185,15 @@ __global__ __launch_bounds__(kBlock, KVC_ALIGNQ8_WPE) void align_q8_kernel(const
     constexpr int HALF = LPR * EPV;
     constexpr int RPB = kBlock / LPR;
 
-    const int chunk = blockIdx.x / p.tiles_total;
-    const int r = blockIdx.x % p.tiles_total;
-    const AlignJob &jb = p.job[job_of_tile(p, r)];
+    const int which = blockIdx.y;
+    const AlignHead &hd = p.head;
+    await_args(arg_word(&hd), arg_word(hd.tile0), arg_word(&p.job[0]), arg_word(&p.job[0].s_base[1]), arg_word(&p.job[0].S), arg_word(p.anc[which]),
+               arg_word(p.scale_exp[which]), arg_word(p.col));
+    const int chunk = div_by(blockIdx.x, hd.by_tiles);
+    const int r = blockIdx.x - chunk * hd.tiles_total;
+    const int ji = job_of_tile(p, r);
+    const AlignJob &jb = p.job[ji];
+    if (ji > 0) await_args(arg_word(&jb), arg_word(&jb.s_base[1]), arg_word(&jb.s_out[1]), arg_word(&jb.S));
     const int n_sel = jb.n_sel, a0 = jb.a0;
 
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -198,22 +202,21 @@ __global__ __launch_bounds__(kBlock, KVC_ALIGNQ8_WPE) void align_q8_kernel(const
 
     const int tid = threadIdx.x;
     const int row = tid / LPR, lir = tid % LPR;
-    const int tile = r - jb.tile0;
-    const int which = blockIdx.y;
+    const int tile = r - hd.tile0[ji];
     const bool is_k = which == 0;
     const int t = tile * RPB + row;
     const bool valid = t < jb.S;
-    const int lh0 = chunk * p.lh_per_block;
-    const int lh1 = min(lh0 + p.lh_per_block, p.LH);
+    const int lh0 = chunk * hd.lh_range;
+    const int lh1 = min(lh0 + hd.lh_range, hd.LH);
 
     if (is_k)
         for (int idx = tid; idx < jb.n_tab * HALF; idx += kBlock)
             cs[idx] = rope_cos_sin(p.tab_delta[jb.t0 + idx / HALF], p.inv_freq[idx % HALF]);
-    if (p.gran != KVCOMM_W_LAYER_HEAD_TOKEN) {
+    if (hd.gran != KVCOMM_W_LAYER_HEAD_TOKEN) {
         for (int idx = tid; idx < RPB * n_sel; idx += kBlock) {
             const int rr = idx / n_sel, a = idx % n_sel;
             const int tt = tile * RPB + rr;
-            const int64_t slot = p.gran == KVCOMM_W_TOKEN ? tt : 0;
+            const int64_t slot = hd.gran == KVCOMM_W_TOKEN ? tt : 0;
             w_lds[idx] = tt < jb.S ? jb.weights[slot * jb.w_pitch + p.col[a0 + a]] * pow2f(p.scale_exp[which][a0 + a]) : 0.f;
         }
     }
@@ -243,11 +246,11 @@ __global__ __launch_bounds__(kBlock, KVC_ALIGNQ8_WPE) void align_q8_kernel(const
         Q8Raw<EPV> x[kQ8InFlight];
     };
     auto anchor_off = [&](int lh) {
-        const int l = lh / p.H, h = lh % p.H;
-        return l * p.s_anc.layer + h * p.s_anc.head + t * p.s_anc.token;
+        const int l = div_by(lh, hd.by_H), h = lh - l * hd.H;
+        return l * hd.s_anc.layer + h * hd.s_anc.head + t * hd.s_anc.token;
     };
     auto issue = [&](int lh, Stage &st) {
-        const int l = lh / p.H, h = lh % p.H;
+        const int l = div_by(lh, hd.by_H), h = lh - l * hd.H;
         const T *xp = bp + l * sb.layer + h * sb.head + t * sb.token + col0;
         st.rlo = load16_stream(xp);
         st.rhi = load16_stream(xp + HALF);
@@ -260,10 +263,10 @@ __global__ __launch_bounds__(kBlock, KVC_ALIGNQ8_WPE) void align_q8_kernel(const
     Stage cur;
     issue(lh0, cur);
     for (int lh = lh0; lh < lh1; ++lh) {
-        const int l = lh / p.H, h = lh % p.H;
+        const int l = div_by(lh, hd.by_H), h = lh - l * hd.H;
         Stage nxt;
         if (lh + 1 < lh1) issue(lh + 1, nxt);
-        const float *wrow = p.gran == KVCOMM_W_LAYER_HEAD_TOKEN ? jb.weights + ((int64_t)lh * jb.S + t) * jb.w_pitch : nullptr;
+        const float *wrow = hd.gran == KVCOMM_W_LAYER_HEAD_TOKEN ? jb.weights + ((int64_t)lh * jb.S + t) * jb.w_pitch : nullptr;
 
         float lo[EPV], hi[EPV];
         unpack<T>(cur.rlo, lo);
@@ -375,6 +378,8 @@ extern "C" int kvcomm_quantize_deltas(const kvcomm_model *model, kvcomm_tensor i
     const int lpr = model->head_dim / (16 / elem_size(dt));
     const int rpb = (kBlock / lpr) * KVC_QUANT_ROWS;   // tokens per block
     p.n_token_tiles = (n_tokens + rpb - 1) / rpb;
+    p.by_tiles = make_divisor((uint32_t)p.n_token_tiles);
+    p.by_H = make_divisor((uint32_t)p.H);
     const int64_t n_blocks = (int64_t)p.n_token_tiles * p.LH;
     if (n_blocks > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -414,7 +419,7 @@ extern "C" int kvcomm_align_kv_q8_batch(const kvcomm_model *model, int32_t gran,
                         });
     if (st) return st;
     if (pl.n_blocks > 0x7fffffff) return KVCOMM_EUNSUPPORTED;
-    p.lh_per_block = pl.lh_per_block;
+    p.head.lh_range = pl.lh_per_block;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int nb = (int)pl.n_blocks;
     if (model->dtype == KVCOMM_BF16) {

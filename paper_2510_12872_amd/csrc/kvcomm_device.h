@@ -119,6 +119,20 @@ __device__ __forceinline__ float2 rope_cos_sin(int32_t delta, double inv_freq)
     return make_float2(((q + 1) & 2) ? -fc : fc, (q & 2) ? -fs : fs);
 }
 
+// Waits for words of the kernel arguments that lie in different 64-byte lines, so that these are requested together.  A launch's arguments lie
+// in memory that no cache of the chip holds yet; read where they are used, one line's address or branch hanging on the line before, they
+// cost a wavefront one trip to that memory after the other.  So what a block of a one-segment launch needs first lies in few lines
+// (the parameter structures begin with it), and these are awaited at its start.  us per call from a queue that is never empty: update of 8
+// tokens, 4 anchors 4.7 -> 4.1, of 8 anchors recorded elsewhere 6.3 -> 5.2, compressed 5.2 -> 4.3; matching and update of 77 tokens, 6 anchors 28.9 ->
+// 26.8.  (All lines of a structure awaited, thirty of them: 5.8 instead of 5.2.)
+__device__ __forceinline__ uint32_t arg_word(const void *field) { return *static_cast<const uint32_t *>(field); }
+__device__ __forceinline__ void await_args(uint32_t a, uint32_t b) { asm volatile("" : : "s"(a), "s"(b)); }
+__device__ __forceinline__ void await_args(uint32_t a, uint32_t b, uint32_t c, uint32_t d) { asm volatile("" : : "s"(a), "s"(b), "s"(c), "s"(d)); }
+__device__ __forceinline__ void await_args(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t e, uint32_t f, uint32_t g, uint32_t h)
+{
+    asm volatile("" : : "s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f), "s"(g), "s"(h));
+}
+
 // ------------------------------------------------------------------------- host-side checks
 static inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 

@@ -15,6 +15,7 @@
 
 #include <cxxabi.h>
 
+#include <algorithm>
 #include <climits>
 
 #include "kvcomm.h"
@@ -519,6 +520,40 @@ PyObject *quantize_deltas(PyObject *, PyObject *const *args, Py_ssize_t n)
     });
 }
 
+// (tensors a, lists of tensors b, tensors c): 1 if no tensor of b comes near a byte of a tensor of a and those of c not near each
+// other, else 0
+PyObject *apart(PyObject *, PyObject *const *args, Py_ssize_t n)
+{
+    struct Range {
+        uintptr_t lo, hi;
+        explicit Range(const at::Tensor &t)
+        {
+            int64_t last = 0;
+            for (int64_t d = 0; d < t.dim(); ++d) last += std::max<int64_t>(0, t.size(d) - 1) * t.stride(d);
+            lo = reinterpret_cast<uintptr_t>(t.data_ptr());
+            hi = lo + (uintptr_t)(last + 1) * t.element_size();
+        }
+    };
+    return entry<3>(args, n, [](PyObject *const *a) {
+        const Items own(a[0], INT_MAX), groups(a[1], INT_MAX), each(a[2], INT_MAX);
+        std::vector<Range> r;
+        auto meets = [&](const Range &o, size_t from, size_t to) {
+            return std::any_of(r.begin() + from, r.begin() + to, [&](const Range &x) { return x.lo < o.hi && o.lo < x.hi; });
+        };
+        for (int i = 0; i < own.n; ++i) r.emplace_back(as_tensor(own.p[i]));
+        for (int g = 0; g < groups.n; ++g) {
+            const Items other(groups.p[g], INT_MAX);
+            for (int k = 0; k < other.n; ++k)
+                if (meets(Range(as_tensor(other.p[k])), 0, own.n)) return 0LL;
+        }
+        for (int i = 0; i < each.n; ++i) {
+            r.emplace_back(as_tensor(each.p[i]));
+            if (meets(r.back(), own.n, r.size() - 1)) return 0LL;
+        }
+        return 1LL;
+    });
+}
+
 // bind(addresses by entry point's name, Model, current_device, current_stream or None)
 PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
@@ -563,6 +598,7 @@ PyMethodDef methods[] = {FAST("bind", bind),
                          FAST("anchor_predict", anchor_predict),
                          FAST("capture_offsets", capture_offsets),
                          FAST("quantize_deltas", quantize_deltas),
+                         FAST("apart", apart),
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -15,6 +15,12 @@ def model_of(w):
     return kv.Model(w.n_layers, w.n_kv_heads, w.n_q_heads, w.head_dim, w.dtype, w.rope_theta)
 
 
+# Up to here a segment's workspace also holds the launch that several segments share.  Per-token weights stay below it in general (1024
+# tokens, 16 anchors: 6 MiB); weights per layer and head pass it with segments that keep the chip busy each by itself (134 MB), and
+# those go one after the other.
+JOINT_WORKSPACE = 16 << 20
+
+
 class Scratch:
     """Reusable device buffers for the weight step (so a timed loop allocates nothing)."""
 
@@ -24,6 +30,10 @@ class Scratch:
         self.nearest = torch.empty((n,), dtype=torch.int32, device=device)
         self.selected = torch.empty((n_anchors,), dtype=torch.int32, device=device)
         need = kv.kvcomm_anchor_weights_workspace(model, seg_len, n_anchors, gran)
+        together = max(1, min(kv.MAX_BATCH, kv.MAX_ANCHORS // max(1, n_anchors)))   # a launch of reuse_agent takes so many like it
+        joint = kv.kvcomm_anchor_weights_batch_workspace(model, [seg_len] * together, [n_anchors] * together, gran)
+        if joint <= JOINT_WORKSPACE:
+            need = max(need, joint)
         self.workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=device)
 
 
@@ -69,6 +79,23 @@ class AgentScratch:
         self.workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=device)
 
 
+def _align_together(w, model, agent, idx, outs, workspace, gran, stream):
+    """One batched call per step for the agent's segments `idx`; outs[j]: weights, nearest and selected of segment j."""
+    segs = agent.segments
+    kv.kvcomm_anchor_weights_batch(model, [dict(
+        seg_base_k=segs[j].base_k, anchor_base_k=segs[j].anchor_k, anchor_len=segs[j].anchor_len,
+        weights_out=outs[j][0], nearest_out=outs[j][1], selected_out=outs[j][2])
+        for j in idx], w.temperature, gran, workspace=workspace, stream=stream)
+    jobs = []
+    for j in idx:
+        p0, S = w.seg_offset(j), segs[j].base_k.shape[2]
+        jobs.append(dict(base_k=segs[j].base_k, base_v=segs[j].base_v, anchor_dk=segs[j].anchor_dk,
+                         anchor_dv=segs[j].anchor_dv, anchor_len=segs[j].anchor_len, weights=outs[j][0],
+                         delta_pos=segs[j].delta_pos, anchor_delta_pos=segs[j].anchor_delta_pos,
+                         out_k=_slot(agent.cache_k, p0, S), out_v=_slot(agent.cache_v, p0, S)))
+    kv.kvcomm_align_kv_batch(model, jobs, gran, stream)
+
+
 def align_agent_batched(w, model, agent, gran=kv.W_TOKEN, scratch=None, stream=None):
     """Anchor weights, then aligned K/V of ALL segments of an agent: one batched call per step and
     chunk of segments (a launch holds at most MAX_BATCH segments and MAX_ANCHORS anchors)."""
@@ -76,29 +103,64 @@ def align_agent_batched(w, model, agent, gran=kv.W_TOKEN, scratch=None, stream=N
     if scratch is None:
         scratch = AgentScratch(model, [s.base_k.shape[2] for s in segs], [len(s.anchor_k) for s in segs], gran,
                                segs[0].base_k.device)
+    outs = list(zip(scratch.weights, scratch.nearest, scratch.selected))
     for idx in launch_chunks([len(s.anchor_k) for s in segs]):
-        kv.kvcomm_anchor_weights_batch(model, [dict(
-            seg_base_k=segs[j].base_k, anchor_base_k=segs[j].anchor_k, anchor_len=segs[j].anchor_len,
-            weights_out=scratch.weights[j], nearest_out=scratch.nearest[j], selected_out=scratch.selected[j])
-            for j in idx], w.temperature, gran, workspace=scratch.workspace, stream=stream)
-        jobs = []
-        for j in idx:
-            p0, S = w.seg_offset(j), segs[j].base_k.shape[2]
-            jobs.append(dict(base_k=segs[j].base_k, base_v=segs[j].base_v, anchor_dk=segs[j].anchor_dk,
-                             anchor_dv=segs[j].anchor_dv, anchor_len=segs[j].anchor_len, weights=scratch.weights[j],
-                             delta_pos=segs[j].delta_pos, anchor_delta_pos=segs[j].anchor_delta_pos,
-                             out_k=agent.cache_k[:, :, p0:p0 + S], out_v=agent.cache_v[:, :, p0:p0 + S]))
-        kv.kvcomm_align_kv_batch(model, jobs, gran, stream)
+        _align_together(w, model, agent, idx, outs, scratch.workspace, gran, stream)
     return scratch
 
 
-def reuse_agent(w, model, agent, out=None, gran=kv.W_TOKEN, scratches=None, stream=None):
-    """Whole hot path for one agent: align every segment into its cache slot, then suffix attention."""
-    for j, seg in enumerate(agent.segments):
+def _slot(cache, p0, S):
+    """Rows [p0, p0 + S) of a cache."""
+    return cache.narrow(2, p0, S) if 0 <= p0 <= cache.shape[2] - S else cache[:, :, p0:p0 + S]   # (narrow: half the time of an index)
+
+
+def _independent(w, agent, lens, outs):
+    """May these segments be aligned in any order, and twice?  Their slots, and what the weights go to, lie apart, and nothing that is read
+    lies in the agent's cache: a key or a delta in a slot that an earlier segment's update writes is read after that update, and an
+    update in place cannot be made again."""
+    end = 0
+    for j, S in enumerate(lens):
         p0 = w.seg_offset(j)
-        S = seg.base_k.shape[2]
-        align_segment(model, seg, agent.cache_k[:, :, p0:p0 + S], agent.cache_v[:, :, p0:p0 + S],
-                      w.temperature, gran, None if scratches is None else scratches[j], stream)
+        if p0 < end:
+            return False
+        end = p0 + S
+    return end <= min(agent.cache_k.shape[2], agent.cache_v.shape[2]) and kv.apart(
+        (agent.cache_k, agent.cache_v),
+        [g for s in agent.segments for g in ((s.base_k, s.base_v), s.anchor_k, s.anchor_dk, s.anchor_dv)], [t for o in outs for t in o])
+
+
+def _align_all(w, model, agent, gran, scratches, stream):
+    """Aligns the segments of an agent in chunks of one launch per step.  Returns False where that may not be done or is refused
+    (segments that depend on each other, anchors of several layouts, too many rotations, a small workspace): nothing that counts has been written then."""
+    segs = agent.segments
+    lens, pools = [s.base_k.shape[2] for s in segs], [len(s.anchor_k) for s in segs]
+    given = scratches is not None
+    if min(pools) == 0 or given and not all(isinstance(s, Scratch) for s in scratches):
+        return False
+    outs = [(s.weights, s.nearest, s.selected) for s in scratches[:len(segs)]] if given else ()
+    if given and len(outs) < len(segs) or not _independent(w, agent, lens, outs):
+        return False
+    try:
+        if not given:
+            align_agent_batched(w, model, agent, gran, None, stream)
+            return True
+        for idx in launch_chunks(pools):
+            _align_together(w, model, agent, idx, outs, max((scratches[j].workspace for j in idx), key=torch.Tensor.numel), gran, stream)
+        return True
+    except (kv.KVCommError, torch.OutOfMemoryError):
+        return False   # one after the other they may be accepted, or are refused as they always were
+
+
+def reuse_agent(w, model, agent, out=None, gran=kv.W_TOKEN, scratches=None, stream=None):
+    """Whole hot path for one agent: align every segment into its cache slot, then suffix attention.  Several segments go through the
+    batched calls: a small agent's step is the number of its launches (4 segments of 10 tokens, 16 anchors, 2 layers x 8 heads: 66 us
+    one after the other, 36 us so; as a graph 58 and 18 us)."""
+    if len(agent.segments) < 2 or not _align_all(w, model, agent, gran, scratches, stream):
+        for j, seg in enumerate(agent.segments):
+            p0 = w.seg_offset(j)
+            S = seg.base_k.shape[2]
+            align_segment(model, seg, _slot(agent.cache_k, p0, S), _slot(agent.cache_v, p0, S),
+                          w.temperature, gran, None if scratches is None else scratches[j], stream)
     if agent.q is None:
         return None
     return kv.kvcomm_suffix_attn(model, agent.q, agent.cache_k, agent.cache_v, w.n_ctx, out=out, stream=stream)

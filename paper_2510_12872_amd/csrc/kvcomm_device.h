@@ -293,8 +293,7 @@ static inline int launch(void (*kernel)(P), dim3 grid, dim3 block, size_t lds_by
 typedef uint64_t divisor_t;   // mul, shift << 32
 static inline divisor_t make_divisor(uint32_t d)
 {
-    uint32_t L = 0;
-    while (((uint64_t)1 << L) < d) ++L;
+    const uint32_t L = d > 1 ? 32 - __builtin_clz(d - 1) : 0;
     return ((uint64_t)1 << (31 + L)) / d + 1 + ((uint64_t)(31 + L) << 32);
 }
 __host__ __device__ __forceinline__ int div_by(int n, divisor_t d) { return (int)(((uint64_t)(uint32_t)n * (uint32_t)d) >> (uint32_t)(d >> 32)); }

@@ -46,22 +46,17 @@ static_assert(sizeof(AlignParams) <= 4096, "kernel arguments are limited to 4 KB
 // Two anchors' rows (four 16-byte loads per lane) are requested together, the first two under the block's set-up.  What bounds the kernel is
 // HBM, and past about 64 KB in flight per compute unit more requests cost: pages are opened and closed out of order.  So the
 // launch reserves LDS that keeps the number of blocks per compute unit at what measured best (lds_reserve()).
-// SMALL (align_form()): what bounds the launch is the latency of a block, one group of anchors behind the other.  Four are requested together
+// SMALL (few_rows()): what bounds the launch is the latency of a block, one group of anchors behind the other.  Four are requested together
 // (all segments have as many), the set-up's own inputs before them, and the rows unconditionally (lanes behind the segment re-read its last
 // row): only then does the compiler wait for the set-up's loads alone while the rows stay in flight.  (Large launches gain nothing
 // from that: their other blocks fill the wait, and it moved them by -5 ... +5 %.)
-// SPLIT (align_form()): where few blocks run a wavefront has a SIMD to itself, and what bounds it is its own instructions, 0.2 us per anchor
-// (60 anchors: 17.1 us with four in flight, 14.5 with eight).  The anchors of a row are spread over the wavefronts of the block, which
-// holds a quarter of the rows; their fp32 sums meet in LDS in a fixed order: 7.4 us.
-template <typename T, int LPR, bool SMALL, int SPLIT = 1>
+template <typename T, int LPR, bool SMALL>
 __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const AlignParams p)
 {
-    static_assert(SPLIT == 1 || (SMALL && SPLIT == kBlock / 64), "a wavefront per part");
     constexpr int INFLIGHT = SMALL ? 4 : 2;
     constexpr int EPV = Elem<T>::EPV;
     constexpr int HALF = LPR * EPV;  // D / 2
-    constexpr int RPB = kBlock / LPR / SPLIT;
-    constexpr int SUMS = SPLIT > 1 ? SPLIT * 2 * EPV * 64 : 0;   // floats of the parts' sums
+    constexpr int RPB = kBlock / LPR;
 
     // Block order: (layer, head) chunk, then segment, then token tile, so that the blocks in flight
     // write neighbouring slices of the same cache rows when the segments of a launch are adjacent.
@@ -79,13 +74,11 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
     const int n_sel = jb.n_sel, a0 = jb.a0;
 
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    f32x4 *sums = reinterpret_cast<f32x4 *>(smem_raw);                                 // [SPLIT][lo, hi][EPV / 4][64]
-    float2 *cs = reinterpret_cast<float2 *>(smem_raw + sizeof(float) * SUMS);           // [n_tab][HALF] (cos, sin)
-    float *w_lds = reinterpret_cast<float *>(smem_raw) + SUMS + 2 * jb.n_tab * HALF;   // [RPB or 1][n_sel]
+    float2 *cs = reinterpret_cast<float2 *>(smem_raw);                          // [n_tab][HALF] (cos, sin)
+    float *w_lds = reinterpret_cast<float *>(smem_raw) + 2 * jb.n_tab * HALF;   // [RPB or 1][n_sel]
 
     const int tid = threadIdx.x;
-    const int part = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
-    const int row = (SPLIT > 1 ? tid & 63 : tid) / LPR;
+    const int row = tid / LPR;
     const int lir = tid % LPR;
     const int tile = r - hd.tile0[ji];
     const bool is_k = which == 0;
@@ -103,7 +96,7 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
     const float *wsrc = jb.weights;
     if (hd.gran != KVCOMM_W_SEGMENT)
         wsrc += ((int64_t)(hd.gran == KVCOMM_W_LAYER_HEAD_TOKEN ? lh : 0) * jb.S + tile * RPB) * jb.w_pitch;
-    constexpr int W = !SMALL || RPB < 8 ? 1 : RPB / 4 < 4 ? RPB / 4 : 4;   // n_w <= RPB * 64 = RPB / 4 weights of every thread
+    constexpr int W = !SMALL ? 1 : RPB / 4 < 4 ? RPB / 4 : 4;   // n_w <= RPB * 64 = RPB / 4 weights of every thread
     float w_first[W] = {};
 #pragma unroll
     for (int u = 0; u < W; ++u)
@@ -123,12 +116,11 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
     const int tr = SMALL ? min(t, jb.S - 1) : t;
     const T *xp = bp + l * sb.layer + h * sb.head + tr * sb.token + col0;
     const int64_t aoff = l * hd.s_anc.layer + h * hd.s_anc.head + tr * hd.s_anc.token + col0;
-    const int a_first = SPLIT > 1 ? part * n_sel / SPLIT : 0, a_end = SPLIT > 1 ? (part + 1) * n_sel / SPLIT : n_sel;   // (a part has one at least)
     u32x4 rlo, rhi, rows[INFLIGHT][2];
     auto request_group = [&](int a) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < INFLIGHT; ++u) {
-            const T *d = static_cast<const T *>(p.anc[which][a0 + (SPLIT > 1 ? min(a + u, a_end - 1) : a + u)]) + aoff;
+            const T *d = static_cast<const T *>(p.anc[which][a0 + a + u]) + aoff;
             rows[u][0] = load16_stream(d);
             rows[u][1] = load16_stream(d + HALF);
         }
@@ -136,7 +128,7 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
     if (SMALL || valid) {
         rlo = load16(xp);   // plain: see the header
         rhi = load16(xp + HALF);
-        if (SMALL || n_sel >= INFLIGHT) request_group(a_first);
+        if (SMALL || n_sel >= INFLIGHT) request_group(0);
     }
 
     if (is_k) {
@@ -154,7 +146,7 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
         if (tid + u * kBlock < n_w) keep_weight(tid + u * kBlock, w_first[u]);
     for (int idx = tid + W * kBlock; idx < n_w; idx += kBlock) keep_weight(idx, wsrc[idx]);
     __syncthreads();
-    if (SPLIT == 1 && !valid) return;
+    if (!valid) return;
 
     const bool rot_base = is_k && jb.base_tab != 0;
     float bc[EPV], bs[EPV];
@@ -167,7 +159,7 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
         }
     }
 
-    const float *wrow = w_lds + (hd.gran == KVCOMM_W_SEGMENT ? 0 : (SPLIT > 1 ? tr - tile * RPB : row) * n_sel);
+    const float *wrow = w_lds + (hd.gran == KVCOMM_W_SEGMENT ? 0 : row * n_sel);
 
     float lo[EPV], hi[EPV];
     unpack<T>(rlo, lo);
@@ -180,10 +172,6 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
             hi[e] = b * bc[e] + a * bs[e];
         }
     }
-
-    if (SPLIT > 1 && part > 0)
-#pragma unroll
-        for (int e = 0; e < EPV; ++e) lo[e] = hi[e] = 0.f;
 
     auto accumulate = [&](int a, const u32x4 &rdlo, const u32x4 &rdhi) {
         const float w = wrow[a];
@@ -208,35 +196,6 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
         }
     };
 
-    T *yp = op + l * so.layer + h * so.head + t * so.token + col0;
-    if constexpr (SPLIT > 1) {
-        for (int a = a_first;;) {
-#pragma unroll
-            for (int u = 0; u < INFLIGHT; ++u)
-                if (a + u < a_end) accumulate(a + u, rows[u][0], rows[u][1]);
-            a += INFLIGHT;
-            if (a >= a_end) break;
-            request_group(a);
-        }
-        const int lane = tid & 63;
-#pragma unroll
-        for (int e = 0; e < EPV; e += 4) {
-            sums[((part * 2 + 0) * (EPV / 4) + e / 4) * 64 + lane] = f32x4{lo[e], lo[e + 1], lo[e + 2], lo[e + 3]};
-            sums[((part * 2 + 1) * (EPV / 4) + e / 4) * 64 + lane] = f32x4{hi[e], hi[e + 1], hi[e + 2], hi[e + 3]};
-        }
-        __syncthreads();
-        if (!valid || part > 1) return;
-#pragma unroll
-        for (int e = 0; e < EPV; e += 4) {
-            f32x4 v[SPLIT];
-#pragma unroll
-            for (int k = 0; k < SPLIT; ++k) v[k] = sums[((k * 2 + part) * (EPV / 4) + e / 4) * 64 + lane];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) lo[e + i] = (v[0][i] + v[1][i]) + (v[2][i] + v[3][i]);
-        }
-        store16_stream(yp + part * HALF, pack<T>(lo));
-        return;
-    }
     int a = 0;
     while (a + INFLIGHT <= n_sel) {
 #pragma unroll
@@ -256,6 +215,7 @@ __global__ __launch_bounds__(kBlock, SMALL ? 3 : 4) void align_kernel(const Alig
         accumulate(a, load16_stream(d), load16_stream(d + HALF));
     }
 
+    T *yp = op + l * so.layer + h * so.head + t * so.token + col0;
     store16_stream(yp, pack<T>(lo));
     store16_stream(yp + HALF, pack<T>(hi));
 }
@@ -296,22 +256,14 @@ size_t lds_reserve(const AlignParams &p, int64_t n_blocks, int lpr, int es, int 
     return units >= 108 && two ? kTwoBlocks : kThreeBlocks;
 }
 
-// The form of a launch.
-// kParts: a row's anchors over the four wavefronts of a block, as long as the launch's `parted_blocks` (a quarter of the rows in each) find two
-// places per compute unit, with pools of eight and more (in every segment) three. us with four in flight / in parts, 90 launches:
-//   2 to 512 blocks, pools of 4 ... 63: 1.02 ... 2.7 times faster, two of them even: 4 layers x 1 head, 6 tokens, 44 anchors, all recorded elsewhere, 15.7 / 7.0; 2 x 8,
-//   27 tokens, 16 anchors 8.5 / 4.4, 60 23.7 / 9.0; 1 x 8, 26 tokens, 18 anchors 9.4 / 5.1; 32 x 8, 8 tokens, 8 anchors 4.9 / 4.5; 34 x 2, 8 tokens, 4 anchors 3.5 / 3.5;
-//   528 blocks, 6 anchors 4.9 / 5.9; 576, 19 8.7 / 7.6; 704, 8 5.3 / 4.9; 768, 7 6.0 / 6.7; 880, 8 5.2 / 6.0; 896, 5 5.2 / 7.3; 1024, 16 7.9 / 8.3
-//   (every block makes its own rotation tables and reads its weights, a quarter of the rows as often).
-// kFourInFlight: pools of four and more (in every segment) whose rows are at most 2.7 MB per anchor, keys and values, where three
+// Four anchors in flight (SMALL): pools of four and more (in every segment) whose rows are at most 2.7 MB per anchor, keys and values, where three
 // blocks per unit (what the registers of four allow) hold the launch or a pool has 32 anchors, long chains.  us with two / four (in brackets:
 // four, rows requested behind the set-up), 32 layers x 8 heads, bf16, D = 128 unless said:
 //   8 tokens, 8 anchors 6.6 / 5.9 (6.1), 64 anchors 25.6 / 18.9 (24.2); 16 tokens, 16 anchors 10.6 / 9.1 (10.0); f32, D = 64, 8 x 4, 77 tokens, 8 anchors
 //   6.7 / 5.8 (5.8), 16: 9.7 / 7.8 (8.1); 80 layers, 8 tokens, 64 anchors 49.0 / 35.3 (31.7); one token, f32, 8 anchors 5.4 / 5.2 (4.7);
 //   but 33 tokens, 8 anchors 12.2 / 13.3 (14.9); 64 tokens, 16 anchors 26.3 / 29.1 (31.1); 80 layers, one token, 8 anchors 6.2 / 7.4 (7.0).
 // Of 480 launches of pools from four on the rule's choice is 0.3 % slower on average than the faster one.
-enum class AlignForm { kTwoInFlight, kFourInFlight, kParts };
-AlignForm align_form(const AlignParams &p, int64_t n_blocks, int64_t parted_blocks, int max_sel, int row_bytes)
+bool few_rows(const AlignParams &p, int64_t n_blocks, int max_sel, int row_bytes)
 {
     int64_t tokens = 0;
     int min_sel = max_sel;
@@ -319,37 +271,18 @@ AlignForm align_form(const AlignParams &p, int64_t n_blocks, int64_t parted_bloc
         tokens += p.job[j].S;
         min_sel = std::min<int>(min_sel, p.job[j].n_sel);
     }
-    if (min_sel < 4) return AlignForm::kTwoInFlight;
-    if (parted_blocks <= (min_sel >= 8 ? 3 : 2) * kComputeUnits) return AlignForm::kParts;
-    return 2 * tokens * p.head.LH * row_bytes <= 2700000 && (2 * n_blocks <= 3 * kComputeUnits || max_sel >= 32) ? AlignForm::kFourInFlight
-                                                                                                             : AlignForm::kTwoInFlight;
+    return min_sel >= 4 && 2 * tokens * p.head.LH * row_bytes <= 2700000 && (2 * n_blocks <= 3 * kComputeUnits || max_sel >= 32);
 }
 
 template <typename T, int LPR>
-int launch_align(AlignParams &p, const AlignLaunch &pl, int units, hipStream_t stream)
+int launch_align(const AlignParams &p, const AlignLaunch &pl, int units, hipStream_t stream)
 {
     constexpr int HALF = LPR * Elem<T>::EPV;
-    constexpr int PARTS = kBlock / 64, ROWS = kBlock / LPR, PART_ROWS = 64 / LPR;
-    AlignHead &hd = p.head;
-    int64_t tiles = 0;
-    for (int j = 0; j < hd.n_jobs; ++j) tiles += (p.job[j].S + PART_ROWS - 1) / PART_ROWS;
-    const AlignForm form = align_form(p, pl.n_blocks, 2 * hd.LH * tiles, pl.max_sel, 32 * LPR);
-    const bool parts = form == AlignForm::kParts;
-    size_t lds = sizeof(float2) * (size_t)pl.max_tab * HALF + sizeof(float) * (size_t)(parts ? PART_ROWS : ROWS) * pl.max_sel;
-    if (parts) {
-        lds += sizeof(float) * PARTS * 2 * Elem<T>::EPV * 64;
-        int32_t tile0 = 0;
-        for (int j = 0; j < hd.n_jobs; ++j) {
-            hd.tile0[j] = tile0;
-            tile0 += p.job[j].n_token_tiles = (p.job[j].S + PART_ROWS - 1) / PART_ROWS;
-        }
-        hd.tiles_total = tile0;
-        hd.by_tiles = make_divisor((uint32_t)tile0);
-    }
+    constexpr int RPB = kBlock / LPR;
+    const size_t lds = sizeof(float2) * (size_t)pl.max_tab * HALF + sizeof(float) * (size_t)RPB * pl.max_sel;
+    const AlignHead &hd = p.head;
     const dim3 grid((unsigned)(hd.lh_range * hd.tiles_total), (unsigned)(2 * ((hd.LH + hd.lh_range - 1) / hd.lh_range)));
-    const auto kernel = parts                               ? align_kernel<T, LPR, true, PARTS>
-                        : form == AlignForm::kFourInFlight ? align_kernel<T, LPR, true>
-                                                            : align_kernel<T, LPR, false>;
+    const auto kernel = few_rows(p, pl.n_blocks, pl.max_sel, 32 * LPR) ? align_kernel<T, LPR, true> : align_kernel<T, LPR, false>;
     return launch(kernel, grid, dim3(kBlock), std::max(lds, lds_reserve(p, pl.n_blocks, LPR, (int)sizeof(T), units)), stream, p);
 }
 

@@ -9,6 +9,7 @@ Calls whose arguments are plain (device tensors, lists, numbers) are marshalled 
 (csrc/marshal.cpp), which declines all others; those take the ctypes code below, which converts or refuses them.  Without
 a _marshal built for this torch and Python every call does (a warning says so: small calls then take longer on the host).
 """
+import contextlib
 import ctypes
 import os
 import sys
@@ -243,6 +244,20 @@ def _stream_ptr(stream):
     return torch.cuda.current_stream().cuda_stream
 
 
+def on_stream(stream):
+    """Context for allocations that kernels on `stream` (None: the current one) work in and that are dropped before these have run: they
+    belong to that stream, so the allocator does not hand them out under the kernels."""
+    if stream is None:
+        return contextlib.nullcontext()
+    return torch.cuda.stream(stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream))
+
+
+def _workspace(need, device, stream):
+    """Scratch of one call."""
+    with on_stream(stream):
+        return torch.empty((need,), dtype=torch.uint8, device=device)
+
+
 def _anchor_ptrs(anchors, dtype, what):
     """List of same-layout anchor tensors -> (host pointer array, layout descriptor)."""
     n = len(anchors)
@@ -294,7 +309,7 @@ def kvcomm_anchor_weights(model, seg_base_k, anchor_base_k, anchor_len=None, tem
         selected_out = torch.empty((A,), dtype=torch.int32, device=dev)
     if workspace is None:
         need = kvcomm_anchor_weights_workspace(model, seg_len, A, gran)
-        workspace = torch.empty((max(need, 1),), dtype=torch.uint8, device=dev)
+        workspace = _workspace(max(need, 1), dev, stream)
     if _done(_native.anchor_weights(model, gran, RULE_L2_SOFTMAX, temperature, seg_base_k, anchor_base_k, anchor_len, weights_out,
                                     nearest_out, selected_out, workspace, stream)):
         return weights_out, nearest_out, selected_out
@@ -373,19 +388,13 @@ def _in_private_pool(t):
 
 
 def _attn_scratch(need, device, stream):
-    """Scratch of the attention, `need` bytes, or None.  It belongs to the stream the kernels run on, so the allocator does not
-    hand it out under them.  Where there is no memory for it, or a graph that torch does not manage is being captured (the
+    """Scratch of the attention, `need` bytes, or None.  Where there is no memory for it, or a graph that torch does not manage is being captured (the
     allocator would hand the memory out again while the graph's replays write to it), the call does without: same result
     up to rounding, only slower."""
     try:
-        if stream is None:
+        with on_stream(stream):
             workspace = torch.empty((need,), dtype=torch.uint8, device=device)
             capturing = torch.cuda.is_current_stream_capturing()
-        else:
-            own = stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream)
-            with torch.cuda.stream(own):
-                workspace = torch.empty((need,), dtype=torch.uint8, device=device)
-                capturing = torch.cuda.is_current_stream_capturing()
     except torch.OutOfMemoryError:
         return None
     return None if capturing and not _in_private_pool(workspace) else workspace
@@ -492,7 +501,7 @@ def kvcomm_anchor_weights_rule(model, rule, seg_base_k, anchor_base_k, anchor_le
         selected_out = torch.empty((A,), dtype=torch.int32, device=dev)
     if workspace is None:
         need = kvcomm_anchor_weights_rule_workspace(model, seg_len, A, gran, rule)
-        workspace = torch.empty((max(need, 1),), dtype=torch.uint8, device=dev)
+        workspace = _workspace(max(need, 1), dev, stream)
     if _done(_native.anchor_weights(model, gran, rule, temperature, seg_base_k, anchor_base_k, anchor_len, weights_out, nearest_out,
                                     selected_out, workspace, stream)):
         return weights_out, nearest_out, selected_out
@@ -525,7 +534,7 @@ def kvcomm_anchor_predict(weights, anchor_len, seg_len, gamma, entropy_out=None,
     if result_out is None:
         result_out = torch.empty((2,), dtype=torch.float32, device=dev)
     if workspace is None:
-        workspace = torch.empty((max(kvcomm_anchor_predict_workspace(n), 8),), dtype=torch.uint8, device=dev)
+        workspace = _workspace(max(kvcomm_anchor_predict_workspace(n), 8), dev, stream)
     if _done(_native.anchor_predict(weights, anchor_len, seg_len, gamma, entropy_out, result_out, workspace, stream)):
         return (result_out, entropy_out) if want_entropy else result_out
     lens = (ctypes.c_int32 * max(A, 1))(*[int(x) for x in anchor_len])
@@ -589,7 +598,7 @@ def kvcomm_anchor_weights_batch(model, jobs, temperature=1.0, gran=W_TOKEN, rule
     if workspace is None:
         need = kvcomm_anchor_weights_batch_workspace(model, [jd["seg_base_k"].shape[2] for jd in jobs],
                                                      [len(jd["anchor_base_k"]) for jd in jobs], gran, rule)
-        workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=jobs[0]["seg_base_k"].device)
+        workspace = _workspace(max(need, 256), jobs[0]["seg_base_k"].device, stream)
     if _done(_native.anchor_weights_batch(model, gran, rule, temperature, jobs, outs, workspace, stream)):
         return outs
     cjobs = (_CWeightsJob * max(n, 1))()

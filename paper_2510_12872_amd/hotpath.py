@@ -40,7 +40,8 @@ class Scratch:
 def align_segment(model, seg, out_k, out_v, temperature=1.0, gran=kv.W_TOKEN, scratch=None, stream=None):
     """Anchor weights, then aligned K/V of one segment written into out_k / out_v."""
     if scratch is None:
-        scratch = Scratch(model, seg.base_k.shape[2], len(seg.anchor_k), gran, seg.base_k.device)
+        with kv.on_stream(stream):
+            scratch = Scratch(model, seg.base_k.shape[2], len(seg.anchor_k), gran, seg.base_k.device)
     kv.kvcomm_anchor_weights(model, seg.base_k, seg.anchor_k, seg.anchor_len, temperature, gran,
                              scratch.weights, scratch.nearest, scratch.selected, scratch.workspace, stream)
     kv.kvcomm_align_kv(model, seg.base_k, seg.base_v, seg.anchor_dk, seg.anchor_dv, scratch.weights,
@@ -101,8 +102,9 @@ def align_agent_batched(w, model, agent, gran=kv.W_TOKEN, scratch=None, stream=N
     chunk of segments (a launch holds at most MAX_BATCH segments and MAX_ANCHORS anchors)."""
     segs = agent.segments
     if scratch is None:
-        scratch = AgentScratch(model, [s.base_k.shape[2] for s in segs], [len(s.anchor_k) for s in segs], gran,
-                               segs[0].base_k.device)
+        with kv.on_stream(stream):
+            scratch = AgentScratch(model, [s.base_k.shape[2] for s in segs], [len(s.anchor_k) for s in segs], gran,
+                                   segs[0].base_k.device)
     outs = list(zip(scratch.weights, scratch.nearest, scratch.selected))
     for idx in launch_chunks([len(s.anchor_k) for s in segs]):
         _align_together(w, model, agent, idx, outs, scratch.workspace, gran, stream)

@@ -27,6 +27,7 @@ W_LAYER_HEAD_TOKEN = 1
 W_SEGMENT = 2
 MAX_ANCHORS = 64
 MAX_BATCH = 8
+MAX_ROTATIONS = MAX_ANCHORS + 1   # of all segments of a batched update
 COMPUTE_UNITS = 256
 ATTN_MIN_SPLIT_KEYS = 512   # shorter caches never use the attention's scratch
 RULE_L2_SOFTMAX = 0

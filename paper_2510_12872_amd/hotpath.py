@@ -131,9 +131,37 @@ def _independent(w, agent, lens, outs):
         [g for s in agent.segments for g in ((s.base_k, s.base_v), s.anchor_k, s.anchor_dk, s.anchor_dv)], [t for o in outs for t in o])
 
 
+def _rotations(seg):
+    """Rotations that the update of a segment needs at most: one per distinct position delta of its keys and its selected deviations."""
+    if seg.anchor_delta_pos is None:
+        return 1
+    S = seg.base_k.shape[2]
+    lens = [t.shape[2] for t in seg.anchor_dk] if seg.anchor_len is None else seg.anchor_len
+    return len(({seg.delta_pos} | {seg.delta_pos - d for d, n in zip(seg.anchor_delta_pos, lens) if n >= S}) - {0})
+
+
+def _joint_runs(segs, pools):
+    """Cuts the segments of an agent into runs of neighbours that the batched calls take together, known before anything is launched: the
+    limits of launch_chunks(), anchors of one layout, and the rotations of an update (four pools of 16 anchors, all recorded elsewhere, need 68
+    and go as three segments and one)."""
+    layouts = [(s.anchor_k[0].stride(), s.anchor_dk[0].stride()) for s in segs]
+    rotations = [1 if s.anchor_delta_pos is None else 1 + len(s.anchor_delta_pos) for s in segs]
+    if sum(rotations) > kv.MAX_ROTATIONS:
+        rotations = [_rotations(s) for s in segs]
+    runs, j = [], 0
+    while j < len(segs):
+        k, anchors, rots = j + 1, pools[j], rotations[j]
+        while (k < len(segs) and k - j < kv.MAX_BATCH and layouts[k] == layouts[j] and anchors + pools[k] <= kv.MAX_ANCHORS
+               and rots + rotations[k] <= kv.MAX_ROTATIONS):
+            anchors, rots, k = anchors + pools[k], rots + rotations[k], k + 1
+        runs.append(list(range(j, k)))
+        j = k
+    return runs
+
+
 def _align_all(w, model, agent, gran, scratches, stream):
-    """Aligns the segments of an agent in chunks of one launch per step.  Returns False where that may not be done or is refused
-    (segments that depend on each other, anchors of several layouts, too many rotations, a small workspace): nothing that counts has been written then."""
+    """Aligns the segments of an agent, those that may share a launch in one launch per step.  Returns False where none do (segments that
+    depend on each other, scratch that segments share); nothing has been launched then."""
     segs = agent.segments
     lens, pools = [s.base_k.shape[2] for s in segs], [len(s.anchor_k) for s in segs]
     given = scratches is not None
@@ -142,15 +170,37 @@ def _align_all(w, model, agent, gran, scratches, stream):
     outs = [(s.weights, s.nearest, s.selected) for s in scratches[:len(segs)]] if given else ()
     if given and len(outs) < len(segs) or not _independent(w, agent, lens, outs):
         return False
+    for idx in _joint_runs(segs, pools):
+        if len(idx) == 1 or not _align_run(w, model, agent, idx, gran, scratches, stream):
+            for j in idx:
+                _align_one(w, model, agent, j, gran, scratches, stream)
+    return True
+
+
+def _align_run(w, model, agent, idx, gran, scratches, stream):
+    """Aligns the segments `idx` together.  Returns False where that is refused: one after the other they may be accepted, or are refused as
+    they always were."""
+    segs = [agent.segments[j] for j in idx]
     try:
-        if not given:
-            align_agent_batched(w, model, agent, gran, None, stream)
-            return True
-        for idx in launch_chunks(pools):
-            _align_together(w, model, agent, idx, outs, max((scratches[j].workspace for j in idx), key=torch.Tensor.numel), gran, stream)
+        if scratches is None:
+            with kv.on_stream(stream):
+                scratch = AgentScratch(model, [s.base_k.shape[2] for s in segs], [len(s.anchor_k) for s in segs], gran, segs[0].base_k.device)
+            outs, workspace = list(zip(scratch.weights, scratch.nearest, scratch.selected)), scratch.workspace
+        else:
+            outs = [(scratches[j].weights, scratches[j].nearest, scratches[j].selected) for j in idx]
+            workspace = max((scratches[j].workspace for j in idx), key=torch.Tensor.numel)
+        _align_together(w, model, agent, idx, dict(zip(idx, outs)), workspace, gran, stream)
         return True
     except (kv.KVCommError, torch.OutOfMemoryError):
-        return False   # one after the other they may be accepted, or are refused as they always were
+        return False
+
+
+def _align_one(w, model, agent, j, gran, scratches, stream):
+    """Segment j into its slot."""
+    seg = agent.segments[j]
+    p0, S = w.seg_offset(j), seg.base_k.shape[2]
+    align_segment(model, seg, _slot(agent.cache_k, p0, S), _slot(agent.cache_v, p0, S),
+                  w.temperature, gran, None if scratches is None else scratches[j], stream)
 
 
 def reuse_agent(w, model, agent, out=None, gran=kv.W_TOKEN, scratches=None, stream=None):
@@ -158,11 +208,8 @@ def reuse_agent(w, model, agent, out=None, gran=kv.W_TOKEN, scratches=None, stre
     batched calls: a small agent's step is the number of its launches (4 segments of 10 tokens, 16 anchors, 2 layers x 8 heads: 66 us
     one after the other, 36 us so; as a graph 58 and 18 us)."""
     if len(agent.segments) < 2 or not _align_all(w, model, agent, gran, scratches, stream):
-        for j, seg in enumerate(agent.segments):
-            p0 = w.seg_offset(j)
-            S = seg.base_k.shape[2]
-            align_segment(model, seg, _slot(agent.cache_k, p0, S), _slot(agent.cache_v, p0, S),
-                          w.temperature, gran, None if scratches is None else scratches[j], stream)
+        for j in range(len(agent.segments)):
+            _align_one(w, model, agent, j, gran, scratches, stream)
     if agent.q is None:
         return None
     return kv.kvcomm_suffix_attn(model, agent.q, agent.cache_k, agent.cache_v, w.n_ctx, out=out, stream=stream)

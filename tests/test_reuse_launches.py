@@ -1,0 +1,130 @@
+"""Which library calls a step of several segments makes: every segment is matched once and updated once, in as few launches as the
+batched calls' limits allow.  (CPU only: the calls are replaced by ones that know those limits and note what they were given.)"""
+import pytest
+import torch
+
+import paper_2510_12872_amd as kv
+from paper_2510_12872_amd import binding, hotpath, workloads
+from paper_2510_12872_amd.workloads import scaled
+
+W = scaled(workloads.LLAMA8B_5AGENTS, n_layers=2, n_kv_heads=2, n_q_heads=4, head_dim=64, prefix_len=2, seg_len=6, n_segments=4,
+           n_anchors=16, tq=0)
+M = hotpath.model_of(W)
+
+
+class Library:
+    """The calls of the weights and the update: `calls` lists (name, segments), `scratch` the workspaces."""
+    def __init__(self, agent):
+        self.agent, self.calls, self.scratch, self.refuse = agent, [], [], {}
+
+    def index(self, base_k):
+        return next(j for j, s in enumerate(self.agent.segments) if s.base_k is base_k)
+
+    def note(self, name, idx):
+        if name in self.refuse:
+            raise kv.KVCommError(self.refuse[name], "refused")
+        self.calls.append((name, idx))
+
+    def layout(self, jobs, *names):
+        if len({t.stride() for jd in jobs for n in names for t in jd[n]}) > 1:
+            raise kv.KVCommError(-1, "one layout")
+
+    def weights_batch(self, model, jobs, temperature, gran, workspace, stream):
+        idx = [self.index(jd["seg_base_k"]) for jd in jobs]
+        pools = [len(jd["anchor_base_k"]) for jd in jobs]
+        self.layout(jobs, "anchor_base_k")
+        if len(jobs) > 8 or sum(pools) > 64:
+            raise kv.KVCommError(-2, "limits")
+        if workspace.numel() < kv.kvcomm_anchor_weights_batch_workspace(model, [jd["seg_base_k"].shape[2] for jd in jobs], pools, gran):
+            raise kv.KVCommError(-3, "workspace")
+        self.scratch.append(workspace)
+        self.note("weights", idx)
+
+    def align_batch(self, model, jobs, gran, stream):
+        tables = sum(len({jd["delta_pos"]} | {jd["delta_pos"] - d for d in jd["anchor_delta_pos"] or ()} - {0}) for jd in jobs)
+        self.layout(jobs, "anchor_dk", "anchor_dv")
+        if len(jobs) > 8 or tables > 65 or sum(len(jd["anchor_dk"]) for jd in jobs) > 64:
+            raise kv.KVCommError(-2, "limits")
+        self.note("align", [self.index(jd["base_k"]) for jd in jobs])
+
+    def weights(self, model, seg_base_k, *rest):
+        self.note("weights", [self.index(seg_base_k)])
+
+    def align(self, model, base_k, *rest):
+        self.note("align", [self.index(base_k)])
+
+
+@pytest.fixture
+def step(monkeypatch):
+    def run(w, change=lambda agent: None, scratches=None, refuse={}, gran=kv.W_TOKEN):
+        agent = workloads.make_agent(w, 0)
+        change(agent)
+        lib = Library(agent)
+        lib.refuse = refuse
+        for name in ("weights", "align"):
+            monkeypatch.setattr(binding, "kvcomm_anchor_weights" if name == "weights" else "kvcomm_align_kv", getattr(lib, name))
+        monkeypatch.setattr(binding, "kvcomm_anchor_weights_batch", lib.weights_batch)
+        monkeypatch.setattr(binding, "kvcomm_align_kv_batch", lib.align_batch)
+        lib.error = None
+        try:
+            hotpath.reuse_agent(w, hotpath.model_of(w), agent, gran=gran, scratches=scratches(agent) if scratches else None)
+        except kv.KVCommError as e:
+            lib.error = e.status
+        return lib
+    kv.load_library()
+    return run
+
+
+def both(*runs):
+    """Weights and update of each run in turn."""
+    return [(name, list(r)) for r in runs for name in ("weights", "align")]
+
+
+def each_alone(n):
+    return both(*([j] for j in range(n)))
+
+
+def elsewhere(agent):   # every anchor recorded at a position of its own
+    for k, s in enumerate(agent.segments):
+        s.anchor_delta_pos = [1000 * k + 7 * a for a in range(len(s.anchor_k))]
+
+
+def padded(*names):
+    def change(agent):
+        s = agent.segments[1]
+        for n in names:
+            setattr(s, n, [torch.cat([t, t], 2) for t in getattr(s, n)])
+    return change
+
+
+def plain(agent):
+    return [hotpath.Scratch(M, s.base_k.shape[2], len(s.anchor_k), kv.W_TOKEN, "cpu") for s in agent.segments]
+
+
+@pytest.mark.parametrize("scratches", [None, plain])
+def test_limits_are_known_before_the_first_launch(step, scratches):
+    """4 x 16 anchors fit a launch, 4 x 17 rotations do not (65 do); neither do anchors of different layouts, of whichever tensor, nor more
+    anchors or segments than a launch holds."""
+    assert step(W, scratches=scratches).calls == both([0, 1, 2, 3])
+    assert step(W, elsewhere, scratches).calls == both([0, 1, 2], [3])
+    fifteen = scaled(W, n_anchors=15)
+    assert step(fifteen, elsewhere, scratches).calls == both([0, 1, 2, 3])
+    for change in (padded("anchor_k"), padded("anchor_dk", "anchor_dv")):
+        assert step(W, change, scratches).calls == both([0], [1], [2, 3])
+    assert step(scaled(W, n_segments=9, n_anchors=7), scratches=scratches).calls == both(range(8), [8])
+    assert step(scaled(W, n_segments=3, n_anchors=40), scratches=scratches).calls == each_alone(3)
+
+
+def test_rotations_that_anchors_share_or_do_not_need(step):
+    def shared(agent):
+        elsewhere(agent)
+        for s in agent.segments[:2]:
+            s.anchor_delta_pos[1] = s.anchor_delta_pos[0]
+            s.anchor_delta_pos[2] = s.delta_pos      # no rotation
+    def short(agent):      # an anchor that is not selected needs none either
+        elsewhere(agent)
+        for s in agent.segments:
+            s.anchor_len = [len_ - (a == 0) for a, len_ in enumerate(s.anchor_len)]
+    assert step(W, shared).calls == both([0, 1, 2, 3])
+    assert [hotpath._rotations(s) for s in step(W, shared).agent.segments] == [14, 15, 17, 17]
+    assert [hotpath._rotations(s) for s in step(W, short).agent.segments] == [16] * 4

@@ -5,6 +5,8 @@ order of the reuse branch of Algorithm 1 (weights -> offset approximation per pl
 then attention over the concatenated cache), on the current stream or, for consecutive
 agents, on two streams (TwoStreamPipeline).
 """
+import functools
+
 import torch
 
 from . import binding as kv
@@ -15,7 +17,9 @@ def model_of(w):
     return kv.Model(w.n_layers, w.n_kv_heads, w.n_q_heads, w.head_dim, w.dtype, w.rope_theta)
 
 
-# Up to here a segment's workspace also holds the launch that several segments share.  Per-token weights stay below it in general (1024
+# Up to here a segment's workspace also holds the launch that it shares with as many segments like it as a launch takes (with other
+# lengths and pools beside it a run may need more than any of its segments holds: it is shortened then, see _joint_runs()).  32 layers x 8 heads: 77
+# tokens, 6 anchors 2.5 MB instead of 0.3, 512 tokens, 8 anchors 4.2 instead of 0.8.  Per-token weights stay below the limit in general (1024
 # tokens, 16 anchors: 6 MiB); weights per layer and head pass it with segments that keep the chip busy each by itself (134 MB), and
 # those go one after the other.
 JOINT_WORKSPACE = 16 << 20
@@ -140,10 +144,15 @@ def _rotations(seg):
     return len(({seg.delta_pos} | {seg.delta_pos - d for d, n in zip(seg.anchor_delta_pos, lens) if n >= S}) - {0})
 
 
-def _joint_runs(segs, pools):
+@functools.lru_cache(maxsize=256)
+def _joint_need(model, lens, pools, gran):
+    return kv.kvcomm_anchor_weights_batch_workspace(model, lens, pools, gran)
+
+
+def _joint_runs(model, segs, lens, pools, gran, scratches):
     """Cuts the segments of an agent into runs of neighbours that the batched calls take together, known before anything is launched: the
-    limits of launch_chunks(), anchors of one layout, and the rotations of an update (four pools of 16 anchors, all recorded elsewhere, need 68
-    and go as three segments and one)."""
+    limits of launch_chunks(), anchors of one layout, the rotations of an update (four pools of 16 anchors, all recorded elsewhere, need 68
+    and go as three segments and one), and the largest workspace among the segments' own scratch where that is given."""
     layouts = [(s.anchor_k[0].stride(), s.anchor_dk[0].stride()) for s in segs]
     rotations = [1 if s.anchor_delta_pos is None else 1 + len(s.anchor_delta_pos) for s in segs]
     if sum(rotations) > kv.MAX_ROTATIONS:
@@ -154,9 +163,16 @@ def _joint_runs(segs, pools):
         while (k < len(segs) and k - j < kv.MAX_BATCH and layouts[k] == layouts[j] and anchors + pools[k] <= kv.MAX_ANCHORS
                and rots + rotations[k] <= kv.MAX_ROTATIONS):
             anchors, rots, k = anchors + pools[k], rots + rotations[k], k + 1
+        while scratches is not None and k - j > 1 and (_joint_need(model, tuple(lens[j:k]), tuple(pools[j:k]), gran)
+                                                       > max(_workspace_bytes(scratches[i]) for i in range(j, k))):
+            k -= 1
         runs.append(list(range(j, k)))
         j = k
     return runs
+
+
+def _workspace_bytes(scratch):
+    return scratch.workspace.numel() * scratch.workspace.element_size()
 
 
 def _align_all(w, model, agent, gran, scratches, stream):
@@ -170,7 +186,7 @@ def _align_all(w, model, agent, gran, scratches, stream):
     outs = [(s.weights, s.nearest, s.selected) for s in scratches[:len(segs)]] if given else ()
     if given and len(outs) < len(segs) or not _independent(w, agent, lens, outs):
         return False
-    for idx in _joint_runs(segs, pools):
+    for idx in _joint_runs(model, segs, lens, pools, gran, scratches):
         if len(idx) == 1 or not _align_run(w, model, agent, idx, gran, scratches, stream):
             for j in idx:
                 _align_one(w, model, agent, j, gran, scratches, stream)
@@ -188,7 +204,7 @@ def _align_run(w, model, agent, idx, gran, scratches, stream):
             outs, workspace = list(zip(scratch.weights, scratch.nearest, scratch.selected)), scratch.workspace
         else:
             outs = [(scratches[j].weights, scratches[j].nearest, scratches[j].selected) for j in idx]
-            workspace = max((scratches[j].workspace for j in idx), key=torch.Tensor.numel)
+            workspace = max((scratches[j] for j in idx), key=_workspace_bytes).workspace
         _align_together(w, model, agent, idx, dict(zip(idx, outs)), workspace, gran, stream)
         return True
     except (kv.KVCommError, torch.OutOfMemoryError):

@@ -13,9 +13,9 @@ M = hotpath.model_of(W)
 
 
 class Library:
-    """The calls of the weights and the update: `calls` lists (name, segments), `scratch` the workspaces."""
+    """The calls of the weights and the update: `calls` lists (name, segments), `declined` counts what their limits refused."""
     def __init__(self, agent):
-        self.agent, self.calls, self.scratch, self.refuse = agent, [], [], {}
+        self.agent, self.calls, self.refuse, self.declined = agent, [], {}, 0
 
     def index(self, base_k):
         return next(j for j, s in enumerate(self.agent.segments) if s.base_k is base_k)
@@ -25,26 +25,29 @@ class Library:
             raise kv.KVCommError(self.refuse[name], "refused")
         self.calls.append((name, idx))
 
+    def limit(self, status):
+        self.declined += 1
+        raise kv.KVCommError(status, "limit")
+
     def layout(self, jobs, *names):
         if len({t.stride() for jd in jobs for n in names for t in jd[n]}) > 1:
-            raise kv.KVCommError(-1, "one layout")
+            self.limit(-1)
 
     def weights_batch(self, model, jobs, temperature, gran, workspace, stream):
         idx = [self.index(jd["seg_base_k"]) for jd in jobs]
         pools = [len(jd["anchor_base_k"]) for jd in jobs]
         self.layout(jobs, "anchor_base_k")
         if len(jobs) > 8 or sum(pools) > 64:
-            raise kv.KVCommError(-2, "limits")
+            self.limit(-2)
         if workspace.numel() < kv.kvcomm_anchor_weights_batch_workspace(model, [jd["seg_base_k"].shape[2] for jd in jobs], pools, gran):
-            raise kv.KVCommError(-3, "workspace")
-        self.scratch.append(workspace)
+            self.limit(-3)
         self.note("weights", idx)
 
     def align_batch(self, model, jobs, gran, stream):
         tables = sum(len({jd["delta_pos"]} | {jd["delta_pos"] - d for d in jd["anchor_delta_pos"] or ()} - {0}) for jd in jobs)
         self.layout(jobs, "anchor_dk", "anchor_dv")
         if len(jobs) > 8 or tables > 65 or sum(len(jd["anchor_dk"]) for jd in jobs) > 64:
-            raise kv.KVCommError(-2, "limits")
+            self.limit(-2)
         self.note("align", [self.index(jd["base_k"]) for jd in jobs])
 
     def weights(self, model, seg_base_k, *rest):
@@ -128,3 +131,42 @@ def test_rotations_that_anchors_share_or_do_not_need(step):
     assert step(W, shared).calls == both([0, 1, 2, 3])
     assert [hotpath._rotations(s) for s in step(W, shared).agent.segments] == [14, 15, 17, 17]
     assert [hotpath._rotations(s) for s in step(W, short).agent.segments] == [16] * 4
+
+
+def ragged(agent):
+    """Lengths and pools of which no segment's own scratch holds the launch of them all."""
+    agent.segments[:] = [workloads.make_segment(scaled(RAGGED, seg_len=S, n_anchors=A), 0, j)
+                         for j, (S, A) in enumerate(zip((595, 772, 354, 378, 1022), (12, 13, 10, 15, 11)))]
+
+
+class Consecutive(type(W)):
+    def seg_offset(self, j):
+        return self.prefix_len + sum((595, 772, 354, 378, 1022)[:j])
+
+
+RAGGED = scaled(W, n_layers=32, n_kv_heads=8, n_q_heads=8, n_segments=5, seg_len=625)
+
+
+def test_runs_fit_the_scratch_that_there_is(step, monkeypatch):
+    """A run whose scratch is too small for it is shortened before anything is launched, nothing is refused, nothing is done twice."""
+    monkeypatch.setattr(workloads, "_normal", lambda shape, sigma, dtype, g, device: torch.empty(1, dtype=dtype).expand(shape))
+    monkeypatch.setattr(binding, "apart", lambda *a: True)      # (tensors without memory of their own)
+    w, m = Consecutive(**vars(RAGGED)), hotpath.model_of(RAGGED)
+    own = lambda agent: [hotpath.Scratch(m, s.base_k.shape[2], len(s.anchor_k), kv.W_TOKEN, "cpu") for s in agent.segments]
+    for scratches in (own, None):
+        lib = step(w, ragged, scratches)
+        runs = [idx for name, idx in lib.calls if name == "weights"]
+        assert lib.calls == both(*runs) and sum(runs, []) == list(range(5)) and lib.declined == 0
+        assert len(runs) == (2 if scratches else 1), runs
+    few = lambda agent: [small(s) for s in plain(agent)]
+
+    def small(s):
+        s.workspace = s.workspace[:kv.kvcomm_anchor_weights_workspace(M, W.seg_len, W.n_anchors)]
+        return s
+    lib = step(W, scratches=few)
+    assert lib.calls == each_alone(4) and lib.declined == 0
+    # weights per layer and head whose joint scratch would pass the limit of what a segment keeps
+    big = scaled(RAGGED, n_segments=3, seg_len=600, n_anchors=8)
+    lib = step(big, scratches=lambda agent: [hotpath.Scratch(m, 600, 8, kv.W_LAYER_HEAD_TOKEN, "cpu") for _ in range(3)],
+               gran=kv.W_LAYER_HEAD_TOKEN)
+    assert lib.calls == each_alone(3) and lib.declined == 0

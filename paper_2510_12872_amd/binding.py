@@ -30,6 +30,7 @@ MAX_BATCH = 8
 MAX_ROTATIONS = MAX_ANCHORS + 1   # of all segments of a batched update
 COMPUTE_UNITS = 256
 ATTN_MIN_SPLIT_KEYS = 512   # shorter caches never use the attention's scratch
+EINVAL, EUNSUPPORTED, EWORKSPACE = -1, -2, -3   # statuses of a call that has launched nothing
 RULE_L2_SOFTMAX = 0
 RULE_NEAREST = 1
 RULE_COSINE_SOFTMAX = 2

@@ -84,14 +84,18 @@ class AgentScratch:
         self.workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=device)
 
 
-def _align_together(w, model, agent, idx, outs, workspace, gran, stream):
-    """One batched call per step for the agent's segments `idx`; outs[j]: weights, nearest and selected of segment j."""
+def _match_together(w, model, agent, idx, outs, workspace, gran, stream):
+    """One batched call for the weights of the agent's segments `idx`; outs[j]: weights, nearest and selected of segment j."""
     segs = agent.segments
     kv.kvcomm_anchor_weights_batch(model, [dict(
         seg_base_k=segs[j].base_k, anchor_base_k=segs[j].anchor_k, anchor_len=segs[j].anchor_len,
         weights_out=outs[j][0], nearest_out=outs[j][1], selected_out=outs[j][2])
         for j in idx], w.temperature, gran, workspace=workspace, stream=stream)
-    jobs = []
+
+
+def _update_together(w, model, agent, idx, outs, gran, stream):
+    """One batched call for their update."""
+    segs, jobs = agent.segments, []
     for j in idx:
         p0, S = w.seg_offset(j), segs[j].base_k.shape[2]
         jobs.append(dict(base_k=segs[j].base_k, base_v=segs[j].base_v, anchor_dk=segs[j].anchor_dk,
@@ -111,7 +115,8 @@ def align_agent_batched(w, model, agent, gran=kv.W_TOKEN, scratch=None, stream=N
                                    segs[0].base_k.device)
     outs = list(zip(scratch.weights, scratch.nearest, scratch.selected))
     for idx in launch_chunks([len(s.anchor_k) for s in segs]):
-        _align_together(w, model, agent, idx, outs, scratch.workspace, gran, stream)
+        _match_together(w, model, agent, idx, outs, scratch.workspace, gran, stream)
+        _update_together(w, model, agent, idx, outs, gran, stream)
     return scratch
 
 
@@ -187,28 +192,51 @@ def _align_all(w, model, agent, gran, scratches, stream):
     if given and len(outs) < len(segs) or not _independent(w, agent, lens, outs):
         return False
     for idx in _joint_runs(model, segs, lens, pools, gran, scratches):
-        if len(idx) == 1 or not _align_run(w, model, agent, idx, gran, scratches, stream):
-            for j in idx:
-                _align_one(w, model, agent, j, gran, scratches, stream)
+        if len(idx) == 1:
+            _align_one(w, model, agent, idx[0], gran, scratches, stream)
+        else:
+            _align_run(w, model, agent, idx, gran, scratches, stream)
     return True
 
 
+def _refused(e):
+    """Was this call refused for its arguments, so that nothing has been launched?"""
+    return e.status in (kv.EINVAL, kv.EUNSUPPORTED, kv.EWORKSPACE)
+
+
 def _align_run(w, model, agent, idx, gran, scratches, stream):
-    """Aligns the segments `idx` together.  Returns False where that is refused: one after the other they may be accepted, or are refused as
+    """Aligns the segments `idx` together, or, where that is refused, one after the other: so they may be accepted, or are refused as
     they always were."""
-    segs = [agent.segments[j] for j in idx]
+    segs, outs = [agent.segments[j] for j in idx], None
     try:
         if scratches is None:
             with kv.on_stream(stream):
                 scratch = AgentScratch(model, [s.base_k.shape[2] for s in segs], [len(s.anchor_k) for s in segs], gran, segs[0].base_k.device)
-            outs, workspace = list(zip(scratch.weights, scratch.nearest, scratch.selected)), scratch.workspace
+            given, workspace = zip(scratch.weights, scratch.nearest, scratch.selected), scratch.workspace
         else:
-            outs = [(scratches[j].weights, scratches[j].nearest, scratches[j].selected) for j in idx]
+            given = [(scratches[j].weights, scratches[j].nearest, scratches[j].selected) for j in idx]
             workspace = max((scratches[j] for j in idx), key=_workspace_bytes).workspace
-        _align_together(w, model, agent, idx, dict(zip(idx, outs)), workspace, gran, stream)
-        return True
-    except (kv.KVCommError, torch.OutOfMemoryError):
-        return False
+        given = dict(zip(idx, given))
+        _match_together(w, model, agent, idx, given, workspace, gran, stream)
+        outs = given
+        return _update_together(w, model, agent, idx, outs, gran, stream)
+    except torch.OutOfMemoryError:   # (only the scratch allocates)
+        pass
+    except kv.KVCommError as e:
+        if not _refused(e):
+            raise
+    for j in idx:
+        if outs is None:
+            _align_one(w, model, agent, j, gran, scratches, stream)
+        else:   # matched, but not updated
+            _update_one(w, model, agent, j, outs[j][0], gran, stream)
+
+
+def _update_one(w, model, agent, j, weights, gran, stream):
+    seg = agent.segments[j]
+    p0, S = w.seg_offset(j), seg.base_k.shape[2]
+    kv.kvcomm_align_kv(model, seg.base_k, seg.base_v, seg.anchor_dk, seg.anchor_dv, weights, seg.delta_pos, _slot(agent.cache_k, p0, S),
+                       _slot(agent.cache_v, p0, S), seg.anchor_len, seg.anchor_delta_pos, gran, stream)
 
 
 def _align_one(w, model, agent, j, gran, scratches, stream):

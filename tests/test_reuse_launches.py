@@ -13,16 +13,19 @@ M = hotpath.model_of(W)
 
 
 class Library:
-    """The calls of the weights and the update: `calls` lists (name, segments), `declined` counts what their limits refused."""
+    """The calls of the weights and the update: `calls` lists (name, segments), `attempts` those that `refuse`
+    made fail, `declined` counts what their limits refused."""
     def __init__(self, agent):
-        self.agent, self.calls, self.refuse, self.declined = agent, [], {}, 0
+        self.agent, self.calls, self.attempts, self.refuse, self.declined = agent, [], [], {}, 0
 
     def index(self, base_k):
         return next(j for j, s in enumerate(self.agent.segments) if s.base_k is base_k)
 
     def note(self, name, idx):
-        if name in self.refuse:
-            raise kv.KVCommError(self.refuse[name], "refused")
+        for what in (name, "together" if name == "align" and len(idx) > 1 else ""):
+            if what in self.refuse:
+                self.attempts.append((name, idx))
+                raise kv.KVCommError(self.refuse[what], "refused")
         self.calls.append((name, idx))
 
     def limit(self, status):
@@ -170,3 +173,17 @@ def test_runs_fit_the_scratch_that_there_is(step, monkeypatch):
     lib = step(big, scratches=lambda agent: [hotpath.Scratch(m, 600, 8, kv.W_LAYER_HEAD_TOKEN, "cpu") for _ in range(3)],
                gran=kv.W_LAYER_HEAD_TOKEN)
     assert lib.calls == each_alone(3) and lib.declined == 0
+
+
+def test_what_is_refused_all_the_same(step):
+    """Refused together, the segments are tried one by one, matched again only if they have not been; what the runtime refuses (-4) and
+    the caller's own mistakes end the step."""
+    for status in (-1, -2):
+        assert step(W, refuse={"align": status}).calls == [("weights", [0, 1, 2, 3])]
+        assert step(W, refuse={"align": status}).attempts == [("align", [0, 1, 2, 3]), ("align", [0])]
+    assert step(W, refuse={"together": -2}).calls == [("weights", [0, 1, 2, 3])] + [("align", [j]) for j in range(4)]
+    lib = step(W, refuse={"weights": -1})
+    assert lib.calls == [] and lib.error == -1 and lib.attempts == [("weights", [0, 1, 2, 3]), ("weights", [0])]
+    for name, before in (("weights", []), ("align", [("weights", [0, 1, 2, 3])])):
+        lib = step(W, refuse={name: -4})
+        assert lib.error == -4 and lib.calls == before and lib.attempts == [(name, [0, 1, 2, 3])]

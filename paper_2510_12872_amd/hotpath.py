@@ -125,19 +125,20 @@ def _slot(cache, p0, S):
     return cache.narrow(2, p0, S) if 0 <= p0 <= cache.shape[2] - S else cache[:, :, p0:p0 + S]   # (narrow: half the time of an index)
 
 
-def _independent(w, agent, lens, outs):
-    """May these segments be aligned in any order, and twice?  Their slots, and what the weights go to, lie apart, and nothing that is read
-    lies in the agent's cache: a key or a delta in a slot that an earlier segment's update writes is read after that update, and an
-    update in place cannot be made again."""
+def _independent(w, agent, lens, scratches):
+    """May these segments be matched together and then updated together?  Their slots, what the weights go to and the workspaces lie apart,
+    and nothing else that is used lies in the agent's cache: a key or a delta in a slot that an earlier segment's update writes is read after
+    that update."""
     end = 0
     for j, S in enumerate(lens):
         p0 = w.seg_offset(j)
         if p0 < end:
             return False
         end = p0 + S
-    return end <= min(agent.cache_k.shape[2], agent.cache_v.shape[2]) and kv.apart(
-        (agent.cache_k, agent.cache_v),
-        [g for s in agent.segments for g in ((s.base_k, s.base_v), s.anchor_k, s.anchor_dk, s.anchor_dv)], [t for o in outs for t in o])
+    own = [t for s in scratches for t in (s.weights, s.nearest, s.selected)]
+    own += {s.workspace.data_ptr(): s.workspace for s in scratches}.values()   # (one workspace may serve all)
+    used = [g for s in agent.segments for g in ((s.base_k, s.base_v), s.anchor_k, s.anchor_dk, s.anchor_dv)]
+    return end <= min(agent.cache_k.shape[2], agent.cache_v.shape[2]) and kv.apart((agent.cache_k, agent.cache_v), used + [own] if own else used, own)
 
 
 def _rotations(seg):
@@ -180,16 +181,28 @@ def _workspace_bytes(scratch):
     return scratch.workspace.numel() * scratch.workspace.element_size()
 
 
+def _whole_scratch(scratches, n):
+    """The Scratch of each of n segments as a list; None where one is missing or lacks something (the single calls make that, or refuse it)."""
+    try:
+        own = [scratches[j] for j in range(n)]
+    except (IndexError, KeyError):
+        return None
+    return own if all(isinstance(s, Scratch) and isinstance(s.weights, torch.Tensor) and isinstance(s.nearest, torch.Tensor) and
+                      isinstance(s.selected, torch.Tensor) and isinstance(s.workspace, torch.Tensor) for s in own) else None
+
+
 def _align_all(w, model, agent, gran, scratches, stream):
     """Aligns the segments of an agent, those that may share a launch in one launch per step.  Returns False where none do (segments that
     depend on each other, scratch that segments share); nothing has been launched then."""
     segs = agent.segments
     lens, pools = [s.base_k.shape[2] for s in segs], [len(s.anchor_k) for s in segs]
-    given = scratches is not None
-    if min(pools) == 0 or given and not all(isinstance(s, Scratch) for s in scratches):
+    if min(pools) == 0:
         return False
-    outs = [(s.weights, s.nearest, s.selected) for s in scratches[:len(segs)]] if given else ()
-    if given and len(outs) < len(segs) or not _independent(w, agent, lens, outs):
+    if scratches is not None:
+        scratches = _whole_scratch(scratches, len(segs))
+        if scratches is None:
+            return False
+    if not _independent(w, agent, lens, scratches or ()):
         return False
     for idx in _joint_runs(model, segs, lens, pools, gran, scratches):
         if len(idx) == 1:

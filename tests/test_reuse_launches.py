@@ -1,5 +1,7 @@
 """Which library calls a step of several segments makes: every segment is matched once and updated once, in as few launches as the
 batched calls' limits allow.  (CPU only: the calls are replaced by ones that know those limits and note what they were given.)"""
+import collections
+
 import pytest
 import torch
 
@@ -187,3 +189,45 @@ def test_what_is_refused_all_the_same(step):
     for name, before in (("weights", []), ("align", [("weights", [0, 1, 2, 3])])):
         lib = step(W, refuse={name: -4})
         assert lib.error == -4 and lib.calls == before and lib.attempts == [(name, [0, 1, 2, 3])]
+
+
+@pytest.mark.parametrize("kind", [tuple, collections.deque, lambda s: dict(enumerate(s)), lambda s: list(s) + list(s)])
+def test_scratch_in_any_container(step, kind):
+    lib = step(W, scratches=lambda agent: kind(plain(agent)))
+    assert lib.calls == both([0, 1, 2, 3])
+
+
+def test_scratch_that_lacks_something(step):
+    """(The single calls make what is not given, or need less.)"""
+    for name in ("nearest", "selected", "workspace"):
+        def lacks(agent):
+            sc = plain(agent)
+            setattr(sc[2], name, None)
+            return sc
+        assert step(W, scratches=lacks).calls == each_alone(4), name
+    class Own:
+        weights = nearest = selected = workspace = None
+    assert step(W, scratches=lambda agent: [Own()] * 4).calls == each_alone(4)
+    with pytest.raises(IndexError):
+        step(W, scratches=lambda agent: plain(agent)[:3])
+
+
+def test_scratch_that_segments_share(step):
+    """One workspace for all is one launch's; outputs, or an output in another segment's workspace, are not."""
+    def shared(agent):
+        sc = plain(agent)
+        for s in sc:
+            s.workspace = sc[0].workspace
+        return sc
+    assert step(W, scratches=shared).calls == both([0, 1, 2, 3])
+    def carved(agent):
+        sc = plain(agent)
+        sc[1].weights = sc[0].workspace[:sc[1].weights.numel() * 4].view(torch.float32).view(sc[1].weights.shape)
+        return sc
+    assert step(W, scratches=carved).calls == each_alone(4)
+    def in_cache(agent):
+        sc = plain(agent)
+        sc[0].workspace = agent.cache_k.view(-1).view(torch.uint8)
+        return sc
+    assert step(W, scratches=in_cache).calls == each_alone(4)
+    assert step(W, scratches=lambda agent: [plain(agent)[0]] * 4).calls == each_alone(4)

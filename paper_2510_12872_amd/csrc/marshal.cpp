@@ -130,11 +130,11 @@ bool same_layout(const kvcomm_tensor &a, const kvcomm_tensor &b)
 struct Items {   // of a list or tuple
     PyObject *const *p;
     int n;
-    Items(PyObject *o, int max)
+    Items(PyObject *o, int max, int min = 1)
     {
         if (!PyList_CheckExact(o) && !PyTuple_CheckExact(o)) throw Decline{};
         const Py_ssize_t len = PySequence_Fast_GET_SIZE(o);
-        if (len < 1 || len > max) throw Decline{};
+        if (len < min || len > max) throw Decline{};
         p = PySequence_Fast_ITEMS(o);
         n = (int)len;
     }
@@ -535,14 +535,14 @@ PyObject *apart(PyObject *, PyObject *const *args, Py_ssize_t n)
         }
     };
     return entry<3>(args, n, [](PyObject *const *a) {
-        const Items own(a[0], INT_MAX), groups(a[1], INT_MAX), each(a[2], INT_MAX);
+        const Items own(a[0], INT_MAX, 0), groups(a[1], INT_MAX, 0), each(a[2], INT_MAX, 0);
         std::vector<Range> r;
         auto meets = [&](const Range &o, size_t from, size_t to) {
             return std::any_of(r.begin() + from, r.begin() + to, [&](const Range &x) { return x.lo < o.hi && o.lo < x.hi; });
         };
         for (int i = 0; i < own.n; ++i) r.emplace_back(as_tensor(own.p[i]));
         for (int g = 0; g < groups.n; ++g) {
-            const Items other(groups.p[g], INT_MAX);
+            const Items other(groups.p[g], INT_MAX, 0);
             for (int k = 0; k < other.n; ++k)
                 if (meets(Range(as_tensor(other.p[k])), 0, own.n)) return 0LL;
         }

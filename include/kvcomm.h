@@ -260,9 +260,10 @@ int kvcomm_suffix_attn(const kvcomm_model *model, kvcomm_tensor q,
  * max_blocks (their kernel is small-block and never fills a compute unit), and so does the kernel that joins the
  * partial results of a split launch.
  * The same bits mean the same work items whatever max_blocks is.  A launch that is too small to fill the GPU is cut
- * into many (32 rows each, or runs of keys), which costs more than it gives where max_blocks is a small part of
- * them.  One layer, 8 kv heads, G = 4, D = 128, 3000 keys, us on 160 / 64 / 8 blocks (in brackets: whole 256-row tiles,
- * which kvcomm_suffix_attn takes for launches that fill the GPU): Tq 64  22 / 37 / 254 (66 / 66 / 66), Tq 256
+ * into many (16 or 32 rows each, or runs of keys), which costs more than it gives where max_blocks is a small part of
+ * them.  (Items of 16 rows go two at a time where there are more than max_blocks.  2 layers, 8 kv heads, G = 4, 364 keys, Tq 64, us
+ * plain / on 160 / 64 / 8 blocks: D = 128, bf16 6.5 / 8.8 / 15.3 / 103, D = 64, f32, 464 keys 11.4 / 16.3 / 30.4 / 230.)  One layer, 8 kv heads, G = 4, D = 128, 3000 keys, us on 160 / 64 / 8 blocks (in brackets: whole 256-row tiles,
+ * which kvcomm_suffix_attn takes for launches that fill the GPU): Tq 64  21 / 36 / 252 (66 / 66 / 66), Tq 256
  * 38 / 70 / 532 (66 / 66 / 255), Tq 512  51 / 89 / 602 (66 / 67 / 488); Tq 1000  76 / 138 / 982 (67 / 125 / 919): there
  * the cut pieces of 128 ... 240 blocks cost 12 ... 16 % as well.
  * Errors: as kvcomm_suffix_attn; KVCOMM_EINVAL for max_blocks < 8 (one block per XCD is the minimum).          */

@@ -135,10 +135,13 @@ static inline size_t attn_workspace(const kvcomm_model &m, const AttnPlan &pl)
 // one / two, 4 layers x 8 heads, G = 4: D = 128, 1056 keys, Tq 32 (256 blocks of one group) 44.5 / 49.8, 1088 keys, Tq 64 (512) 58.6 / 55.6; one
 // layer, 1152 keys, Tq 128 (256) 34.8 / 52.5; 2 layers, 400 keys, Tq 100 (400) 26.0 / 25.4; D = 64, 540 keys, Tq 40 (320) 21.0 / 18.7; D = 256,
 // 1056 keys, Tq 32 (256) 84 / 90, 1088 keys, Tq 64 (512) 118 / 97; but 128 keys, Tq 128, 4 layers x 4 heads, G = 8 (1024) 23.2 / 24.3.
-static inline int attn_f32_groups(const kvcomm_model &m, int tq)
+// A row's sums do not depend on it, so a confined launch takes two where it has more groups than blocks (max_blocks; 0: not confined): one layer, D = 128,
+// 1152 keys, Tq 128 (256 groups) on 160 / 64 / 8 blocks one by one 66.9 / 125 / 950, two at a time 51.2 / 98.8 / 743.
+static inline int attn_f32_groups(const kvcomm_model &m, int tq, int max_blocks)
 {
     const int64_t rows = (int64_t)(m.n_q_heads / m.n_kv_heads) * tq;
-    return (int64_t)m.n_layers * m.n_kv_heads * ((rows + 15) / 16) <= kChipCUs ? 1 : 2;
+    const int64_t at_once = max_blocks > 0 && rows > 16 ? std::min(max_blocks, kChipCUs) : kChipCUs;
+    return (int64_t)m.n_layers * m.n_kv_heads * ((rows + 15) / 16) <= at_once ? 1 : 2;
 }
 
 int launch_attn_rows(const AttnParams &p, int D, int rows, unsigned n_blocks, hipStream_t stream);

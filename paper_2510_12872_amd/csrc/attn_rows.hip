@@ -300,24 +300,28 @@ __device__ __forceinline__ void load_half(const unsigned char *bytes, int64_t to
 // us per launch (HIP graph, with the combine launch where keys are cut), 32 rows -> 16: one layer, 8 kv heads, G = 4, one token: 1 key 6.3 -> 4.8,
 // 701 keys 10.2 -> 8.2, 3101 keys 12.1 -> 8.4 (D = 64 9.7 -> 7.0, G = 2, D = 256 15.9 -> 11.3; 9.6, 8.0 and 13.3 with the combine kernel of 32 rows);
 // 4 layers x 8 heads, Tq 16, 516 keys 9.4 -> 7.5; 32 layers, one token, 3101 keys 73.2 -> 70.8.
-template <int D, bool NT, bool PERSIST>
+// RH = 2: two neighbouring tiles per block, which share every K and V operand; every row's sums are those of RH = 1, bit for bit (the runs of
+// the two tiles may begin a sub-step apart).  For confined launches of more tiles than blocks.  us on 160 / 64 / 8 blocks one by one, two at a time (and as tiles
+// of 32 rows on 32x32x16 MFMAs, whose sums are others): 2 layers x 8 heads, G = 4, Tq 64, 364 keys 10.8 / 19.5 / 136, 8.8 / 15.3 / 103 (8.1 / 13.9 / 95);
+// D = 64, one layer, Tq 128, 2128 keys 16.1 / 29.2 / 220, 12.7 / 22.7 / 165 (11.2 / 19.6 / 139); 4 layers, Tq 16, 516 keys on 64 / 8 12.5 / 82, 9.7 / 63 (8.8 / 57).
+template <int D, bool NT, bool PERSIST, int RH>
 __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_rows_kernel16(const AttnParams p)
 {
-    constexpr int NW = rows_waves(D), ROWS = 16;
+    constexpr int NW = rows_waves(D), ROWS = 16;   // rows of a tile
     constexpr int NF = D / 16, KCH = D / 8, ROWB = D * 2, HALFB = 32 * ROWB;
     constexpr int RPL = 64 / KCH;                    // key rows filled by one wavefront-wide direct load
     constexpr int LPT = 32 / RPL;                    // direct loads of a 32-key half
     constexpr int KD = 16 / RPL, VD = RPL < 8 ? 8 / RPL : 1;   // loads after which the swizzle pattern of the rows repeats
     constexpr int JW = D * ROWS / 4;                 // 16-byte slots of a wavefront's outputs
     constexpr int JP = 2 * HALFB / 16;               // 16-byte slots of its buffers
-    static_assert(JW <= JP, "a wavefront's outputs fit its own buffers");
+    static_assert(RH * JW <= JP, "a wavefront's outputs fit its own buffers");
     // Chunk c of key `key` sits at position c ^ swz(key), as in attn_mfma_kernel.
     auto k_swz = [](int key) __attribute__((always_inline)) -> int { return D == 64 ? (key >> 1) & 7 : key & 15; };
     auto v_swz = [](int key) __attribute__((always_inline)) -> int {
         return D == 64 ? (2 * (key & 2)) | ((key >> 1) & 2) : 4 * (key & 3) | ((key >> 1) & 2);
     };
     __shared__ __align__(16) unsigned char smem[NW * 2 * HALFB];
-    __shared__ float ml[2][NW][ROWS];
+    __shared__ float ml[2][NW][RH * ROWS];
 
     await_attn_args(p);
     const int tid = threadIdx.x;
@@ -335,18 +339,30 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
     do {
         const int logical = x_first + item;
         const int run = div_by(logical, p.by_row_tiles);
-        const int rt = logical - run * p.n_row_tiles;   // the row tiles of a key run are neighbours: they share its L2 lines
+        const int rt0 = (logical - run * p.n_row_tiles) * RH;   // the row tiles of a key run are neighbours: they share its L2 lines
         const int lh = div_by(run, p.by_splits), split = run - lh * p.n_splits;
         const int l = div_by(lh, p.by_Hkv), hkv = lh - l * p.Hkv;
+        const int n_tiles = RH == 1 ? p.n_row_tiles : (p.G * p.tq + ROWS - 1) / ROWS;   // of a (layer, kv head)
 
-        const int r_row = rt * ROWS + n, i_row = div_by(r_row, p.by_G);   // (also the row that this thread joins: tid % ROWS == n)
-        const bool valid = i_row < p.tq;
-        const int qi = min(i_row, p.tq - 1);
-        const int hq = hkv * p.G + r_row - i_row * p.G;
-        const int imax = min(p.tq - 1, div_by(rt * ROWS + ROWS - 1, p.by_G)), imin = min(p.tq - 1, div_by(rt * ROWS, p.by_G));
-        const int units = (p.n_ctx + imax + 32) / 32;   // sub-steps that some query of the tile sees
-        // split_bound() without a causal edge: s * units / n_splits (<= 2^30: see there)
-        const int u0 = div_by(split * units, p.by_splits), u1 = div_by((split + 1) * units, p.by_splits);
+        int qi[RH], hq[RH], imin[RH], u0[RH], u1[RH];
+        bool valid[RH];
+#pragma unroll
+        for (int h = 0; h < RH; ++h) {
+            const int r_row = (rt0 + h) * ROWS + n, i_row = div_by(r_row, p.by_G);   // (also the row that this thread joins: tid % ROWS == n)
+            valid[h] = i_row < p.tq;
+            qi[h] = min(i_row, p.tq - 1);
+            hq[h] = hkv * p.G + r_row - i_row * p.G;
+            const int imax = min(p.tq - 1, div_by((rt0 + h) * ROWS + ROWS - 1, p.by_G));
+            imin[h] = min(p.tq - 1, div_by((rt0 + h) * ROWS, p.by_G));
+            const int units = (p.n_ctx + imax + 32) / 32;   // sub-steps that some query of the tile sees
+            // split_bound() without a causal edge: s * units / n_splits (<= 2^30: see there)
+            u0[h] = div_by(split * units, p.by_splits), u1[h] = div_by((split + 1) * units, p.by_splits);
+        }
+        if (RH == 2 && rt0 + 1 == n_tiles) u0[RH - 1] = u1[RH - 1] = u0[0];   // there is no second tile
+        const int u_end = RH == 2 ? max(u1[0], u1[RH - 1]) : u1[0];
+        // 0 or 1, and so the ends: the tiles' last queries are at most 16 keys apart.  1: a wavefront's sub-steps belong to one tile and the other in turn.
+        const int apart = u0[RH - 1] - u0[0];
+        const int u_end0 = apart ? u1[0] : u_end;   // of turn 0 (that of turn 1 is u_end)
 
         const unsigned char *kbytes = reinterpret_cast<const unsigned char *>(static_cast<const bf16_t *>(p.k) + l * p.s_k.layer + hkv * p.s_k.head);
         const unsigned char *vbytes = reinterpret_cast<const unsigned char *>(static_cast<const bf16_t *>(p.v) + l * p.s_v.layer + hkv * p.s_v.head);
@@ -355,12 +371,15 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
         lane_offsets<D>(v_in, lane, p.s_v.token, v_swz);
         auto load_k = [&](int u) __attribute__((always_inline)) { load_half<D, NT>(kbytes, p.s_k.token, 32 * u, p.N, k_in, lane, k_swz, kbuf); };
         auto load_v = [&](int u) __attribute__((always_inline)) { load_half<D, NT>(vbytes, p.s_v.token, 32 * u, p.N, v_in, lane, v_swz, vbuf); };
-        int u = u0 + wave;
-        bf16x8 qf[NF / 2];
-        const bf16_t *qrow = static_cast<const bf16_t *>(p.q) + l * p.s_q.layer + (int64_t)hq * p.s_q.head + (int64_t)qi * p.s_q.token;
+        int u = u0[0] + wave, turn = 0;
+        bf16x8 qf[RH][NF / 2];
 #pragma unroll
-        for (int ks = 0; ks < NF / 2; ++ks) qf[ks] = as_bf16x8(load16(qrow + ks * 32 + g * 8));
-        if (u < u1) {
+        for (int h = 0; h < RH; ++h) {
+            const bf16_t *qrow = static_cast<const bf16_t *>(p.q) + l * p.s_q.layer + (int64_t)hq[h] * p.s_q.head + (int64_t)qi[h] * p.s_q.token;
+#pragma unroll
+            for (int ks = 0; ks < NF / 2; ++ks) qf[h][ks] = as_bf16x8(load16(qrow + ks * 32 + g * 8));
+        }
+        if (u < u_end0) {
             load_k(u);
             load_v(u);
         }
@@ -378,57 +397,80 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
             }
         }
 
-        f32x4 o[NF];
+        f32x4 o[RH][NF];
+        float m[RH], mc[RH], lsum[RH];   // lsum: this lane's quarter of the row sum
 #pragma unroll
-        for (int db = 0; db < NF; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
-        float m = -INFINITY, mc = 0.f, lsum = 0.f;   // lsum: this lane's quarter of the row sum
+        for (int h = 0; h < RH; ++h) {
+#pragma unroll
+            for (int db = 0; db < NF; ++db) o[h][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+            m[h] = -INFINITY, mc[h] = 0.f, lsum[h] = 0.f;
+        }
         __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0), seen by the compiler: it puts no wait for the queries into the loop
 
-        for (; u < u1; u += NW) {
-            const bool more = u + NW < u1;   // wavefront-uniform
+        // The sub-step u for the tiles [H0, H1), which take it in step: their chains of instructions run beside each other.
+        auto sub_step = [&](auto h0_c, auto h1_c, int next, bool more) __attribute__((always_inline)) {   // (u, next, more: wavefront-uniform)
+            constexpr int H0 = decltype(h0_c)::value, H1 = decltype(h1_c)::value;
             wait_loads<LPT>();               // K(u) has landed (V(u) may be outstanding)
             bf16x8 ka[NF];                   // all operand reads in flight at once: ks = i / 2, keys 16 * (i & 1) ...
 #pragma unroll
             for (int i = 0; i < NF; ++i)
                 ka[i] = as_bf16x8(*(const __attribute__((address_space(3))) u32x4 *)(kbuf + (i & 1) * 16 * ROWB + k_off[i >> 1]));
             wait_lds();                      // K(u) has been read: its buffer is free
-            if (more) load_k(u + NW);
-            f32x4 s[2];                      // score j of this lane: key 16 * (j / 4) + 4 * g + j % 4
+            if (more) load_k(next);
+            f32x4 s[RH][2];                  // score j of this lane: key 16 * (j / 4) + 4 * g + j % 4
 #pragma unroll
             for (int i = 0; i < NF; ++i)
-                s[i & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[i], qf[i >> 1], i < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[i & 1], 0, 0, 0);
+#pragma unroll
+                for (int h = H0; h < H1; ++h)
+                    s[h][i & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[i], qf[h][i >> 1], i < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[h][i & 1], 0, 0, 0);
 
-            if (32 * u + 31 > p.n_ctx + imin) {   // some key is hidden from some query
-                const int limit = p.n_ctx + qi - 32 * u - 4 * g;
+            if (32 * u + 31 > p.n_ctx + imin[H0]) {   // some key is hidden from some query (imin grows from tile to tile)
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (16 * (j >> 2) + (j & 3) > limit) s[j >> 2][j & 3] = -INFINITY;
+                for (int h = H0; h < H1; ++h) {
+                    const int limit = p.n_ctx + qi[h] - 32 * u - 4 * g;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        if (16 * (j >> 2) + (j & 3) > limit) s[h][j >> 2][j & 3] = -INFINITY;
+                }
             }
-            float mx = s[0][0];
+            float mx[RH];
+            bool grows = false;
 #pragma unroll
-            for (int j = 1; j < 8; ++j) mx = fmaxf(mx, s[j >> 2][j & 3]);
-            mx = query_max(mx);
-            if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
-                const float m_new = fmaxf(m, mx);
-                const float corr = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - m_new) * p.scale_log2);
-                lsum *= corr;
+            for (int h = H0; h < H1; ++h) {
+                mx[h] = s[h][0][0];
 #pragma unroll
-                for (int db = 0; db < NF; ++db) o[db] *= corr;
-                m = m_new;
-                mc = m == -INFINITY ? 0.f : m * p.scale_log2;   // a row that sees no key of this run yet: exponentials 0
+                for (int j = 1; j < 8; ++j) mx[h] = fmaxf(mx[h], s[h][j >> 2][j & 3]);
+                mx[h] = query_max(mx[h]);
+                grows |= mx[h] > m[h];
             }
-            u32x4 pk;
-            float rs0 = 0.f, rs1 = 0.f;
+            if (__builtin_amdgcn_ballot_w64(grows) != 0) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j >> 1][2 * (j & 1)], p.scale_log2, -mc));
-                const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[j >> 1][2 * (j & 1) + 1], p.scale_log2, -mc));
-                rs0 += e0;
-                rs1 += e1;
-                pk[j] = pack_bf16x2(e0, e1);
+                for (int h = H0; h < H1; ++h) {   // (a row whose reference stays is multiplied by 1)
+                    const float m_new = fmaxf(m[h], mx[h]);
+                    const float corr = m[h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m[h] - m_new) * p.scale_log2);
+                    lsum[h] *= corr;
+#pragma unroll
+                    for (int db = 0; db < NF; ++db) o[h][db] *= corr;
+                    m[h] = m_new;
+                    mc[h] = m[h] == -INFINITY ? 0.f : m[h] * p.scale_log2;   // a row that sees no key of this run yet: exponentials 0
+                }
             }
-            const bf16x8 pf = as_bf16x8(pk);
-            lsum += rs0 + rs1;
+            bf16x8 pf[RH];
+#pragma unroll
+            for (int h = H0; h < H1; ++h) {
+                u32x4 pk;
+                float rs0 = 0.f, rs1 = 0.f;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[h][j >> 1][2 * (j & 1)], p.scale_log2, -mc[h]));
+                    const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[h][j >> 1][2 * (j & 1) + 1], p.scale_log2, -mc[h]));
+                    rs0 += e0;
+                    rs1 += e1;
+                    pk[j] = pack_bf16x2(e0, e1);
+                }
+                pf[h] = as_bf16x8(pk);
+                lsum[h] += rs0 + rs1;
+            }
 
             if (more)
                 wait_loads<LPT>();   // V(u) has landed (K of the next sub-step may be outstanding)
@@ -438,59 +480,85 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
 #pragma unroll
             for (int db = 0; db < NF; ++db) va[db] = lds_read_tr_pair(vbuf + v_off[db], vbuf + v_off[db] + 16 * ROWB);
             wait_lds();                      // V(u) has been read
-            if (more) load_v(u + NW);
+            if (more) load_v(next);
 #pragma unroll
-            for (int db = 0; db < NF; ++db) o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[db], pf, o[db], 0, 0, 0);
+            for (int db = 0; db < NF; ++db)
+#pragma unroll
+                for (int h = H0; h < H1; ++h) o[h][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[db], pf[h], o[h][db], 0, 0, 0);
+        };
+        if constexpr (RH == 1) {
+            for (; u < u_end; u += NW) sub_step(template_int<0>{}, template_int<1>{}, u + NW, u + NW < u_end);
+        } else {
+            if (apart == 0)
+                for (; u < min(u1[0], u1[RH - 1]); u += NW) sub_step(template_int<0>{}, template_int<2>{}, u + NW, u + NW < u_end);
+            while (u < (turn == 0 ? u_end0 : u_end)) {   // the tiles are apart, or one of them ends before the other
+                const int next = apart == 0 ? u + NW : turn == 0 ? u + apart : u + NW - apart;
+                const int next_turn = apart == 0 ? 0 : turn ^ 1;
+                const bool more = next < (next_turn == 0 ? u_end0 : u_end);
+                if (turn == 0 && u < u1[0])
+                    sub_step(template_int<0>{}, template_int<1>{}, next, more);
+                else
+                    sub_step(template_int<1>{}, template_int<2>{}, next, more);
+                u = next;
+                turn = next_turn;
+            }
         }
 
         // ---- join the wavefronts' states as in attn_rows_kernel.  Lane (n, g) holds channels 16 * db + 4 * g ... + 3 of row n: slot
         // (4 * db + g, n).
-        lsum = query_sum(lsum);
-        if (g == 0) {
-            ml[0][wave][n] = m;
-            ml[1][wave][n] = lsum;
-        }
         f32x4 *join = reinterpret_cast<f32x4 *>(smem);
-        if (valid) {
 #pragma unroll
-            for (int db = 0; db < NF; ++db) join[wave * JP + 64 * db + lane] = o[db];
+        for (int h = 0; h < RH; ++h) {
+            lsum[h] = query_sum(lsum[h]);
+            if (g == 0) {
+                ml[0][wave][ROWS * h + n] = m[h];
+                ml[1][wave][ROWS * h + n] = lsum[h];
+            }
+            if (valid[h]) {
+#pragma unroll
+                for (int db = 0; db < NF; ++db) join[wave * JP + JW * h + 64 * db + lane] = o[h][db];
+            }
         }
         __syncthreads();
-        float M = ml[0][0][n];
+        // A wavefront joins rows of one tile: RH = 2 the even ones of the first, the odd ones of the second.
+        const int jh = RH == 1 ? 0 : wave & 1, jw = RH == 1 ? wave : wave >> 1;
+        const int jrow = ROWS * jh + n, jqi = jh ? qi[RH - 1] : qi[0], jhq = jh ? hq[RH - 1] : hq[0];
+        float M = ml[0][0][jrow];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[0][w][n]);
+        for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[0][w][jrow]);
         float f[NW], ltot = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const float mw = ml[0][w][n], lw = ml[1][w][n];
+            const float mw = ml[0][w][jrow], lw = ml[1][w][jrow];
             f[w] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mw - M) * p.scale_log2);
             ltot += mw == -INFINITY ? lw : lw * f[w];   // reference -inf: no key seen and sum 0, or nothing but NaN scores and a sum that says so
         }
-        const int64_t part = (int64_t)(lh * p.n_row_tiles + rt) * p.n_splits + split;
-        if (valid) {
+        const int64_t part = (int64_t)(lh * n_tiles + rt0 + jh) * p.n_splits + split;
+        if (jh ? valid[RH - 1] : valid[0]) {
             const float inv = 1.f / ltot;
 #pragma unroll
-            for (int i = 0; i < JW; i += 64 * NW) {
-                const int slot = i + tid;
-                if (JW % (64 * NW) && slot >= JW) break;
-                f32x4 a = join[slot] * f[0];
+            for (int i = 0; i < JW; i += 64 * NW / RH) {
+                const int slot = i + 64 * jw + lane;
+                if (JW % (64 * NW / RH) && slot >= JW) break;
+                const f32x4 *own = join + JW * jh + slot;
+                f32x4 a = own[0] * f[0];
 #pragma unroll
-                for (int w = 1; w < NW; ++w) a += join[w * JP + slot] * f[w];
+                for (int w = 1; w < NW; ++w) a += own[w * JP] * f[w];
                 if (p.n_splits > 1) {
                     reinterpret_cast<f32x4 *>(p.part_o + part * (ROWS * D))[slot] = a;
                 } else {
-                    bf16_t *orow = static_cast<bf16_t *>(p.out) + l * p.s_o.layer + (int64_t)hq * p.s_o.head + (int64_t)qi * p.s_o.token;
+                    bf16_t *orow = static_cast<bf16_t *>(p.out) + l * p.s_o.layer + (int64_t)jhq * p.s_o.head + (int64_t)jqi * p.s_o.token;
                     const u32x2 w2 = {pack_bf16x2(a[0] * inv, a[1] * inv), pack_bf16x2(a[2] * inv, a[3] * inv)};
                     *reinterpret_cast<u32x2 *>(orow + slot / ROWS * 4) = w2;
                 }
             }
-        }
-        if (tid < ROWS && valid) {
-            if (p.n_splits > 1) {
-                p.part_ml[part * 2 * ROWS + n] = M;
-                p.part_ml[part * 2 * ROWS + ROWS + n] = ltot;
-            } else if (p.lse) {
-                p.lse[((int64_t)l * p.Hkv * p.G + hq) * p.tq + qi] = M * p.scale + logf(ltot);
+            if (jw == 0 && g == 0) {
+                if (p.n_splits > 1) {
+                    p.part_ml[part * 2 * ROWS + n] = M;
+                    p.part_ml[part * 2 * ROWS + ROWS + n] = ltot;
+                } else if (p.lse) {
+                    p.lse[((int64_t)l * p.Hkv * p.G + jhq) * p.tq + jqi] = M * p.scale + logf(ltot);
+                }
             }
         }
         if (!PERSIST) break;
@@ -676,9 +744,17 @@ int launch_combine(const AttnParams &p, int rows, hipStream_t stream)
 template <int D>
 int launch_rows(const AttnParams &p, int rows, bool nt, bool persist, unsigned n_blocks, hipStream_t stream)
 {
-    const dim3 grid(n_blocks), block(64 * rows_waves(D));
-    const auto rows16 = persist ? (nt ? attn_rows_kernel16<D, true, true> : attn_rows_kernel16<D, false, true>)
-                                : (nt ? attn_rows_kernel16<D, true, false> : attn_rows_kernel16<D, false, false>);
+    const dim3 block(64 * rows_waves(D));
+    if (rows == 16 && persist && p.n_row_tiles > 1) {   // more tiles than blocks: two of a (layer, kv head) at a time
+        AttnParams pairs = p;
+        pairs.n_row_tiles = (p.n_row_tiles + 1) / 2;
+        pairs.by_row_tiles = make_divisor((uint32_t)pairs.n_row_tiles);
+        pairs.n_items = p.n_items / p.n_row_tiles * pairs.n_row_tiles;
+        return launch(attn_rows_kernel16<D, false, true, 2>, dim3(std::min(n_blocks, (unsigned)pairs.n_items)), block, 0, stream, pairs);
+    }
+    const dim3 grid(n_blocks);
+    const auto rows16 = persist ? (nt ? attn_rows_kernel16<D, true, true, 1> : attn_rows_kernel16<D, false, true, 1>)
+                                : (nt ? attn_rows_kernel16<D, true, false, 1> : attn_rows_kernel16<D, false, false, 1>);
     const auto rows32 = persist ? (nt ? attn_rows_kernel<D, true, true> : attn_rows_kernel<D, false, true>)
                                 : (nt ? attn_rows_kernel<D, true, false> : attn_rows_kernel<D, false, false>);
     return launch(rows == 16 ? rows16 : rows32, grid, block, 0, stream, p);

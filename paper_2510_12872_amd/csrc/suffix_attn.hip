@@ -651,7 +651,7 @@ int suffix_attn(const kvcomm_model *model, kvcomm_tensor q, kvcomm_tensor cache_
     const int D = model->head_dim;
 
     if (dt == KVCOMM_F32) {
-        p.groups_per_tile = attn_f32_groups(*model, tq);
+        p.groups_per_tile = attn_f32_groups(*model, tq, max_blocks);
         const int rows = 16 * p.groups_per_tile;
         p.n_row_tiles = (int32_t)(((int64_t)p.G * tq + rows - 1) / rows);
         const int64_t n_items = (int64_t)p.L * p.Hkv * p.n_row_tiles;

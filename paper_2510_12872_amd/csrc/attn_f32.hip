@@ -16,6 +16,7 @@ constexpr int f32_row_keys(int D) { return D == 256 ? 16 : 8; }
 template <int D>
 __global__ __launch_bounds__(256) void attn_f32_row_kernel(const AttnParams p)
 {
+    static_assert(f32_row_keys(D) <= 64, "every key has its lane");
     constexpr int CPL = D / 64;  // output channels per lane
     __shared__ float q_lds[4][D];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -35,48 +36,36 @@ __global__ __launch_bounds__(256) void attn_f32_row_kernel(const AttnParams p)
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-    const int last = p.n_ctx + i;
-    float m = -INFINITY, lsum = 0.f;
+    const int last = p.n_ctx + i;   // < f32_row_keys(D)
+    float sc = -INFINITY;
+    if (lane <= last) {
+        const float *kr = k + (int64_t)lane * p.s_k.token;
+        float dot = 0.f;
+#pragma unroll 4
+        for (int c = 0; c < D; c += 4) {
+            const f32x4 kv = *reinterpret_cast<const f32x4 *>(kr + c);
+            dot = fmaf(q_lds[wave][c], kv[0], dot);
+            dot = fmaf(q_lds[wave][c + 1], kv[1], dot);
+            dot = fmaf(q_lds[wave][c + 2], kv[2], dot);
+            dot = fmaf(q_lds[wave][c + 3], kv[3], dot);
+        }
+        sc = dot * p.scale;
+    }
+    float m = sc;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+    const float pj = lane <= last ? expf(sc - m) : 0.f;
+    float lsum = pj;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off);
     float acc[CPL];
 #pragma unroll
     for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
-
-    for (int j0 = 0; j0 <= last; j0 += 64) {
-        const int j = j0 + lane;
-        float sc = -INFINITY;
-        if (j <= last) {
-            const float *kr = k + (int64_t)j * p.s_k.token;
-            float dot = 0.f;
-#pragma unroll 4
-            for (int c = 0; c < D; c += 4) {
-                const f32x4 kv = *reinterpret_cast<const f32x4 *>(kr + c);
-                dot = fmaf(q_lds[wave][c], kv[0], dot);
-                dot = fmaf(q_lds[wave][c + 1], kv[1], dot);
-                dot = fmaf(q_lds[wave][c + 2], kv[2], dot);
-                dot = fmaf(q_lds[wave][c + 3], kv[3], dot);
-            }
-            sc = dot * p.scale;
-        }
-        float cmax = sc;
+    for (int j = 0; j <= last; ++j) {
+        const float pv = __shfl(pj, j);
+        const float *vr = v + (int64_t)j * p.s_v.token;
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, off));
-        const float m_new = fmaxf(m, cmax);  // finite: lane 0 of every chunk is visible
-        const float corr = expf(m - m_new);
-        const float pj = j <= last ? expf(sc - m_new) : 0.f;
-        float psum = pj;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) psum += __shfl_xor(psum, off);
-        lsum = lsum * corr + psum;
-        m = m_new;
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) acc[c] *= corr;
-        const int cnt = min(64, last - j0 + 1);
-        for (int jj = 0; jj < cnt; ++jj) {
-            const float pv = __shfl(pj, jj);
-            const float *vr = v + (int64_t)(j0 + jj) * p.s_v.token;
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) acc[c] = fmaf(pv, vr[lane + 64 * c], acc[c]);
-        }
+        for (int c = 0; c < CPL; ++c) acc[c] = fmaf(pv, vr[lane + 64 * c], acc[c]);
     }
     float *o = static_cast<float *>(p.out) + l * p.s_o.layer + (int64_t)hq * p.s_o.head + i * p.s_o.token;
     const float inv = 1.f / lsum;

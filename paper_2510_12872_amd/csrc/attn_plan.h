@@ -105,13 +105,14 @@ static inline AttnPlan attn_plan(const kvcomm_model &m, int n_ctx, int tq, bool 
     const bool half = rows <= 16 || items16 * rows_ns <= kChipCUs;
     if (pl.rows_kernel && half && rows_ns == 1 && may_split && items16 <= kChipCUs / 4) {
         // Their cuts pay earlier: an iteration takes 0.9 us (D = 64: 0.6), the combine launch 3.3.  8 blocks, G = 4, D = 128, one run / the cut: 520
-        // keys (3 iterations) 7.3 / 7.7 us, 1000 (4) 9.1 / 8.1, 2000 (8) 12.8 / 8.2; 64 blocks, 1250 keys (5, in runs of two) 12.6 / 13.6, 2000 (in
+        // keys (3 iterations) 7.3 / 7.7 us, 1000 (4) 8.7 / 7.5 (1 block 8.3 / 7.8, 32 9.0 / 7.7, 64 9.5 / 9.0; 780 keys 7.1 / 7.7, 7.5 / 7.3, 7.7 / 7.6,
+        // 7.8 / 7.9), 2000 (8) 12.8 / 8.2; 64 blocks, 1250 keys (5, in runs of two) 12.6 / 13.6, 2000 (in
         // runs of two) 16.9 / 16.2; D = 64, 8 blocks, 1000 keys 6.7 / 6.7, 1250 7.2 / 6.7; 64 blocks, 1250 keys 7.4 / 7.7, 1500 7.9 / 7.8.  More blocks
         // have the memory's rate already: 128 blocks, G = 2, 2000 keys, D = 128 22.0 / 26.0, D = 64 13.0 / 15.6.
         int64_t ns = std::min<int64_t>(std::min<int64_t>(kRowsMaxSplits, kChipCUs / items16), its);
         const int64_t split_its = (its + ns - 1) / ns;
         ns = (its + split_its - 1) / split_its;
-        if (its - split_its >= 4 || (D == 128 && its == 4 && split_its == 1)) rows_ns = (int)ns;
+        if (its - split_its >= (D == 128 && split_its == 1 ? 3 : 4)) rows_ns = (int)ns;   // iterations saved
     }
     pl.tile_rows = !pl.rows_kernel ? tile_rows : half ? 16 : 32;
     pl.group_rows = std::min(pl.tile_rows, 32);

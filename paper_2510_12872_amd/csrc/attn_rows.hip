@@ -13,6 +13,38 @@ __device__ __forceinline__ void wait_loads()   // at most N of this wavefront's 
 }
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
 
+// Direct loads of 32 rows from key0 on into a wavefront's buffer, chunk c of row `key` at position c ^ swz(key): a wavefront-uniform row
+// pointer plus per-lane offsets that do not change from one sub-step to the next (lane_offsets(); the pattern repeats after
+// NIN loads).  Rows past the cache end (last sub-step only) re-read the last row; they are always masked.
+template <int D, int NIN, class Swz>
+__device__ __forceinline__ void lane_offsets(uint32_t (&in)[NIN], int lane, int64_t tok, Swz swz)
+{
+    constexpr int KCH = D / 8, RPL = 64 / KCH;
+    const int lq = lane / KCH;
+#pragma unroll
+    for (int i = 0; i < NIN; ++i) in[i] = (uint32_t)lq * (uint32_t)(tok * 2) + (uint32_t)(((lane % KCH) ^ swz(i * RPL + lq)) * 16);
+}
+template <int D, bool NT, int NIN, class Swz>
+__device__ __forceinline__ void load_half(const unsigned char *bytes, int64_t tok, int key0, int n_keys, const uint32_t (&in)[NIN], int lane, Swz swz,
+                                          lds_byte *dst)
+{
+    constexpr int KCH = D / 8, ROWB = D * 2, RPL = 64 / KCH, LPT = 32 / RPL;   // chunks and bytes of a row, rows of a load, loads
+    if (key0 + 32 <= n_keys) {   // wavefront-uniform
+        const unsigned char *row = bytes + (int64_t)key0 * tok * 2;
+#pragma unroll
+        for (int it = 0; it < LPT; ++it, row += (int64_t)RPL * tok * 2) dma16_sbase<NT>(row, in[it % NIN], dst + it * RPL * ROWB);
+    } else {
+        const int lq = lane / KCH;
+#pragma unroll 1
+        for (int it = 0; it < LPT; ++it) {
+            const int row0 = min(key0 + it * RPL, n_keys - 1);
+            const int row = min(lq, n_keys - 1 - row0);   // steps back by whole rows where the cache ends
+            dma16_sbase<NT>(bytes + (int64_t)row0 * tok * 2,
+                            (uint32_t)row * (uint32_t)(tok * 2) + (uint32_t)(((lane % KCH) ^ swz(it * RPL + lq)) * 16), dst + it * RPL * ROWB);
+        }
+    }
+}
+
 // attn_rows_kernel: 32 packed (query, head) rows per block (GQA packing and transposed products as in
 // attn_mfma_kernel), which the wavefronts SHARE: each takes every NW-th 32-key sub-step of the block's key
 // run with its own softmax state, and the states are joined through LDS at the end.  The 256-row kernel would leave
@@ -29,12 +61,14 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
     constexpr int NKS = D / 16, NDB = D / 32, KCH = D / 8, ROWB = D * 2, HALFB = 32 * ROWB;
     constexpr int RPL = 64 / KCH;    // key rows filled by one wavefront-wide direct load
     constexpr int LPT = 32 / RPL;    // direct loads of a 32-key half
-    constexpr int KSWZ = (KCH < 16 ? KCH : 16) - 1;  // chunk c of key k sits at c ^ (k & KSWZ) (K), c ^ (4 * (k & 3) & VSWZ) (V)
-    constexpr int VSWZ = KCH - 1;
+    constexpr int KSWZ = (KCH < 16 ? KCH : 16) - 1, VSWZ = KCH - 1;
     constexpr int KD = (KSWZ + 1) / RPL > 1 ? (KSWZ + 1) / RPL : 1;  // loads after which the swizzle pattern of the rows repeats
     constexpr int VD = 4 / RPL > 1 ? 4 / RPL : 1;
     constexpr int JW = 2 * HALFB / 16;               // 16-byte slots of a wavefront's buffers: all its outputs at the end
     static_assert(NDB * 256 == JW, "a wavefront's outputs fill its own buffers");
+    // Chunk c of key `key` sits at position c ^ swz(key).
+    auto k_swz = [](int key) __attribute__((always_inline)) -> int { return key & KSWZ; };
+    auto v_swz = [](int key) __attribute__((always_inline)) -> int { return (4 * (key & 3)) & VSWZ; };
     __shared__ __align__(16) unsigned char smem[NW * 2 * HALFB];
     __shared__ float ml[2][NW][32];
 
@@ -69,36 +103,11 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
 
         const unsigned char *kbytes = reinterpret_cast<const unsigned char *>(static_cast<const bf16_t *>(p.k) + l * p.s_k.layer + hkv * p.s_k.head);
         const unsigned char *vbytes = reinterpret_cast<const unsigned char *>(static_cast<const bf16_t *>(p.v) + l * p.s_v.layer + hkv * p.s_v.head);
-        // Direct loads of 32 rows from key 32 * u on: a wavefront-uniform row pointer plus a per-lane offset that does
-        // not change from one sub-step to the next.  Rows past the cache end (last sub-step only) re-read the last
-        // row; they are always masked.
-        const int lq = lane / KCH;
         uint32_t k_in[KD], v_in[VD];
-#pragma unroll
-        for (int i = 0; i < KD; ++i)
-            k_in[i] = (uint32_t)lq * (uint32_t)(p.s_k.token * 2) + (uint32_t)(((lane % KCH) ^ ((i * RPL + lq) & KSWZ)) * 16);
-#pragma unroll
-        for (int i = 0; i < VD; ++i)
-            v_in[i] = (uint32_t)lq * (uint32_t)(p.s_v.token * 2) + (uint32_t)(((lane % KCH) ^ ((4 * ((i * RPL + lq) & 3)) & VSWZ)) * 16);
-        auto load_half = [&](const unsigned char *bytes, int64_t tok, int key0, auto &in, int mask, int mul, lds_byte *dst) __attribute__((always_inline)) {
-            constexpr int NIN = sizeof(in) / sizeof(in[0]);
-            if (key0 + 32 <= p.N) {   // wavefront-uniform
-                const unsigned char *row = bytes + (int64_t)key0 * tok * 2;
-#pragma unroll
-                for (int it = 0; it < LPT; ++it, row += (int64_t)RPL * tok * 2) dma16_sbase<NT>(row, in[it % NIN], dst + it * RPL * ROWB);
-            } else {
-#pragma unroll 1
-                for (int it = 0; it < LPT; ++it) {
-                    const int row0 = min(key0 + it * RPL, p.N - 1);
-                    const int row = min(lq, p.N - 1 - row0);   // steps back by whole rows where the cache ends
-                    dma16_sbase<NT>(bytes + (int64_t)row0 * tok * 2,
-                                    (uint32_t)row * (uint32_t)(tok * 2) + (uint32_t)(((lane % KCH) ^ ((mul * (it * RPL + lq)) & mask)) * 16),
-                                    dst + it * RPL * ROWB);
-                }
-            }
-        };
-        auto load_k = [&](int u) __attribute__((always_inline)) { load_half(kbytes, p.s_k.token, 32 * u, k_in, KSWZ, 1, kbuf); };
-        auto load_v = [&](int u) __attribute__((always_inline)) { load_half(vbytes, p.s_v.token, 32 * u, v_in, VSWZ & 12, 4, vbuf); };
+        lane_offsets<D>(k_in, lane, p.s_k.token, k_swz);
+        lane_offsets<D>(v_in, lane, p.s_v.token, v_swz);
+        auto load_k = [&](int u) __attribute__((always_inline)) { load_half<D, NT>(kbytes, p.s_k.token, 32 * u, p.N, k_in, lane, k_swz, kbuf); };
+        auto load_v = [&](int u) __attribute__((always_inline)) { load_half<D, NT>(vbytes, p.s_v.token, 32 * u, p.N, v_in, lane, v_swz, vbuf); };
         int u = u0 + wave;
         bf16x8 qf[NKS];
         const bf16_t *qrow = static_cast<const bf16_t *>(p.q) + l * p.s_q.layer + (int64_t)hq * p.s_q.head + (int64_t)qi * p.s_q.token;
@@ -111,14 +120,14 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
 
         int k_off[NKS];
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) k_off[ks] = n * ROWB + (((2 * ks + hg) ^ (n & KSWZ)) * 16);
+        for (int ks = 0; ks < NKS; ++ks) k_off[ks] = n * ROWB + (((2 * ks + hg) ^ k_swz(n)) * 16);
         int v_off[NDB];
         {
             const int i16 = lane & 15, gi = (lane >> 4) & 1, row = 4 * hg + (i16 >> 2);
 #pragma unroll
             for (int db = 0; db < NDB; ++db) {
                 const int col = 32 * db + 16 * gi + 4 * (i16 & 3);
-                v_off[db] = row * ROWB + ((col >> 3) ^ ((4 * (row & 3)) & VSWZ)) * 16 + (col & 7) * 2;
+                v_off[db] = row * ROWB + ((col >> 3) ^ v_swz(row)) * 16 + (col & 7) * 2;
             }
         }
 
@@ -260,38 +269,6 @@ __global__ __launch_bounds__(64 * rows_waves(D), D == 256 ? 1 : 2) void attn_row
         __syncthreads();   // the joined states have been read: LDS becomes the next item's buffers
         item += x_blocks;
     } while (item < x_count);
-}
-
-// Direct loads of 32 rows from key0 on into a wavefront's buffer, chunk c of row `key` at position c ^ swz(key): a wavefront-uniform row
-// pointer plus per-lane offsets that do not change from one sub-step to the next (lane_offsets(); the pattern repeats after
-// NIN loads).  Rows past the cache end (last sub-step only) re-read the last row; they are always masked.
-template <int D, int NIN, class Swz>
-__device__ __forceinline__ void lane_offsets(uint32_t (&in)[NIN], int lane, int64_t tok, Swz swz)
-{
-    constexpr int KCH = D / 8, RPL = 64 / KCH;
-    const int lq = lane / KCH;
-#pragma unroll
-    for (int i = 0; i < NIN; ++i) in[i] = (uint32_t)lq * (uint32_t)(tok * 2) + (uint32_t)(((lane % KCH) ^ swz(i * RPL + lq)) * 16);
-}
-template <int D, bool NT, int NIN, class Swz>
-__device__ __forceinline__ void load_half(const unsigned char *bytes, int64_t tok, int key0, int n_keys, const uint32_t (&in)[NIN], int lane, Swz swz,
-                                          lds_byte *dst)
-{
-    constexpr int KCH = D / 8, ROWB = D * 2, RPL = 64 / KCH, LPT = 32 / RPL;   // chunks and bytes of a row, rows of a load, loads
-    if (key0 + 32 <= n_keys) {   // wavefront-uniform
-        const unsigned char *row = bytes + (int64_t)key0 * tok * 2;
-#pragma unroll
-        for (int it = 0; it < LPT; ++it, row += (int64_t)RPL * tok * 2) dma16_sbase<NT>(row, in[it % NIN], dst + it * RPL * ROWB);
-    } else {
-        const int lq = lane / KCH;
-#pragma unroll 1
-        for (int it = 0; it < LPT; ++it) {
-            const int row0 = min(key0 + it * RPL, n_keys - 1);
-            const int row = min(lq, n_keys - 1 - row0);   // steps back by whole rows where the cache ends
-            dma16_sbase<NT>(bytes + (int64_t)row0 * tok * 2,
-                            (uint32_t)row * (uint32_t)(tok * 2) + (uint32_t)(((lane % KCH) ^ swz(it * RPL + lq)) * 16), dst + it * RPL * ROWB);
-        }
-    }
 }
 
 // attn_rows_kernel16: the same split of the keys for 16 packed rows per block, on 16x16x32 MFMAs in the operand layout of attn_mfma_kernel.  What

@@ -196,8 +196,8 @@ def _align_all(w, model, agent, gran, scratches, stream):
     depend on each other, scratch that segments share); nothing has been launched then."""
     segs = agent.segments
     lens, pools = [s.base_k.shape[2] for s in segs], [len(s.anchor_k) for s in segs]
-    if min(pools) == 0:
-        return False
+    if min(pools) == 0 or any(len(s.anchor_dk) != n or len(s.anchor_dv) != n for s, n in zip(segs, pools)):
+        return False   # (matched, but nothing to add: the single update takes that)
     if scratches is not None:
         scratches = _whole_scratch(scratches, len(segs))
         if scratches is None:

@@ -191,6 +191,17 @@ def test_what_is_refused_all_the_same(step):
         assert lib.error == -4 and lib.calls == before and lib.attempts == [(name, [0, 1, 2, 3])]
 
 
+def test_pools_without_deviations(step):
+    """A segment that is matched, but has no deviations to add, is rotated only: the single update accepts that."""
+    def bare(agent):
+        agent.segments[1].anchor_dk = agent.segments[1].anchor_dv = []
+    def fewer(agent):      # (refused by the single update)
+        agent.segments[2].anchor_dv = agent.segments[2].anchor_dv[:3]
+    for scratches in (None, plain):
+        assert step(W, bare, scratches).calls == each_alone(4)
+        assert step(W, fewer, scratches).calls == each_alone(4)
+
+
 @pytest.mark.parametrize("kind", [tuple, collections.deque, lambda s: dict(enumerate(s)), lambda s: list(s) + list(s)])
 def test_scratch_in_any_container(step, kind):
     lib = step(W, scratches=lambda agent: kind(plain(agent)))

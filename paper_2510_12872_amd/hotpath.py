@@ -28,16 +28,17 @@ JOINT_WORKSPACE = 16 << 20
 class Scratch:
     """Reusable device buffers for the weight step (so a timed loop allocates nothing)."""
 
-    def __init__(self, model, seg_len, n_anchors, gran, device):
+    def __init__(self, model, seg_len, n_anchors, gran, device, joint=True):
         n = kv.kvcomm_weight_slots(model, seg_len, gran)
         self.weights = torch.empty((n, n_anchors), dtype=torch.float32, device=device)
         self.nearest = torch.empty((n,), dtype=torch.int32, device=device)
         self.selected = torch.empty((n_anchors,), dtype=torch.int32, device=device)
         need = kv.kvcomm_anchor_weights_workspace(model, seg_len, n_anchors, gran)
-        together = max(1, min(kv.MAX_BATCH, kv.MAX_ANCHORS // max(1, n_anchors)))   # a launch of reuse_agent takes so many like it
-        joint = kv.kvcomm_anchor_weights_batch_workspace(model, [seg_len] * together, [n_anchors] * together, gran)
-        if joint <= JOINT_WORKSPACE:
-            need = max(need, joint)
+        together = max(1, min(kv.MAX_BATCH, kv.MAX_ANCHORS // max(1, n_anchors))) if joint else 1   # a launch of reuse_agent takes so many like it
+        if together > 1:
+            all_need = kv.kvcomm_anchor_weights_batch_workspace(model, [seg_len] * together, [n_anchors] * together, gran)
+            if all_need <= JOINT_WORKSPACE:
+                need = max(need, all_need)
         self.workspace = torch.empty((max(need, 256),), dtype=torch.uint8, device=device)
 
 
@@ -45,7 +46,7 @@ def align_segment(model, seg, out_k, out_v, temperature=1.0, gran=kv.W_TOKEN, sc
     """Anchor weights, then aligned K/V of one segment written into out_k / out_v."""
     if scratch is None:
         with kv.on_stream(stream):
-            scratch = Scratch(model, seg.base_k.shape[2], len(seg.anchor_k), gran, seg.base_k.device)
+            scratch = Scratch(model, seg.base_k.shape[2], len(seg.anchor_k), gran, seg.base_k.device, joint=False)
     kv.kvcomm_anchor_weights(model, seg.base_k, seg.anchor_k, seg.anchor_len, temperature, gran,
                              scratch.weights, scratch.nearest, scratch.selected, scratch.workspace, stream)
     kv.kvcomm_align_kv(model, seg.base_k, seg.base_v, seg.anchor_dk, seg.anchor_dv, scratch.weights,

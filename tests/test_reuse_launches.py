@@ -242,3 +242,15 @@ def test_scratch_that_segments_share(step):
         return sc
     assert step(W, scratches=in_cache).calls == each_alone(4)
     assert step(W, scratches=lambda agent: [plain(agent)[0]] * 4).calls == each_alone(4)
+
+
+def test_scratch_of_one_segment_holds_one(monkeypatch):
+    """What align_segment makes for itself is for that segment only; a Scratch that is kept also holds a launch of several like it."""
+    kv.load_library()
+    for name in ("kvcomm_anchor_weights", "kvcomm_align_kv"):
+        monkeypatch.setattr(binding, name, lambda *a: None)
+    seg = workloads.make_agent(W, 0).segments[0]
+    one = kv.kvcomm_anchor_weights_workspace(M, W.seg_len, W.n_anchors)
+    assert hotpath.align_segment(M, seg, None, None).workspace.numel() == max(one, 256)
+    four = kv.kvcomm_anchor_weights_batch_workspace(M, [W.seg_len] * 4, [W.n_anchors] * 4)
+    assert hotpath.Scratch(M, W.seg_len, W.n_anchors, kv.W_TOKEN, "cpu").workspace.numel() == max(four, 256) > one

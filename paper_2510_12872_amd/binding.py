@@ -403,15 +403,15 @@ def _attn_scratch(need, device, stream):
 
 
 def apart(own, groups, each=()):
-    """Do the tensors of the lists `groups` come nowhere near a byte of the tensors `own`, and those of `each` not near each other?  (By the
-    range from their first to their last element.)"""
+    """Do the tensors of the lists `groups` and of `each` come nowhere near a byte of the tensors `own`, and those of `each` not near each
+    other?  (By the range from their first to their last element.)"""
     load_library()
     answer = _native.apart(own, groups, each)
     if answer is None:
         def span(t):
             return t.data_ptr(), t.data_ptr() + (1 + sum(max(0, n - 1) * s for n, s in zip(t.shape, t.stride()))) * t.element_size()
         meet = lambda a, b: a[0] < b[1] and b[0] < a[1]
-        own, others, each = [span(t) for t in own], [span(t) for g in groups for t in g], [span(t) for t in each]
+        own, others, each = [span(t) for t in own], [span(t) for g in (*groups, each) for t in g], [span(t) for t in each]
         answer = not (any(meet(a, b) for a in own for b in others) or any(meet(a, b) for i, a in enumerate(each) for b in each[:i]))
     return bool(answer)
 

@@ -520,8 +520,8 @@ PyObject *quantize_deltas(PyObject *, PyObject *const *args, Py_ssize_t n)
     });
 }
 
-// (tensors a, lists of tensors b, tensors c): 1 if no tensor of b comes near a byte of a tensor of a and those of c not near each
-// other, else 0
+// (tensors a, lists of tensors b, tensors c): 1 if no tensor of b or c comes near a byte of a tensor of a and those of c not near
+// each other, else 0
 PyObject *apart(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     struct Range {
@@ -548,7 +548,7 @@ PyObject *apart(PyObject *, PyObject *const *args, Py_ssize_t n)
         }
         for (int i = 0; i < each.n; ++i) {
             r.emplace_back(as_tensor(each.p[i]));
-            if (meets(r.back(), own.n, r.size() - 1)) return 0LL;
+            if (meets(r.back(), 0, r.size() - 1)) return 0LL;
         }
         return 1LL;
     });

@@ -94,16 +94,14 @@ def _match_together(w, model, agent, idx, outs, workspace, gran, stream):
         for j in idx], w.temperature, gran, workspace=workspace, stream=stream)
 
 
-def _update_together(w, model, agent, idx, outs, gran, stream):
-    """One batched call for their update."""
-    segs, jobs = agent.segments, []
-    for j in idx:
-        p0, S = w.seg_offset(j), segs[j].base_k.shape[2]
-        jobs.append(dict(base_k=segs[j].base_k, base_v=segs[j].base_v, anchor_dk=segs[j].anchor_dk,
-                         anchor_dv=segs[j].anchor_dv, anchor_len=segs[j].anchor_len, weights=outs[j][0],
-                         delta_pos=segs[j].delta_pos, anchor_delta_pos=segs[j].anchor_delta_pos,
-                         out_k=_slot(agent.cache_k, p0, S), out_v=_slot(agent.cache_v, p0, S)))
-    kv.kvcomm_align_kv_batch(model, jobs, gran, stream)
+def _update_together(model, agent, idx, outs, at, gran, stream):
+    """One batched call for their update; at[j]: first row and rows of segment j's slot."""
+    at = [at[j] for j in idx]
+    kv.kvcomm_align_kv_batch(model, [dict(
+        base_k=s.base_k, base_v=s.base_v, anchor_dk=s.anchor_dk, anchor_dv=s.anchor_dv, anchor_len=s.anchor_len, weights=outs[j][0],
+        delta_pos=s.delta_pos, anchor_delta_pos=s.anchor_delta_pos, out_k=out_k, out_v=out_v)
+        for j, s, out_k, out_v in zip(idx, [agent.segments[j] for j in idx], _slots(agent.cache_k, at), _slots(agent.cache_v, at))],
+        gran, stream)
 
 
 def align_agent_batched(w, model, agent, gran=kv.W_TOKEN, scratch=None, stream=None):
@@ -115,9 +113,10 @@ def align_agent_batched(w, model, agent, gran=kv.W_TOKEN, scratch=None, stream=N
             scratch = AgentScratch(model, [s.base_k.shape[2] for s in segs], [len(s.anchor_k) for s in segs], gran,
                                    segs[0].base_k.device)
     outs = list(zip(scratch.weights, scratch.nearest, scratch.selected))
+    at = [(w.seg_offset(j), s.base_k.shape[2]) for j, s in enumerate(segs)]
     for idx in launch_chunks([len(s.anchor_k) for s in segs]):
         _match_together(w, model, agent, idx, outs, scratch.workspace, gran, stream)
-        _update_together(w, model, agent, idx, outs, gran, stream)
+        _update_together(model, agent, idx, outs, at, gran, stream)
     return scratch
 
 
@@ -126,20 +125,20 @@ def _slot(cache, p0, S):
     return cache.narrow(2, p0, S) if 0 <= p0 <= cache.shape[2] - S else cache[:, :, p0:p0 + S]   # (narrow: half the time of an index)
 
 
-def _independent(w, agent, lens, scratches):
-    """May these segments be matched together and then updated together?  Their slots, what the weights go to and the workspaces lie apart,
-    and nothing else that is used lies in the agent's cache: a key or a delta in a slot that an earlier segment's update writes is read after
-    that update."""
-    end = 0
-    for j, S in enumerate(lens):
-        p0 = w.seg_offset(j)
-        if p0 < end:
-            return False
+def _slots(cache, at):
+    """Rows [p0, p0 + S) of a cache for each (p0, S): one call for all where they follow each other (half the time of one each)."""
+    sizes, slots, end = [], [], 0
+    for p0, S in at:
+        if p0 != end:
+            sizes.append(p0 - end)
+        slots.append(len(sizes))
+        sizes.append(S)
         end = p0 + S
-    own = [t for s in scratches for t in (s.weights, s.nearest, s.selected)]
-    own += {s.workspace.data_ptr(): s.workspace for s in scratches}.values()   # (one workspace may serve all)
-    used = [g for s in agent.segments for g in ((s.base_k, s.base_v), s.anchor_k, s.anchor_dk, s.anchor_dv)]
-    return end <= min(agent.cache_k.shape[2], agent.cache_v.shape[2]) and kv.apart((agent.cache_k, agent.cache_v), used + [own] if own else used, own)
+    sizes.append(cache.shape[2] - end)
+    if min(sizes) < 0:
+        return [_slot(cache, p0, S) for p0, S in at]
+    parts = cache.split_with_sizes(sizes, 2)
+    return [parts[i] for i in slots]
 
 
 def _rotations(seg):
@@ -156,60 +155,91 @@ def _joint_need(model, lens, pools, gran):
     return kv.kvcomm_anchor_weights_batch_workspace(model, lens, pools, gran)
 
 
-def _joint_runs(model, segs, lens, pools, gran, scratches):
+def _joint_runs(model, segs, lens, pools, gran, room):
     """Cuts the segments of an agent into runs of neighbours that the batched calls take together, known before anything is launched: the
     limits of launch_chunks(), anchors of one layout, the rotations of an update (four pools of 16 anchors, all recorded elsewhere, need 68
-    and go as three segments and one), and the largest workspace among the segments' own scratch where that is given."""
+    and go as three segments and one), and the largest workspace among the segments' own scratch where that is given (room: its bytes)."""
     layouts = [(s.anchor_k[0].stride(), s.anchor_dk[0].stride()) for s in segs]
-    rotations = [1 if s.anchor_delta_pos is None else 1 + len(s.anchor_delta_pos) for s in segs]
-    if sum(rotations) > kv.MAX_ROTATIONS:
-        rotations = [_rotations(s) for s in segs]
-    runs, j = [], 0
-    while j < len(segs):
+    rotations = [_rotations(s) for s in segs]
+    runs, j, n = [], 0, len(segs)
+    while j < n:
         k, anchors, rots = j + 1, pools[j], rotations[j]
-        while (k < len(segs) and k - j < kv.MAX_BATCH and layouts[k] == layouts[j] and anchors + pools[k] <= kv.MAX_ANCHORS
-               and rots + rotations[k] <= kv.MAX_ROTATIONS):
-            anchors, rots, k = anchors + pools[k], rots + rotations[k], k + 1
-        while scratches is not None and k - j > 1 and (_joint_need(model, tuple(lens[j:k]), tuple(pools[j:k]), gran)
-                                                       > max(_workspace_bytes(scratches[i]) for i in range(j, k))):
+        while k < n and k - j < kv.MAX_BATCH and layouts[k] == layouts[j]:
+            anchors, rots = anchors + pools[k], rots + rotations[k]
+            if anchors > kv.MAX_ANCHORS or rots > kv.MAX_ROTATIONS:
+                break
+            k += 1
+        while room is not None and k - j > 1 and _joint_need(model, tuple(lens[j:k]), tuple(pools[j:k]), gran) > max(room[j:k]):
             k -= 1
-        runs.append(list(range(j, k)))
+        runs.append(range(j, k))
         j = k
     return runs
 
 
-def _workspace_bytes(scratch):
-    return scratch.workspace.numel() * scratch.workspace.element_size()
-
-
 def _whole_scratch(scratches, n):
-    """The Scratch of each of n segments as a list; None where one is missing or lacks something (the single calls make that, or refuse it)."""
+    """The Scratch of each of n segments: itself, its (weights, nearest, selected), its workspace's bytes, and all their tensors (a workspace that
+    serves several once).  None where one is missing or lacks something (the single calls make that, or refuse it)."""
+    tensor = torch.Tensor
+    own, outs, room, tensors, spaces = [], [], [], [], {}
     try:
-        own = [scratches[j] for j in range(n)]
+        for j in range(n):
+            s = scratches[j]
+            if not isinstance(s, Scratch):
+                return None
+            out = weights, nearest, selected = s.weights, s.nearest, s.selected
+            space = s.workspace
+            if not (isinstance(weights, tensor) and isinstance(nearest, tensor) and isinstance(selected, tensor) and isinstance(space, tensor)):
+                return None
+            own.append(s)
+            outs.append(out)
+            room.append(space.nbytes)
+            tensors += out
+            spaces[space.data_ptr()] = space
     except (IndexError, KeyError):
         return None
-    return own if all(isinstance(s, Scratch) and isinstance(s.weights, torch.Tensor) and isinstance(s.nearest, torch.Tensor) and
-                      isinstance(s.selected, torch.Tensor) and isinstance(s.workspace, torch.Tensor) for s in own) else None
+    tensors += spaces.values()
+    return own, outs, room, tensors
 
 
 def _align_all(w, model, agent, gran, scratches, stream):
-    """Aligns the segments of an agent, those that may share a launch in one launch per step.  Returns False where none do (segments that
-    depend on each other, scratch that segments share); nothing has been launched then."""
-    segs = agent.segments
-    lens, pools = [s.base_k.shape[2] for s in segs], [len(s.anchor_k) for s in segs]
-    if min(pools) == 0 or any(len(s.anchor_dk) != n or len(s.anchor_dv) != n for s, n in zip(segs, pools)):
-        return False   # (matched, but nothing to add: the single update takes that)
+    """Aligns the segments of an agent, those that may share a launch in one launch per step.  Returns False where none do; nothing has been launched
+    then.  Segments may be matched together and then updated together where their slots, what the weights go to and the workspaces lie
+    apart, and nothing else that is used lies in the agent's cache: a key or a delta in a slot that an earlier segment's update writes
+    is read after that update."""
+    segs, cache_k, cache_v = agent.segments, agent.cache_k, agent.cache_v
+    n, outs, room, own, used = len(segs), None, None, (), []
     if scratches is not None:
-        scratches = _whole_scratch(scratches, len(segs))
-        if scratches is None:
+        whole = _whole_scratch(scratches, n)
+        if whole is None:
             return False
-    if not _independent(w, agent, lens, scratches or ()):
+        scratches, outs, room, own = whole
+    at, lens, pools, end, rotations, alike, layout = [], [], [], 0, 0, n <= kv.MAX_BATCH, None
+    for j, s in enumerate(segs):
+        base_k, pool, dk, dv, moved = s.base_k, s.anchor_k, s.anchor_dk, s.anchor_dv, s.anchor_delta_pos
+        S, A, p0 = base_k.shape[2], len(pool), w.seg_offset(j)
+        if p0 < end or A == 0 or len(dk) != A or len(dv) != A:   # (matched, but nothing to add: the single update takes that)
+            return False
+        end = p0 + S
+        at.append((p0, S))
+        lens.append(S)
+        pools.append(A)
+        used += ((base_k, s.base_v), pool, dk, dv)
+        rotations += 1 if moved is None else 1 + len(moved)   # at most
+        strides = pool[0].stride(), dk[0].stride()
+        if strides != layout:
+            alike, layout = alike and j == 0, strides
+    if end > cache_k.shape[2] or end > cache_v.shape[2] or not kv.apart((cache_k, cache_v), used, own):
         return False
-    for idx in _joint_runs(model, segs, lens, pools, gran, scratches):
+    if (alike and rotations <= kv.MAX_ROTATIONS and sum(pools) <= kv.MAX_ANCHORS and
+            (room is None or _joint_need(model, tuple(lens), tuple(pools), gran) <= max(room))):
+        runs = (range(n),)
+    else:
+        runs = _joint_runs(model, segs, lens, pools, gran, room)
+    for idx in runs:
         if len(idx) == 1:
             _align_one(w, model, agent, idx[0], gran, scratches, stream)
         else:
-            _align_run(w, model, agent, idx, gran, scratches, stream)
+            _align_run(w, model, agent, idx, at, gran, scratches, outs, room, stream)
     return True
 
 
@@ -218,32 +248,31 @@ def _refused(e):
     return e.status in (kv.EINVAL, kv.EUNSUPPORTED, kv.EWORKSPACE)
 
 
-def _align_run(w, model, agent, idx, gran, scratches, stream):
+def _align_run(w, model, agent, idx, at, gran, scratches, outs, room, stream):
     """Aligns the segments `idx` together, or, where that is refused, one after the other: so they may be accepted, or are refused as
-    they always were."""
-    segs, outs = [agent.segments[j] for j in idx], None
+    they always were.  outs: weights, nearest and selected of every segment, room: bytes of its workspace; None where these are to be made."""
+    matched = False
     try:
         if scratches is None:
+            segs = [agent.segments[j] for j in idx]
             with kv.on_stream(stream):
-                scratch = AgentScratch(model, [s.base_k.shape[2] for s in segs], [len(s.anchor_k) for s in segs], gran, segs[0].base_k.device)
-            given, workspace = zip(scratch.weights, scratch.nearest, scratch.selected), scratch.workspace
+                made = AgentScratch(model, [s.base_k.shape[2] for s in segs], [len(s.anchor_k) for s in segs], gran, segs[0].base_k.device)
+            outs, workspace = dict(zip(idx, zip(made.weights, made.nearest, made.selected))), made.workspace
         else:
-            given = [(scratches[j].weights, scratches[j].nearest, scratches[j].selected) for j in idx]
-            workspace = max((scratches[j] for j in idx), key=_workspace_bytes).workspace
-        given = dict(zip(idx, given))
-        _match_together(w, model, agent, idx, given, workspace, gran, stream)
-        outs = given
-        return _update_together(w, model, agent, idx, outs, gran, stream)
+            workspace = scratches[max(idx, key=room.__getitem__)].workspace
+        _match_together(w, model, agent, idx, outs, workspace, gran, stream)
+        matched = True
+        return _update_together(model, agent, idx, outs, at, gran, stream)
     except torch.OutOfMemoryError:   # (only the scratch allocates)
         pass
     except kv.KVCommError as e:
         if not _refused(e):
             raise
     for j in idx:
-        if outs is None:
-            _align_one(w, model, agent, j, gran, scratches, stream)
-        else:   # matched, but not updated
+        if matched:
             _update_one(w, model, agent, j, outs[j][0], gran, stream)
+        else:
+            _align_one(w, model, agent, j, gran, scratches, stream)
 
 
 def _update_one(w, model, agent, j, weights, gran, stream):

@@ -23,7 +23,7 @@ def _bytes(t):
 
 def _want(own, groups, each):
     meet = lambda a, b: max(_bytes(a).start, _bytes(b).start) < min(_bytes(a).stop, _bytes(b).stop)
-    return not (any(meet(a, b) for a in own for g in groups for b in g) or any(meet(a, b) for a, b in itertools.combinations(each, 2)))
+    return not (any(meet(a, b) for a in own for g in (*groups, each) for b in g) or any(meet(a, b) for a, b in itertools.combinations(each, 2)))
 
 
 def _forms(dev):

@@ -254,3 +254,14 @@ def test_scratch_of_one_segment_holds_one(monkeypatch):
     assert hotpath.align_segment(M, seg, None, None).workspace.numel() == max(one, 256)
     four = kv.kvcomm_anchor_weights_batch_workspace(M, [W.seg_len] * 4, [W.n_anchors] * 4)
     assert hotpath.Scratch(M, W.seg_len, W.n_anchors, kv.W_TOKEN, "cpu").workspace.numel() == max(four, 256) > one
+
+
+@pytest.mark.parametrize("at", [[(0, 3), (3, 4), (7, 3)], [(2, 3), (6, 1), (7, 2)], [(4, 6)], [(5, 2), (1, 3)], [(1, 4), (4, 2)], [(7, 5)], [(3, 0), (3, 2)], [(10, 2)], [(-2, 1)]])
+def test_slots_of_a_cache(at):
+    """The rows that slices give, also of segments with gaps between them, out of order, on each other or past the end."""
+    cache = torch.arange(2 * 3 * 10 * 4).view(2, 3, 10, 4)
+    for c in (cache, cache.transpose(0, 1), cache[:, :, :, ::2]):
+        for got, (p0, S) in zip(hotpath._slots(c, at), at):
+            want = c[:, :, p0:p0 + S]
+            assert got.shape == want.shape and got.stride() == want.stride() and torch.equal(got, want)
+            assert got.numel() == 0 or got.data_ptr() == want.data_ptr()

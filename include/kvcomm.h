@@ -251,8 +251,8 @@ int kvcomm_suffix_attn(const kvcomm_model *model, kvcomm_tensor q,
 
 /* The same attention (workflow step 4), same arguments, results bit-identical to kvcomm_suffix_attn without a
  * workspace (the _ws form: with the same workspace), launched as at most `max_blocks` thread blocks that each walk
- * a fixed share of the work items.  A block of the bf16 kernels fills a compute unit, so the launch occupies
- * max_blocks of the GPU's 256 compute units and leaves the others to kernels that run beside it on another stream:
+ * a fixed share of the work items.  A block of the bf16 kernels fills a compute unit (few query rows at D = 64: half of
+ * one), so the launch occupies at most max_blocks of the GPU's 256 compute units and leaves the others to kernels that run beside it on another stream:
  * the memory-bound alignment of the next agent next to the matrix-core-bound attention of the current one.  (Under
  * the chip's power limit the attention loses less than its share of compute units: measured 0.85-0.86 ms on 160 of 256
  * against 0.67-0.70 ms on all of them.)  max_blocks is spread over the 8 XCDs in launch order; values of at least the

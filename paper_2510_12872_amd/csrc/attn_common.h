@@ -21,10 +21,10 @@ struct AttnParams {
     float scale_log2;  // scale * log2(e)
     // Split launches: the keys of a row tile are cut into n_splits runs of 64-key tiles (split_bound below) and
     // every (row group, split) leaves its unnormalised output, reference and row sum here.
-    float *part_o;     // [group][split][D / 4 slots of 4 channels x 32 rows], see part_slot
-    float *part_ml;    // [group][split][2][32]: reference m (raw score units), row sum
+    float *part_o;     // [group][split][D / 4 slots of 4 channels x rows of a group], see part_slot
+    float *part_ml;    // [group][split][2][rows of a group]: reference m (raw score units), row sum
     int32_t n_splits;  // 1: results go straight to `out`
-    int32_t groups_per_tile;  // 32-row groups of a row tile (= wavefronts that own rows)
+    int32_t groups_per_tile;  // groups of a row tile: bf16, of 32 rows (= wavefronts that own rows; one of 16 in a tile of 16 rows); fp32, of 16
     divisor_t by_G, by_Hkv, by_row_tiles, by_splits, by_groups;   // set_divisors()
 };
 __device__ __forceinline__ void await_attn_args(const AttnParams &p)
@@ -115,7 +115,7 @@ __host__ __device__ __forceinline__ int split_bound(int s, int n_splits, int uni
     return b < first_hidden ? b : (s == 0 ? 0 : units);
 }
 
-// Output accumulators of a 32-row group travel as 16-byte slots: slot (c4, n) = channels 4 * c4 ... + 3 of row n, rows
+// Output accumulators of a 32-row group (attn_rows_kernel16: of 16, likewise) travel as 16-byte slots: slot (c4, n) = channels 4 * c4 ... + 3 of row n, rows
 // fastest, as the MFMAs leave them (256- and 512-byte runs).
 __device__ __forceinline__ int part_slot(int c4, int n) { return c4 * 32 + n; }
 

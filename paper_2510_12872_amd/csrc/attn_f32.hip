@@ -81,10 +81,10 @@ __global__ __launch_bounds__(256) void attn_f32_row_kernel(const AttnParams p)
 // 16 * j + 4 * g ... + 3), of V four consecutive channels of one key (row m of accumulator (t, c) stands for channel 64 * t + 4 * m + c),
 // P from the score registers.
 // What bounds it: at large sizes matrix cores (fp32 MFMA, 1/16 of the bf16 rate), at small ones the length of a wavefront's chain.  So 16 rows
-// where all blocks run at once (attn_f32_groups()): half the products of a sub-step and twice the blocks; else two groups of 16 that share every
+// up to a block per compute unit (attn_f32_groups()): half the products of a sub-step and twice the blocks; else two groups of 16 that share every
 // K and V operand.  us before (32 rows and 32 keys on 32x32x2 MFMAs, K loads of 64 lines) and now: 2 layers x 4 heads x 64 rows, 224
 // keys, D = 64 10.3 -> 7.7; 4 x 8, G = 8, one token, 1025 keys, D = 128 54.8 -> 29.6, 256 96 -> 58; 4 x 8, G = 4, Tq 128, 1152 keys, D = 64 60.5 -> 55.5,
-// 128 118 -> 105, 256 195 -> 193; one layer, Tq 512, 3072 keys, D = 128 272 -> 243 (97 TFLOP/s).
+// 128 118 -> 105, 256 195 -> 193; one layer, Tq 512, 3072 keys, D = 128 272 -> 243 (97 TFLOP/s; back to back, as all of these).
 template <int D, int RH>
 __device__ __forceinline__ void attn_f32_item(const AttnParams &p, int item)   // item: one row tile of a (layer, kv head)
 {

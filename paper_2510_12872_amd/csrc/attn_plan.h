@@ -132,7 +132,8 @@ static inline size_t attn_workspace(const kvcomm_model &m, const AttnPlan &pl)
     return pl.n_splits > 1 ? attn_parts(m, pl) * sizeof(float) * (size_t)pl.group_rows * ((size_t)m.head_dim + 2) : 0;
 }
 
-// Groups of 16 packed rows of an fp32 block: one as long as all blocks run at once, two above (they share what they load).  us with
+// Groups of 16 packed rows of an fp32 block: one up to a block per compute unit, two above (they share what they load; the line is where the
+// measured times cross, also at D = 64, where two blocks fit a unit).  us with
 // one / two, 4 layers x 8 heads, G = 4: D = 128, 1056 keys, Tq 32 (256 blocks of one group) 44.5 / 49.8, 1088 keys, Tq 64 (512) 58.6 / 55.6; one
 // layer, 1152 keys, Tq 128 (256) 34.8 / 52.5; 2 layers, 400 keys, Tq 100 (400) 26.0 / 25.4; D = 64, 540 keys, Tq 40 (320) 21.0 / 18.7; D = 256,
 // 1056 keys, Tq 32 (256) 84 / 90, 1088 keys, Tq 64 (512) 118 / 97; but 128 keys, Tq 128, 4 layers x 4 heads, G = 8 (1024) 23.2 / 24.3.

@@ -1,4 +1,4 @@
-"""fp32 suffix attention: both kernels (up to 8 keys, 16 at D = 256, and beyond) and both row tiles of the second one (16 rows where all blocks run at once, 32
+"""fp32 suffix attention: both kernels (up to 8 keys, 16 at D = 256, and beyond) and both row tiles of the second one (16 rows up to a block per compute unit, 32
 above), at the edges of the 16-key sub-steps, the eight wavefronts and the 16-row groups.  Against the float64 oracle, 1e-5 as for
 every fp32 output; the confined form bit for bit; values that are not finite at the causal edge reach the queries that see them."""
 import pytest

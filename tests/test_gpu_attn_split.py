@@ -168,7 +168,7 @@ def test_workspace_query():
                 assert q(_model(L, 8, 8, 256), n_ctx, tq) <= 2 * 256 * 256 * 16 * 4 * (256 + 2)
 
 
-# fp32: both kernels (up to 64 keys and beyond), edges of the 32-key sub-steps and 32-row groups, every head dimension
+# fp32: both kernels (up to 8 keys, 16 at D = 256, and beyond), around the 16-key sub-steps and the tiles of 16 and 32 rows, every head dimension
 F32_SHAPES = [(1, 1, 1, 64, 0, 1), (2, 2, 2, 128, 60, 4), (2, 2, 2, 128, 60, 5), (1, 2, 4, 64, 95, 8), (1, 2, 3, 256, 96, 11),
               (1, 1, 8, 256, 300, 33), (2, 1, 1, 64, 1000, 65), (1, 2, 8, 128, 0, 70)]
 

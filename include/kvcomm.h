@@ -251,14 +251,14 @@ int kvcomm_suffix_attn(const kvcomm_model *model, kvcomm_tensor q,
 
 /* The same attention (workflow step 4), same arguments, results bit-identical to kvcomm_suffix_attn without a
  * workspace (the _ws form: with the same workspace), launched as at most `max_blocks` thread blocks that each walk
- * a fixed share of the work items.  A block of the bf16 kernels fills a compute unit (few query rows at D = 64: half of
- * one), so the launch occupies at most max_blocks of the GPU's 256 compute units and leaves the others to kernels that run beside it on another stream:
- * the memory-bound alignment of the next agent next to the matrix-core-bound attention of the current one.  (Under
- * the chip's power limit the attention loses less than its share of compute units: measured 0.85-0.86 ms on 160 of 256
- * against 0.67-0.70 ms on all of them.)  max_blocks is spread over the 8 XCDs in launch order; values of at least the
- * number of work items give the plain launch.  The same holds for f32 tensors; f32 caches of up to 16 tokens may ignore
- * max_blocks (their kernel is small-block and never fills a compute unit), and so does the kernel that joins the
- * partial results of a split launch.
+ * a fixed share of the work items.  A block of the bf16 kernels fills a compute unit (few query rows at D = 64:
+ * half of one), so the launch occupies at most max_blocks of the GPU's 256 compute units and leaves the others to
+ * kernels that run beside it on another stream: the memory-bound alignment of the next agent next to the
+ * matrix-core-bound attention of the current one.  (Under the chip's power limit the attention loses less than its
+ * share of compute units: measured 0.85-0.86 ms on 160 of 256 against 0.67-0.70 ms on all of them.)  max_blocks is
+ * spread over the 8 XCDs in launch order; values of at least the number of work items give the plain launch.  The
+ * same holds for f32 tensors; f32 caches of up to 16 tokens may ignore max_blocks (their kernel is small-block and
+ * never fills a compute unit), and so does the kernel that joins the partial results of a split launch.
  * The same bits mean the same work items whatever max_blocks is.  A launch that is too small to fill the GPU is cut
  * into many (16 or 32 rows each, or runs of keys), which costs more than it gives where max_blocks is a small part of
  * them.  (Items of 16 rows go two at a time where there are more than max_blocks.  2 layers, 8 kv heads, G = 4, 364 keys, Tq 64, us

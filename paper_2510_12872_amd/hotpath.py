@@ -292,8 +292,9 @@ def _align_one(w, model, agent, j, gran, scratches, stream):
 
 def reuse_agent(w, model, agent, out=None, gran=kv.W_TOKEN, scratches=None, stream=None):
     """Whole hot path for one agent: align every segment into its cache slot, then suffix attention.  Several segments go through the
-    batched calls: a small agent's step is the number of its launches (4 segments of 10 tokens, 16 anchors, 2 layers x 8 heads: 66 us
-    one after the other, 36 us so; as a graph 58 and 18 us)."""
+    batched calls: a small agent's step is the number of its launches (4 segments of 10 tokens, 16 anchors, 2 layers x 8 heads: 74 us
+    one after the other, 41 us so; as a graph 59 and 18 us).  The weights are then those of the shared launch, summed in another order
+    (which the other segments and the size of the workspaces decide): within their tolerance, not bit for bit, align_segment's."""
     if len(agent.segments) < 2 or not _align_all(w, model, agent, gran, scratches, stream):
         for j in range(len(agent.segments)):
             _align_one(w, model, agent, j, gran, scratches, stream)
